@@ -54,8 +54,8 @@ void launch_train_forward(int N, int D, int H, int W, const uint16_t* x, const u
 // [pos][16]).  part_w / part_b: per-block partials (nn_blocks of them).
 void launch_train_backward(int N, int D, int H, int W, const uint16_t* x, const uint4* wpk, const float* logits,
                            const uint8_t* y, float pw, const float* a1, const float* a2, float* dz1, float* dz2,
-                           float* dz3, float* dx, float* part_w, float* part_b, float* gw, float* gb,
-                           float* part_loss, float* loss, const NetShapes& sh, float* grads, hipStream_t s);
+                           float* dz3, float* dx, float* part_w, float* part_b, float* part_loss, float* loss,
+                           const NetShapes& sh, float* grads, hipStream_t s);
 // fp32 parameters -> packed bf16 operands (forward and input gradient of each
 // layer) and biases [3][16].
 void launch_pack_weights(const float* params, const NetShapes& sh, uint4* wpk, float* bias, hipStream_t s);

@@ -34,7 +34,7 @@ struct mf4d_net {
     uint64_t cap_tpos = 0;
     uint32_t cap_blocks = 0;
     float *t1 = nullptr, *t2 = nullptr, *dz1 = nullptr, *dz2 = nullptr, *dz3 = nullptr, *tlogits = nullptr;
-    float *part_w = nullptr, *part_b = nullptr, *gw = nullptr, *gb = nullptr;
+    float *part_w = nullptr, *part_b = nullptr;
     float *part_loss = nullptr, *loss = nullptr;
     float* h_loss = nullptr;
 };
@@ -177,7 +177,7 @@ int check_dims(int N, int D, int H, int W) {
 void train_pass(mf4d_net* n, const uint16_t* x, const uint8_t* y, int N, int D, int H, int W, float pw, float* dx) {
     launch_train_forward(N, D, H, W, x, n->wpk, n->bias, n->t1, n->t2, n->tlogits, n->stream);
     launch_train_backward(N, D, H, W, x, n->wpk, n->tlogits, y, pw, n->t1, n->t2, n->dz1, n->dz2, n->dz3, dx,
-                          n->part_w, n->part_b, n->gw, n->gb, n->part_loss, n->loss, n->sh, n->grads, n->stream);
+                          n->part_w, n->part_b, n->part_loss, n->loss, n->sh, n->grads, n->stream);
 }
 
 }  // namespace
@@ -219,8 +219,6 @@ int mf4d_net_create(mf4d_net** out, int device, void* stream) {
     if (!rc) rc = nalloc(&n->v, P);
     if (!rc) rc = nalloc(&n->wpk, 6 * kPackSlot);
     if (!rc) rc = nalloc(&n->bias, 48);
-    if (!rc) rc = nalloc(&n->gw, 27 * 256);
-    if (!rc) rc = nalloc(&n->gb, 16);
     if (!rc) rc = nalloc(&n->part_loss, kLossBlocks);
     if (!rc) rc = nalloc(&n->loss, 1);
     if (!rc && hipHostMalloc((void**)&n->h_loss, sizeof(float)) != hipSuccess)
@@ -252,8 +250,6 @@ void mf4d_net_destroy(mf4d_net* n) {
     nfree(n->v);
     nfree(n->wpk);
     nfree(n->bias);
-    nfree(n->gw);
-    nfree(n->gb);
     nfree(n->part_loss);
     nfree(n->loss);
     if (n->h_loss) (void)hipHostFree(n->h_loss);

@@ -113,6 +113,14 @@ def test_forward_and_gradients_match_fp64_reference(shape):
     assert not dx[..., 8:].any()
 
 
+@pytest.mark.parametrize("shape", [(1, 1, 1, 1), (1, 4, 4, 16), (1, 5, 5, 17), (3, 2, 3, 33), (9, 5, 4, 18)])
+def test_tile_edges_match_fp64_reference(shape):
+    """The same comparison on grids of a single brick, exactly one 16 x 4 x 4
+    tile, one position past it on every axis, and 1 to 36 tiles (fewer and
+    more partial sums than the gradients' reduction has lane groups, 8)."""
+    test_forward_and_gradients_match_fp64_reference(shape)
+
+
 def _split_flat(g):
     from paper_1903_12294_amd.learned import split_params
     return [np.asarray(p, np.float64) for p in split_params(g)]
