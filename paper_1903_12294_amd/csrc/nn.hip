@@ -109,21 +109,41 @@ __device__ __forceinline__ int halo_shift(int k) {
     return (dz * HY + dy) * HX + dx;
 }
 
+// Matrix operand pieces of an activation type: bf16 as it is, fp32 in three.
+template <class T>
+constexpr int pieces() { return sizeof(T) == 4 ? 3 : 1; }
+
 // Stage the (TZ+2)(TY+2)(TX+2)-position input tile, CIN channels of each
-// position (of the 16 stored), zero outside the grid.  T = uint16_t (bf16) or
-// float.
+// position (of the 16 stored), zero outside the grid, as matrix operands: plane
+// (piece, 8-channel half) holds 16 bytes (8 bf16) per position, so the 16
+// positions an instruction reads lie side by side (no bank conflict), and an
+// fp32 value is split here, once, not again for each of the 27 offsets.
+// T = uint16_t (bf16) or float.
 template <int CIN, class T>
 __device__ void load_halo(const ConvDims& c, const T* __restrict__ x, int n, int z0, int y0, int x0,
-                          T* s_x) {
-    constexpr int kVec = CIN * (int)sizeof(T) / 16;  // 16-byte pieces per position
-    for (int i = threadIdx.x; i < kHalo * kVec; i += blockDim.x) {
-        const int p = i / kVec, v = i % kVec;
+                          uint4* s_x) {
+    constexpr int kHalf = CIN / 8;
+    for (int i = threadIdx.x; i < kHalo * kHalf; i += blockDim.x) {
+        const int p = i / kHalf, v = i % kHalf;
         const int hx = p % HX, hy = (p / HX) % HY, hz = p / (HX * HY);
         const int zz = z0 + hz - 1, yy = y0 + hy - 1, xx = x0 + hx - 1;
-        uint4 val = make_uint4(0, 0, 0, 0);
-        if (zz >= 0 && zz < c.D && yy >= 0 && yy < c.H && xx >= 0 && xx < c.W)
-            val = reinterpret_cast<const uint4*>(x + ((((size_t)n * c.D + zz) * c.H + yy) * c.W + xx) * 16)[v];
-        reinterpret_cast<uint4*>(s_x + (size_t)p * CIN)[v] = val;
+        const bool in = zz >= 0 && zz < c.D && yy >= 0 && yy < c.H && xx >= 0 && xx < c.W;
+        const T* src = x + ((((size_t)n * c.D + zz) * c.H + yy) * c.W + xx) * 16 + v * 8;
+        if constexpr (sizeof(T) == 4) {
+            float4 u0 = make_float4(0.f, 0.f, 0.f, 0.f), u1 = u0;
+            if (in) {
+                u0 = reinterpret_cast<const float4*>(src)[0];
+                u1 = reinterpret_cast<const float4*>(src)[1];
+            }
+            const float f[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
+            uint4 hi, mid, lo;
+            split8x3(f, hi, mid, lo);
+            s_x[v * kHalo + p] = hi;
+            s_x[(kHalf + v) * kHalo + p] = mid;
+            s_x[(2 * kHalf + v) * kHalo + p] = lo;
+        } else {
+            s_x[v * kHalo + p] = in ? *reinterpret_cast<const uint4*>(src) : make_uint4(0, 0, 0, 0);
+        }
     }
 }
 
@@ -149,23 +169,34 @@ enum ConvOut : int { OUT_BF16 = 0, OUT_F32 = 1, OUT_LOGIT = 2 };
 
 // out = conv(x, w) + bias, optionally ReLU, optionally zero where mask <= 0
 // (mask: the layer's forward activation, fp32 [..][16]: the ReLU derivative).
-// x: T [..][16], CIN channels read; F32 inputs are split into two bf16
-// operands.  wpk: packed B operands, [ksteps][64 lanes] x 16 bytes.  Output
-// OUT_BF16: bf16 [..][16]; OUT_F32: fp32 [..][16]; OUT_LOGIT: channel 0 as
-// fp32 [N][D][H][W].
+// x: T [..][16], CIN channels read; fp32 inputs as three bf16 operands.  wpk:
+// packed weight operands, [ksteps][64 lanes] x 16 bytes.  Output OUT_BF16: bf16
+// [..][16]; OUT_F32: fp32 [..][16] (16-byte stores with vec, else one value at
+// a time for a caller's unaligned buffer); OUT_LOGIT: channel 0 as fp32
+// [N][D][H][W].
+//
+// The weights are the first operand, the positions the second: a lane then
+// holds four consecutive channels of one position, and a wave stores 16 whole
+// positions (512 bytes bf16, 1 KB fp32) in one instruction.  Bound by the
+// latency of a block's load - split - multiply - store phases (512 blocks of
+// work for 256 CUs at 32 x 16^3); the fp32 layers went from 60 to 18 us there
+// and the bf16 ones at 64 x 32^3 from 77 to 66 us when the split moved out of the
+// offset loop and the stores became whole.
 template <int CIN, class T, int OUT>
 __global__ __launch_bounds__(256) void k_conv(ConvDims c, const T* __restrict__ x, const uint4* __restrict__ wpk,
                                               const float* __restrict__ bias, int relu,
-                                              const float* __restrict__ mask, void* __restrict__ out) {
-    constexpr bool kF32 = sizeof(T) == 4;
-    constexpr int NK = ksteps<CIN>();
-    __shared__ T s_x[kHalo * CIN];
+                                              const float* __restrict__ mask, void* __restrict__ out, int vec) {
+    constexpr int NP = pieces<T>(), NK = ksteps<CIN>(), kHalf = CIN / 8;
+    __shared__ uint4 s_x[NP * kHalf * kHalo];
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     const int row = lane & 15, grp = lane >> 4;
     uint4 bw[NK];
 #pragma unroll
     for (int j = 0; j < NK; ++j) bw[j] = wpk[j * 64 + lane];
-    const float b = bias ? bias[row] : 0.0f;
+    v4f b = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (bias)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b[i] = bias[4 * grp + i];
     const uint32_t nblocks = (uint32_t)c.N * c.nbz * c.nby * c.nbx;
     for (uint32_t blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
         int n, z0, y0, x0;
@@ -181,43 +212,59 @@ __global__ __launch_bounds__(256) void k_conv(ConvDims c, const T* __restrict__ 
             for (int j = 0; j < NK; ++j) {
                 int k, c0;
                 step_part<CIN>(j, grp, k, c0);
-                const int p = base + halo_shift(k < 27 ? k : 26);
-                if (kF32) {
-                    float v[8];
-                    const float4* src = reinterpret_cast<const float4*>(reinterpret_cast<const float*>(s_x) +
-                                                                        (size_t)p * CIN + c0);
-                    const float4 u0 = src[0], u1 = src[1];
-                    v[0] = u0.x; v[1] = u0.y; v[2] = u0.z; v[3] = u0.w;
-                    v[4] = u1.x; v[5] = u1.y; v[6] = u1.z; v[7] = u1.w;
-                    uint4 hi, mid, lo;
-                    split8x3(v, hi, mid, lo);
-                    if (k >= 27) hi = mid = lo = make_uint4(0, 0, 0, 0);
-                    acc = mfma(hi, bw[j], acc);
-                    acc = mfma(mid, bw[j], acc);
-                    acc = mfma(lo, bw[j], acc);
-                } else {
-                    uint4 a = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(s_x) +
-                                                             (size_t)p * CIN + c0);
+                const int p = (c0 >> 3) * kHalo + base + halo_shift(k < 27 ? k : 26);
+#pragma unroll
+                for (int q = 0; q < NP; ++q) {
+                    uint4 a = s_x[q * kHalf * kHalo + p];
                     if (k >= 27) a = make_uint4(0, 0, 0, 0);
-                    acc = mfma(a, bw[j], acc);
+                    acc = mfma(bw[j], a, acc);
                 }
             }
-            // acc[i] = D[position x0 + 4*grp + i][output channel row]
-            const int z = z0 + zl, y = y0 + yl;
-            if (z >= c.D || y >= c.H) continue;
+            // acc[i] = D[output channel 4*grp + i][position x0 + row]
+            const int z = z0 + zl, y = y0 + yl, xx = x0 + row;
+            if (z >= c.D || y >= c.H || xx >= c.W) continue;
+            const size_t pos = (((size_t)n * c.D + z) * c.H + y) * c.W + xx;
+            acc += b;
+            if (relu)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int xx = x0 + 4 * grp + i;
-                if (xx >= c.W) continue;
-                const size_t pos = (((size_t)n * c.D + z) * c.H + y) * c.W + xx;
-                float v = acc[i] + b;
-                if (relu) v = fmaxf(v, 0.0f);
-                if (mask && !(mask[pos * 16 + row] > 0.0f)) v = 0.0f;
-                if (OUT == OUT_BF16) static_cast<uint16_t*>(out)[pos * 16 + row] = f2bf(v);
-                else if (OUT == OUT_F32) static_cast<float*>(out)[pos * 16 + row] = v;
-                else if (row == 0) static_cast<float*>(out)[pos] = v;
+                for (int i = 0; i < 4; ++i) acc[i] = fmaxf(acc[i], 0.0f);
+            if (mask) {
+                const v4f m = *reinterpret_cast<const v4f*>(mask + pos * 16 + 4 * grp);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (!(m[i] > 0.0f)) acc[i] = 0.0f;
+            }
+            if (OUT == OUT_BF16) {
+                const uint2 h = make_uint2(f2bf(acc[0]) | ((uint32_t)f2bf(acc[1]) << 16),
+                                           f2bf(acc[2]) | ((uint32_t)f2bf(acc[3]) << 16));
+                reinterpret_cast<uint2*>(static_cast<uint16_t*>(out) + pos * 16)[grp] = h;
+            } else if (OUT == OUT_F32) {
+                float* o = static_cast<float*>(out) + pos * 16 + 4 * grp;
+                if (vec) {
+                    *reinterpret_cast<v4f*>(o) = acc;
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) o[i] = acc[i];
+                }
+            } else if (grp == 0) {
+                static_cast<float*>(out)[pos] = acc[0];
             }
         }
+    }
+}
+
+template <int CIN, class T>
+__device__ void load_halo_plain(const ConvDims& c, const T* __restrict__ x, int n, int z0, int y0, int x0,
+                          T* s_x) {
+    constexpr int kVec = CIN * (int)sizeof(T) / 16;  // 16-byte pieces per position
+    for (int i = threadIdx.x; i < kHalo * kVec; i += blockDim.x) {
+        const int p = i / kVec, v = i % kVec;
+        const int hx = p % HX, hy = (p / HX) % HY, hz = p / (HX * HY);
+        const int zz = z0 + hz - 1, yy = y0 + hy - 1, xx = x0 + hx - 1;
+        uint4 val = make_uint4(0, 0, 0, 0);
+        if (zz >= 0 && zz < c.D && yy >= 0 && yy < c.H && xx >= 0 && xx < c.W)
+            val = reinterpret_cast<const uint4*>(x + ((((size_t)n * c.D + zz) * c.H + yy) * c.W + xx) * 16)[v];
+        reinterpret_cast<uint4*>(s_x + (size_t)p * CIN)[v] = val;
     }
 }
 
@@ -238,7 +285,7 @@ __global__ __launch_bounds__(256) void k_wgrad(ConvDims c, const T* __restrict__
     const uint32_t blk = blockIdx.x;
     int n, z0, y0, x0;
     block_origin(c, blk, n, z0, y0, x0);
-    load_halo<CIN>(c, x, n, z0, y0, x0, s_x);
+    load_halo_plain<CIN>(c, x, n, z0, y0, x0, s_x);
     for (int i = threadIdx.x; i < kTilePos * 4; i += blockDim.x) {
         const int p = i >> 2, v = i & 3;
         const int px = p % TX, py = (p / TX) % TY, pz = p / (TX * TY);
@@ -390,8 +437,8 @@ __global__ __launch_bounds__(256) void k_bce(const float* __restrict__ logits,
     if (threadIdx.x == 0) part_loss[blockIdx.x] = (s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3]) * inv;
 }
 
-// fp32 parameters (reference layout) -> packed bf16 B operands and biases.
-// Forward of layer l (input channels cin_l): B[kappa][out], kappa = (offset,
+// fp32 parameters (reference layout) -> packed bf16 weight operands and biases.
+// Forward of layer l (input channels cin_l): W[kappa][out], kappa = (offset,
 // input channel) in the order step_part gives.  Input gradient of layer l: the
 // convolution of the layer's output gradient (cout_l channels, read as 16, or
 // as 8 when cout_l = 1) with W[out][in][26 - k] transposed.
@@ -611,8 +658,9 @@ void conv_launch(int N, int D, int H, int W, const T* x, const uint4* wpk, const
                  const float* mask, void* out, hipStream_t s) {
     const ConvDims c = conv_dims(N, D, H, W);
     const uint32_t nb = (uint32_t)c.N * c.nbz * c.nby * c.nbx;
+    const int vec = (reinterpret_cast<uintptr_t>(out) & 15) == 0;  // a caller's dx may not be
     hipLaunchKernelGGL((k_conv<CIN, T, OUT>), dim3(grid_for(nb, 1, 8192)), dim3(256), 0, s, c, x, wpk, bias, relu,
-                       mask, out);
+                       mask, out, vec);
 }
 
 // Gradients of layer `layer` (and, with loss, the mean loss from part_loss).
