@@ -26,6 +26,8 @@
 // (deterministic).  Parameters are fp32 masters updated by Adam.
 #include "nn.h"
 
+#include <algorithm>
+
 namespace mf4d {
 
 namespace {
@@ -53,22 +55,9 @@ __device__ __forceinline__ uint4 pack8(const uint16_t* h) {
     return make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
 }
 
-// Eight fp32 values -> bf16 high parts and bf16 remainders (v - hi, exact in
-// fp32, then rounded): about 16 significant bits.
-__device__ __forceinline__ void split8(const float* v, uint4& hi, uint4& lo) {
-    uint16_t h[8], l[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        h[e] = f2bf(v[e]);
-        l[e] = f2bf(v[e] - bf2f(h[e]));
-    }
-    hi = pack8(h);
-    lo = pack8(l);
-}
-
-// The same in three pieces (the remainder split once more): all 24
-// significant bits of an fp32 value, so that a convolution of these operands
-// with fp32 accumulation is as accurate as fp32 arithmetic.
+// Eight fp32 values in three bf16 pieces (high part, then the exact fp32
+// remainder split once more): all 24 significant bits, so that a convolution
+// of these operands with fp32 accumulation is as accurate as fp32 arithmetic.
 __device__ __forceinline__ void split8x3(const float* v, uint4& hi, uint4& mid, uint4& lo) {
     uint16_t h[8], m[8], l[8];
 #pragma unroll
@@ -253,108 +242,171 @@ __global__ __launch_bounds__(256) void k_conv(ConvDims c, const T* __restrict__ 
     }
 }
 
-template <int CIN, class T>
-__device__ void load_halo_plain(const ConvDims& c, const T* __restrict__ x, int n, int z0, int y0, int x0,
-                          T* s_x) {
-    constexpr int kVec = CIN * (int)sizeof(T) / 16;  // 16-byte pieces per position
-    for (int i = threadIdx.x; i < kHalo * kVec; i += blockDim.x) {
-        const int p = i / kVec, v = i % kVec;
-        const int hx = p % HX, hy = (p / HX) % HY, hz = p / (HX * HY);
-        const int zz = z0 + hz - 1, yy = y0 + hy - 1, xx = x0 + hx - 1;
-        uint4 val = make_uint4(0, 0, 0, 0);
-        if (zz >= 0 && zz < c.D && yy >= 0 && yy < c.H && xx >= 0 && xx < c.W)
-            val = reinterpret_cast<const uint4*>(x + ((((size_t)n * c.D + zz) * c.H + yy) * c.W + xx) * 16)[v];
-        reinterpret_cast<uint4*>(s_x + (size_t)p * CIN)[v] = val;
-    }
+// Weight and bias gradients of one layer, per block:
+// part_w[blk][k][out][in] = sum_pos dz[pos][out] * x[pos + off(k)][in],
+// part_b[blk][out] = sum_pos dz[pos][out], over the tiles blk, blk + gridDim.x,
+// ... of 16 x 4 x 4 positions (at most kMaxParts blocks, so that many partials
+// whatever the grid).  dz: fp32 [..][16] (COUT channels real); x: T [..][16], CIN
+// channels read.  Positions are the reduction axis: one instruction takes 32
+// positions (two rows of the tile); each fp32 operand is split into bf16 high
+// part and remainder.
+//
+// Both operands want eight consecutive positions of one channel, so a tile is
+// staged channel-major (transposed and split while staging, once per value), and
+// wave w owns the kernel offsets (dz, dy) = w of the nine: it reads the ten
+// values x - 1 .. x + 8 of a row once and forms the operands of dx = -1, 0, 1
+// from them by funnel shifts.  Channel rows are padded so that 8 lanes reading
+// 16 bytes of 8 channels hit different banks.  Bound by the staging's latency and
+// LDS writes: 19 us for 16 fp32 channels at 32 x 16^3 positions; gathering the
+// values one by one and splitting them again for every offset took 51 us.
+constexpr int kWX = 24;                                  // LDS row: 18 positions, padded to 16-byte steps
+constexpr int kWPlane = HY * HZ * kWX + 8;               // elements per channel
+constexpr int kDPlane = kTilePos + 8;
+constexpr int kWgradBlock = 9 * 64;
+constexpr uint32_t kMaxParts = 1024;  // two resident blocks per CU, twice
+
+// Elements 0..9 (w: 0..7, t: 8, 9) of eight bf16 pairs; the eight starting at S.
+template <int S>
+__device__ __forceinline__ uint4 window(const uint4& w, uint32_t t) {
+    if (S == 0) return w;
+    if (S == 2) return make_uint4(w.y, w.z, w.w, t);
+    return make_uint4(__builtin_amdgcn_alignbit(w.y, w.x, 16), __builtin_amdgcn_alignbit(w.z, w.y, 16),
+                      __builtin_amdgcn_alignbit(w.w, w.z, 16), __builtin_amdgcn_alignbit(t, w.w, 16));
 }
 
-// Weight and bias gradients of one layer, per block of positions:
-// part_w[blk][k][out][in] = sum_pos dz[pos][out] * x[pos + off(k)][in],
-// part_b[blk][out] = sum_pos dz[pos][out].  dz: fp32 [..][16] (COUT channels
-// real); x: T [..][16], CIN channels read.  Positions are the reduction axis:
-// one instruction takes 32 positions (two rows of the tile); each fp32
-// operand is split into bf16 high part and remainder.
 template <int CIN, class T>
-__global__ __launch_bounds__(256) void k_wgrad(ConvDims c, const T* __restrict__ x, const float* __restrict__ dz,
-                                               float* __restrict__ part_w, float* __restrict__ part_b) {
+__global__ __launch_bounds__(kWgradBlock) void k_wgrad(ConvDims c, const T* __restrict__ x,
+                                                       const float* __restrict__ dz, float* __restrict__ part_w,
+                                                       float* __restrict__ part_b) {
     constexpr bool kF32 = sizeof(T) == 4;
-    __shared__ T s_x[kHalo * CIN];
-    __shared__ float s_d[kTilePos * 16];
+    constexpr int NX = kF32 ? 2 : 1;                     // operand pieces of x
+    __shared__ __align__(16) uint16_t s_x[NX * CIN * kWPlane];
+    __shared__ __align__(16) uint16_t s_d[2 * 16 * kDPlane];
+    __shared__ float s_b[9][16];
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     const int row = lane & 15, grp = lane >> 4;
-    const uint32_t blk = blockIdx.x;
-    int n, z0, y0, x0;
-    block_origin(c, blk, n, z0, y0, x0);
-    load_halo_plain<CIN>(c, x, n, z0, y0, x0, s_x);
-    for (int i = threadIdx.x; i < kTilePos * 4; i += blockDim.x) {
-        const int p = i >> 2, v = i & 3;
-        const int px = p % TX, py = (p / TX) % TY, pz = p / (TX * TY);
-        const int zz = z0 + pz, yy = y0 + py, xx = x0 + px;
-        float4 val = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (zz < c.D && yy < c.H && xx < c.W)
-            val = reinterpret_cast<const float4*>(dz + ((((size_t)n * c.D + zz) * c.H + yy) * c.W + xx) * 16)[v];
-        reinterpret_cast<float4*>(s_d + (size_t)p * 16)[v] = val;
-    }
-    __syncthreads();
-    // wave w accumulates offsets k = w, w + 4, ... (at most 7)
-    v4f acc[7];
+    v4f acc[3];
 #pragma unroll
-    for (int j = 0; j < 7; ++j) acc[j] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
-    for (int ch = 0; ch < kTilePos / 32; ++ch) {
-        // positions q = 32 ch + 8 grp + e: rows 2 ch + (q >> 4) & 1, x = q & 15
-        float dv[8];
+    for (int j = 0; j < 3; ++j) acc[j] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+    float bsum[4] = {0.0f, 0.0f, 0.0f, 0.0f};            // channels 4 * (thread & 3) ..
+    const uint32_t nblocks = (uint32_t)c.N * c.nbz * c.nby * c.nbx;
+    for (uint32_t blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
+        int n, z0, y0, x0;
+        block_origin(c, blk, n, z0, y0, x0);
+        __syncthreads();  // the previous tile's reads are done
+        // x: a thread takes 4 channels of two neighbouring positions (one word
+        // per channel and piece)
+        constexpr int kQuads = CIN / 4, kPairs = HX / 2;
+        for (int i = threadIdx.x; i < HZ * HY * kPairs * kQuads; i += kWgradBlock) {
+            const int v = i % kQuads, r = i / kQuads;
+            const int px = (r % kPairs) * 2, rz = r / kPairs;  // rz = hz * HY + hy
+            const int zz = z0 + rz / HY - 1, yy = y0 + rz % HY - 1;
+            const bool inr = zz >= 0 && zz < c.D && yy >= 0 && yy < c.H;
+            uint16_t h[2][4] = {}, l[2][4] = {};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) dv[e] = s_d[(size_t)(32 * ch + 8 * grp + e) * 16 + row];
-        uint4 ahi, alo;
-        split8(dv, ahi, alo);
+            for (int e = 0; e < 2; ++e) {
+                const int xx = x0 + px + e - 1;
+                if (!inr || xx < 0 || xx >= c.W) continue;
+                const T* src = x + ((((size_t)n * c.D + zz) * c.H + yy) * c.W + xx) * 16 + v * 4;
+                if constexpr (kF32) {
+                    const float4 u = *reinterpret_cast<const float4*>(src);
+                    const float f[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
-        for (int j = 0; j < 7; ++j) {
-            const int k = wave + 4 * j;
-            if (k >= 27) continue;
-            const int sh = halo_shift(k);
-            uint4 bhi, blo = make_uint4(0, 0, 0, 0);
-            if (row < CIN) {
-                if (kF32) {
-                    float xv[8];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const int q = 32 * ch + 8 * grp + e;
-                        const int r = q >> 4, px = q & 15, zl = r / TY, yl = r % TY;
-                        const int p = ((zl + 1) * HY + (yl + 1)) * HX + (px + 1) + sh;
-                        xv[e] = reinterpret_cast<const float*>(s_x)[(size_t)p * CIN + row];
+                    for (int q = 0; q < 4; ++q) {
+                        h[e][q] = f2bf(f[q]);
+                        l[e][q] = f2bf(f[q] - bf2f(h[e][q]));
                     }
-                    split8(xv, bhi, blo);
                 } else {
-                    uint16_t h[8];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const int q = 32 * ch + 8 * grp + e;
-                        const int r = q >> 4, px = q & 15, zl = r / TY, yl = r % TY;
-                        const int p = ((zl + 1) * HY + (yl + 1)) * HX + (px + 1) + sh;
-                        h[e] = reinterpret_cast<const uint16_t*>(s_x)[(size_t)p * CIN + row];
-                    }
-                    bhi = pack8(h);
+                    const uint2 u = *reinterpret_cast<const uint2*>(src);
+                    h[e][0] = (uint16_t)u.x;
+                    h[e][1] = (uint16_t)(u.x >> 16);
+                    h[e][2] = (uint16_t)u.y;
+                    h[e][3] = (uint16_t)(u.y >> 16);
                 }
-            } else {
-                bhi = make_uint4(0, 0, 0, 0);
             }
-            acc[j] = mfma(ahi, bhi, acc[j]);
-            acc[j] = mfma(alo, bhi, acc[j]);
-            if (kF32) acc[j] = mfma(ahi, blo, acc[j]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int at = (v * 4 + q) * kWPlane + rz * kWX + px;
+                *reinterpret_cast<uint32_t*>(&s_x[at]) = h[0][q] | ((uint32_t)h[1][q] << 16);
+                if (kF32) *reinterpret_cast<uint32_t*>(&s_x[CIN * kWPlane + at]) = l[0][q] | ((uint32_t)l[1][q] << 16);
+            }
+        }
+        // dz: likewise, pairs of positions along x
+        for (int i = threadIdx.x; i < kTilePos / 2 * 4; i += kWgradBlock) {
+            const int v = i & 3, p = (i >> 2) * 2;
+            const int px = p % TX, py = (p / TX) % TY, pz = p / (TX * TY);
+            const int zz = z0 + pz, yy = y0 + py;
+            uint16_t h[2][4] = {}, l[2][4] = {};
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int xx = x0 + px + e;
+                if (zz >= c.D || yy >= c.H || xx >= c.W) continue;
+                const float4 u =
+                    *reinterpret_cast<const float4*>(dz + ((((size_t)n * c.D + zz) * c.H + yy) * c.W + xx) * 16 + v * 4);
+                const float f[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    h[e][q] = f2bf(f[q]);
+                    l[e][q] = f2bf(f[q] - bf2f(h[e][q]));
+                    bsum[q] += f[q];
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int at = (v * 4 + q) * kDPlane + p;
+                *reinterpret_cast<uint32_t*>(&s_d[at]) = h[0][q] | ((uint32_t)h[1][q] << 16);
+                *reinterpret_cast<uint32_t*>(&s_d[16 * kDPlane + at]) = l[0][q] | ((uint32_t)l[1][q] << 16);
+            }
+        }
+        __syncthreads();
+        const int ch = row < CIN ? row : 0;              // lanes past the channels read zeros (below)
+        const int oz = wave / 3, oy = wave % 3;          // dz + 1, dy + 1
+#pragma unroll
+        for (int k = 0; k < kTilePos / 32; ++k) {
+            // positions 32 k + 8 grp + e: row 2 k + (grp >> 1) of the tile, x = 8 (grp & 1) + e
+            const int r = 2 * k + (grp >> 1), px = 8 * (grp & 1);
+            const int dat = row * kDPlane + r * TX + px;
+            const uint4 ahi = *reinterpret_cast<const uint4*>(&s_d[dat]);
+            const uint4 alo = *reinterpret_cast<const uint4*>(&s_d[16 * kDPlane + dat]);
+            const int xat = ch * kWPlane + ((r / TY + oz) * HY + r % TY + oy) * kWX + px;
+            uint4 w[NX];
+            uint32_t t[NX];
+#pragma unroll
+            for (int q = 0; q < NX; ++q) {
+                w[q] = *reinterpret_cast<const uint4*>(&s_x[q * CIN * kWPlane + xat]);
+                t[q] = *reinterpret_cast<const uint32_t*>(&s_x[q * CIN * kWPlane + xat + 8]);
+                if (row >= CIN) {
+                    w[q] = make_uint4(0, 0, 0, 0);
+                    t[q] = 0;
+                }
+            }
+            auto step = [&](v4f& a, const uint4& bhi, const uint4& blo) {
+                a = mfma(ahi, bhi, a);
+                a = mfma(alo, bhi, a);
+                if (kF32) a = mfma(ahi, blo, a);
+            };
+            step(acc[0], window<0>(w[0], t[0]), window<0>(w[NX - 1], t[NX - 1]));
+            step(acc[1], window<1>(w[0], t[0]), window<1>(w[NX - 1], t[NX - 1]));
+            step(acc[2], window<2>(w[0], t[0]), window<2>(w[NX - 1], t[NX - 1]));
         }
     }
-    // acc[j][i] = D[out = 4*grp + i][in = row]
+    // acc[j][i] = D[out = 4*grp + i][in = row] of offset 3 * wave + j
 #pragma unroll
-    for (int j = 0; j < 7; ++j) {
-        const int k = wave + 4 * j;
-        if (k < 27)
-            for (int i = 0; i < 4; ++i)
-                part_w[(((size_t)blk * 27 + k) * 16 + 4 * grp + i) * 16 + row] = acc[j][i];
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            part_w[(((size_t)blockIdx.x * 27 + 3 * wave + j) * 16 + 4 * grp + i) * 16 + row] = acc[j][i];
+    // channel sums: lanes with the same thread & 3 hold the same channels
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        for (int o = 4; o < 64; o <<= 1) bsum[q] += __shfl_xor(bsum[q], o);
+        if (lane < 4) s_b[wave][lane * 4 + q] = bsum[q];
     }
+    __syncthreads();
     if (threadIdx.x < 16) {
         float s = 0.0f;
-        for (int p = 0; p < kTilePos; ++p) s += s_d[(size_t)p * 16 + threadIdx.x];
-        part_b[(size_t)blk * 16 + threadIdx.x] = s;
+        for (int w = 0; w < 9; ++w) s += s_b[w][threadIdx.x];
+        part_b[(size_t)blockIdx.x * 16 + threadIdx.x] = s;
     }
 }
 
@@ -668,8 +720,8 @@ template <int CIN, class T>
 void wgrad_launch(int N, int D, int H, int W, const T* x, const float* dz, float* part_w, float* part_b,
                   const NetShapes& sh, int layer, float* grads, const float* part_loss, float* loss, hipStream_t s) {
     const ConvDims c = conv_dims(N, D, H, W);
-    const uint32_t nb = (uint32_t)c.N * c.nbz * c.nby * c.nbx;
-    hipLaunchKernelGGL((k_wgrad<CIN, T>), dim3(nb), dim3(256), 0, s, c, x, dz, part_w, part_b);
+    const uint32_t nb = nn_blocks(N, D, H, W);
+    hipLaunchKernelGGL((k_wgrad<CIN, T>), dim3(nb), dim3(kWgradBlock), 0, s, c, x, dz, part_w, part_b);
     const int sums = sh.cout[layer] * sh.cin[layer] * 27 + sh.cout[layer] + 1;
     hipLaunchKernelGGL(k_reduce_grads, dim3((sums + kRedCols - 1) / kRedCols), dim3(kRedCols * kRedRows), 0, s,
                        part_w, part_b, nb, sh, layer, grads, part_loss, loss);
@@ -679,7 +731,7 @@ void wgrad_launch(int N, int D, int H, int W, const T* x, const float* dz, float
 
 uint32_t nn_blocks(int N, int D, int H, int W) {
     const ConvDims c = conv_dims(N, D, H, W);
-    return (uint32_t)c.N * c.nbz * c.nby * c.nbx;
+    return std::min((uint32_t)c.N * c.nbz * c.nby * c.nbx, kMaxParts);
 }
 
 void launch_infer(int N, int D, int H, int W, const uint16_t* x, const uint4* wpk, const float* bias,
