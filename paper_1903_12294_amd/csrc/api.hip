@@ -2305,10 +2305,14 @@ int mf4d_slic_run(mf4d_ctx* c, int* iterations) {
     s.counters = c->scounters;
     s.slab = c->sslab;
     s.reach = reinterpret_cast<int*>(c->sslab + 8 * 4096);
-    // debug switch: MF4D_SLIC_MASK_SLABS = 0 sends every sample through the
-    // general candidate loop (the tests compare both paths)
+    // debug switch: MF4D_SLIC_MASK_SLABS below 32 searches sample by sample, 0
+    // through the general candidate loop (the tests compare the paths)
     s.mask_slabs = 32;
     if (const char* e = getenv("MF4D_SLIC_MASK_SLABS")) s.mask_slabs = std::min(32, std::max(0, atoi(e)));
+    // the boxes' bounds need every distance finite: coordinates and values are
+    // less than 2^12 apart, so these weights keep D below 10^32
+    s.boxes = s.mask_slabs == 32 && s.wd <= 1e15f && s.wf <= 1e15f && s.wp <= 1e15f && s.cf <= 1e12f;
+    s.tie = s.wd * 1e-18f;
     s.lsum = c->slsum;
     s.kmax = std::max(std::max(c->sk[0], c->sk[1]), std::max(c->sk[2], c->sk[3]));
     hipStream_t st = c->stream;

@@ -45,6 +45,8 @@ struct DevS {
     int* reach;
     int mask_slabs;      // widest reach range searched through bit masks (0..32); wider ranges
                          // take the general loop
+    int boxes;           // candidate lists per box of samples (0: every sample on its own)
+    float tie;           // distances this close (w_d 1e-18) are compared again with denormals scaled
     int kmax;            // max(k[0..3])
     uint32_t* counters;  // SlicCounter
     unsigned long long* lsum;  // [K][kSlicAcc]: the sums of the last update (for the features)

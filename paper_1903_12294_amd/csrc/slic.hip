@@ -4,16 +4,26 @@
 // one small update.  A pass assigns each sample to the centre with the
 // smallest distance among those whose window holds it (Section 3.2.2-3.2.3)
 // and adds the sample's quantised coordinates and value to its centre's
-// sums: first in a block-local LDS table keyed by centre (a block of 1024
-// consecutive samples touches few centres), then with one 64-bit atomic per
-// touched centre and sum.  Integer sums make the centres independent of the
+// sums: first block-local in LDS, then with one 64-bit atomic per touched
+// centre and sum.  Integer sums make the centres independent of the
 // order of the additions, so they are bit-identical run to run.  The update
 // turns the sums into means, compares them with the previous centres
 // (convergence, Section 3.2.2) and clears the sums.
 //
-// Arithmetic that decides a label is IEEE fp32 with every operation rounded
-// on its own (no fused multiply-add), in a fixed order:
-//   S = sqrt(((dx*dx + dy*dy) + dz*dz) + (cf*dt)*(cf*dt)),  D = w_v*|v - v_c| + w_d*S.
+// A block takes a compact box of samples (field: up to 32 x 8 x 8 x 2
+// voxel-steps; points: 1,024 consecutive ones in visiting order, sorted by
+// sub-box), lists the centres whose windows meet the box, and each wave keeps
+// of these, per 256 samples, the ones that can win for any of them (bounds of
+// the distance over the wave's box).  A sample so rates about ten centres
+// instead of testing the hundreds of its neighbourhood.  A block whose list
+// would not fit searches sample by sample.
+//
+// Arithmetic that decides a label is fp32 in a fixed order, with the products
+// fused into the sums and the hardware's square root (1 ulp):
+//   S^2 = (cf*dt)^2 + (dz^2 + (dx^2 + dy^2)),  D = w_v*|v - v_c| + w_d*S,
+// dist2 and distance below.  (The oracle rounds every operation on its own: two
+// centres whose distances from a sample agree to about 2^-22 may rank
+// otherwise there.)
 #include "slic.h"
 
 #include <math.h>
@@ -23,21 +33,23 @@
 namespace mf4d {
 namespace {
 
-constexpr double kQScale = 1048576.0;  // 2^20: quantisation of coordinates and values
 constexpr double kQInv = 1.0 / 1048576.0;
 constexpr float kMaxAbs = 2048.0f;     // |coordinate|, |value| below this keep the sums in int64
 constexpr int kTab = 64;               // LDS table slots (centres one block touches)
 constexpr int kBlock = 256;
 constexpr int kPer = 4;                // samples per thread per pass
+constexpr int kCand = 256;             // centres a box's list holds (4 per lane of a wave)
+constexpr int kAxis = 64;              // slabs per axis a box may meet
+constexpr int kRaw = 16384;            // slab combinations tested for a box's list
 
 __device__ __forceinline__ int seed_cell(float pos, float C, int kd) {
     const float q = floorf(__fdiv_rn(pos, C));
     return (int)fminf(fmaxf(q, 0.0f), (float)(kd - 1));
 }
 
-__device__ __forceinline__ long long quantise(float v) {
-    return __double2ll_rn((double)v * kQScale);
-}
+// rint(v * 2^20) for |v| < 2048: the product by a power of two is exact in fp32
+// and below 2^31.
+__device__ __forceinline__ int quantise(float v) { return __float2int_rn(__fmul_rn(v, 1048576.0f)); }
 
 // dbl(s) = float64(s >> 32) * 2^32 + float64(s & 0xffffffff): the product is
 // exact, so one rounding whether or not the two are fused.
@@ -90,6 +102,13 @@ __device__ __forceinline__ unsigned axis_mask(const DevS& s, int d, int c, float
     return m;
 }
 
+__device__ __forceinline__ float dist2(const DevS& s, float dx, float dy, float dz, float dt) {
+    const float ctd = s.cf * dt, yy = dy * dy;
+    return __builtin_fmaf(ctd, ctd, __builtin_fmaf(dz, dz, __builtin_fmaf(dx, dx, yy)));
+}
+// A = w_v |v - v_c|
+__device__ __forceinline__ float distance(const DevS& s, float A, float S) { return __builtin_fmaf(s.wd, S, A); }
+
 // Rate centre id for the sample if its window holds it; keep the smallest D,
 // ties to the lowest id.
 __device__ __forceinline__ void consider(const DevS& s, int id, float px, float py, float pz, float pt, float v,
@@ -104,10 +123,7 @@ __device__ __forceinline__ void consider(const DevS& s, int id, float px, float 
     // D = A + (w_d S) rounded is >= A: a value term above the best distance
     // cannot win (nor tie), so skip the rest
     if (A > best_d) return;
-    const float ctd = __fmul_rn(s.cf, dt);
-    const float sq = __fadd_rn(__fadd_rn(__fadd_rn(__fmul_rn(dx, dx), __fmul_rn(dy, dy)), __fmul_rn(dz, dz)),
-                               __fmul_rn(ctd, ctd));
-    const float D = __fadd_rn(A, __fmul_rn(s.wd, __fsqrt_rn(sq)));
+    const float D = distance(s, A, __fsqrt_rn(dist2(s, dx, dy, dz, dt)));
     if (D < best_d || (D == best_d && id < best)) {
         best_d = D;
         best = id;
@@ -242,131 +258,625 @@ __device__ __forceinline__ void table_flush(const DevS& s, Table& tb) {
     }
 }
 
-// Field samples: block b takes samples [b * 1024, (b + 1) * 1024) in
-// [T][Z][Y][X] order, 4 consecutive ones per thread (mostly of one centre:
-// the thread sums them before touching the block's table).  assign = 0:
-// labels from the seed cells.
-__global__ __launch_bounds__(kBlock) void k_slic_field(DevS s, int assign) {
-    __shared__ Table tb;
-    table_init(tb);
-    const uint32_t V = (uint32_t)s.X * s.Y * s.Z * s.T;  // < 2^31 (checked by the host)
-    const uint32_t i0 = blockIdx.x * (uint32_t)(kBlock * kPer) + threadIdx.x * kPer;
-    Run run;
-    run.id = -1;
-    // coordinates of the thread's first sample (32-bit arithmetic), then
-    // stepped along x; what depends only on (y, z, t) is computed per row
-    int x = 0, y = 0, z = 0, t = 0;
-    if (i0 < V) {
-        uint32_t r = i0;
-        x = (int)(r % (uint32_t)s.X);
-        r /= (uint32_t)s.X;
-        y = (int)(r % (uint32_t)s.Y);
-        r /= (uint32_t)s.Y;
-        z = (int)(r % (uint32_t)s.Z);
-        t = (int)(r / (uint32_t)s.Z);
-    }
-    float py = 0.f, pz = 0.f, pt = 0.f;
-    int cy0 = 0, cz0 = 0, ct0 = 0;
-    int by0 = 0, bz0 = 0, bt0 = 0;
-    unsigned my = 0, mz = 0, mt = 0;
-    bool row = false;       // row values current
-    bool row_wide = false;  // a reach range of the row wider than 32 slabs
-    for (int j = 0; j < kPer; ++j) {
-        const uint32_t i = i0 + j;
-        if (i >= V) break;
-        if (j > 0 && ++x == s.X) {  // next row
-            x = 0;
-            row = false;
-            if (++y == s.Y) {
-                y = 0;
-                if (++z == s.Z) {
-                    z = 0;
-                    ++t;
-                }
-            }
-        }
-        const float v = s.field[i];
-        if (!isfinite(v)) {
-            s.labels[i] = -1;
-            continue;
-        }
-        if (!(fabsf(v) < kMaxAbs)) s.counters[SC_RANGE] = 1u;
-        if (!row) {
-            py = (float)y + 0.5f;
-            pz = (float)z + 0.5f;
-            pt = (float)t;
-            cy0 = seed_cell(py, s.C[1], s.k[1]);
-            cz0 = seed_cell(pz, s.C[2], s.k[2]);
-            ct0 = seed_cell(pt, s.C[3], s.k[3]);
-            if (assign) {
-                row_wide = false;
-                my = axis_mask(s, 1, cy0, py, by0, row_wide);
-                mz = axis_mask(s, 2, cz0, pz, bz0, row_wide);
-                mt = axis_mask(s, 3, ct0, pt, bt0, row_wide);
-            }
-            row = true;
-        }
-        const float px = (float)x + 0.5f;
-        const int cx0 = seed_cell(px, s.C[0], s.k[0]);
-        int id;
-        if (assign) {
-            int bx0;
-            bool wide = row_wide;
-            const unsigned mx = axis_mask(s, 0, cx0, px, bx0, wide);
-            id = wide ? assign_wide(s, px, py, pz, pt, v, true, s.labels[i])
-                      : assign_cands(s, px, py, pz, pt, v, true, s.labels[i], bx0, by0, bz0, bt0, mx, my, mz,
-                                     mt);
-        } else {
-            id = ((ct0 * s.k[2] + cz0) * s.k[1] + cy0) * s.k[0] + cx0;
-        }
-        s.labels[i] = id;
-        const long long q[5] = {quantise(px), quantise(py), quantise(pz), (long long)t << 20, quantise(v)};
-        run_sample(s, tb, run, id, q, true);
-    }
-    add_run(s, tb, run, true);
-    table_flush(s, tb);
+// ---- passes over boxes of samples ------------------------------------------
+
+// Centres a box's list holds: location, (value of the box's sample type, id).
+struct Cands {
+    float4 c[kCand];
+    float2 v[kCand];
+    uint16_t ax[4][kAxis];  // slabs met, per axis
+    int nax[4];
+    int n;
+    float box[4][8];        // per wave: least and greatest x, y, z, t of its samples
+};
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float x) {
+    const int b = __float_as_int(x);
+    return __int_as_float(__builtin_amdgcn_update_dpp(b, b, CTRL, 0xF, 0xF, false));
+}
+// Greatest value of the wave (uniform): shifts inside the rows of 16 lanes, then
+// the rows' last lanes broadcast onwards; lane 63 has seen every lane.
+__device__ __forceinline__ float wave_max(float x) {
+    x = fmaxf(x, dpp_move<0x111>(x));
+    x = fmaxf(x, dpp_move<0x112>(x));
+    x = fmaxf(x, dpp_move<0x114>(x));
+    x = fmaxf(x, dpp_move<0x118>(x));
+    x = fmaxf(x, dpp_move<0x142>(x));
+    x = fmaxf(x, dpp_move<0x143>(x));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+__device__ __forceinline__ float wave_min(float x) { return -wave_max(-x); }
+
+// Least and greatest |fl(p - c)| over p in [lo, hi]: rounding is monotone in
+// p, so they are taken at the ends (or 0 between them).
+struct Span {
+    float least, most;
+};
+__device__ __forceinline__ Span span(float lo, float hi, float c) {
+    const float a = __fsub_rn(lo, c), b = __fsub_rn(hi, c);
+    return {fmaxf(0.0f, fmaxf(a, -b)), fmaxf(-a, b)};
 }
 
-// Point samples in visiting order (particle-steps sorted by the tile holding
-// them, so that a block meets few centres, with positions, times and values
+// The centres whose window meets the box [lo, hi], into L (any order).  Wave d
+// finds the slabs of axis d that can hold one; the block then tests the centres
+// of their combinations.  Returns the number, or -1 when the list would not
+// fit.  Every thread of the block calls it.
+template <bool FIELD>
+__device__ int list_cands(const DevS& s, Cands& L, const float* lo, const float* hi) {
+    const int lane = threadIdx.x & 63, d = threadIdx.x >> 6;
+    if (threadIdx.x == 0) L.n = 0;
+    int n = 0;
+    for (int i0 = 0; i0 < s.k[d]; i0 += 64) {
+        const int i = i0 + lane;
+        bool ok = false;
+        if (i < s.k[d]) {
+            const float sl = key_float(s.slab[(0 * 4 + d) * s.kmax + i]);
+            const float sh = key_float(s.slab[(1 * 4 + d) * s.kmax + i]);
+            ok = __fsub_rn(lo[d], sh) <= s.C[d] && __fsub_rn(hi[d], sl) >= -s.C[d];
+        }
+        const unsigned long long m = __ballot(ok);
+        const int at = n + __popcll(m & ((1ull << lane) - 1));
+        if (ok && at < kAxis) L.ax[d][at] = (uint16_t)i;
+        n += __popcll(m);
+    }
+    if (lane == 0) L.nax[d] = n;
+    __syncthreads();
+    const int n0 = L.nax[0], n1 = L.nax[1], n2 = L.nax[2], n3 = L.nax[3];
+    if (n0 > kAxis || n1 > kAxis || n2 > kAxis || n3 > kAxis || n0 * n1 * n2 * n3 > kRaw) return -1;
+    for (unsigned r = threadIdx.x; r < (unsigned)(n0 * n1 * n2 * n3); r += kBlock) {
+        unsigned q = r;
+        const int cx = L.ax[0][q % n0];
+        q /= n0;
+        const int cy = L.ax[1][q % n1];
+        q /= n1;
+        const int cz = L.ax[2][q % n2], ct = L.ax[3][q / n2];
+        const int id = ((ct * s.k[2] + cz) * s.k[1] + cy) * s.k[0] + cx;
+        const float4 c = reinterpret_cast<const float4*>(s.cen32)[2 * id];
+        const float2 cv = reinterpret_cast<const float2*>(s.cen32)[4 * id + 2];
+        if (span(lo[0], hi[0], c.x).least <= s.C[0] && span(lo[1], hi[1], c.y).least <= s.C[1] &&
+            span(lo[2], hi[2], c.z).least <= s.C[2] && span(lo[3], hi[3], c.w).least <= s.C[3]) {
+            const int at = atomicAdd(&L.n, 1);
+            if (at < kCand) {
+                L.c[at] = c;
+                L.v[at] = make_float2(FIELD ? cv.y : cv.x, __int_as_float(id));
+            }
+        }
+    }
+    __syncthreads();
+    return L.n > kCand ? -1 : L.n;
+}
+
+// The seed cells of the box as its list (their ids); -1 when they would not
+// fit.  first / num: the cells of the box per axis.
+__device__ int list_cells(const DevS& s, Cands& L, const float* lo, const float* hi, int* first, int* num) {
+    int64_t n = 1;
+    for (int d = 0; d < 4; ++d) {
+        first[d] = seed_cell(lo[d], s.C[d], s.k[d]);
+        num[d] = seed_cell(hi[d], s.C[d], s.k[d]) - first[d] + 1;
+        n *= num[d];
+    }
+    if (n > kCand) return -1;
+    for (int i = threadIdx.x; i < (int)n; i += kBlock) {
+        int q = i;
+        const int cx = first[0] + q % num[0];
+        q /= num[0];
+        const int cy = first[1] + q % num[1];
+        q /= num[1];
+        const int cz = first[2] + q % num[2], ct = first[3] + q / num[2];
+        L.v[i].y = __int_as_float(((ct * s.k[2] + cz) * s.k[1] + cy) * s.k[0] + cx);
+    }
+    __syncthreads();
+    return (int)n;
+}
+
+// Of the n listed centres, those that can win for a sample in the wave's box
+// [lo, hi] with a value in [vlo, vhi], as bits.  The distance's operations are
+// monotone in |p - c| and |v - v_c|, so evaluating them, rounding and all, at the
+// least and greatest of these bounds every sample's distance (the margin of
+// 2^-20 covers the square root's last place); a centre whose lower bound exceeds
+// the upper bound of one whose window holds the whole box loses for every sample.
+__device__ __forceinline__ void keep_cands(const DevS& s, const Cands& L, int n, const float* lo, const float* hi,
+                                           float vlo, float vhi, float wv, unsigned long long* keep) {
+    float lb[kCand / 64], best = INFINITY;
+    bool meets[kCand / 64];
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int r = 0; r < kCand / 64; ++r) {
+        meets[r] = false;
+        lb[r] = 0.0f;
+        if (r * 64 >= n) continue;  // wave-uniform
+        const int i = min(r * 64 + lane, n - 1);
+        const float4 c = L.c[i];
+        const Span x = span(lo[0], hi[0], c.x), y = span(lo[1], hi[1], c.y);
+        const Span z = span(lo[2], hi[2], c.z), t = span(lo[3], hi[3], c.w);
+        const Span v = span(vlo, vhi, L.v[i].x);
+        meets[r] = r * 64 + lane < n && x.least <= s.C[0] && y.least <= s.C[1] && z.least <= s.C[2] &&
+                   t.least <= s.C[3];
+        lb[r] = distance(s, wv * v.least, __builtin_amdgcn_sqrtf(dist2(s, x.least, y.least, z.least, t.least)));
+        const bool covers = meets[r] && x.most <= s.C[0] && y.most <= s.C[1] && z.most <= s.C[2] && t.most <= s.C[3];
+        const float ub = distance(s, wv * v.most, __builtin_amdgcn_sqrtf(dist2(s, x.most, y.most, z.most, t.most)));
+        if (covers) best = fminf(best, ub);
+    }
+    best = wave_min(best);
+    best += best * 0x1p-20f + s.tie;
+#pragma unroll
+    for (int r = 0; r < kCand / 64; ++r) keep[r] = r * 64 < n ? __ballot(meets[r] && !(lb[r] > best)) : 0ull;
+}
+
+// fn(i) for each kept centre's list index i (wave-uniform).
+template <typename Fn>
+__device__ __forceinline__ void each_kept(const unsigned long long* keep, int n, Fn&& fn) {
+#pragma unroll
+    for (int r = 0; r < kCand / 64; ++r) {
+        if (r * 64 >= n) break;
+        for (unsigned long long m = keep[r]; m; m &= m - 1)
+            fn(__builtin_amdgcn_readfirstlane(r * 64 + __builtin_ctzll(m)));
+    }
+}
+
+// The list index of the best of the kept centres for each of the lane's
+// samples (-1: no window holds it).  Only where the two smallest distances are
+// equal (or there are none) are the centres rated again, ties to the lowest id;
+// s.tie covers the square root's scaling of denormals, which the first rating
+// leaves out.
+template <int N>
+__device__ __forceinline__ void rate_samples(const DevS& s, const Cands& L, const unsigned long long* keep, int n,
+                                             const float* px, const float* py, const float* pz, const float* pt,
+                                             const float* v, const bool* live, float wv, int* win) {
+    float d1[N], d2[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        d1[j] = d2[j] = INFINITY;
+        win[j] = -1;
+    }
+    each_kept(keep, n, [&](int i) {
+        const float4 c = L.c[i];
+        const float vc = L.v[i].x;
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const float dx = px[j] - c.x, dy = py[j] - c.y, dz = pz[j] - c.z, dt = pt[j] - c.w;
+            const bool in = fabsf(dx) <= s.C[0] && fabsf(dy) <= s.C[1] && fabsf(dz) <= s.C[2] && fabsf(dt) <= s.C[3];
+            const float S = __builtin_amdgcn_sqrtf(dist2(s, dx, dy, dz, dt));
+            const float D = in ? distance(s, wv * fabsf(v[j] - vc), S) : INFINITY;
+            if (D < d1[j]) win[j] = i;
+            d2[j] = __builtin_amdgcn_fmed3f(d1[j], d2[j], D);
+            d1[j] = fminf(d1[j], D);
+        }
+    });
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const bool close = live[j] && !(d2[j] - d1[j] > s.tie);  // none in a window: NaN
+        if (__ballot(close) == 0) continue;
+        float best_d = INFINITY;
+        int best = 0x7FFFFFFF, at = -1;
+        each_kept(keep, n, [&](int i) {
+            const float4 c = L.c[i];
+            const int id = __float_as_int(L.v[i].y);
+            const float dx = px[j] - c.x, dy = py[j] - c.y, dz = pz[j] - c.z, dt = pt[j] - c.w;
+            if (!(fabsf(dx) <= s.C[0] && fabsf(dy) <= s.C[1] && fabsf(dz) <= s.C[2] && fabsf(dt) <= s.C[3])) return;
+            const float D = distance(s, wv * fabsf(v[j] - L.v[i].x), __fsqrt_rn(dist2(s, dx, dy, dz, dt)));
+            if (D < best_d || (D == best_d && id < best)) {
+                best_d = D;
+                best = id;
+                at = i;
+            }
+        });
+        if (close) win[j] = at;
+    }
+}
+
+// Box shape of the field pass, as logarithms: a lane takes four samples along
+// x, a wave 8 x 2^ly x 2^lz x 2^lt, a block 2^wx waves along x and the others
+// along y, each 2^(iy + iz + it) wave boxes (at most 4,096 samples in all).
+struct FieldBox {
+    int ly, lz, lt, wx, iy, iz, it;
+    int nx, ny, nz, nt;  // boxes per axis
+    int vec;             // rows are whole 16-byte vectors
+    __host__ __device__ int ex() const { return 8 << wx; }
+    __host__ __device__ int ey() const { return 1 << (ly + 2 - wx + iy); }
+    __host__ __device__ int ez() const { return 1 << (lz + iz); }
+    __host__ __device__ int et() const { return 1 << (lt + it); }
+};
+
+// A block's sums of field samples per listed centre, in box coordinates packed
+// into two words: n | x << 13 | y << 30 | t << 47 and value + (z << 44).  At most
+// 4,096 samples, x and y below 32, z and t below 16 keep each field in its bits;
+// the value (44 bits, signed) borrows from z and is taken out first.
+struct FieldRun {
+    int at;  // list index (-1: none)
+    unsigned n, x, y, z, t;
+    long long v;
+};
+
+union FieldLds {
+    struct {
+        Cands L;
+        unsigned long long acc[kCand][2];
+    } b;
+    Table tb;
+};
+
+// Field samples, one box of FieldBox shape per block.  ASSIGN 0: labels from
+// the seed cells.  Bound by the candidates' arithmetic: 9.8 ms for 1.07e9
+// samples and 16,384 centres (256^3 x 64, 4 B read and 4 B written per sample),
+// where testing the slab combinations sample by sample took 66 ms.
+template <int ASSIGN>
+__global__ __launch_bounds__(kBlock) void k_slic_field(DevS s, FieldBox b) {
+    __shared__ FieldLds lds;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t r = blockIdx.x;
+    const int x0 = (int)(r % b.nx) * b.ex();
+    r /= b.nx;
+    const int y0 = (int)(r % b.ny) * b.ey();
+    r /= b.ny;
+    const int z0 = (int)(r % b.nz) * b.ez(), t0 = (int)(r / b.nz) * b.et();
+    // this lane's place in the wave box
+    const int lx = (wave & ((1 << b.wx) - 1)) * 8 + (lane & 1) * 4;
+    const int ly = ((wave >> b.wx) << b.ly) + ((lane >> 1) & ((1 << b.ly) - 1));
+    const int lz = (lane >> (1 + b.ly)) & ((1 << b.lz) - 1), lt = lane >> (1 + b.ly + b.lz);
+    const int steps = 1 << (b.iy + b.iz + b.it);
+    const int sy = 1 << (b.ly + 2 - b.wx);  // y extent of one step
+    const float lo[4] = {(float)x0 + 0.5f, (float)y0 + 0.5f, (float)z0 + 0.5f, (float)t0};
+    const float hi[4] = {(float)min(x0 + b.ex(), s.X) - 0.5f, (float)min(y0 + b.ey(), s.Y) - 0.5f,
+                         (float)min(z0 + b.ez(), s.Z) - 0.5f, (float)min(t0 + b.et(), s.T) - 1.0f};
+    auto step_at = [&](int k, int& y, int& z, int& t) {
+        y = (k & ((1 << b.iy) - 1)) * sy;
+        z = ((k >> b.iy) & ((1 << b.iz) - 1)) << b.lz;
+        t = (k >> (b.iy + b.iz)) << b.lt;
+    };
+    // four samples of the row at (x, y, z, t): values; which exist and are finite
+    auto load = [&](size_t i, bool row, float* v, bool* in, bool* live) {
+        const int x = x0 + lx;
+        if (row && b.vec && x < s.X) {
+            const float4 f = *reinterpret_cast<const float4*>(s.field + i);
+            v[0] = f.x; v[1] = f.y; v[2] = f.z; v[3] = f.w;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            in[j] = row && x + j < s.X;
+            if (!in[j]) v[j] = 0.0f;
+            else if (!b.vec) v[j] = s.field[i + j];
+            live[j] = in[j] && isfinite(v[j]);
+            if (live[j] && !(fabsf(v[j]) < kMaxAbs)) s.counters[SC_RANGE] = 1u;
+        }
+    };
+
+    int n, first[4], num[4];
+    if (ASSIGN) n = s.boxes ? list_cands<true>(s, lds.b.L, lo, hi) : -1;
+    else n = list_cells(s, lds.b.L, lo, hi, first, num);
+    if (n < 0) {  // block-uniform: every sample on its own
+        __syncthreads();
+        table_init(lds.tb);
+        Run run;
+        run.id = -1;
+        for (int k = 0; k < steps; ++k) {
+            int ky, kz, kt;
+            step_at(k, ky, kz, kt);
+            const int y = y0 + ky + ly, z = z0 + kz + lz, t = t0 + kt + lt;
+            const bool row = y < s.Y && z < s.Z && t < s.T;
+            const size_t i = (((size_t)t * s.Z + z) * s.Y + y) * s.X + x0 + lx;
+            float v[4];
+            bool in[4], live[4];
+            load(i, row, v, in, live);
+            for (int j = 0; j < 4; ++j) {
+                if (!in[j]) continue;
+                if (!live[j]) {
+                    s.labels[i + j] = -1;
+                    continue;
+                }
+                const float px = (float)(x0 + lx + j) + 0.5f, py = (float)y + 0.5f, pz = (float)z + 0.5f, pt = (float)t;
+                int id;
+                if (ASSIGN) {
+                    id = assign_one(s, px, py, pz, pt, v[j], true, s.labels[i + j]);
+                } else {
+                    const int cx = seed_cell(px, s.C[0], s.k[0]), cy = seed_cell(py, s.C[1], s.k[1]);
+                    const int cz = seed_cell(pz, s.C[2], s.k[2]), ct = seed_cell(pt, s.C[3], s.k[3]);
+                    id = ((ct * s.k[2] + cz) * s.k[1] + cy) * s.k[0] + cx;
+                }
+                s.labels[i + j] = id;
+                const long long q[5] = {quantise(px), quantise(py), quantise(pz), (long long)t << 20, quantise(v[j])};
+                run_sample(s, lds.tb, run, id, q, true);
+            }
+        }
+        add_run(s, lds.tb, run, true);
+        table_flush(s, lds.tb);
+        return;
+    }
+
+    Cands& L = lds.b.L;
+    for (int i = threadIdx.x; i < n; i += kBlock) lds.b.acc[i][0] = lds.b.acc[i][1] = 0ull;
+    __syncthreads();
+    FieldRun run{-1, 0, 0, 0, 0, 0, 0};
+    auto flush = [&]() {
+        if (run.at < 0) return;
+        atomicAdd(&lds.b.acc[run.at][0], (unsigned long long)run.n | ((unsigned long long)run.x << 13) |
+                                             ((unsigned long long)run.y << 30) | ((unsigned long long)run.t << 47));
+        atomicAdd(&lds.b.acc[run.at][1], (unsigned long long)run.v + ((unsigned long long)run.z << 44));
+    };
+    for (int k = 0; k < steps; ++k) {
+        int ky, kz, kt;
+        step_at(k, ky, kz, kt);
+        const int y = y0 + ky + ly, z = z0 + kz + lz, t = t0 + kt + lt;
+        const bool row = y < s.Y && z < s.Z && t < s.T;
+        const size_t i = (((size_t)t * s.Z + z) * s.Y + y) * s.X + x0 + lx;
+        float v[4];
+        bool in[4], live[4];
+        load(i, row, v, in, live);
+        const float px[4] = {(float)(x0 + lx) + 0.5f, (float)(x0 + lx + 1) + 0.5f, (float)(x0 + lx + 2) + 0.5f,
+                             (float)(x0 + lx + 3) + 0.5f};
+        const float fy = (float)y + 0.5f, fz = (float)z + 0.5f, ft = (float)t;
+        int win[4];
+        if (ASSIGN) {
+            float vlo = INFINITY, vhi = -INFINITY;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (live[j]) {
+                    vlo = fminf(vlo, v[j]);
+                    vhi = fmaxf(vhi, v[j]);
+                }
+            vlo = wave_min(vlo);
+            vhi = wave_max(vhi);
+            // the wave box, cut to the grid (empty only where no sample is live)
+            const int wx = x0 + (wave & ((1 << b.wx) - 1)) * 8, wy = y0 + ky + ((wave >> b.wx) << b.ly);
+            const int wz = z0 + kz, wt = t0 + kt;
+            const float wlo[4] = {(float)wx + 0.5f, (float)wy + 0.5f, (float)wz + 0.5f, (float)wt};
+            const float whi[4] = {(float)min(wx + 8, s.X) - 0.5f, (float)min(wy + (1 << b.ly), s.Y) - 0.5f,
+                                  (float)min(wz + (1 << b.lz), s.Z) - 0.5f, (float)min(wt + (1 << b.lt), s.T) - 1.0f};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) win[j] = -1;
+            if (vlo <= vhi) {  // wave-uniform: some sample is live
+                unsigned long long keep[kCand / 64];
+                keep_cands(s, L, n, wlo, whi, vlo, vhi, s.wf, keep);
+                const float py[4] = {fy, fy, fy, fy}, pz[4] = {fz, fz, fz, fz}, pt[4] = {ft, ft, ft, ft};
+                rate_samples<4>(s, L, keep, n, px, py, pz, pt, v, live, s.wf, win);
+            }
+        } else {
+            const int c = ((seed_cell(ft, s.C[3], s.k[3]) - first[3]) * num[2] +
+                           (seed_cell(fz, s.C[2], s.k[2]) - first[2])) * num[1] +
+                          (seed_cell(fy, s.C[1], s.k[1]) - first[1]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) win[j] = c * num[0] + seed_cell(px[j], s.C[0], s.k[0]) - first[0];
+        }
+        int id[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            id[j] = -1;
+            if (!live[j]) continue;
+            if (win[j] < 0) {  // no window holds it: it keeps its centre, listed or not
+                id[j] = s.labels[i + j];
+                unsigned long long* a = s.acc + (size_t)id[j] * kSlicAcc;
+                atomicAdd(&a[SA_X], (unsigned long long)(long long)quantise(px[j]));
+                atomicAdd(&a[SA_Y], (unsigned long long)(long long)quantise(fy));
+                atomicAdd(&a[SA_Z], (unsigned long long)(long long)quantise(fz));
+                atomicAdd(&a[SA_T], (unsigned long long)((long long)t << 20));
+                atomicAdd(&a[SA_F], (unsigned long long)(long long)quantise(v[j]));
+                atomicAdd(&a[SA_NF], 1ull);
+                continue;
+            }
+            id[j] = __float_as_int(L.v[win[j]].y);
+            if (win[j] != run.at) {
+                flush();
+                run = FieldRun{win[j], 0, 0, 0, 0, 0, 0};
+            }
+            run.n += 1;
+            run.x += lx + j;
+            run.y += ky + ly;
+            run.z += kz + lz;
+            run.t += kt + lt;
+            run.v += quantise(v[j]);
+        }
+        if (b.vec && in[0]) {
+            *reinterpret_cast<int4*>(s.labels + i) = make_int4(id[0], id[1], id[2], id[3]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (in[j]) s.labels[i + j] = id[j];
+        }
+    }
+    flush();
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += kBlock) {
+        const unsigned long long a = lds.b.acc[i][0], w = lds.b.acc[i][1];
+        const long long cnt = (long long)(a & 0x1FFF);
+        if (!cnt) continue;
+        const long long sx = (long long)((a >> 13) & 0x1FFFF), sy2 = (long long)((a >> 30) & 0x1FFFF);
+        const long long st = (long long)(a >> 47);
+        const long long sv = (long long)(w << 20) >> 20;  // the low 44 bits, signed
+        const long long sz = (long long)(w - (unsigned long long)sv) >> 44;
+        unsigned long long* o = s.acc + (size_t)__float_as_int(L.v[i].y) * kSlicAcc;
+        // q(x0 + x + 0.5) = (2 (x0 + x) + 1) 2^19
+        atomicAdd(&o[SA_X], (unsigned long long)((2 * sx + (2 * x0 + 1) * cnt) << 19));
+        atomicAdd(&o[SA_Y], (unsigned long long)((2 * sy2 + (2 * y0 + 1) * cnt) << 19));
+        atomicAdd(&o[SA_Z], (unsigned long long)((2 * sz + (2 * z0 + 1) * cnt) << 19));
+        atomicAdd(&o[SA_T], (unsigned long long)((st + t0 * cnt) << 20));
+        atomicAdd(&o[SA_F], (unsigned long long)sv);
+        atomicAdd(&o[SA_NF], (unsigned long long)cnt);
+    }
+}
+
+// A block's sums of point samples per listed centre: x, y, z, value, and
+// t | n << 48 (1,024 samples with 0 <= t < 2^31 keep t below 2^41).
+struct PointRun {
+    int at;
+    unsigned n;
+    long long q[5];
+};
+
+union PointLds {
+    struct {
+        Cands L;
+        unsigned long long acc[kCand][5];
+    } b;
+    Table tb;
+};
+
+// Point samples in visiting order (particle-steps sorted by the sub-box holding
+// them, so that a wave's are close together, with positions, times and values
 // copied in that order): block b takes positions [b * 1024, (b + 1) * 1024),
 // 4 consecutive ones per thread.  Their labels follow the field's, in the
-// same order.
-__global__ __launch_bounds__(kBlock) void k_slic_points(DevS s, int assign) {
-    __shared__ Table tb;
-    table_init(tb);
+// same order.  Bound like the field pass: 9.1 ms for 2.7e8 points and 16,384
+// centres, 24 ms sample by sample.
+template <int ASSIGN>
+__global__ __launch_bounds__(kBlock) void k_slic_points(DevS s) {
+    __shared__ PointLds lds;
+    const int wave = threadIdx.x >> 6;
     const uint64_t V = (uint64_t)s.X * s.Y * s.Z * s.T;
     const uint64_t Q = (uint64_t)s.Tp * s.P;
     const uint64_t base = (uint64_t)blockIdx.x * (kBlock * kPer) + (uint64_t)threadIdx.x * kPer;
-    Run run;
-    run.id = -1;
-    for (int j = 0; j < kPer; ++j) {
-        const uint64_t o = base + j;
-        if (o >= Q) break;
-        const float4 pp = s.spos[o];
-        const float v = s.sattr[o];
-        const float px = pp.x, py = pp.y, pz = pp.z, pt = pp.w;
-        int32_t* lab = s.labels + V + o;
-        if (!(isfinite(v) && isfinite(px) && isfinite(py) && isfinite(pz))) {
-            *lab = -1;
+    int32_t* lab = s.labels + V + base;
+    float px[4], py[4], pz[4], pt[4], v[4];
+    bool in[4], live[4];
+    float lo[4] = {INFINITY, INFINITY, INFINITY, INFINITY}, hi[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    float vlo = INFINITY, vhi = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        in[j] = base + j < Q;
+        const float4 pp = in[j] ? s.spos[base + j] : make_float4(0.f, 0.f, 0.f, 0.f);
+        v[j] = in[j] ? s.sattr[base + j] : 0.0f;
+        px[j] = pp.x; py[j] = pp.y; pz[j] = pp.z; pt[j] = pp.w;
+        live[j] = in[j] && isfinite(v[j]) && isfinite(pp.x) && isfinite(pp.y) && isfinite(pp.z);
+        if (!live[j]) continue;
+        if (!(fabsf(v[j]) < kMaxAbs && fabsf(pp.x) < kMaxAbs && fabsf(pp.y) < kMaxAbs && fabsf(pp.z) < kMaxAbs))
+            s.counters[SC_RANGE] = 1u;
+        const float p[4] = {pp.x, pp.y, pp.z, pp.w};
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            lo[d] = fminf(lo[d], p[d]);
+            hi[d] = fmaxf(hi[d], p[d]);
+        }
+        vlo = fminf(vlo, v[j]);
+        vhi = fmaxf(vhi, v[j]);
+    }
+    vlo = wave_min(vlo);
+    vhi = wave_max(vhi);
+    float blo[4], bhi[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        lo[d] = wave_min(lo[d]);
+        hi[d] = wave_max(hi[d]);
+        if ((threadIdx.x & 63) == 0) {
+            lds.b.L.box[wave][d] = lo[d];
+            lds.b.L.box[wave][4 + d] = hi[d];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        blo[d] = bhi[d] = 0.0f;
+        float a = INFINITY, c = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            a = fminf(a, lds.b.L.box[w][d]);
+            c = fmaxf(c, lds.b.L.box[w][4 + d]);
+        }
+        if (a <= c) {  // some sample of the block is live
+            blo[d] = a;
+            bhi[d] = c;
+        }
+    }
+
+    int n, first[4], num[4];
+    if (ASSIGN) n = s.boxes ? list_cands<false>(s, lds.b.L, blo, bhi) : -1;
+    else n = list_cells(s, lds.b.L, blo, bhi, first, num);
+    if (n < 0) {  // block-uniform: every sample on its own
+        __syncthreads();
+        table_init(lds.tb);
+        Run run;
+        run.id = -1;
+        for (int j = 0; j < 4; ++j) {
+            if (!in[j]) continue;
+            if (!live[j]) {
+                lab[j] = -1;
+                continue;
+            }
+            int id;
+            if (ASSIGN) {
+                id = assign_one(s, px[j], py[j], pz[j], pt[j], v[j], false, lab[j]);
+            } else {
+                const int cx = seed_cell(px[j], s.C[0], s.k[0]), cy = seed_cell(py[j], s.C[1], s.k[1]);
+                const int cz = seed_cell(pz[j], s.C[2], s.k[2]), ct = seed_cell(pt[j], s.C[3], s.k[3]);
+                id = ((ct * s.k[2] + cz) * s.k[1] + cy) * s.k[0] + cx;
+            }
+            lab[j] = id;
+            const long long q[5] = {quantise(px[j]), quantise(py[j]), quantise(pz[j]), quantise(pt[j]), quantise(v[j])};
+            run_sample(s, lds.tb, run, id, q, false);
+        }
+        add_run(s, lds.tb, run, false);
+        table_flush(s, lds.tb);
+        return;
+    }
+
+    Cands& L = lds.b.L;
+    for (int i = threadIdx.x; i < n * 5; i += kBlock) (&lds.b.acc[0][0])[i] = 0ull;
+    __syncthreads();
+    int win[4] = {-1, -1, -1, -1};
+    if (ASSIGN) {
+        if (vlo <= vhi) {  // wave-uniform
+            unsigned long long keep[kCand / 64];
+            keep_cands(s, L, n, lo, hi, vlo, vhi, s.wp, keep);
+            rate_samples<4>(s, L, keep, n, px, py, pz, pt, v, live, s.wp, win);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (live[j])
+                win[j] = (((seed_cell(pt[j], s.C[3], s.k[3]) - first[3]) * num[2] +
+                           (seed_cell(pz[j], s.C[2], s.k[2]) - first[2])) * num[1] +
+                          (seed_cell(py[j], s.C[1], s.k[1]) - first[1])) * num[0] +
+                         (seed_cell(px[j], s.C[0], s.k[0]) - first[0]);
+    }
+    PointRun run{-1, 0, {0, 0, 0, 0, 0}};
+    auto flush = [&]() {
+        if (run.at < 0) return;
+        unsigned long long* a = lds.b.acc[run.at];
+        atomicAdd(&a[0], (unsigned long long)run.q[0]);
+        atomicAdd(&a[1], (unsigned long long)run.q[1]);
+        atomicAdd(&a[2], (unsigned long long)run.q[2]);
+        atomicAdd(&a[3], (unsigned long long)run.q[3] + ((unsigned long long)run.n << 48));
+        atomicAdd(&a[4], (unsigned long long)run.q[4]);
+    };
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        if (!in[j]) continue;
+        if (!live[j]) {
+            lab[j] = -1;
             continue;
         }
-        if (!(fabsf(v) < kMaxAbs && fabsf(px) < kMaxAbs && fabsf(py) < kMaxAbs && fabsf(pz) < kMaxAbs))
-            s.counters[SC_RANGE] = 1u;
-        int id;
-        if (assign) {
-            id = assign_one(s, px, py, pz, pt, v, false, *lab);
-        } else {
-            const int cx = seed_cell(px, s.C[0], s.k[0]), cy = seed_cell(py, s.C[1], s.k[1]);
-            const int cz = seed_cell(pz, s.C[2], s.k[2]), ct = seed_cell(pt, s.C[3], s.k[3]);
-            id = ((ct * s.k[2] + cz) * s.k[1] + cy) * s.k[0] + cx;
+        const int q[5] = {quantise(px[j]), quantise(py[j]), quantise(pz[j]), quantise(pt[j]), quantise(v[j])};
+        if (win[j] < 0) {  // no window holds it: it keeps its centre, listed or not
+            unsigned long long* a = s.acc + (size_t)lab[j] * kSlicAcc;
+            atomicAdd(&a[SA_X], (unsigned long long)(long long)q[0]);
+            atomicAdd(&a[SA_Y], (unsigned long long)(long long)q[1]);
+            atomicAdd(&a[SA_Z], (unsigned long long)(long long)q[2]);
+            atomicAdd(&a[SA_T], (unsigned long long)(long long)q[3]);
+            atomicAdd(&a[SA_P], (unsigned long long)(long long)q[4]);
+            atomicAdd(&a[SA_NP], 1ull);
+            continue;
         }
-        *lab = id;
-        const long long q[5] = {quantise(px), quantise(py), quantise(pz), quantise(pt), quantise(v)};
-        run_sample(s, tb, run, id, q, false);
+        lab[j] = __float_as_int(L.v[win[j]].y);
+        if (win[j] != run.at) {
+            flush();
+            run = PointRun{win[j], 0, {0, 0, 0, 0, 0}};
+        }
+        run.n += 1;
+#pragma unroll
+        for (int e = 0; e < 5; ++e) run.q[e] += q[e];
     }
-    add_run(s, tb, run, false);
-    table_flush(s, tb);
+    flush();
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += kBlock) {
+        const unsigned long long* a = lds.b.acc[i];
+        const unsigned long long cnt = a[3] >> 48;
+        if (!cnt) continue;
+        unsigned long long* o = s.acc + (size_t)__float_as_int(L.v[i].y) * kSlicAcc;
+        atomicAdd(&o[SA_X], a[0]);
+        atomicAdd(&o[SA_Y], a[1]);
+        atomicAdd(&o[SA_Z], a[2]);
+        atomicAdd(&o[SA_T], a[3] & 0xFFFFFFFFFFFFull);
+        atomicAdd(&o[SA_P], a[4]);
+        atomicAdd(&o[SA_NP], cnt);
+    }
 }
 
 // One thread per centre.  seed: write the seed centre first (its location
@@ -968,17 +1478,52 @@ int launch_slic_order(const uint32_t* bins, const float* xyz, const float* attr,
     return (int)hipGetLastError();
 }
 
-void launch_slic_init(const DevS& s, hipStream_t st) {
-    const uint64_t V = (uint64_t)s.X * s.Y * s.Z * s.T, Q = (uint64_t)s.Tp * s.P;
-    if (V) hipLaunchKernelGGL(k_slic_field, dim3(blocks_for(V, kBlock * kPer)), dim3(kBlock), 0, st, s, 0);
-    if (Q) hipLaunchKernelGGL(k_slic_points, dim3(blocks_for(Q, kBlock * kPer)), dim3(kBlock), 0, st, s, 0);
+// Box shape of the field pass.  The wave box of 8 x 4 x 4 x 2 samples is compact
+// in the distance (time counts c_f times) and reads whole 32-byte sectors; a
+// planar grid gives z's share to y and t.  Four waves lie along x, so that a
+// block reads whole 128-byte lines, unless the grid is too narrow for that.  A
+// block takes four wave boxes per wave, which spreads its list over 4,096
+// samples, as long as that leaves 2,048 blocks (8 per CU); below that one.
+static FieldBox field_box(const DevS& s) {
+    FieldBox b{};
+    b.ly = s.Z > 1 ? 2 : 3;
+    b.lz = s.Z > 1 ? 2 : 0;
+    b.lt = s.Z > 1 ? 1 : 2;
+    b.wx = s.X > 16 ? 2 : (s.X > 8 ? 1 : 0);
+    b.vec = (s.X & 3) == 0;
+    auto shape = [&](int iy, int iz, int it) {
+        b.iy = iy;
+        b.iz = iz;
+        b.it = it;
+        b.nx = (s.X + b.ex() - 1) / b.ex();
+        b.ny = (s.Y + b.ey() - 1) / b.ey();
+        b.nz = (s.Z + b.ez() - 1) / b.ez();
+        b.nt = (s.T + b.et() - 1) / b.et();
+        return (uint64_t)b.nx * b.ny * b.nz * b.nt;
+    };
+    const uint64_t big = s.Z > 1 ? shape(1, 1, 0) : shape(1, 0, 1);
+    if (big < 2048) shape(0, 0, 0);
+    return b;
 }
 
-void launch_slic_assign(const DevS& s, hipStream_t st) {
+static void launch_pass(const DevS& s, int assign, hipStream_t st) {
     const uint64_t V = (uint64_t)s.X * s.Y * s.Z * s.T, Q = (uint64_t)s.Tp * s.P;
-    if (V) hipLaunchKernelGGL(k_slic_field, dim3(blocks_for(V, kBlock * kPer)), dim3(kBlock), 0, st, s, 1);
-    if (Q) hipLaunchKernelGGL(k_slic_points, dim3(blocks_for(Q, kBlock * kPer)), dim3(kBlock), 0, st, s, 1);
+    if (V) {
+        const FieldBox b = field_box(s);
+        const uint32_t n = (uint32_t)b.nx * b.ny * b.nz * b.nt;
+        if (assign) hipLaunchKernelGGL(k_slic_field<1>, dim3(n), dim3(kBlock), 0, st, s, b);
+        else hipLaunchKernelGGL(k_slic_field<0>, dim3(n), dim3(kBlock), 0, st, s, b);
+    }
+    if (Q) {
+        const unsigned n = blocks_for(Q, kBlock * kPer);
+        if (assign) hipLaunchKernelGGL(k_slic_points<1>, dim3(n), dim3(kBlock), 0, st, s);
+        else hipLaunchKernelGGL(k_slic_points<0>, dim3(n), dim3(kBlock), 0, st, s);
+    }
 }
+
+void launch_slic_init(const DevS& s, hipStream_t st) { launch_pass(s, 0, st); }
+
+void launch_slic_assign(const DevS& s, hipStream_t st) { launch_pass(s, 1, st); }
 
 __global__ void k_slic_slab_reset(DevS s) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
