@@ -276,7 +276,7 @@ struct mf4d_ctx {
 
     // particles as loaded, for the clustering: xyz [T][P][3] then attr [T][P]
     float* praw = nullptr;
-    uint32_t* porder = nullptr;  // point samples sorted by tile (built on the first clustering)
+    uint32_t* porder = nullptr;  // point samples sorted by sub-box (built on the first clustering)
     float4* spos = nullptr;      // their positions and times in that order
     float* sattr = nullptr;      // their values in that order
     // 4D SLIC clustering (Section 3.2)
@@ -2263,15 +2263,15 @@ int mf4d_slic_run(mf4d_ctx* c, int* iterations) {
         c->slabels_n = V + Qp;
     }
     if (P > 0 && !c->porder) {
-        // point samples in tile order, so that a block of them meets few centres
+        // point samples in sub-box order, so that a block of them meets few centres
         int rc = dev_alloc(&c->porder, Qp);
         if (!rc) rc = dev_alloc(&c->spos, Qp);
         if (!rc) rc = dev_alloc(&c->sattr, Qp);
         uint32_t* scratch = nullptr;
-        if (!rc) rc = dev_alloc(&scratch, (size_t)g.NT + 1 + 1 + 1025);
+        if (!rc) rc = dev_alloc(&scratch, (size_t)slic_order_keys(g.NT, g.logBT) + 1 + 1024);
         if (!rc) {
             const int e = launch_slic_order(c->bins, c->praw, c->praw + (size_t)3 * Qp, P, c->pg.Tpad, c->pg.T,
-                                            c->pg.tr, 5 + 6 + g.logBT, g.NT, scratch, c->porder, c->spos,
+                                            c->pg.tr, g.logBT, g.NT, scratch, c->porder, c->spos,
                                             c->sattr, c->stream);
             if (e != hipSuccess) rc = fail(MF4D_ERR_HIP, "clustering order: %s", hipGetErrorString((hipError_t)e));
         }

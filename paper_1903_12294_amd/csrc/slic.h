@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "mf4d_internal.h"
+
 namespace mf4d {
 
 // Accumulators of one centre: quantised sums (x, y, z, t, point value, field
@@ -78,16 +80,17 @@ struct DevM {
 // compute the features' statistics into m.out.  Errors as a HIP result.
 int launch_slic_merge(const DevS& s, const DevM& m, hipStream_t st);
 
-// Visiting order of the point samples: particle-steps sorted by the tile
-// holding them (tile = voxel bit >> shift), steps in no voxel last; order[t *
-// P + p] = the position of that step in the visiting order.  Their positions
-// and times (spos; time t / r in field steps, r particle steps per field step)
-// and values (sattr) are copied in that order from xyz [T][P][3] and attr
-// [T][P] (T particle steps).  bins: [P][Tpad] voxel bits (~0u: none);
-// scratch: nb + 1 + 1025 words, nb = number of tiles + 1.  Errors as a HIP
-// result.
+// Visiting order of the point samples: particle-steps sorted by the sub-box (8 x
+// 4 x 4 x 4 voxel-steps) holding them, tile by tile, steps in no voxel last;
+// order[t * P + p] = the position of that step in the visiting order.  Their
+// positions and times (spos; time t / r in field steps, r particle steps per
+// field step) and values (sattr) are copied in that order from xyz [T][P][3]
+// and attr [T][P] (T particle steps).  bins: [P][Tpad] voxel bits of tiles with
+// 2^logBT steps (~0u: none); scratch: slic_order_keys() + 1 + 1024 words.  Errors
+// as a HIP result.
+inline uint32_t slic_order_keys(uint32_t ntiles, int logBT) { return (ntiles << (2 + logBT)) + 1; }
 int launch_slic_order(const uint32_t* bins, const float* xyz, const float* attr, int64_t P, int Tpad,
-                      int T, int r, int shift, uint32_t ntiles, uint32_t* scratch, uint32_t* order,
+                      int T, int r, int logBT, uint32_t ntiles, uint32_t* scratch, uint32_t* order,
                       float4* spos, float* sattr, hipStream_t st);
 // Point labels from visiting order back to [T][P]: out[q] = in[order[q]]
 // (order as written by launch_slic_order).
