@@ -294,7 +294,9 @@ struct mf4d_ctx {
     long long* scnt = nullptr;
     uint32_t* scounters = nullptr;
     uint32_t* h_scounters = nullptr;
-    uint32_t* sslab = nullptr;  // 8 x 4096 slab bounds, then 8 x 4096 reach ranges (k_d <= 4096)
+    uint32_t* sslab = nullptr;  // two buffers of 8 x 4096 slab bounds, then 8 x 4096 reach ranges (k_d <= 4096)
+    uint32_t* sover = nullptr;  // boxes a pass leaves to the search sample by sample (sized by the samples)
+    size_t sover_n = 0;
     unsigned long long* slsum = nullptr;  // [K][8] sums of the last update
     // cluster merging (Section 3.3), sized by K
     char* mbuf = nullptr;
@@ -310,6 +312,8 @@ namespace {
 void free_slic(mf4d_ctx* c) {
     dev_free(c->slabels);
     c->slabels_n = 0;
+    dev_free(c->sover);
+    c->sover_n = 0;
     c->slic_done = false;
     c->merged = false;
 }
@@ -2220,7 +2224,7 @@ int mf4d_slic_set_params(mf4d_ctx* c, const int* k4, float w_d, float w_f, float
         if (!rc) rc = dev_alloc(&c->scnt, (size_t)K * 2);
         if (!rc) rc = dev_alloc(&c->slsum, (size_t)K * kSlicAcc);
         if (!rc && !c->scounters) rc = dev_alloc(&c->scounters, (size_t)kSlicCounters);
-        if (!rc && !c->sslab) rc = dev_alloc(&c->sslab, (size_t)16 * 4096);
+        if (!rc && !c->sslab) rc = dev_alloc(&c->sslab, (size_t)24 * 4096);
         if (!rc && !c->h_scounters &&
             hipHostMalloc((void**)&c->h_scounters, kSlicCounters * sizeof(uint32_t), hipHostMallocDefault) != hipSuccess)
             rc = fail(MF4D_ERR_OOM, "pinned counters");
@@ -2303,8 +2307,8 @@ int mf4d_slic_run(mf4d_ctx* c, int* iterations) {
     s.cen32 = c->scen32;
     s.cnt = c->scnt;
     s.counters = c->scounters;
-    s.slab = c->sslab;
-    s.reach = reinterpret_cast<int*>(c->sslab + 8 * 4096);
+    s.host = c->h_scounters;
+    s.reach = reinterpret_cast<int*>(c->sslab + 16 * 4096);
     // debug switch: MF4D_SLIC_MASK_SLABS below 32 searches sample by sample, 0
     // through the general candidate loop (the tests compare the paths)
     s.mask_slabs = 32;
@@ -2315,28 +2319,38 @@ int mf4d_slic_run(mf4d_ctx* c, int* iterations) {
     s.tie = s.wd * 1e-18f;
     s.lsum = c->slsum;
     s.kmax = std::max(std::max(c->sk[0], c->sk[1]), std::max(c->sk[2], c->sk[3]));
+    const size_t boxes = (size_t)slic_boxes(s) + 1;
+    if (c->sover_n < boxes) {
+        dev_free(c->sover);
+        c->sover_n = 0;
+        int rc = dev_alloc(&c->sover, boxes);
+        if (rc) return rc;
+        c->sover_n = boxes;
+    }
+    s.over = c->sover;
     hipStream_t st = c->stream;
-    launch_fill_u32((uint32_t*)c->sacc, 0, (uint64_t)c->sK * kSlicAcc * 2, st);
-    launch_fill_u32(c->scounters, 0, kSlicCounters, st);
-    launch_slic_init(s, st);
-    launch_slic_update(s, 1, st);
-    int it = 0;
-    while (it < c->smax_iter) {
-        launch_fill_u32(c->scounters + SC_MOVED, 0, 1, st);
-        launch_slic_assign(s, st);
-        ++it;
-        launch_slic_update(s, 0, st);
-        HIP_TRY(hipMemcpyAsync(c->h_scounters, c->scounters, kSlicCounters * sizeof(uint32_t),
-                               hipMemcpyDeviceToHost, st));
+    // the passes read one slab buffer, the update that ends them fills the other
+    uint32_t* slab[2] = {c->sslab, c->sslab + 8 * 4096};
+    s.slab = slab[0];
+    s.slab_next = slab[1];
+    for (int j = 0; j < kSlicCounters; ++j) c->h_scounters[j] = 0;  // (no kernel of an earlier run is left)
+    launch_slic_begin(s, st);
+    // Iterations are queued kAhead at a time where waiting for each costs more
+    // than an iteration that finds the run done (four empty launches, about 12 us
+    // against about 25 us per wait, measured at 32^3 x 8); with more samples the
+    // empty launches' blocks cost more, and the wait is small beside the passes.
+    constexpr int kAhead = 4;
+    const int ahead = V + Qp <= (size_t)1 << 22 ? kAhead : 1;
+    int queued = 0;
+    do {
+        for (int j = 0; j < ahead && queued < c->smax_iter; ++j, ++queued) {
+            std::swap(s.slab, s.slab_next);
+            launch_slic_iteration(s, st);
+        }
         int rc = sync(c);
         if (rc) return rc;
-        if (c->h_scounters[SC_RANGE]) break;
-        if (c->h_scounters[SC_MOVED] == 0) break;
-    }
-    HIP_TRY(hipMemcpyAsync(c->h_scounters, c->scounters, kSlicCounters * sizeof(uint32_t),
-                           hipMemcpyDeviceToHost, st));
-    int rc = sync(c);
-    if (rc) return rc;
+    } while (queued < c->smax_iter && !c->h_scounters[SC_DONE]);
+    const int it = (int)c->h_scounters[SC_ITERS];
     if (c->h_scounters[SC_RANGE])
         return fail(MF4D_ERR_RANGE, "a coordinate or value with |v| >= 2048: the clustering's exact sums could overflow");
     c->slic_iters = it;

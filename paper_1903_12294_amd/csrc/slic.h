@@ -16,7 +16,10 @@ enum SlicAcc : int { SA_X = 0, SA_Y, SA_Z, SA_T, SA_P, SA_F, SA_NF, SA_NP, kSlic
 enum SlicCounter : int {
     SC_MOVED = 0,   // centres whose values changed by more than eps this update
     SC_RANGE = 1,   // a value outside |v| < 2048 was met (quantised sums could overflow)
-    kSlicCounters = 4
+    SC_ITERS = 2,   // assignment passes done
+    SC_DONE = 3,    // nothing moved, or out of range: passes still queued do nothing
+    SC_TICKET = 4,  // blocks of the update that have finished
+    kSlicCounters = 8
 };
 
 struct DevS {
@@ -40,7 +43,8 @@ struct DevS {
     // Per axis d and seed-grid slab i (centres with cell index i on axis d):
     // the least and greatest centre coordinate, as order-preserving keys,
     // at [(0 * 4 + d) * kmax + i] (least) and [(1 * 4 + d) * kmax + i].
-    uint32_t* slab;
+    // Two buffers: the passes read slab, the update that ends them fills slab_next.
+    uint32_t *slab, *slab_next;
     // Per axis d and seed cell j: the least and greatest slab index whose
     // centres can reach a sample of cell j, at [(d * kmax + j) * 2] and + 1
     // (empty: least > greatest).
@@ -51,6 +55,8 @@ struct DevS {
     float tie;           // distances this close (w_d 1e-18) are compared again with denormals scaled
     int kmax;            // max(k[0..3])
     uint32_t* counters;  // SlicCounter
+    uint32_t* host;      // pinned host memory: SC_RANGE, SC_ITERS, SC_DONE after each update
+    uint32_t* over;      // boxes whose list did not fit: their number, then slic_boxes() entries
     unsigned long long* lsum;  // [K][kSlicAcc]: the sums of the last update (for the features)
 };
 
@@ -99,13 +105,15 @@ void launch_slic_unsort(const int32_t* in, const uint32_t* order, uint64_t Q, in
 // feature id (feat[label]) where the particle has that feature at t - 1 or
 // t + 1, else -1.
 void launch_slic_segments(int32_t* lab, const int32_t* feat, int T, int64_t P, hipStream_t st);
-// Labels from the seed cells, and their sums.
-void launch_slic_init(const DevS& s, hipStream_t st);
-// One assignment pass over both sample types, with the sums of the new labels.
-void launch_slic_assign(const DevS& s, hipStream_t st);
-// Centres from the sums (the sums cleared), compared with the previous ones,
-// and the slab bounds of the new centres.  seed: 1 to write the seed centres
-// first (before the first update).
-void launch_slic_update(const DevS& s, int seed, hipStream_t st);
+// Boxes of samples a pass takes (field boxes and point blocks).
+uint32_t slic_boxes(const DevS& s);
+// Start of a run: sums and counters cleared, labels from the seed cells, their
+// sums, and the first centres (with slab bounds in s.slab_next).
+void launch_slic_begin(const DevS& s, hipStream_t st);
+// One iteration: an assignment pass over both sample types with the sums of the
+// new labels, then the centres from the sums (the sums cleared), compared with
+// the previous ones, and the slab bounds of the new centres.  Does nothing once
+// SC_DONE is set, so that iterations can be queued ahead of the host.
+void launch_slic_iteration(const DevS& s, hipStream_t st);
 
 }  // namespace mf4d

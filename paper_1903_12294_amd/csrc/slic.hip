@@ -15,8 +15,8 @@
 // sub-box), lists the centres whose windows meet the box, and each wave keeps
 // of these, per 256 samples, the ones that can win for any of them (bounds of
 // the distance over the wave's box).  A sample so rates about ten centres
-// instead of testing the hundreds of its neighbourhood.  A block whose list
-// would not fit searches sample by sample.
+// instead of testing the hundreds of its neighbourhood.  Boxes whose list would
+// not fit are noted, and a third kernel searches them sample by sample.
 //
 // Arithmetic that decides a label is fp32 in a fixed order, with the products
 // fused into the sums and the hardware's square root (1 ulp):
@@ -248,6 +248,14 @@ __device__ __forceinline__ void run_sample(const DevS& s, Table& tb, Run& r, int
     ++r.n;
 }
 
+// One sample straight to its centre's sums.
+__device__ __forceinline__ void add_sample(const DevS& s, int id, const int* q, bool field) {
+    unsigned long long* a = s.acc + (size_t)id * kSlicAcc;
+    for (int k = 0; k < 4; ++k) atomicAdd(&a[SA_X + k], (unsigned long long)(long long)q[k]);
+    atomicAdd(&a[field ? SA_F : SA_P], (unsigned long long)(long long)q[4]);
+    atomicAdd(&a[field ? SA_NF : SA_NP], 1ull);
+}
+
 __device__ __forceinline__ void table_flush(const DevS& s, Table& tb) {
     __syncthreads();
     for (int i = threadIdx.x; i < kTab * kSlicAcc; i += blockDim.x) {
@@ -371,19 +379,23 @@ __device__ int list_cells(const DevS& s, Cands& L, const float* lo, const float*
 }
 
 // Of the n listed centres, those that can win for a sample in the wave's box
-// [lo, hi] with a value in [vlo, vhi], as bits.  The distance's operations are
-// monotone in |p - c| and |v - v_c|, so evaluating them, rounding and all, at the
-// least and greatest of these bounds every sample's distance (the margin of
-// 2^-20 covers the square root's last place); a centre whose lower bound exceeds
-// the upper bound of one whose window holds the whole box loses for every sample.
+// [lo, hi] with a value in [vlo, vhi], as bits: `whole` the ones whose windows
+// hold the whole box, `part` the others.  The distance's operations are monotone
+// in |p - c| and |v - v_c|, so evaluating them, rounding and all, at the least and
+// greatest of these bounds every sample's distance (the margin of 2^-20 covers the
+// square root's last place); a centre whose lower bound exceeds the upper bound of
+// one whose window holds the whole box loses for every sample.
+struct Kept {
+    unsigned long long whole[kCand / 64], part[kCand / 64];
+};
 __device__ __forceinline__ void keep_cands(const DevS& s, const Cands& L, int n, const float* lo, const float* hi,
-                                           float vlo, float vhi, float wv, unsigned long long* keep) {
+                                           float vlo, float vhi, float wv, Kept& keep) {
     float lb[kCand / 64], best = INFINITY;
-    bool meets[kCand / 64];
+    bool meets[kCand / 64], covers[kCand / 64];
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int r = 0; r < kCand / 64; ++r) {
-        meets[r] = false;
+        meets[r] = covers[r] = false;
         lb[r] = 0.0f;
         if (r * 64 >= n) continue;  // wave-uniform
         const int i = min(r * 64 + lane, n - 1);
@@ -394,23 +406,27 @@ __device__ __forceinline__ void keep_cands(const DevS& s, const Cands& L, int n,
         meets[r] = r * 64 + lane < n && x.least <= s.C[0] && y.least <= s.C[1] && z.least <= s.C[2] &&
                    t.least <= s.C[3];
         lb[r] = distance(s, wv * v.least, __builtin_amdgcn_sqrtf(dist2(s, x.least, y.least, z.least, t.least)));
-        const bool covers = meets[r] && x.most <= s.C[0] && y.most <= s.C[1] && z.most <= s.C[2] && t.most <= s.C[3];
+        covers[r] = meets[r] && x.most <= s.C[0] && y.most <= s.C[1] && z.most <= s.C[2] && t.most <= s.C[3];
         const float ub = distance(s, wv * v.most, __builtin_amdgcn_sqrtf(dist2(s, x.most, y.most, z.most, t.most)));
-        if (covers) best = fminf(best, ub);
+        if (covers[r]) best = fminf(best, ub);
     }
     best = wave_min(best);
     best += best * 0x1p-20f + s.tie;
 #pragma unroll
-    for (int r = 0; r < kCand / 64; ++r) keep[r] = r * 64 < n ? __ballot(meets[r] && !(lb[r] > best)) : 0ull;
+    for (int r = 0; r < kCand / 64; ++r) {
+        const bool k = meets[r] && !(lb[r] > best);
+        keep.whole[r] = r * 64 < n ? __ballot(k && covers[r]) : 0ull;
+        keep.part[r] = r * 64 < n ? __ballot(k && !covers[r]) : 0ull;
+    }
 }
 
-// fn(i) for each kept centre's list index i (wave-uniform).
+// fn(i) for each set bit's list index i (wave-uniform).
 template <typename Fn>
-__device__ __forceinline__ void each_kept(const unsigned long long* keep, int n, Fn&& fn) {
+__device__ __forceinline__ void each_kept(const unsigned long long* bits, int n, Fn&& fn) {
 #pragma unroll
     for (int r = 0; r < kCand / 64; ++r) {
         if (r * 64 >= n) break;
-        for (unsigned long long m = keep[r]; m; m &= m - 1)
+        for (unsigned long long m = bits[r]; m; m &= m - 1)
             fn(__builtin_amdgcn_readfirstlane(r * 64 + __builtin_ctzll(m)));
     }
 }
@@ -421,36 +437,42 @@ __device__ __forceinline__ void each_kept(const unsigned long long* keep, int n,
 // s.tie covers the square root's scaling of denormals, which the first rating
 // leaves out.
 template <int N>
-__device__ __forceinline__ void rate_samples(const DevS& s, const Cands& L, const unsigned long long* keep, int n,
-                                             const float* px, const float* py, const float* pz, const float* pt,
-                                             const float* v, const bool* live, float wv, int* win) {
+__device__ __forceinline__ void rate_samples(const DevS& s, const Cands& L, const Kept& keep, int n, const float* px,
+                                             const float* py, const float* pz, const float* pt, const float* v,
+                                             const bool* live, float wv, int* win) {
     float d1[N], d2[N];
 #pragma unroll
     for (int j = 0; j < N; ++j) {
         d1[j] = d2[j] = INFINITY;
         win[j] = -1;
     }
-    each_kept(keep, n, [&](int i) {
+    auto rate = [&](int i, bool test) {
         const float4 c = L.c[i];
         const float vc = L.v[i].x;
 #pragma unroll
         for (int j = 0; j < N; ++j) {
             const float dx = px[j] - c.x, dy = py[j] - c.y, dz = pz[j] - c.z, dt = pt[j] - c.w;
-            const bool in = fabsf(dx) <= s.C[0] && fabsf(dy) <= s.C[1] && fabsf(dz) <= s.C[2] && fabsf(dt) <= s.C[3];
             const float S = __builtin_amdgcn_sqrtf(dist2(s, dx, dy, dz, dt));
-            const float D = in ? distance(s, wv * fabsf(v[j] - vc), S) : INFINITY;
+            float D = distance(s, wv * fabsf(v[j] - vc), S);
+            if (test && !(fabsf(dx) <= s.C[0] && fabsf(dy) <= s.C[1] && fabsf(dz) <= s.C[2] && fabsf(dt) <= s.C[3]))
+                D = INFINITY;
             if (D < d1[j]) win[j] = i;
             d2[j] = __builtin_amdgcn_fmed3f(d1[j], d2[j], D);
             d1[j] = fminf(d1[j], D);
         }
-    });
+    };
+    each_kept(keep.whole, n, [&](int i) { rate(i, false); });
+    each_kept(keep.part, n, [&](int i) { rate(i, true); });
+    bool again = false;
+#pragma unroll
+    for (int j = 0; j < N; ++j) again |= live[j] && !(d2[j] - d1[j] > s.tie);  // none in a window: NaN
+    if (__ballot(again) == 0) return;
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-        const bool close = live[j] && !(d2[j] - d1[j] > s.tie);  // none in a window: NaN
-        if (__ballot(close) == 0) continue;
+        const bool close = live[j] && !(d2[j] - d1[j] > s.tie);
         float best_d = INFINITY;
         int best = 0x7FFFFFFF, at = -1;
-        each_kept(keep, n, [&](int i) {
+        auto exact = [&](int i) {
             const float4 c = L.c[i];
             const int id = __float_as_int(L.v[i].y);
             const float dx = px[j] - c.x, dy = py[j] - c.y, dz = pz[j] - c.z, dt = pt[j] - c.w;
@@ -461,7 +483,9 @@ __device__ __forceinline__ void rate_samples(const DevS& s, const Cands& L, cons
                 best = id;
                 at = i;
             }
-        });
+        };
+        each_kept(keep.whole, n, exact);
+        each_kept(keep.part, n, exact);
         if (close) win[j] = at;
     }
 }
@@ -489,21 +513,20 @@ struct FieldRun {
     long long v;
 };
 
-union FieldLds {
-    struct {
-        Cands L;
-        unsigned long long acc[kCand][2];
-    } b;
-    Table tb;
-};
+// Note box e (field boxes, then point blocks) for the search sample by sample.
+__device__ __forceinline__ void note_box(const DevS& s, uint32_t e) {
+    if (threadIdx.x == 0) s.over[1 + atomicAdd(&s.over[0], 1u)] = e;
+}
 
 // Field samples, one box of FieldBox shape per block.  ASSIGN 0: labels from
-// the seed cells.  Bound by the candidates' arithmetic: 9.8 ms for 1.07e9
+// the seed cells.  Bound by the candidates' arithmetic: 4.9 ms for 1.07e9
 // samples and 16,384 centres (256^3 x 64, 4 B read and 4 B written per sample),
 // where testing the slab combinations sample by sample took 66 ms.
 template <int ASSIGN>
 __global__ __launch_bounds__(kBlock) void k_slic_field(DevS s, FieldBox b) {
-    __shared__ FieldLds lds;
+    __shared__ Cands L;
+    __shared__ unsigned long long acc[kCand][2];
+    if (s.counters[SC_DONE]) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     uint32_t r = blockIdx.x;
     const int x0 = (int)(r % b.nx) * b.ex();
@@ -543,56 +566,20 @@ __global__ __launch_bounds__(kBlock) void k_slic_field(DevS s, FieldBox b) {
     };
 
     int n, first[4], num[4];
-    if (ASSIGN) n = s.boxes ? list_cands<true>(s, lds.b.L, lo, hi) : -1;
-    else n = list_cells(s, lds.b.L, lo, hi, first, num);
-    if (n < 0) {  // block-uniform: every sample on its own
-        __syncthreads();
-        table_init(lds.tb);
-        Run run;
-        run.id = -1;
-        for (int k = 0; k < steps; ++k) {
-            int ky, kz, kt;
-            step_at(k, ky, kz, kt);
-            const int y = y0 + ky + ly, z = z0 + kz + lz, t = t0 + kt + lt;
-            const bool row = y < s.Y && z < s.Z && t < s.T;
-            const size_t i = (((size_t)t * s.Z + z) * s.Y + y) * s.X + x0 + lx;
-            float v[4];
-            bool in[4], live[4];
-            load(i, row, v, in, live);
-            for (int j = 0; j < 4; ++j) {
-                if (!in[j]) continue;
-                if (!live[j]) {
-                    s.labels[i + j] = -1;
-                    continue;
-                }
-                const float px = (float)(x0 + lx + j) + 0.5f, py = (float)y + 0.5f, pz = (float)z + 0.5f, pt = (float)t;
-                int id;
-                if (ASSIGN) {
-                    id = assign_one(s, px, py, pz, pt, v[j], true, s.labels[i + j]);
-                } else {
-                    const int cx = seed_cell(px, s.C[0], s.k[0]), cy = seed_cell(py, s.C[1], s.k[1]);
-                    const int cz = seed_cell(pz, s.C[2], s.k[2]), ct = seed_cell(pt, s.C[3], s.k[3]);
-                    id = ((ct * s.k[2] + cz) * s.k[1] + cy) * s.k[0] + cx;
-                }
-                s.labels[i + j] = id;
-                const long long q[5] = {quantise(px), quantise(py), quantise(pz), (long long)t << 20, quantise(v[j])};
-                run_sample(s, lds.tb, run, id, q, true);
-            }
-        }
-        add_run(s, lds.tb, run, true);
-        table_flush(s, lds.tb);
+    if (ASSIGN) n = s.boxes ? list_cands<true>(s, L, lo, hi) : -1;
+    else n = list_cells(s, L, lo, hi, first, num);
+    if (n < 0) {  // block-uniform
+        note_box(s, blockIdx.x);
         return;
     }
-
-    Cands& L = lds.b.L;
-    for (int i = threadIdx.x; i < n; i += kBlock) lds.b.acc[i][0] = lds.b.acc[i][1] = 0ull;
+    for (int i = threadIdx.x; i < n; i += kBlock) acc[i][0] = acc[i][1] = 0ull;
     __syncthreads();
     FieldRun run{-1, 0, 0, 0, 0, 0, 0};
     auto flush = [&]() {
         if (run.at < 0) return;
-        atomicAdd(&lds.b.acc[run.at][0], (unsigned long long)run.n | ((unsigned long long)run.x << 13) |
+        atomicAdd(&acc[run.at][0], (unsigned long long)run.n | ((unsigned long long)run.x << 13) |
                                              ((unsigned long long)run.y << 30) | ((unsigned long long)run.t << 47));
-        atomicAdd(&lds.b.acc[run.at][1], (unsigned long long)run.v + ((unsigned long long)run.z << 44));
+        atomicAdd(&acc[run.at][1], (unsigned long long)run.v + ((unsigned long long)run.z << 44));
     };
     for (int k = 0; k < steps; ++k) {
         int ky, kz, kt;
@@ -626,7 +613,7 @@ __global__ __launch_bounds__(kBlock) void k_slic_field(DevS s, FieldBox b) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) win[j] = -1;
             if (vlo <= vhi) {  // wave-uniform: some sample is live
-                unsigned long long keep[kCand / 64];
+                Kept keep;
                 keep_cands(s, L, n, wlo, whi, vlo, vhi, s.wf, keep);
                 const float py[4] = {fy, fy, fy, fy}, pz[4] = {fz, fz, fz, fz}, pt[4] = {ft, ft, ft, ft};
                 rate_samples<4>(s, L, keep, n, px, py, pz, pt, v, live, s.wf, win);
@@ -645,13 +632,8 @@ __global__ __launch_bounds__(kBlock) void k_slic_field(DevS s, FieldBox b) {
             if (!live[j]) continue;
             if (win[j] < 0) {  // no window holds it: it keeps its centre, listed or not
                 id[j] = s.labels[i + j];
-                unsigned long long* a = s.acc + (size_t)id[j] * kSlicAcc;
-                atomicAdd(&a[SA_X], (unsigned long long)(long long)quantise(px[j]));
-                atomicAdd(&a[SA_Y], (unsigned long long)(long long)quantise(fy));
-                atomicAdd(&a[SA_Z], (unsigned long long)(long long)quantise(fz));
-                atomicAdd(&a[SA_T], (unsigned long long)((long long)t << 20));
-                atomicAdd(&a[SA_F], (unsigned long long)(long long)quantise(v[j]));
-                atomicAdd(&a[SA_NF], 1ull);
+                const int q[5] = {quantise(px[j]), quantise(fy), quantise(fz), t << 20, quantise(v[j])};
+                add_sample(s, id[j], q, true);
                 continue;
             }
             id[j] = __float_as_int(L.v[win[j]].y);
@@ -677,7 +659,7 @@ __global__ __launch_bounds__(kBlock) void k_slic_field(DevS s, FieldBox b) {
     flush();
     __syncthreads();
     for (int i = threadIdx.x; i < n; i += kBlock) {
-        const unsigned long long a = lds.b.acc[i][0], w = lds.b.acc[i][1];
+        const unsigned long long a = acc[i][0], w = acc[i][1];
         const long long cnt = (long long)(a & 0x1FFF);
         if (!cnt) continue;
         const long long sx = (long long)((a >> 13) & 0x1FFFF), sy2 = (long long)((a >> 30) & 0x1FFFF);
@@ -703,34 +685,28 @@ struct PointRun {
     long long q[5];
 };
 
-union PointLds {
-    struct {
-        Cands L;
-        unsigned long long acc[kCand][5];
-    } b;
-    Table tb;
-};
-
 // Point samples in visiting order (particle-steps sorted by the sub-box holding
 // them, so that a wave's are close together, with positions, times and values
 // copied in that order): block b takes positions [b * 1024, (b + 1) * 1024),
 // 4 consecutive ones per thread.  Their labels follow the field's, in the
-// same order.  Bound like the field pass: 7.8 ms for 2.7e8 points and 16,384
+// same order.  Bound like the field pass: 4.4 ms for 2.7e8 points and 16,384
 // centres, 24 ms sample by sample.
-template <int ASSIGN>
-__global__ __launch_bounds__(kBlock) void k_slic_points(DevS s) {
-    __shared__ PointLds lds;
+template <int ASSIGN, int N>
+__global__ __launch_bounds__(kBlock) void k_slic_points(DevS s, uint32_t nfield) {
+    __shared__ Cands L;
+    __shared__ unsigned long long acc[kCand][5];
+    if (s.counters[SC_DONE]) return;
     const int wave = threadIdx.x >> 6;
     const uint64_t V = (uint64_t)s.X * s.Y * s.Z * s.T;
     const uint64_t Q = (uint64_t)s.Tp * s.P;
-    const uint64_t base = (uint64_t)blockIdx.x * (kBlock * kPer) + (uint64_t)threadIdx.x * kPer;
+    const uint64_t base = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) * N;
     int32_t* lab = s.labels + V + base;
-    float px[4], py[4], pz[4], pt[4], v[4];
-    bool in[4], live[4];
+    float px[N], py[N], pz[N], pt[N], v[N];
+    bool in[N], live[N];
     float lo[4] = {INFINITY, INFINITY, INFINITY, INFINITY}, hi[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
     float vlo = INFINITY, vhi = -INFINITY;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < N; ++j) {
         in[j] = base + j < Q;
         const float4 pp = in[j] ? s.spos[base + j] : make_float4(0.f, 0.f, 0.f, 0.f);
         v[j] = in[j] ? s.sattr[base + j] : 0.0f;
@@ -756,70 +732,45 @@ __global__ __launch_bounds__(kBlock) void k_slic_points(DevS s) {
         lo[d] = wave_min(lo[d]);
         hi[d] = wave_max(hi[d]);
         if ((threadIdx.x & 63) == 0) {
-            lds.b.L.box[wave][d] = lo[d];
-            lds.b.L.box[wave][4 + d] = hi[d];
+            L.box[wave][d] = lo[d];
+            L.box[wave][4 + d] = hi[d];
         }
     }
     __syncthreads();
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-        blo[d] = bhi[d] = 0.0f;
         float a = INFINITY, c = -INFINITY;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-            a = fminf(a, lds.b.L.box[w][d]);
-            c = fmaxf(c, lds.b.L.box[w][4 + d]);
+            a = fminf(a, L.box[w][d]);
+            c = fmaxf(c, L.box[w][4 + d]);
         }
-        if (a <= c) {  // some sample of the block is live
-            blo[d] = a;
-            bhi[d] = c;
-        }
+        // no live sample in the block: any box will do
+        blo[d] = a <= c ? a : 0.0f;
+        bhi[d] = a <= c ? c : 0.0f;
     }
 
     int n, first[4], num[4];
-    if (ASSIGN) n = s.boxes ? list_cands<false>(s, lds.b.L, blo, bhi) : -1;
-    else n = list_cells(s, lds.b.L, blo, bhi, first, num);
-    if (n < 0) {  // block-uniform: every sample on its own
-        __syncthreads();
-        table_init(lds.tb);
-        Run run;
-        run.id = -1;
-        for (int j = 0; j < 4; ++j) {
-            if (!in[j]) continue;
-            if (!live[j]) {
-                lab[j] = -1;
-                continue;
-            }
-            int id;
-            if (ASSIGN) {
-                id = assign_one(s, px[j], py[j], pz[j], pt[j], v[j], false, lab[j]);
-            } else {
-                const int cx = seed_cell(px[j], s.C[0], s.k[0]), cy = seed_cell(py[j], s.C[1], s.k[1]);
-                const int cz = seed_cell(pz[j], s.C[2], s.k[2]), ct = seed_cell(pt[j], s.C[3], s.k[3]);
-                id = ((ct * s.k[2] + cz) * s.k[1] + cy) * s.k[0] + cx;
-            }
-            lab[j] = id;
-            const long long q[5] = {quantise(px[j]), quantise(py[j]), quantise(pz[j]), quantise(pt[j]), quantise(v[j])};
-            run_sample(s, lds.tb, run, id, q, false);
-        }
-        add_run(s, lds.tb, run, false);
-        table_flush(s, lds.tb);
+    if (ASSIGN) n = s.boxes ? list_cands<false>(s, L, blo, bhi) : -1;
+    else n = list_cells(s, L, blo, bhi, first, num);
+    if (n < 0) {  // block-uniform
+        note_box(s, nfield + blockIdx.x);
         return;
     }
-
-    Cands& L = lds.b.L;
-    for (int i = threadIdx.x; i < n * 5; i += kBlock) (&lds.b.acc[0][0])[i] = 0ull;
+    for (int i = threadIdx.x; i < n * 5; i += kBlock) (&acc[0][0])[i] = 0ull;
     __syncthreads();
-    int win[4] = {-1, -1, -1, -1};
+    int win[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) win[j] = -1;
     if (ASSIGN) {
-        if (vlo <= vhi) {  // wave-uniform
-            unsigned long long keep[kCand / 64];
+        if (vlo <= vhi) {  // wave-uniform: some sample is live
+            Kept keep;
             keep_cands(s, L, n, lo, hi, vlo, vhi, s.wp, keep);
-            rate_samples<4>(s, L, keep, n, px, py, pz, pt, v, live, s.wp, win);
+            rate_samples<N>(s, L, keep, n, px, py, pz, pt, v, live, s.wp, win);
         }
     } else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < N; ++j)
             if (live[j])
                 win[j] = (((seed_cell(pt[j], s.C[3], s.k[3]) - first[3]) * num[2] +
                            (seed_cell(pz[j], s.C[2], s.k[2]) - first[2])) * num[1] +
@@ -829,7 +780,7 @@ __global__ __launch_bounds__(kBlock) void k_slic_points(DevS s) {
     PointRun run{-1, 0, {0, 0, 0, 0, 0}};
     auto flush = [&]() {
         if (run.at < 0) return;
-        unsigned long long* a = lds.b.acc[run.at];
+        unsigned long long* a = acc[run.at];
         atomicAdd(&a[0], (unsigned long long)run.q[0]);
         atomicAdd(&a[1], (unsigned long long)run.q[1]);
         atomicAdd(&a[2], (unsigned long long)run.q[2]);
@@ -837,7 +788,7 @@ __global__ __launch_bounds__(kBlock) void k_slic_points(DevS s) {
         atomicAdd(&a[4], (unsigned long long)run.q[4]);
     };
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < N; ++j) {
         if (!in[j]) continue;
         if (!live[j]) {
             lab[j] = -1;
@@ -845,13 +796,7 @@ __global__ __launch_bounds__(kBlock) void k_slic_points(DevS s) {
         }
         const int q[5] = {quantise(px[j]), quantise(py[j]), quantise(pz[j]), quantise(pt[j]), quantise(v[j])};
         if (win[j] < 0) {  // no window holds it: it keeps its centre, listed or not
-            unsigned long long* a = s.acc + (size_t)lab[j] * kSlicAcc;
-            atomicAdd(&a[SA_X], (unsigned long long)(long long)q[0]);
-            atomicAdd(&a[SA_Y], (unsigned long long)(long long)q[1]);
-            atomicAdd(&a[SA_Z], (unsigned long long)(long long)q[2]);
-            atomicAdd(&a[SA_T], (unsigned long long)(long long)q[3]);
-            atomicAdd(&a[SA_P], (unsigned long long)(long long)q[4]);
-            atomicAdd(&a[SA_NP], 1ull);
+            add_sample(s, lab[j], q, false);
             continue;
         }
         lab[j] = __float_as_int(L.v[win[j]].y);
@@ -866,7 +811,7 @@ __global__ __launch_bounds__(kBlock) void k_slic_points(DevS s) {
     flush();
     __syncthreads();
     for (int i = threadIdx.x; i < n; i += kBlock) {
-        const unsigned long long* a = lds.b.acc[i];
+        const unsigned long long* a = acc[i];
         const unsigned long long cnt = a[3] >> 48;
         if (!cnt) continue;
         unsigned long long* o = s.acc + (size_t)__float_as_int(L.v[i].y) * kSlicAcc;
@@ -879,12 +824,123 @@ __global__ __launch_bounds__(kBlock) void k_slic_points(DevS s) {
     }
 }
 
+// The boxes whose list did not fit, sample by sample through the slabs' reach
+// ranges, and the buffers the coming update fills (slab bounds, moved count)
+// reset.  npoint: points per noted block.  A kernel of its own, so that its
+// registers do not cost the passes their occupancy: inside them it held them at
+// 119 and 101 registers, four waves per SIMD, and 9.8 and 7.8 ms instead of 4.9
+// and 4.4 ms at 256^3 x 64.
+template <int ASSIGN>
+__global__ __launch_bounds__(kBlock) void k_slic_rest(DevS s, FieldBox b, uint32_t nfield, uint32_t npoint) {
+    __shared__ Table tb;
+    if (s.counters[SC_DONE]) return;
+    const uint32_t gid = blockIdx.x * kBlock + threadIdx.x;
+    for (uint32_t i = gid; i < 8u * s.kmax; i += gridDim.x * kBlock)
+        s.slab_next[i] = i < 4u * s.kmax ? 0xFFFFFFFFu : 0u;
+    if (gid == 0) s.counters[SC_MOVED] = 0u;
+    const uint32_t count = s.over[0];
+    const uint64_t V = (uint64_t)s.X * s.Y * s.Z * s.T, Q = (uint64_t)s.Tp * s.P;
+    for (uint32_t e = blockIdx.x; e < count; e += gridDim.x) {
+        const uint32_t box = s.over[1 + e];
+        const bool field = box < nfield;
+        __syncthreads();
+        table_init(tb);
+        Run run;
+        run.id = -1;
+        int x0 = 0, y0 = 0, z0 = 0, t0 = 0;
+        if (field) {
+            uint32_t r = box;
+            x0 = (int)(r % b.nx) * b.ex();
+            r /= b.nx;
+            y0 = (int)(r % b.ny) * b.ey();
+            r /= b.ny;
+            z0 = (int)(r % b.nz) * b.ez();
+            t0 = (int)(r / b.nz) * b.et();
+        }
+        // four consecutive samples per thread (along x for the field)
+        const uint32_t n = field ? (uint32_t)(b.ex() * b.ey() * b.ez() * b.et()) : npoint;
+        for (uint32_t i0 = threadIdx.x * 4; i0 < n; i0 += kBlock * 4) {
+            for (int j = 0; j < 4; ++j) {
+                float px, py, pz, pt, v;
+                size_t at;  // label
+                if (field) {
+                    uint32_t r = i0 + j;
+                    const int x = x0 + (int)(r % b.ex());
+                    r /= b.ex();
+                    const int y = y0 + (int)(r % b.ey());
+                    r /= b.ey();
+                    const int z = z0 + (int)(r % b.ez()), t = t0 + (int)(r / b.ez());
+                    if (x >= s.X || y >= s.Y || z >= s.Z || t >= s.T) continue;
+                    at = (((size_t)t * s.Z + z) * s.Y + y) * s.X + x;
+                    px = (float)x + 0.5f;
+                    py = (float)y + 0.5f;
+                    pz = (float)z + 0.5f;
+                    pt = (float)t;
+                    v = s.field[at];
+                } else {
+                    const uint64_t o = (uint64_t)(box - nfield) * npoint + i0 + j;
+                    if (i0 + j >= n || o >= Q) continue;
+                    const float4 pp = s.spos[o];
+                    px = pp.x;
+                    py = pp.y;
+                    pz = pp.z;
+                    pt = pp.w;
+                    v = s.sattr[o];
+                    at = V + o;
+                }
+                if (!(isfinite(v) && isfinite(px) && isfinite(py) && isfinite(pz))) {
+                    s.labels[at] = -1;
+                    continue;
+                }
+                if (!(fabsf(v) < kMaxAbs && fabsf(px) < kMaxAbs && fabsf(py) < kMaxAbs && fabsf(pz) < kMaxAbs))
+                    s.counters[SC_RANGE] = 1u;
+                int id;
+                if (ASSIGN) {
+                    id = assign_one(s, px, py, pz, pt, v, field, s.labels[at]);
+                } else {
+                    const int cx = seed_cell(px, s.C[0], s.k[0]), cy = seed_cell(py, s.C[1], s.k[1]);
+                    const int cz = seed_cell(pz, s.C[2], s.k[2]), ct = seed_cell(pt, s.C[3], s.k[3]);
+                    id = ((ct * s.k[2] + cz) * s.k[1] + cy) * s.k[0] + cx;
+                }
+                s.labels[at] = id;
+                const long long q[5] = {quantise(px), quantise(py), quantise(pz), quantise(pt), quantise(v)};
+                run_sample(s, tb, run, id, q, field);
+            }
+        }
+        add_run(s, tb, run, field);
+        table_flush(s, tb);
+    }
+}
+
+// The update's slab bounds, read by the block that finishes it (written by
+// other blocks' atomics: agent-scope loads, so that no stale line is read).
+__device__ __forceinline__ float next_slab(const DevS& s, int i) {
+    return key_float(__hip_atomic_load(&s.slab_next[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
 // One thread per centre.  seed: write the seed centre first (its location
 // ((i + 0.5) C_d), values 0).  Then the means of the sums (a centre without
 // samples, or without samples of one type, keeps the previous values), the
-// convergence test against the previous centre, and the sums cleared.
+// convergence test against the previous centre, and the sums cleared.  A block
+// gathers its centres' slab bounds in LDS first: 256 neighbouring centres share
+// a few dozen slabs, and the same address takes 11 ns per device atomic (16,384
+// centres: 312 us of them straight to memory, 15 us now).
+//
+// The last block to finish writes the reach ranges of the new slabs, counts the
+// iteration, notes a run that is done (nothing moved, a value out of range) and
+// reports to the host.
+constexpr int kSlabLds = 256;  // slabs per axis gathered in LDS
 __global__ __launch_bounds__(256) void k_slic_update(DevS s, int seed) {
+    __shared__ uint32_t s_slab[2][4][kSlabLds];
+    __shared__ uint32_t s_last;
+    if (s.counters[SC_DONE]) return;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const bool gather = s.kmax <= kSlabLds;
+    for (int j = threadIdx.x; gather && j < 4 * kSlabLds; j += blockDim.x) {
+        (&s_slab[0][0][0])[j] = 0xFFFFFFFFu;
+        (&s_slab[1][0][0])[j] = 0u;
+    }
+    __syncthreads();
     bool moved = false;
     if (i < s.K) {
         double* c = s.cen + (size_t)i * 6;
@@ -934,12 +990,74 @@ __global__ __launch_bounds__(256) void k_slic_update(DevS s, int seed) {
             const int cell = d < 3 ? r % s.k[d] : r;
             r /= s.k[d];
             const uint32_t key = float_key((float)nw[d]);
-            atomicMin(&s.slab[(0 * 4 + d) * s.kmax + cell], key);
-            atomicMax(&s.slab[(1 * 4 + d) * s.kmax + cell], key);
+            uint32_t* lo = gather ? &s_slab[0][d][cell] : &s.slab_next[(0 * 4 + d) * s.kmax + cell];
+            uint32_t* hi = gather ? &s_slab[1][d][cell] : &s.slab_next[(1 * 4 + d) * s.kmax + cell];
+            atomicMin(lo, key);
+            atomicMax(hi, key);
         }
     }
     const unsigned long long m = __ballot(moved);
     if ((threadIdx.x & 63) == 0 && m) atomicAdd(&s.counters[SC_MOVED], (unsigned)__popcll(m));
+    __syncthreads();
+    for (int j = threadIdx.x; gather && j < 4 * s.kmax; j += blockDim.x) {
+        const int d = j / s.kmax, cell = j - d * s.kmax;
+        if (s_slab[0][d][cell] > s_slab[1][d][cell]) continue;  // none of the block's centres
+        atomicMin(&s.slab_next[j], s_slab[0][d][cell]);
+        atomicMax(&s.slab_next[4 * s.kmax + j], s_slab[1][d][cell]);
+    }
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0)
+        s_last = __hip_atomic_fetch_add(&s.counters[SC_TICKET], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
+                 gridDim.x - 1;
+    __syncthreads();
+    if (!s_last) return;
+    // Reach: slab i of axis d (bounds lo, hi) can hold a centre within C of any p
+    // in [lo - C, hi + C], widened by C 2^-20 for the rounding of the window test's
+    // difference.  Those p fall in the seed cells from floor of the lower end / C to
+    // floor of the upper end / C (clamped like seed_cell), widened by 10^-3 of a
+    // cell for the rounding of the division (below 2.5e-4 of a cell wherever the
+    // cell index is below 4096).  Each of those cells takes i into its range.
+    for (int j = threadIdx.x; j < 8 * s.kmax; j += blockDim.x) s.reach[j] = (j & 1) ? -1 : 0x7FFFFFFF;
+    __threadfence();
+    __syncthreads();
+    for (int g = threadIdx.x; g < 4 * s.kmax; g += blockDim.x) {
+        const int d = g / s.kmax, cell = g - d * s.kmax;
+        if (cell >= s.k[d]) continue;
+        const double C = s.C[d];
+        const double lo = next_slab(s, g), hi = next_slab(s, 4 * s.kmax + g);
+        const double w = C * (1.0 + 0x1p-20);
+        const double kd = s.k[d] - 1;
+        const int j0 = (int)fmin(fmax(floor((lo - w) / C - 1e-3), 0.0), kd);
+        const int j1 = (int)fmin(fmax(floor((hi + w) / C + 1e-3), 0.0), kd);
+        for (int j = j0; j <= j1; ++j) {
+            atomicMin(&s.reach[(d * s.kmax + j) * 2], cell);
+            atomicMax(&s.reach[(d * s.kmax + j) * 2 + 1], cell);
+        }
+    }
+    if (threadIdx.x == 0) {
+        const uint32_t mv =
+            __hip_atomic_load(&s.counters[SC_MOVED], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t range = s.counters[SC_RANGE];
+        const uint32_t iters = s.counters[SC_ITERS] + (seed ? 0u : 1u);
+        s.counters[SC_ITERS] = iters;
+        s.counters[SC_TICKET] = 0u;
+        s.over[0] = 0u;
+        const uint32_t done = range || (!seed && mv == 0u);
+        if (done) s.counters[SC_DONE] = 1u;
+        s.host[SC_RANGE] = range;
+        s.host[SC_ITERS] = iters;
+        s.host[SC_DONE] = done;
+    }
+}
+
+// The start of a run: sums, counters and the first slab buffer cleared.
+__global__ __launch_bounds__(256) void k_slic_begin(DevS s) {
+    const uint64_t n = (uint64_t)s.K * kSlicAcc;
+    const uint64_t gid = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
+    for (uint64_t i = gid; i < n; i += (uint64_t)gridDim.x * blockDim.x) s.acc[i] = 0ull;
+    if (gid < kSlicCounters) s.counters[gid] = 0u;
+    if (gid == 0) s.over[0] = 0u;
 }
 
 inline unsigned blocks_for(uint64_t n, uint64_t per) { return (unsigned)((n + per - 1) / per); }
@@ -1289,7 +1407,7 @@ constexpr int kScanBlocks = 1024;
 // it, tile by tile, in an order that doubles one axis after another (y, z, x, t),
 // so that 256 consecutive points fill a compact box.  Keys by tile (32 x 8 x 8 x
 // BT) left a wave's points spread over the whole tile: 9.1 instead of 7.8 ms
-// per point pass at 256^3 x 64 with 4.2 million particles.  Sub-boxes of 4 x 4 x 4
+// per point pass (as it was then) at 256^3 x 64 with 4.2 million particles.  Sub-boxes of 4 x 4 x 4
 // x 2 sort 9 ms longer for the same pass.
 __device__ __forceinline__ uint32_t order_key(uint32_t bin, int logBT, uint32_t none) {
     if (bin == kNoVoxel) return none;
@@ -1527,61 +1645,41 @@ static FieldBox field_box(const DevS& s) {
     return b;
 }
 
-static void launch_pass(const DevS& s, int assign, hipStream_t st) {
-    const uint64_t V = (uint64_t)s.X * s.Y * s.Z * s.T, Q = (uint64_t)s.Tp * s.P;
-    if (V) {
-        const FieldBox b = field_box(s);
-        const uint32_t n = (uint32_t)b.nx * b.ny * b.nz * b.nt;
-        if (assign) hipLaunchKernelGGL(k_slic_field<1>, dim3(n), dim3(kBlock), 0, st, s, b);
-        else hipLaunchKernelGGL(k_slic_field<0>, dim3(n), dim3(kBlock), 0, st, s, b);
-    }
-    if (Q) {
-        const unsigned n = blocks_for(Q, kBlock * kPer);
-        if (assign) hipLaunchKernelGGL(k_slic_points<1>, dim3(n), dim3(kBlock), 0, st, s);
-        else hipLaunchKernelGGL(k_slic_points<0>, dim3(n), dim3(kBlock), 0, st, s);
-    }
+// Points per thread of the point pass: four, while that leaves 2,048 blocks.
+static int points_per_thread(const DevS& s) { return (uint64_t)s.Tp * s.P >= 2048ull * kBlock * kPer ? kPer : 1; }
+
+uint32_t slic_boxes(const DevS& s) {
+    const FieldBox b = field_box(s);
+    return (uint32_t)b.nx * b.ny * b.nz * b.nt +
+           blocks_for((uint64_t)s.Tp * s.P, (uint64_t)kBlock * points_per_thread(s));
 }
 
-void launch_slic_init(const DevS& s, hipStream_t st) { launch_pass(s, 0, st); }
-
-void launch_slic_assign(const DevS& s, hipStream_t st) { launch_pass(s, 1, st); }
-
-__global__ void k_slic_slab_reset(DevS s) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < 8 * s.kmax) {
-        s.slab[i] = i < 4 * s.kmax ? 0xFFFFFFFFu : 0u;
-        s.reach[i] = (i & 1) ? -1 : 0x7FFFFFFF;
-    }
+template <int ASSIGN>
+static void launch_pass(const DevS& s, hipStream_t st) {
+    const uint64_t Q = (uint64_t)s.Tp * s.P;
+    const FieldBox b = field_box(s);
+    const uint32_t nf = (uint32_t)b.nx * b.ny * b.nz * b.nt;
+    hipLaunchKernelGGL(k_slic_field<ASSIGN>, dim3(nf), dim3(kBlock), 0, st, s, b);
+    const int per = points_per_thread(s);
+    const uint32_t np = blocks_for(Q, (uint64_t)kBlock * per);
+    if (Q && per == kPer)
+        hipLaunchKernelGGL((k_slic_points<ASSIGN, kPer>), dim3(np), dim3(kBlock), 0, st, s, nf);
+    else if (Q)
+        hipLaunchKernelGGL((k_slic_points<ASSIGN, 1>), dim3(np), dim3(kBlock), 0, st, s, nf);
+    hipLaunchKernelGGL(k_slic_rest<ASSIGN>, dim3(std::min(nf + np, 2048u)), dim3(kBlock), 0, st, s, b, nf,
+                       (uint32_t)(kBlock * per));
 }
 
-// Slab i of axis d (bounds lo, hi from the update) can hold a centre within
-// C of any p in [lo - C, hi + C], widened by C 2^-20 for the rounding of the
-// window test's difference.  Those p fall in the seed cells from floor of
-// the lower end / C to floor of the upper end / C (clamped like seed_cell),
-// widened by 10^-3 of a cell for the rounding of the division (below 2.5e-4
-// of a cell wherever the cell index is below 4096).  Each of those cells
-// takes i into its reach range.
-__global__ void k_slic_reach(DevS s) {
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    const int d = g / s.kmax, i = g - d * s.kmax;
-    if (d >= 4 || i >= s.k[d]) return;
-    const double C = s.C[d];
-    const double lo = key_float(s.slab[(0 * 4 + d) * s.kmax + i]);
-    const double hi = key_float(s.slab[(1 * 4 + d) * s.kmax + i]);
-    const double m = C * (1.0 + 0x1p-20);
-    const double kd = s.k[d] - 1;
-    const int j0 = (int)fmin(fmax(floor((lo - m) / C - 1e-3), 0.0), kd);
-    const int j1 = (int)fmin(fmax(floor((hi + m) / C + 1e-3), 0.0), kd);
-    for (int j = j0; j <= j1; ++j) {
-        atomicMin(&s.reach[(d * s.kmax + j) * 2], i);
-        atomicMax(&s.reach[(d * s.kmax + j) * 2 + 1], i);
-    }
+void launch_slic_begin(const DevS& s, hipStream_t st) {
+    const unsigned g = (unsigned)std::min<uint64_t>(blocks_for((uint64_t)s.K * kSlicAcc, 256), 2048);
+    hipLaunchKernelGGL(k_slic_begin, dim3(g), dim3(256), 0, st, s);
+    launch_pass<0>(s, st);
+    hipLaunchKernelGGL(k_slic_update, dim3(blocks_for((uint64_t)s.K, 256)), dim3(256), 0, st, s, 1);
 }
 
-void launch_slic_update(const DevS& s, int seed, hipStream_t st) {
-    hipLaunchKernelGGL(k_slic_slab_reset, dim3(blocks_for((uint64_t)8 * s.kmax, 256)), dim3(256), 0, st, s);
-    hipLaunchKernelGGL(k_slic_update, dim3(blocks_for((uint64_t)s.K, 256)), dim3(256), 0, st, s, seed);
-    hipLaunchKernelGGL(k_slic_reach, dim3(blocks_for((uint64_t)4 * s.kmax, 256)), dim3(256), 0, st, s);
+void launch_slic_iteration(const DevS& s, hipStream_t st) {
+    launch_pass<1>(s, st);
+    hipLaunchKernelGGL(k_slic_update, dim3(blocks_for((uint64_t)s.K, 256)), dim3(256), 0, st, s, 0);
 }
 
 int launch_slic_merge(const DevS& s, const DevM& m, hipStream_t st) {
