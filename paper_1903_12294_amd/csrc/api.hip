@@ -2381,7 +2381,7 @@ int mf4d_slic_read_labels(mf4d_ctx* c, int32_t* field_labels, size_t nf, int32_t
             if (rc) return rc;
             out = (int32_t*)st;
         }
-        launch_slic_unsort(c->slabels + V, c->porder, Qp, out, c->stream);
+        launch_slic_unsort(c->slabels + V, c->porder, c->pg.T, (int64_t)(Qp / c->pg.T), out, c->stream);
         if (where == MF4D_HOST)
             HIP_TRY(hipMemcpyAsync(point_labels, out, Qp * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
     }
@@ -2503,7 +2503,7 @@ int mf4d_slic_read_segments(mf4d_ctx* c, int32_t* dst, size_t n, int where) {
         if (rc) return rc;
         out = (int32_t*)st;
     }
-    launch_slic_unsort(c->slabels + V, c->porder, Qp, out, c->stream);
+    launch_slic_unsort(c->slabels + V, c->porder, c->pg.T, (int64_t)(Qp / c->pg.T), out, c->stream);
     launch_slic_segments(out, c->m.feat, c->pg.T, (int64_t)(Qp / c->pg.T), c->stream);
     if (where == MF4D_HOST)
         HIP_TRY(hipMemcpyAsync(dst, out, Qp * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));

@@ -100,7 +100,7 @@ int launch_slic_order(const uint32_t* bins, const float* xyz, const float* attr,
                       float4* spos, float* sattr, hipStream_t st);
 // Point labels from visiting order back to [T][P]: out[q] = in[order[q]]
 // (order as written by launch_slic_order).
-void launch_slic_unsort(const int32_t* in, const uint32_t* order, uint64_t Q, int32_t* out, hipStream_t st);
+void launch_slic_unsort(const int32_t* in, const uint32_t* order, int T, int64_t P, int32_t* out, hipStream_t st);
 // Trajectory segments (Section 3.4), in place on point labels [T][P]: the
 // feature id (feat[label]) where the particle has that feature at t - 1 or
 // t + 1, else -1.

@@ -503,6 +503,32 @@ struct FieldBox {
     __host__ __device__ int et() const { return 1 << (lt + it); }
 };
 
+// A lane's place in its block's box: x, and y, z, t in each of the wave boxes.
+struct FieldLane {
+    int x, y, z, t, sy, steps;
+    __device__ explicit FieldLane(const FieldBox& b) {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        x = (wave & ((1 << b.wx) - 1)) * 8 + (lane & 1) * 4;
+        y = ((wave >> b.wx) << b.ly) + ((lane >> 1) & ((1 << b.ly) - 1));
+        z = (lane >> (1 + b.ly)) & ((1 << b.lz) - 1);
+        t = lane >> (1 + b.ly + b.lz);
+        sy = 1 << (b.ly + 2 - b.wx);  // y extent of one step
+        steps = 1 << (b.iy + b.iz + b.it);
+    }
+    // origin of step k
+    __device__ void step(const FieldBox& b, int k, int& ky, int& kz, int& kt) const {
+        ky = (k & ((1 << b.iy) - 1)) * sy;
+        kz = ((k >> b.iy) & ((1 << b.iz) - 1)) << b.lz;
+        kt = (k >> (b.iy + b.iz)) << b.lt;
+    }
+    __device__ void place(const FieldBox& b, int k, int& py, int& pz, int& pt) const {
+        step(b, k, py, pz, pt);
+        py += y;
+        pz += z;
+        pt += t;
+    }
+};
+
 // A block's sums of field samples per listed centre, in box coordinates packed
 // into two words: n | x << 13 | y << 30 | t << 47 and value + (z << 44).  At most
 // 4,096 samples, x and y below 32, z and t below 16 keep each field in its bits;
@@ -527,27 +553,18 @@ __global__ __launch_bounds__(kBlock) void k_slic_field(DevS s, FieldBox b) {
     __shared__ Cands L;
     __shared__ unsigned long long acc[kCand][2];
     if (s.counters[SC_DONE]) return;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wave = threadIdx.x >> 6;
     uint32_t r = blockIdx.x;
     const int x0 = (int)(r % b.nx) * b.ex();
     r /= b.nx;
     const int y0 = (int)(r % b.ny) * b.ey();
     r /= b.ny;
     const int z0 = (int)(r % b.nz) * b.ez(), t0 = (int)(r / b.nz) * b.et();
-    // this lane's place in the wave box
-    const int lx = (wave & ((1 << b.wx) - 1)) * 8 + (lane & 1) * 4;
-    const int ly = ((wave >> b.wx) << b.ly) + ((lane >> 1) & ((1 << b.ly) - 1));
-    const int lz = (lane >> (1 + b.ly)) & ((1 << b.lz) - 1), lt = lane >> (1 + b.ly + b.lz);
-    const int steps = 1 << (b.iy + b.iz + b.it);
-    const int sy = 1 << (b.ly + 2 - b.wx);  // y extent of one step
+    const FieldLane at(b);
+    const int lx = at.x, ly = at.y, lz = at.z, lt = at.t;
     const float lo[4] = {(float)x0 + 0.5f, (float)y0 + 0.5f, (float)z0 + 0.5f, (float)t0};
     const float hi[4] = {(float)min(x0 + b.ex(), s.X) - 0.5f, (float)min(y0 + b.ey(), s.Y) - 0.5f,
                          (float)min(z0 + b.ez(), s.Z) - 0.5f, (float)min(t0 + b.et(), s.T) - 1.0f};
-    auto step_at = [&](int k, int& y, int& z, int& t) {
-        y = (k & ((1 << b.iy) - 1)) * sy;
-        z = ((k >> b.iy) & ((1 << b.iz) - 1)) << b.lz;
-        t = (k >> (b.iy + b.iz)) << b.lt;
-    };
     // four samples of the row at (x, y, z, t): values; which exist and are finite
     auto load = [&](size_t i, bool row, float* v, bool* in, bool* live) {
         const int x = x0 + lx;
@@ -581,9 +598,9 @@ __global__ __launch_bounds__(kBlock) void k_slic_field(DevS s, FieldBox b) {
                                              ((unsigned long long)run.y << 30) | ((unsigned long long)run.t << 47));
         atomicAdd(&acc[run.at][1], (unsigned long long)run.v + ((unsigned long long)run.z << 44));
     };
-    for (int k = 0; k < steps; ++k) {
+    for (int k = 0; k < at.steps; ++k) {
         int ky, kz, kt;
-        step_at(k, ky, kz, kt);
+        at.step(b, k, ky, kz, kt);
         const int y = y0 + ky + ly, z = z0 + kz + lz, t = t0 + kt + lt;
         const bool row = y < s.Y && z < s.Z && t < s.T;
         const size_t i = (((size_t)t * s.Z + z) * s.Y + y) * s.X + x0 + lx;
@@ -1133,13 +1150,32 @@ __global__ __launch_bounds__(256) void k_merge_init(DevS s, DevM m) {
 // work (K^2 / 2 tests in all): block (bx, by >= bx) compares the centres of
 // tile bx, one per thread, with the later centres of tile by, held in LDS.  Two
 // centres match when they have the same sample types and, per type, means
-// within eps of the larger magnitude (Section 3.3).
+// within eps of the larger magnitude (Section 3.3).  The block's matches are
+// united in a union-find of its 512 centres in LDS, and each centre then with its
+// local root in memory: at most 512 walks over memory per block, side by side,
+// instead of one after another for every match of a thread (128 centres: 117 to
+// 54 us; 16,384 centres: 1.5 to 0.8 ms).
 constexpr int kMergeTile = 256;
+__device__ __forceinline__ int lds_link(const int* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// Root of local centre i, halving the path (links strictly decrease, as above).
+__device__ __forceinline__ int lds_root(int* link, int i) {
+    for (;;) {
+        const int p = lds_link(&link[i]);
+        if (p == i) return i;
+        const int gp = lds_link(&link[p]);
+        if (gp != p) __hip_atomic_store(&link[i], gp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        i = gp;
+    }
+}
 __global__ __launch_bounds__(kMergeTile) void k_merge_pairs(DevS s, DevM m) {
     if (blockIdx.y < blockIdx.x) return;  // block-uniform: lower triangle
     __shared__ double sv[2][kMergeTile];  // field mean, point mean
     __shared__ unsigned sh[kMergeTile];   // bit 0: has field samples, bit 1: has point samples
+    __shared__ int link[2 * kMergeTile];  // tile bx, then tile by (a diagonal block uses the first half)
     const int j0 = blockIdx.y * kMergeTile;
+    const int jl = blockIdx.x == blockIdx.y ? 0 : kMergeTile;
     {
         const int j = j0 + threadIdx.x;
         unsigned h = 0;
@@ -1152,27 +1188,44 @@ __global__ __launch_bounds__(kMergeTile) void k_merge_pairs(DevS s, DevM m) {
         sh[threadIdx.x] = h;
         sv[0][threadIdx.x] = vf;
         sv[1][threadIdx.x] = vp;
+        link[threadIdx.x] = threadIdx.x;
+        link[kMergeTile + threadIdx.x] = kMergeTile + threadIdx.x;
     }
     __syncthreads();
     const int i = blockIdx.x * kMergeTile + threadIdx.x;
-    if (i >= m.K) return;
-    const unsigned hi = (s.cnt[2 * (size_t)i] > 0 ? 1u : 0u) | (s.cnt[2 * (size_t)i + 1] > 0 ? 2u : 0u);
-    if (!hi) return;  // no samples: merges with nothing
-    const double af = s.cen[6 * (size_t)i + 5], ap = s.cen[6 * (size_t)i + 4];
-    const int jn = min(kMergeTile, m.K - j0);
-    for (int jj = 0; jj < jn; ++jj) {
-        const int j = j0 + jj;
-        if (j <= i || sh[jj] != hi) continue;  // a type only one has: different phenomena
-        bool ok = true;
-        if (hi & 1u) {
-            const double b = sv[0][jj];
-            ok = fabs(__dsub_rn(af, b)) <= __dmul_rn(m.eps, fmax(fabs(af), fabs(b)));
+    const unsigned hi = i >= m.K ? 0u : (s.cnt[2 * (size_t)i] > 0 ? 1u : 0u) | (s.cnt[2 * (size_t)i + 1] > 0 ? 2u : 0u);
+    if (hi) {  // a centre without samples merges with nothing
+        const double af = s.cen[6 * (size_t)i + 5], ap = s.cen[6 * (size_t)i + 4];
+        const int jn = min(kMergeTile, m.K - j0);
+        int root = threadIdx.x;  // this centre's root when last looked up
+        for (int jj = 0; jj < jn; ++jj) {
+            const int j = j0 + jj;
+            if (j <= i || sh[jj] != hi) continue;  // a type only one has: different phenomena
+            if (lds_link(&link[jl + jj]) == root) continue;  // known to be in one component already
+            bool ok = true;
+            if (hi & 1u) {
+                const double b = sv[0][jj];
+                ok = fabs(__dsub_rn(af, b)) <= __dmul_rn(m.eps, fmax(fabs(af), fabs(b)));
+            }
+            if (ok && (hi & 2u)) {
+                const double b = sv[1][jj];
+                ok = fabs(__dsub_rn(ap, b)) <= __dmul_rn(m.eps, fmax(fabs(ap), fabs(b)));
+            }
+            if (!ok) continue;
+            for (;;) {  // every failed swap means another union succeeded
+                const int a = lds_root(link, root), b = lds_root(link, jl + jj);
+                root = min(a, b);
+                if (a == b || atomicCAS(&link[max(a, b)], max(a, b), root) == max(a, b)) break;
+            }
         }
-        if (ok && (hi & 2u)) {
-            const double b = sv[1][jj];
-            ok = fabs(__dsub_rn(ap, b)) <= __dmul_rn(m.eps, fmax(fabs(ap), fabs(b)));
-        }
-        if (ok && !unite(m.parent, i, j, m.K)) m.err[0] = 1u;
+    }
+    __syncthreads();
+    for (int l = threadIdx.x; l < jl + kMergeTile; l += kMergeTile) {
+        const int r = lds_root(link, l);
+        if (r == l) continue;  // (centres past K match nothing and stay roots)
+        const int gl = l < kMergeTile ? blockIdx.x * kMergeTile + l : j0 + l - kMergeTile;
+        const int gr = r < kMergeTile ? blockIdx.x * kMergeTile + r : j0 + r - kMergeTile;
+        if (!unite(m.parent, gl, gr, m.K)) m.err[0] = 1u;
     }
 }
 
@@ -1188,20 +1241,27 @@ __global__ __launch_bounds__(256) void k_merge_flatten(DevS s, DevM m) {
 }
 
 // The lanes of a wave that hold centres of one feature combine their values
-// first, so that one lane per (wave, feature) updates the feature (most
-// centres of a wave usually share one).  Visits each distinct feature of the
-// wave in turn: fn(feature, this lane holds it, this lane updates it); F < 0:
-// no centre.
+// first, so that one lane per (wave, feature) updates the feature, where at least
+// kCombine lanes share it (most centres of a wave usually share one); a feature
+// with fewer lanes is updated by each: combining costs about 1 us per feature
+// whatever its lanes, 78 and 70 us of the two kernels when 64 centres were 64
+// features.  Visits each distinct feature of the wave in turn: fn(feature, this
+// lane holds it, this lane updates it, the lanes combine); F < 0: no centre.
+constexpr int kCombine = 8;
 template <typename Fn>
 __device__ __forceinline__ void per_wave_feature(int F, Fn&& fn) {
     unsigned long long pending = __ballot(F >= 0);
+    bool alone = false;
     while (pending) {  // wave-uniform
         const int leader = __ffsll((long long)pending) - 1;
         const int FL = __shfl(F, leader);
         const bool mine = F == FL;
-        pending &= ~__ballot(mine);
-        fn(FL, mine, (int)__lane_id() == leader);
+        const unsigned long long group = __ballot(mine);
+        pending &= ~group;
+        if (__popcll(group) >= kCombine) fn(FL, mine, (int)__lane_id() == leader, true);
+        else alone |= mine;
     }
+    if (__ballot(alone)) fn(F, alone, alone, false);
 }
 
 __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
@@ -1214,9 +1274,9 @@ __global__ __launch_bounds__(256) void k_feature_sums(DevS s, DevM m) {
     const int F = i < m.K ? m.feat[i] : -1;
     unsigned long long v[kSlicAcc];
     for (int j = 0; j < kSlicAcc; ++j) v[j] = F >= 0 ? s.lsum[8 * (size_t)i + j] : 0ull;
-    per_wave_feature(F, [&](int FL, bool mine, bool lead) {
+    per_wave_feature(F, [&](int FL, bool mine, bool lead, bool combine) {
         for (int j = 0; j < kSlicAcc; ++j) {
-            const unsigned long long x = wave_sum_u64(mine ? v[j] : 0ull);
+            const unsigned long long x = combine ? wave_sum_u64(mine ? v[j] : 0ull) : v[j];
             if (lead) atomicAdd(&m.fsum[8 * (size_t)FL + j], x);
         }
     });
@@ -1310,43 +1370,128 @@ __device__ __forceinline__ void stat_flush(const DevM& m, StatTable& tb, int ty)
     }
 }
 
-// ty 0: field samples [T][Z][Y][X]; ty 1: point samples in visiting order.
-__global__ __launch_bounds__(kBlock) void k_feature_pass(DevS s, DevM m, int ty) {
+// Field samples, a box of FieldBox shape per block.  The extent of a centre's
+// samples within the box is one word of bits, one per coordinate (x from bit 0,
+// then y, z, t), so a run of samples costs an OR and an addition in LDS instead of
+// eight minima and maxima, and the mean is looked up once per run: 2.6 ms for
+// 1.07e9 samples (6.4 ms with consecutive samples and a table of bounds; 2.0 ms
+// is what reading values and labels takes).
+struct BoxTable {
+    int key[kTab];
+    unsigned long long bits[kTab];
+    double ss[kTab];
+};
+
+// A centre's samples in a box, to its extents and squared deviations.
+__device__ __forceinline__ void box_extent(const DevM& m, const FieldBox& b, int id, unsigned long long bits, double ss,
+                                           int x0, int y0, int z0, int t0) {
+    uint32_t* ext = m.cext + 8 * (size_t)id;
+    const int o[4] = {x0, y0, z0, t0}, n[4] = {b.ex(), b.ey(), b.ez(), b.et()};
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const unsigned long long w = bits & (~0ull >> (64 - n[d]));
+        bits >>= n[d];
+        const float h = d < 3 ? 0.5f : 0.0f;
+        atomicMin(&ext[d], float_key((float)(o[d] + __builtin_ctzll(w)) + h));
+        atomicMax(&ext[4 + d], float_key((float)(o[d] + 63 - __builtin_clzll(w)) + h));
+    }
+    atomicAdd(&m.css[2 * (size_t)id], ss);
+}
+
+__global__ __launch_bounds__(kBlock) void k_feature_field(DevS s, DevM m, FieldBox b) {
+    __shared__ BoxTable tb;
+    for (int i = threadIdx.x; i < kTab; i += kBlock) {
+        tb.key[i] = -1;
+        tb.bits[i] = 0ull;
+        tb.ss[i] = 0.0;
+    }
+    __syncthreads();
+    uint32_t r = blockIdx.x;
+    const int x0 = (int)(r % b.nx) * b.ex();
+    r /= b.nx;
+    const int y0 = (int)(r % b.ny) * b.ey();
+    r /= b.ny;
+    const int z0 = (int)(r % b.nz) * b.ez(), t0 = (int)(r / b.nz) * b.et();
+    const FieldLane at(b);
+    int id = -1;
+    unsigned long long bits = 0;
+    double ss = 0.0, mean = 0.0;
+    auto flush = [&]() {
+        if (id < 0) return;
+        const unsigned h = ((unsigned)id * 2654435761u) >> 26;
+        for (int k = 0; k < kTab; ++k) {
+            const int slot = (h + k) & (kTab - 1);
+            const int was = atomicCAS(&tb.key[slot], -1, id);
+            if (was == -1 || was == id) {
+                atomicOr(&tb.bits[slot], bits);
+                atomicAdd(&tb.ss[slot], ss);
+                return;
+            }
+        }
+        box_extent(m, b, id, bits, ss, x0, y0, z0, t0);  // table full
+    };
+    for (int k = 0; k < at.steps; ++k) {
+        int y, z, t;
+        at.place(b, k, y, z, t);
+        if (y0 + y >= s.Y || z0 + z >= s.Z || t0 + t >= s.T || x0 + at.x >= s.X) continue;
+        const size_t i = (((size_t)(t0 + t) * s.Z + z0 + z) * s.Y + y0 + y) * s.X + x0 + at.x;
+        const unsigned long long row = ((((1ull << t) << b.ez() | (1ull << z)) << b.ey()) | (1ull << y)) << b.ex();
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
+        int L[4] = {-1, -1, -1, -1};
+        if (b.vec) {
+            const float4 f = *reinterpret_cast<const float4*>(s.field + i);
+            const int4 q = *reinterpret_cast<const int4*>(s.labels + i);
+            v[0] = f.x; v[1] = f.y; v[2] = f.z; v[3] = f.w;
+            L[0] = q.x; L[1] = q.y; L[2] = q.z; L[3] = q.w;
+        } else {
+            for (int j = 0; j < 4 && x0 + at.x + j < s.X; ++j) {
+                v[j] = s.field[i + j];
+                L[j] = s.labels[i + j];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (L[j] < 0) continue;
+            if (L[j] != id) {
+                flush();
+                id = L[j];
+                bits = 0;
+                ss = 0.0;
+                mean = m.fmean[2 * (size_t)m.feat[id]];
+            }
+            bits |= row | (1ull << (at.x + j));
+            const double dev = (double)v[j] - mean;
+            ss += dev * dev;
+        }
+    }
+    flush();
+    __syncthreads();
+    for (int slot = threadIdx.x; slot < kTab; slot += kBlock)
+        if (tb.key[slot] >= 0) box_extent(m, b, tb.key[slot], tb.bits[slot], tb.ss[slot], x0, y0, z0, t0);
+}
+
+// Point samples in visiting order.
+__global__ __launch_bounds__(kBlock) void k_feature_points(DevS s, DevM m) {
     __shared__ StatTable tb;
     stat_init(tb);
     const uint64_t V = (uint64_t)s.X * s.Y * s.Z * s.T;
-    const uint64_t N = ty == 0 ? V : (uint64_t)s.Tp * s.P;
+    const uint64_t N = (uint64_t)s.Tp * s.P;
     const uint64_t base = (uint64_t)blockIdx.x * (kBlock * kPer) + (uint64_t)threadIdx.x * kPer;
     StatRun run;
     run.id = -1;
+    double mean = 0.0;
     for (int j = 0; j < kPer; ++j) {
         const uint64_t i = base + j;
         if (i >= N) break;
-        const int L = s.labels[(ty == 0 ? 0 : V) + i];
+        const int L = s.labels[V + i];
         if (L < 0) continue;
-        float c[4], v;
-        if (ty == 0) {
-            uint32_t r = (uint32_t)i;
-            c[0] = (float)(r % (uint32_t)s.X) + 0.5f;
-            r /= (uint32_t)s.X;
-            c[1] = (float)(r % (uint32_t)s.Y) + 0.5f;
-            r /= (uint32_t)s.Y;
-            c[2] = (float)(r % (uint32_t)s.Z) + 0.5f;
-            c[3] = (float)(r / (uint32_t)s.Z);
-            v = s.field[i];
-        } else {
-            const float4 pp = s.spos[i];
-            c[0] = pp.x;
-            c[1] = pp.y;
-            c[2] = pp.z;
-            c[3] = pp.w;
-            v = s.sattr[i];
-        }
-        const double dev = (double)v - m.fmean[2 * (size_t)m.feat[L] + ty];
-        stat_sample(m, tb, run, L, c, dev, ty);
+        const float4 pp = s.spos[i];
+        const float c[4] = {pp.x, pp.y, pp.z, pp.w};
+        if (L != run.id) mean = m.fmean[2 * (size_t)m.feat[L] + 1];
+        stat_sample(m, tb, run, L, c, (double)s.sattr[i] - mean, 1);
     }
-    stat_add(m, tb, run, ty);
-    stat_flush(m, tb, ty);
+    stat_add(m, tb, run, 1);
+    stat_flush(m, tb, 1);
 }
 
 // Per-centre extents and squared deviations folded into their features, one
@@ -1358,10 +1503,10 @@ __global__ __launch_bounds__(256) void k_feature_fold(DevM m) {
     double q[2];
     for (int d = 0; d < 8; ++d) e[d] = F >= 0 ? m.cext[8 * (size_t)i + d] : (d < 4 ? 0xFFFFFFFFu : 0u);
     for (int t = 0; t < 2; ++t) q[t] = F >= 0 ? m.css[2 * (size_t)i + t] : 0.0;
-    per_wave_feature(F, [&](int FL, bool mine, bool lead) {
+    per_wave_feature(F, [&](int FL, bool mine, bool lead, bool combine) {
         for (int d = 0; d < 8; ++d) {
             uint32_t x = mine ? e[d] : (d < 4 ? 0xFFFFFFFFu : 0u);
-            for (int o = 32; o > 0; o >>= 1) {
+            for (int o = combine ? 32 : 0; o > 0; o >>= 1) {
                 const uint32_t y = __shfl_xor(x, o);
                 x = d < 4 ? min(x, y) : max(x, y);
             }
@@ -1372,7 +1517,7 @@ __global__ __launch_bounds__(256) void k_feature_fold(DevM m) {
         }
         for (int t = 0; t < 2; ++t) {
             double x = mine ? q[t] : 0.0;
-            for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+            for (int o = combine ? 32 : 0; o > 0; o >>= 1) x += __shfl_xor(x, o);
             if (lead) atomicAdd(&m.fss[2 * (size_t)FL + t], x);
         }
     });
@@ -1555,12 +1700,26 @@ __global__ __launch_bounds__(256) void k_order_scatter(const uint32_t* __restric
 
 }  // namespace
 
-// Gathers, so that the writes of [T][P] are coalesced: out[q] = in[pos[q]].
-__global__ __launch_bounds__(256) void k_slic_unsort(const int32_t* __restrict__ in,
-                                                     const uint32_t* __restrict__ pos, uint64_t Q,
-                                                     int32_t* __restrict__ out) {
-    for (uint64_t q = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; q < Q; q += (uint64_t)gridDim.x * blockDim.x)
-        out[q] = in[pos[q]];
+// out[q] = in[pos[q]] over [T][P].  A block takes 64 particles x 64 steps: the
+// places are read and the labels written with lanes along the particles (whole
+// lines), the gather between them runs along each particle's steps, whose
+// neighbours mostly lie side by side in the visiting order: 4.4 ms for 2.7e8
+// labels, 5.2 ms gathered with lanes along the particles.
+__global__ __launch_bounds__(256) void k_slic_unsort(const int32_t* __restrict__ in, const uint32_t* __restrict__ pos,
+                                                     int T, int64_t P, int32_t* __restrict__ out) {
+    __shared__ uint32_t s_v[kOrderP][kOrderT + 1];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t p0 = (int64_t)blockIdx.x * kOrderP;
+    const int t0 = blockIdx.y * kOrderT;
+    const int64_t p = p0 + lane;
+    for (int k = wave; k < kOrderT && t0 + k < T; k += 4)
+        if (p < P) s_v[lane][k] = pos[(uint64_t)(t0 + k) * P + p];
+    __syncthreads();
+    for (int j = wave; j < kOrderP && p0 + j < P; j += 4)
+        if (t0 + lane < T) s_v[j][lane] = (uint32_t)in[s_v[j][lane]];
+    __syncthreads();
+    for (int k = wave; k < kOrderT && t0 + k < T; k += 4)
+        if (p < P) out[(uint64_t)(t0 + k) * P + p] = (int32_t)s_v[lane][k];
 }
 
 // Trajectory segments of the features (Section 3.4): a particle-step keeps
@@ -1592,10 +1751,10 @@ void launch_slic_segments(int32_t* lab, const int32_t* feat, int T, int64_t P, h
     hipLaunchKernelGGL(k_slic_segments, dim3(g), dim3(256), 0, st, lab, feat, T, P);
 }
 
-void launch_slic_unsort(const int32_t* in, const uint32_t* order, uint64_t Q, int32_t* out, hipStream_t st) {
-    if (Q == 0) return;
-    const unsigned g = (unsigned)std::min<uint64_t>((Q + 255) / 256, 16384);
-    hipLaunchKernelGGL(k_slic_unsort, dim3(g), dim3(256), 0, st, in, order, Q, out);
+void launch_slic_unsort(const int32_t* in, const uint32_t* order, int T, int64_t P, int32_t* out, hipStream_t st) {
+    if (T <= 0 || P <= 0) return;
+    hipLaunchKernelGGL(k_slic_unsort, dim3((unsigned)((P + kOrderP - 1) / kOrderP), (unsigned)((T + kOrderT - 1) / kOrderT)),
+                       dim3(256), 0, st, in, order, T, P, out);
 }
 
 int launch_slic_order(const uint32_t* bins, const float* xyz, const float* attr, int64_t P, int Tpad,
@@ -1640,7 +1799,7 @@ static FieldBox field_box(const DevS& s) {
         b.nt = (s.T + b.et() - 1) / b.et();
         return (uint64_t)b.nx * b.ny * b.nz * b.nt;
     };
-    const uint64_t big = s.Z > 1 ? shape(1, 1, 0) : shape(1, 0, 1);
+    const uint64_t big = s.Z > 1 ? shape(1, 1, 0) : shape(b.wx > 0, 0, 1);
     if (big < 2048) shape(0, 0, 0);
     return b;
 }
@@ -1684,15 +1843,16 @@ void launch_slic_iteration(const DevS& s, hipStream_t st) {
 
 int launch_slic_merge(const DevS& s, const DevM& m, hipStream_t st) {
     const dim3 gk(blocks_for((uint64_t)m.K, 256)), b256(256);
-    const uint64_t V = (uint64_t)s.X * s.Y * s.Z * s.T, Q = (uint64_t)s.Tp * s.P;
+    const uint64_t Q = (uint64_t)s.Tp * s.P;
     hipLaunchKernelGGL(k_merge_init, gk, b256, 0, st, s, m);
     const unsigned nt = (unsigned)((m.K + kMergeTile - 1) / kMergeTile);
     hipLaunchKernelGGL(k_merge_pairs, dim3(nt, nt), dim3(kMergeTile), 0, st, s, m);
     hipLaunchKernelGGL(k_merge_flatten, gk, b256, 0, st, s, m);
     hipLaunchKernelGGL(k_feature_sums, gk, b256, 0, st, s, m);
     hipLaunchKernelGGL(k_feature_means, gk, b256, 0, st, s, m);
-    if (V) hipLaunchKernelGGL(k_feature_pass, dim3(blocks_for(V, kBlock * kPer)), dim3(kBlock), 0, st, s, m, 0);
-    if (Q) hipLaunchKernelGGL(k_feature_pass, dim3(blocks_for(Q, kBlock * kPer)), dim3(kBlock), 0, st, s, m, 1);
+    const FieldBox b = field_box(s);
+    hipLaunchKernelGGL(k_feature_field, dim3((uint32_t)b.nx * b.ny * b.nz * b.nt), dim3(kBlock), 0, st, s, m, b);
+    if (Q) hipLaunchKernelGGL(k_feature_points, dim3(blocks_for(Q, kBlock * kPer)), dim3(kBlock), 0, st, s, m);
     hipLaunchKernelGGL(k_feature_fold, gk, b256, 0, st, m);
     hipLaunchKernelGGL(k_feature_write, gk, b256, 0, st, m);
     return (int)hipGetLastError();
