@@ -151,10 +151,11 @@ __device__ int assign_cands(const DevS& s, float px, float py, float pz, float p
 }
 
 // The same search over reach ranges of any width (the slab test inline).
-__device__ __noinline__ int assign_wide(const DevS& s, float px, float py, float pz, float pt, float v,
+__device__ __forceinline__ int assign_wide(const DevS& s, float px, float py, float pz, float pt, float v,
                                         bool field, int prev) {
     const float p[4] = {px, py, pz, pt};
     int lo[4], hi[4];
+#pragma unroll
     for (int d = 0; d < 4; ++d) {
         const int c = seed_cell(p[d], s.C[d], s.k[d]);
         lo[d] = s.reach[(d * s.kmax + c) * 2];
@@ -549,12 +550,10 @@ __device__ __forceinline__ void note_box(const DevS& s, uint32_t e) {
 // samples and 16,384 centres (256^3 x 64, 4 B read and 4 B written per sample),
 // where testing the slab combinations sample by sample took 66 ms.
 template <int ASSIGN>
-__global__ __launch_bounds__(kBlock) void k_slic_field(DevS s, FieldBox b) {
-    __shared__ Cands L;
-    __shared__ unsigned long long acc[kCand][2];
-    if (s.counters[SC_DONE]) return;
+__device__ __forceinline__ void field_pass(const DevS& s, const FieldBox& b, uint32_t box, Cands& L,
+                                           unsigned long long (*acc)[2]) {
     const int wave = threadIdx.x >> 6;
-    uint32_t r = blockIdx.x;
+    uint32_t r = box;
     const int x0 = (int)(r % b.nx) * b.ex();
     r /= b.nx;
     const int y0 = (int)(r % b.ny) * b.ey();
@@ -586,7 +585,7 @@ __global__ __launch_bounds__(kBlock) void k_slic_field(DevS s, FieldBox b) {
     if (ASSIGN) n = s.boxes ? list_cands<true>(s, L, lo, hi) : -1;
     else n = list_cells(s, L, lo, hi, first, num);
     if (n < 0) {  // block-uniform
-        note_box(s, blockIdx.x);
+        note_box(s, box);
         return;
     }
     for (int i = threadIdx.x; i < n; i += kBlock) acc[i][0] = acc[i][1] = 0ull;
@@ -709,14 +708,12 @@ struct PointRun {
 // same order.  Bound like the field pass: 4.4 ms for 2.7e8 points and 16,384
 // centres, 24 ms sample by sample.
 template <int ASSIGN, int N>
-__global__ __launch_bounds__(kBlock) void k_slic_points(DevS s, uint32_t nfield) {
-    __shared__ Cands L;
-    __shared__ unsigned long long acc[kCand][5];
-    if (s.counters[SC_DONE]) return;
+__device__ __forceinline__ void point_pass(const DevS& s, uint32_t nfield, uint32_t blk, Cands& L,
+                                           unsigned long long (*acc)[5]) {
     const int wave = threadIdx.x >> 6;
     const uint64_t V = (uint64_t)s.X * s.Y * s.Z * s.T;
     const uint64_t Q = (uint64_t)s.Tp * s.P;
-    const uint64_t base = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) * N;
+    const uint64_t base = ((uint64_t)blk * kBlock + threadIdx.x) * N;
     int32_t* lab = s.labels + V + base;
     float px[N], py[N], pz[N], pt[N], v[N];
     bool in[N], live[N];
@@ -771,7 +768,7 @@ __global__ __launch_bounds__(kBlock) void k_slic_points(DevS s, uint32_t nfield)
     if (ASSIGN) n = s.boxes ? list_cands<false>(s, L, blo, bhi) : -1;
     else n = list_cells(s, L, blo, bhi, first, num);
     if (n < 0) {  // block-uniform
-        note_box(s, nfield + blockIdx.x);
+        note_box(s, nfield + blk);
         return;
     }
     for (int i = threadIdx.x; i < n * 5; i += kBlock) (&acc[0][0])[i] = 0ull;
@@ -841,9 +838,38 @@ __global__ __launch_bounds__(kBlock) void k_slic_points(DevS s, uint32_t nfield)
     }
 }
 
+template <int ASSIGN>
+__global__ __launch_bounds__(kBlock) void k_slic_field(DevS s, FieldBox b) {
+    __shared__ Cands L;
+    __shared__ unsigned long long acc[kCand][2];
+    if (s.counters[SC_DONE]) return;
+    field_pass<ASSIGN>(s, b, blockIdx.x, L, acc);
+}
+
+template <int ASSIGN, int N>
+__global__ __launch_bounds__(kBlock) void k_slic_points(DevS s, uint32_t nfield) {
+    __shared__ Cands L;
+    __shared__ unsigned long long acc[kCand][5];
+    if (s.counters[SC_DONE]) return;
+    point_pass<ASSIGN, N>(s, nfield, blockIdx.x, L, acc);
+}
+
+// Both passes in one launch, one point per thread, where neither fills the GPU
+// (a block's chain of loads, about 15 us, is what an iteration of 32^3 x 8 then
+// waits for: once instead of twice).
+template <int ASSIGN>
+__global__ __launch_bounds__(kBlock) void k_slic_both(DevS s, FieldBox b, uint32_t nfield) {
+    __shared__ Cands L;
+    __shared__ unsigned long long acc[kCand][5];
+    if (s.counters[SC_DONE]) return;
+    if (blockIdx.x < nfield)
+        field_pass<ASSIGN>(s, b, blockIdx.x, L, reinterpret_cast<unsigned long long(*)[2]>(&acc[0][0]));
+    else
+        point_pass<ASSIGN, 1>(s, nfield, blockIdx.x - nfield, L, acc);
+}
+
 // The boxes whose list did not fit, sample by sample through the slabs' reach
-// ranges, and the buffers the coming update fills (slab bounds, moved count)
-// reset.  npoint: points per noted block.  A kernel of its own, so that its
+// ranges.  npoint: points per noted block.  A kernel of its own, so that its
 // registers do not cost the passes their occupancy: inside them it held them at
 // 119 and 101 registers, four waves per SIMD, and 9.8 and 7.8 ms instead of 4.9
 // and 4.4 ms at 256^3 x 64.
@@ -851,10 +877,6 @@ template <int ASSIGN>
 __global__ __launch_bounds__(kBlock) void k_slic_rest(DevS s, FieldBox b, uint32_t nfield, uint32_t npoint) {
     __shared__ Table tb;
     if (s.counters[SC_DONE]) return;
-    const uint32_t gid = blockIdx.x * kBlock + threadIdx.x;
-    for (uint32_t i = gid; i < 8u * s.kmax; i += gridDim.x * kBlock)
-        s.slab_next[i] = i < 4u * s.kmax ? 0xFFFFFFFFu : 0u;
-    if (gid == 0) s.counters[SC_MOVED] = 0u;
     const uint32_t count = s.over[0];
     const uint64_t V = (uint64_t)s.X * s.Y * s.Z * s.T, Q = (uint64_t)s.Tp * s.P;
     for (uint32_t e = blockIdx.x; e < count; e += gridDim.x) {
@@ -943,9 +965,10 @@ __device__ __forceinline__ float next_slab(const DevS& s, int i) {
 // a few dozen slabs, and the same address takes 11 ns per device atomic (16,384
 // centres: 312 us of them straight to memory, 15 us now).
 //
-// The last block to finish writes the reach ranges of the new slabs, counts the
-// iteration, notes a run that is done (nothing moved, a value out of range) and
-// reports to the host.
+// The last block to finish writes the reach ranges of the new slabs, clears the
+// slab buffer the passes have read (the next update's), counts the iteration,
+// notes a run that is done (nothing moved, a value out of range) and reports to
+// the host.
 constexpr int kSlabLds = 256;  // slabs per axis gathered in LDS
 __global__ __launch_bounds__(256) void k_slic_update(DevS s, int seed) {
     __shared__ uint32_t s_slab[2][4][kSlabLds];
@@ -1035,7 +1058,10 @@ __global__ __launch_bounds__(256) void k_slic_update(DevS s, int seed) {
     // floor of the upper end / C (clamped like seed_cell), widened by 10^-3 of a
     // cell for the rounding of the division (below 2.5e-4 of a cell wherever the
     // cell index is below 4096).  Each of those cells takes i into its range.
-    for (int j = threadIdx.x; j < 8 * s.kmax; j += blockDim.x) s.reach[j] = (j & 1) ? -1 : 0x7FFFFFFF;
+    for (int j = threadIdx.x; j < 8 * s.kmax; j += blockDim.x) {
+        s.reach[j] = (j & 1) ? -1 : 0x7FFFFFFF;
+        s.slab[j] = j < 4 * s.kmax ? 0xFFFFFFFFu : 0u;
+    }
     __threadfence();
     __syncthreads();
     for (int g = threadIdx.x; g < 4 * s.kmax; g += blockDim.x) {
@@ -1059,6 +1085,7 @@ __global__ __launch_bounds__(256) void k_slic_update(DevS s, int seed) {
         const uint32_t iters = s.counters[SC_ITERS] + (seed ? 0u : 1u);
         s.counters[SC_ITERS] = iters;
         s.counters[SC_TICKET] = 0u;
+        s.counters[SC_MOVED] = 0u;
         s.over[0] = 0u;
         const uint32_t done = range || (!seed && mv == 0u);
         if (done) s.counters[SC_DONE] = 1u;
@@ -1068,13 +1095,15 @@ __global__ __launch_bounds__(256) void k_slic_update(DevS s, int seed) {
     }
 }
 
-// The start of a run: sums, counters and the first slab buffer cleared.
+// The start of a run: sums, counters and the first update's slab buffer cleared.
 __global__ __launch_bounds__(256) void k_slic_begin(DevS s) {
     const uint64_t n = (uint64_t)s.K * kSlicAcc;
     const uint64_t gid = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
     for (uint64_t i = gid; i < n; i += (uint64_t)gridDim.x * blockDim.x) s.acc[i] = 0ull;
     if (gid < kSlicCounters) s.counters[gid] = 0u;
     if (gid == 0) s.over[0] = 0u;
+    for (uint64_t i = gid; i < 8u * s.kmax; i += (uint64_t)gridDim.x * blockDim.x)
+        s.slab_next[i] = i < 4u * s.kmax ? 0xFFFFFFFFu : 0u;
 }
 
 inline unsigned blocks_for(uint64_t n, uint64_t per) { return (unsigned)((n + per - 1) / per); }
@@ -1148,14 +1177,16 @@ __global__ __launch_bounds__(256) void k_merge_init(DevS s, DevM m) {
 
 // Pair tests in tiles of 256 x 256 centres, so that every block does the same
 // work (K^2 / 2 tests in all): block (bx, by >= bx) compares the centres of
-// tile bx, one per thread, with the later centres of tile by, held in LDS.  Two
+// tile bx, a row each, with the later centres of tile by, held in LDS.  Two
 // centres match when they have the same sample types and, per type, means
 // within eps of the larger magnitude (Section 3.3).  The block's matches are
-// united in a union-find of its 512 centres in LDS, and each centre then with its
-// local root in memory: at most 512 walks over memory per block, side by side,
-// instead of one after another for every match of a thread (128 centres: 117 to
-// 54 us; 16,384 centres: 1.5 to 0.8 ms).
-constexpr int kMergeTile = 256;
+// united in a union-find of the two tiles' centres in LDS, and each centre then with its
+// local root in memory: at most one walk over memory per centre and block, side by side,
+// instead of one after another for every match of a thread (16,384 centres: 1.5
+// to 0.8 ms).  Up to kMergeSmall centres the tiles are 64 x 64 and four threads
+// share a row, so that no thread walks more than 16 pairs (128 centres: 16 us, 117
+// at first); with more the extra blocks only add walks.
+constexpr int kMergeSmall = 4096;
 __device__ __forceinline__ int lds_link(const int* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
@@ -1169,14 +1200,16 @@ __device__ __forceinline__ int lds_root(int* link, int i) {
         i = gp;
     }
 }
-__global__ __launch_bounds__(kMergeTile) void k_merge_pairs(DevS s, DevM m) {
+template <int TILE>
+__global__ __launch_bounds__(256) void k_merge_pairs(DevS s, DevM m) {
+    constexpr int kShare = 256 / TILE;  // threads per row
     if (blockIdx.y < blockIdx.x) return;  // block-uniform: lower triangle
-    __shared__ double sv[2][kMergeTile];  // field mean, point mean
-    __shared__ unsigned sh[kMergeTile];   // bit 0: has field samples, bit 1: has point samples
-    __shared__ int link[2 * kMergeTile];  // tile bx, then tile by (a diagonal block uses the first half)
-    const int j0 = blockIdx.y * kMergeTile;
-    const int jl = blockIdx.x == blockIdx.y ? 0 : kMergeTile;
-    {
+    __shared__ double sv[2][TILE];  // field mean, point mean
+    __shared__ unsigned sh[TILE];   // bit 0: has field samples, bit 1: has point samples
+    __shared__ int link[2 * TILE];  // tile bx, then tile by (a diagonal block uses the first half)
+    const int j0 = blockIdx.y * TILE;
+    const int jl = blockIdx.x == blockIdx.y ? 0 : TILE;
+    if (threadIdx.x < TILE) {
         const int j = j0 + threadIdx.x;
         unsigned h = 0;
         double vf = 0.0, vp = 0.0;
@@ -1189,16 +1222,16 @@ __global__ __launch_bounds__(kMergeTile) void k_merge_pairs(DevS s, DevM m) {
         sv[0][threadIdx.x] = vf;
         sv[1][threadIdx.x] = vp;
         link[threadIdx.x] = threadIdx.x;
-        link[kMergeTile + threadIdx.x] = kMergeTile + threadIdx.x;
+        link[TILE + threadIdx.x] = TILE + threadIdx.x;
     }
     __syncthreads();
-    const int i = blockIdx.x * kMergeTile + threadIdx.x;
+    const int il = threadIdx.x % TILE, i = blockIdx.x * TILE + il;
     const unsigned hi = i >= m.K ? 0u : (s.cnt[2 * (size_t)i] > 0 ? 1u : 0u) | (s.cnt[2 * (size_t)i + 1] > 0 ? 2u : 0u);
     if (hi) {  // a centre without samples merges with nothing
         const double af = s.cen[6 * (size_t)i + 5], ap = s.cen[6 * (size_t)i + 4];
-        const int jn = min(kMergeTile, m.K - j0);
-        int root = threadIdx.x;  // this centre's root when last looked up
-        for (int jj = 0; jj < jn; ++jj) {
+        const int jn = min(TILE, m.K - j0);
+        int root = il;  // this centre's root when last looked up
+        for (int jj = threadIdx.x / TILE; jj < jn; jj += kShare) {
             const int j = j0 + jj;
             if (j <= i || sh[jj] != hi) continue;  // a type only one has: different phenomena
             if (lds_link(&link[jl + jj]) == root) continue;  // known to be in one component already
@@ -1214,17 +1247,22 @@ __global__ __launch_bounds__(kMergeTile) void k_merge_pairs(DevS s, DevM m) {
             if (!ok) continue;
             for (;;) {  // every failed swap means another union succeeded
                 const int a = lds_root(link, root), b = lds_root(link, jl + jj);
-                root = min(a, b);
-                if (a == b || atomicCAS(&link[max(a, b)], max(a, b), root) == max(a, b)) break;
+                root = a;
+                if (a == b) break;
+                const int lo = min(a, b), up = max(a, b);
+                if (atomicCAS(&link[up], up, lo) == up) {
+                    root = lo;
+                    break;
+                }
             }
         }
     }
     __syncthreads();
-    for (int l = threadIdx.x; l < jl + kMergeTile; l += kMergeTile) {
+    for (int l = threadIdx.x; l < jl + TILE; l += 256) {
         const int r = lds_root(link, l);
         if (r == l) continue;  // (centres past K match nothing and stay roots)
-        const int gl = l < kMergeTile ? blockIdx.x * kMergeTile + l : j0 + l - kMergeTile;
-        const int gr = r < kMergeTile ? blockIdx.x * kMergeTile + r : j0 + r - kMergeTile;
+        const int gl = l < TILE ? blockIdx.x * TILE + l : j0 + l - TILE;
+        const int gr = r < TILE ? blockIdx.x * TILE + r : j0 + r - TILE;
         if (!unite(m.parent, gl, gr, m.K)) m.err[0] = 1u;
     }
 }
@@ -1818,13 +1856,15 @@ static void launch_pass(const DevS& s, hipStream_t st) {
     const uint64_t Q = (uint64_t)s.Tp * s.P;
     const FieldBox b = field_box(s);
     const uint32_t nf = (uint32_t)b.nx * b.ny * b.nz * b.nt;
-    hipLaunchKernelGGL(k_slic_field<ASSIGN>, dim3(nf), dim3(kBlock), 0, st, s, b);
     const int per = points_per_thread(s);
     const uint32_t np = blocks_for(Q, (uint64_t)kBlock * per);
-    if (Q && per == kPer)
-        hipLaunchKernelGGL((k_slic_points<ASSIGN, kPer>), dim3(np), dim3(kBlock), 0, st, s, nf);
-    else if (Q)
-        hipLaunchKernelGGL((k_slic_points<ASSIGN, 1>), dim3(np), dim3(kBlock), 0, st, s, nf);
+    if (per == 1 && nf < 2048) {
+        hipLaunchKernelGGL(k_slic_both<ASSIGN>, dim3(nf + np), dim3(kBlock), 0, st, s, b, nf);
+    } else {
+        hipLaunchKernelGGL(k_slic_field<ASSIGN>, dim3(nf), dim3(kBlock), 0, st, s, b);
+        if (Q && per == 1) hipLaunchKernelGGL((k_slic_points<ASSIGN, 1>), dim3(np), dim3(kBlock), 0, st, s, nf);
+        else if (Q) hipLaunchKernelGGL((k_slic_points<ASSIGN, kPer>), dim3(np), dim3(kBlock), 0, st, s, nf);
+    }
     hipLaunchKernelGGL(k_slic_rest<ASSIGN>, dim3(std::min(nf + np, 2048u)), dim3(kBlock), 0, st, s, b, nf,
                        (uint32_t)(kBlock * per));
 }
@@ -1845,8 +1885,10 @@ int launch_slic_merge(const DevS& s, const DevM& m, hipStream_t st) {
     const dim3 gk(blocks_for((uint64_t)m.K, 256)), b256(256);
     const uint64_t Q = (uint64_t)s.Tp * s.P;
     hipLaunchKernelGGL(k_merge_init, gk, b256, 0, st, s, m);
-    const unsigned nt = (unsigned)((m.K + kMergeTile - 1) / kMergeTile);
-    hipLaunchKernelGGL(k_merge_pairs, dim3(nt, nt), dim3(kMergeTile), 0, st, s, m);
+    const int tile = m.K <= kMergeSmall ? 64 : 256;
+    const unsigned nt = (unsigned)((m.K + tile - 1) / tile);
+    if (tile == 64) hipLaunchKernelGGL(k_merge_pairs<64>, dim3(nt, nt), dim3(256), 0, st, s, m);
+    else hipLaunchKernelGGL(k_merge_pairs<256>, dim3(nt, nt), dim3(256), 0, st, s, m);
     hipLaunchKernelGGL(k_merge_flatten, gk, b256, 0, st, s, m);
     hipLaunchKernelGGL(k_feature_sums, gk, b256, 0, st, s, m);
     hipLaunchKernelGGL(k_feature_means, gk, b256, 0, st, s, m);

@@ -85,3 +85,35 @@ def test_boxes_equal_sample_by_sample(monkeypatch, case, flat):
         ofl, opl, ocen, ocnt, oit = oslic.slic(field, xyz, attr, k, w, cf, 0.0, iters)
         assert got[0] == oit and np.array_equal(got[1], ofl) and np.array_equal(got[2], opl)
         assert np.array_equal(got[4], ocnt) and got[3].tobytes() == ocen.tobytes()
+
+
+@pytest.mark.parametrize("k", [(8, 8, 1, 1), (13, 5, 1, 1), (16, 16, 16, 1), (17, 16, 16, 1)])
+def test_merge_tiles_match_oracle(k):
+    """Merging at the edges of the pair tiles (64 centres, 65, 4,096, where the
+    tiles become 256 x 256, and above): features, counts, means and extents
+    equal the oracle's, deviations to the 1e-9 of the other merge tests, from
+    no matches to nearly all."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1903_12294_amd import Grower
+    field, xyz, attr = _inputs(34, 32, 16, 2, 700, False)
+    g = Grower(device=0)
+    try:
+        g.load_field(field)
+        g.load_particles(xyz, attr)
+        g.slic_set_params(k, 1.0, 4.0, 4.0, 1.0, 0.0, 1)
+        g.slic_run()
+        fl, pl = g.slic_read_labels()
+        cen, cnt = g.slic_read_centres()
+        for eps in (0.0, 0.01, 0.2, 5.0):
+            print(f"[merge tiles] {k} eps={eps}", flush=True)
+            n = g.slic_merge(eps)
+            feat, st = g.slic_read_features()
+            ofeat = oslic.merge_centres(cen, cnt, eps)
+            assert np.array_equal(feat, ofeat) and n == int((ofeat == np.arange(len(ofeat))).sum())
+            ost = oslic.feature_stats(field, xyz, attr, fl, pl, ofeat)
+            exact = [0, 1, 2, 3] + list(range(6, 14))
+            assert st[:, exact].tobytes() == ost[:, exact].tobytes()
+            assert np.allclose(st[:, 4:6], ost[:, 4:6], rtol=1e-9, atol=1e-12)
+    finally:
+        g.close()
