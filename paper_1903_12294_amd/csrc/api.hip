@@ -132,6 +132,14 @@ struct mf4d_ctx {
 
     bool has_particles = false;
     PGeom pg{};
+    // Buffers of the last load, kept for a next one of the same sizes (a
+    // simulation's next window of steps): the particle buffers between a
+    // mf4d_load_field and the mf4d_load_particles that follows it hold kept_P x
+    // kept_T steps (0: none).  Any call that uses the context without
+    // particles, needs memory or loads other sizes gives them back
+    // (release_kept).
+    int64_t kept_P = 0;
+    int kept_T = 0;
     uint32_t* bins = nullptr;
     float* attr_t = nullptr;
     unsigned long long* Ap = nullptr;
@@ -329,26 +337,13 @@ void mark_labels(mf4d_ctx* c) {
     c->labels_marked = hipEventRecord(c->ev_labels, c->stream) == hipSuccess;
 }
 
-void free_field(mf4d_ctx* c) {
+// What a field load replaces whatever its size: buffers made on first use.
+void free_field_extras(mf4d_ctx* c) {
     quiesce_side(c);
     free_slic(c);
-    dev_free(c->field);
-    dev_free(c->Af);
-    dev_free(c->Lf);
-    dev_free(c->active);
     dev_free(c->Lf_alt);
     dev_free(c->active_alt);
     c->alt_ready = false;
-    dev_free(c->dirty);
-    dev_free(c->work);
-    dev_free(c->wcnt);
-    dev_free(c->chg);
-    dev_free(c->tsum);
-    dev_free(c->cand);
-    dev_free(c->bstats);
-    dev_free(c->feat);
-    dev_free(c->blogits);
-    dev_free(c->tpred);
     dev_free(c->pr_buf);
     dev_free(c->jlf);
     {
@@ -371,33 +366,67 @@ void free_field(mf4d_ctx* c) {
     c->has_field = false;
 }
 
-void free_particles(mf4d_ctx* c) {
+void free_field(mf4d_ctx* c) {
+    free_field_extras(c);
+    dev_free(c->field);
+    dev_free(c->Af);
+    dev_free(c->Lf);
+    dev_free(c->active);
+    dev_free(c->dirty);
+    dev_free(c->work);
+    dev_free(c->wcnt);
+    dev_free(c->chg);
+    dev_free(c->tsum);
+    dev_free(c->cand);
+    dev_free(c->bstats);
+    dev_free(c->feat);
+    dev_free(c->blogits);
+    dev_free(c->tpred);
+}
+
+// No particles from here on; the buffers of their load are kept (kept_P, kept_T).
+void drop_particles(mf4d_ctx* c) {
     quiesce_side(c);
     dev_free(c->jlp);
     dev_free(c->b_prank);
-    dev_free(c->praw);
     dev_free(c->porder);
     dev_free(c->spos);
     dev_free(c->sattr);
     free_slic(c);
+    dev_free(c->Lp_alt);
+    dev_free(c->pflag_alt);
+    c->alt_ready = false;
+    dev_free(c->b_pown);
+    c->b_pown_n = 0;
+    c->b_grown = false;
+    if (c->has_particles) {
+        c->kept_P = c->pg.P;
+        c->kept_T = c->pg.T;
+    }
+    c->has_particles = false;
+    c->pg = PGeom{};
+    c->bstats_valid = false;
+}
+
+void free_particles(mf4d_ctx* c) {
+    drop_particles(c);
+    dev_free(c->praw);
     dev_free(c->bins);
     dev_free(c->attr_t);
     dev_free(c->Ap);
     dev_free(c->Lp);
-    dev_free(c->Lp_alt);
-    dev_free(c->pflag_alt);
-    c->alt_ready = false;
     dev_free(c->clist);
     dev_free(c->pdirty);
     dev_free(c->pflag);
     dev_free(c->dlist);
     dev_free(c->psum);
-    dev_free(c->b_pown);
-    c->b_pown_n = 0;
-    c->b_grown = false;
-    c->has_particles = false;
-    c->pg = PGeom{};
-    c->bstats_valid = false;
+    c->kept_P = 0;
+    c->kept_T = 0;
+}
+
+// Give back particle buffers that no particles use.
+void release_kept(mf4d_ctx* c) {
+    if (!c->has_particles && c->kept_P) free_particles(c);
 }
 
 int staging_for(mf4d_ctx* c, size_t bytes, void** out) {
@@ -931,39 +960,55 @@ int mf4d_load_field(mf4d_ctx* c, const float* field, int X, int Y, int Z, int T,
     g.NT = (uint32_t)nt;
     g.WCAP = (uint32_t)((nt + kWorkSubs - 1) / kWorkSubs);
     HIP_TRY(hipSetDevice(c->device));
-    free_particles(c);
-    free_field(c);
-    c->state = 0;
     const size_t V = (size_t)X * Y * Z * T;
-    int rc = dev_alloc(&c->field, V);
-    if (!rc) rc = dev_alloc(&c->Af, g.nwords);
-    if (!rc) rc = dev_alloc(&c->Lf, g.nwords);
-    if (!rc) rc = dev_alloc(&c->active, (size_t)g.NT + 8);
-    if (!rc) rc = dev_alloc(&c->dirty, 2 * (size_t)g.NT);
-    if (!rc) rc = dev_alloc(&c->chg, 2 * (size_t)g.NT + 8);
-    if (!rc) rc = dev_alloc(&c->work, 2 * (size_t)kWorkSubs * g.WCAP);
-    if (!rc) rc = dev_alloc(&c->wcnt, 2 * (size_t)kWorkSubs * kWcntStride);
-    if (!rc) rc = dev_alloc(&c->tsum, (size_t)g.NT);
-    if (!rc) rc = dev_alloc(&c->cand, (size_t)g.NT);
     const BrickDims bd{T, (Z + 7) / 8, (Y + 7) / 8, (X + 7) / 8};
-    const size_t nbricks = (size_t)bd.T * bd.D * bd.H * bd.W;
-    if (!rc) rc = dev_alloc(&c->bstats, nbricks);
-    if (!rc) rc = dev_alloc(&c->feat, nbricks * 16);
-    if (!rc) rc = dev_alloc(&c->blogits, nbricks);
-    if (!rc) rc = dev_alloc(&c->tpred, (size_t)g.NT);
+    const bool same = c->has_field && c->g.X == X && c->g.Y == Y && c->g.Z == Z && c->g.T == T && c->g.BT == g.BT;
+    c->state = 0;
+    int rc = MF4D_OK;
+    if (same) {
+        // hipMalloc and hipFree of these took 4 of the 5.2 ms that loading,
+        // growing and reading 128^3 x 32 with 262,144 particles took
+        drop_particles(c);
+        free_field_extras(c);
+    } else {
+        free_particles(c);
+        free_field(c);
+        rc = dev_alloc(&c->field, V);
+        if (!rc) rc = dev_alloc(&c->Af, g.nwords);
+        if (!rc) rc = dev_alloc(&c->Lf, g.nwords);
+        if (!rc) rc = dev_alloc(&c->active, (size_t)g.NT + 8);
+        if (!rc) rc = dev_alloc(&c->dirty, 2 * (size_t)g.NT);
+        if (!rc) rc = dev_alloc(&c->chg, 2 * (size_t)g.NT + 8);
+        if (!rc) rc = dev_alloc(&c->work, 2 * (size_t)kWorkSubs * g.WCAP);
+        if (!rc) rc = dev_alloc(&c->wcnt, 2 * (size_t)kWorkSubs * kWcntStride);
+        if (!rc) rc = dev_alloc(&c->tsum, (size_t)g.NT);
+        if (!rc) rc = dev_alloc(&c->cand, (size_t)g.NT);
+        const size_t nbricks = (size_t)bd.T * bd.D * bd.H * bd.W;
+        if (!rc) rc = dev_alloc(&c->bstats, nbricks);
+        if (!rc) rc = dev_alloc(&c->feat, nbricks * 16);
+        if (!rc) rc = dev_alloc(&c->blogits, nbricks);
+        if (!rc) rc = dev_alloc(&c->tpred, (size_t)g.NT);
+    }
     if (rc) {
         free_field(c);
         return rc;
     }
-    HIP_TRY(hipMemcpyAsync(c->field, field, V * sizeof(float),
-                           where == MF4D_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice,
-                           c->stream));
+    // a device field is copied by the pass that summarises its tiles
+    if (where == MF4D_HOST) {
+        const hipError_t e = hipMemcpyAsync(c->field, field, V * sizeof(float), hipMemcpyHostToDevice, c->stream);
+        if (e != hipSuccess) {
+            free_field(c);
+            return fail(MF4D_ERR_HIP, "field upload failed: %s", hipGetErrorString(e));
+        }
+    }
     launch_fill_u32(c->Af, 0, g.nwords, c->stream);
     launch_fill_u32(c->Lf, 0, g.nwords, c->stream);
-    launch_summaries(g, c->field, c->tsum, c->stream);
+    if (where == MF4D_HOST) launch_summaries(g, c->field, nullptr, c->tsum, c->stream);
+    else launch_summaries(g, field, c->field, c->tsum, c->stream);
     c->bstats_valid = false;
     rc = sync(c);
     if (rc) {
+        free_particles(c);
         free_field(c);
         return rc;
     }
@@ -1014,69 +1059,51 @@ int mf4d_load_particles_rate(mf4d_ctx* c, const float* xyz, const float* attr, i
         return fail(MF4D_ERR_UNSUPPORTED, "%lld particles x %d padded steps exceed 2^31",
                     (long long)P, pg.Tpad);
     HIP_TRY(hipSetDevice(c->device));
-    free_particles(c);
     c->state = 0;
-    if (P == 0) return MF4D_OK;
+    drop_particles(c);
     const size_t Q = (size_t)P * pg.Tpad;
-    int rc = dev_alloc(&c->bins, Q);
-    if (!rc) rc = dev_alloc(&c->attr_t, Q);
-    if (!rc) rc = dev_alloc(&c->Ap, (size_t)P * pg.W);
-    if (!rc) rc = dev_alloc(&c->Lp, (size_t)P * pg.W);
-    if (!rc) rc = dev_alloc(&c->clist, Q);
-    if (!rc) rc = dev_alloc(&c->pdirty, (size_t)(P + 31) / 32);
-    if (!rc) rc = dev_alloc(&c->pflag, (size_t)P);
-    if (!rc) rc = dev_alloc(&c->dlist, (size_t)P);
-    if (!rc) rc = dev_alloc(&c->psum, (size_t)P);
-    if (rc) {
+    const size_t nxyz = (size_t)P * pg.T * 3, nat = (size_t)P * pg.T;
+    int rc = MF4D_OK;
+    if (P != c->kept_P || pg.T != c->kept_T) {  // other sizes (Tpad and W follow from T)
         free_particles(c);
-        return rc;
+        if (P == 0) return MF4D_OK;
+        rc = dev_alloc(&c->bins, Q);
+        if (!rc) rc = dev_alloc(&c->attr_t, Q);
+        if (!rc) rc = dev_alloc(&c->Ap, (size_t)P * pg.W);
+        if (!rc) rc = dev_alloc(&c->Lp, (size_t)P * pg.W);
+        if (!rc) rc = dev_alloc(&c->clist, Q);
+        if (!rc) rc = dev_alloc(&c->pdirty, (size_t)(P + 31) / 32);
+        if (!rc) rc = dev_alloc(&c->pflag, (size_t)P);
+        if (!rc) rc = dev_alloc(&c->dlist, (size_t)P);
+        if (!rc) rc = dev_alloc(&c->psum, (size_t)P);
+        // positions and values as loaded, for the clustering
+        if (!rc) rc = dev_alloc(&c->praw, nxyz + nat);
     }
+    if (!rc && P == 0) return MF4D_OK;
     const float* dx = xyz;
     const float* da = attr;
-    float* tmp = nullptr;
-    const size_t nxyz = (size_t)P * pg.T * 3, nat = (size_t)P * pg.T;
-    if (where == MF4D_HOST) {
-        rc = dev_alloc(&tmp, nxyz + nat);
-        if (rc) {
-            free_particles(c);
-            return rc;
-        }
-        hipError_t e = hipMemcpyAsync(tmp, xyz, nxyz * sizeof(float), hipMemcpyHostToDevice, c->stream);
+    float* copy = c->praw;  // device inputs are copied by the binning pass
+    if (!rc && where == MF4D_HOST) {
+        hipError_t e = hipMemcpyAsync(c->praw, xyz, nxyz * sizeof(float), hipMemcpyHostToDevice, c->stream);
         if (e == hipSuccess)
-            e = hipMemcpyAsync(tmp + nxyz, attr, nat * sizeof(float), hipMemcpyHostToDevice, c->stream);
-        if (e != hipSuccess) {
-            dev_free(tmp);
-            free_particles(c);
-            return fail(MF4D_ERR_HIP, "particle upload failed: %s", hipGetErrorString(e));
-        }
-        dx = tmp;
-        da = tmp + nxyz;
+            e = hipMemcpyAsync(c->praw + nxyz, attr, nat * sizeof(float), hipMemcpyHostToDevice, c->stream);
+        if (e != hipSuccess) rc = fail(MF4D_ERR_HIP, "particle upload failed: %s", hipGetErrorString(e));
+        dx = c->praw;
+        da = c->praw + nxyz;
+        copy = nullptr;
     }
-    launch_bin_particles(c->g, pg, dx, da, c->bins, c->attr_t, c->stream);
-    launch_particle_summaries(pg, c->attr_t, c->psum, c->stream);
-    c->bstats_valid = false;
-    launch_fill_u32(c->pdirty, 0, (P + 31) / 32, c->stream);
-    // the clustering reads positions and values as loaded: keep the upload
-    // buffer, or copy device inputs into one laid out the same way
-    if (tmp) {
-        c->praw = tmp;
-        tmp = nullptr;
-    } else {
-        rc = dev_alloc(&c->praw, nxyz + nat);
-        if (!rc) {
-            hipError_t e = hipMemcpyAsync(c->praw, xyz, nxyz * sizeof(float), hipMemcpyDeviceToDevice, c->stream);
-            if (e == hipSuccess)
-                e = hipMemcpyAsync(c->praw + nxyz, attr, nat * sizeof(float), hipMemcpyDeviceToDevice,
-                                   c->stream);
-            if (e != hipSuccess) rc = fail(MF4D_ERR_HIP, "particle copy failed: %s", hipGetErrorString(e));
-        }
+    if (!rc) {
+        launch_bin_particles(c->g, pg, dx, da, c->bins, c->attr_t, copy, c->psum, c->stream);
+        launch_fill_u32(c->pdirty, 0, (P + 31) / 32, c->stream);
+        c->bstats_valid = false;
+        rc = sync(c);
     }
-    if (!rc) rc = sync(c);
-    dev_free(tmp);
     if (rc) {
         free_particles(c);
         return rc;
     }
+    c->kept_P = 0;
+    c->kept_T = 0;
     c->pg = pg;
     c->has_particles = true;
     return MF4D_OK;
@@ -1127,6 +1154,7 @@ int mf4d_set_seeds(mf4d_ctx* c, const int32_t* xyzt, int64_t S, int where) {
         }
     }
     if (S > c->seeds_cap) {
+        release_kept(c);
         int32_t* ns = nullptr;
         int rc = dev_alloc(&ns, (size_t)S * 4);
         if (rc) {
@@ -1261,6 +1289,7 @@ static int grow_begin(mf4d_ctx* c, GrowRun* gr) {
     if (!c->has_field) return fail(MF4D_ERR_STATE, "no field loaded");
     if (!c->has_crit) return fail(MF4D_ERR_STATE, "no criteria set");
     HIP_TRY(hipSetDevice(c->device));
+    release_kept(c);
     if (c->async_grow) {
         // the read-outs of the grow before are deferred (or still run) on
         // the current set: grow on the other one (allocated on first use),
@@ -1739,6 +1768,7 @@ int mf4d_grow_seed_ids(mf4d_ctx* c, int32_t* field_ids, size_t nf, int32_t* part
     if (S > 0) HIP_TRY(hipMemcpy(hs.data(), c->seeds, hs.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
     int32_t* fo = field_ids;
     int32_t* po = want_p ? particle_ids : nullptr;
+    release_kept(c);
     if (where == MF4D_HOST) {
         void* st = nullptr;
         int rc = staging_for(c, (V + (want_p ? Qp : 0)) * sizeof(int32_t), &st);
@@ -1856,6 +1886,7 @@ int mf4d_set_queries(mf4d_ctx* c, int Q, const float* crit, const int32_t* qxyzt
             }
         }
     }
+    if (!c->btab || S > c->qseeds_cap) release_kept(c);
     if (!c->btab) {
         int rc = dev_alloc(&c->btab, (size_t)kTabWords);
         if (rc) return rc;
@@ -1921,6 +1952,7 @@ int mf4d_grow_batched(mf4d_ctx* c, uint32_t* fplanes, size_t fwords, uint32_t* p
             return fail(MF4D_ERR_ARG, "plane buffers must be 16-byte aligned");
     }
     HIP_TRY(hipSetDevice(c->device));
+    release_kept(c);
     c->b_grown = false;
     if (owned) {
         if (c->b_fown_n < 8 * V) {
@@ -2210,6 +2242,7 @@ int mf4d_slic_set_params(mf4d_ctx* c, const int* k4, float w_d, float w_f, float
     if (max_iter < 0 || max_iter > 100000) return fail(MF4D_ERR_ARG, "max_iter %d not in [0, 100000]", max_iter);
     HIP_TRY(hipSetDevice(c->device));
     if ((int)K != c->sK) {
+        release_kept(c);
         dev_free(c->sacc);
         dev_free(c->scen);
         dev_free(c->scen32);
@@ -2258,6 +2291,7 @@ int mf4d_slic_run(mf4d_ctx* c, int* iterations) {
     const size_t V = (size_t)g.X * g.Y * g.Z * g.T, Qp = P > 0 ? (size_t)c->pg.T * P : 0;
     if (V + Qp >= (size_t)1 << 31) return fail(MF4D_ERR_UNSUPPORTED, "more than 2^31 samples");
     HIP_TRY(hipSetDevice(c->device));
+    release_kept(c);
     c->slic_done = false;
     if (c->slabels_n != V + Qp) {
         dev_free(c->slabels);

@@ -1016,6 +1016,13 @@ __global__ void k_reset(Dev d) {
     for (uint64_t i = tid; i < 2ull * kWorkSubs; i += stride) d.wcnt[i * kWcntStride] = 0u;
 }
 
+__device__ __forceinline__ void minmax_skip_nan(float v, float& mn, float& mx) {
+    if (v == v) {
+        mn = fminf(mn, v);
+        mx = fmaxf(mx, v);
+    }
+}
+
 // Load: bin every particle-step into the voxel covering it (at the field step
 // holding the step's time, t / tr) and transpose the values to particle-major
 // rows.  Block = 64 particles; LDS tile [64][65].
@@ -1023,11 +1030,14 @@ __global__ __launch_bounds__(256) void k_bin_particles(Geom g, PGeom pg,
                                                        const float* __restrict__ xyz,
                                                        const float* __restrict__ attr,
                                                        uint32_t* __restrict__ bins,
-                                                       float* __restrict__ attr_t) {
+                                                       float* __restrict__ attr_t,
+                                                       float* __restrict__ copy,
+                                                       float2* __restrict__ psum) {
     __shared__ uint32_t sb[64][65];
     __shared__ float sa[64][65];
     const int64_t p0 = (int64_t)blockIdx.x * 64;
     const int TC = pg.Tpad < 64 ? pg.Tpad : 64;
+    float mn = __builtin_inff(), mx = -__builtin_inff();  // of particle threadIdx.x / 4, a quarter of its steps
     for (int t0 = 0; t0 < pg.Tpad; t0 += TC) {
         for (int i = threadIdx.x; i < 64 * TC; i += blockDim.x) {
             const int pl = i & 63, tl = i >> 6;
@@ -1036,12 +1046,19 @@ __global__ __launch_bounds__(256) void k_bin_particles(Geom g, PGeom pg,
             uint32_t b = kNoVoxel;
             float a = __builtin_nanf("");
             if (p < pg.P && t < pg.T) {
-                const float* q = xyz + ((int64_t)t * pg.P + p) * 3;
-                const float cx = floorf(q[0]), cy = floorf(q[1]), cz = floorf(q[2]);
+                const int64_t e = (int64_t)t * pg.P + p;
+                const float x = xyz[3 * e], y = xyz[3 * e + 1], z = xyz[3 * e + 2];
+                const float cx = floorf(x), cy = floorf(y), cz = floorf(z);
                 if (cx >= 0.0f && cx < (float)g.X && cy >= 0.0f && cy < (float)g.Y &&
                     cz >= 0.0f && cz < (float)g.Z)
                     b = bit_index(g, (int)cx, (int)cy, (int)cz, t / pg.tr);
-                a = attr[(int64_t)t * pg.P + p];
+                a = attr[e];
+                if (copy) {
+                    copy[3 * e] = x;
+                    copy[3 * e + 1] = y;
+                    copy[3 * e + 2] = z;
+                    copy[3 * (int64_t)pg.T * pg.P + e] = a;
+                }
             }
             sb[pl][tl] = b;
             sa[pl][tl] = a;
@@ -1056,8 +1073,15 @@ __global__ __launch_bounds__(256) void k_bin_particles(Geom g, PGeom pg,
                 attr_t[e] = sa[pl][tl];
             }
         }
+        for (int tl = threadIdx.x & 3; tl < TC; tl += 4) minmax_skip_nan(sa[threadIdx.x >> 2][tl], mn, mx);
         __syncthreads();
     }
+    for (int o = 1; o < 4; o <<= 1) {
+        mn = fminf(mn, __shfl_xor(mn, o));
+        mx = fmaxf(mx, __shfl_xor(mx, o));
+    }
+    const int64_t p = p0 + (threadIdx.x >> 2);
+    if ((threadIdx.x & 3) == 0 && p < pg.P) psum[p] = make_float2(mn, mx);
 }
 
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -1124,28 +1148,21 @@ __global__ __launch_bounds__(256) void k_admit_field(Dev d) {
     }
 }
 
-__device__ __forceinline__ void minmax_skip_nan(float v, float& mn, float& mx) {
-    if (v == v) {
-        mn = fminf(mn, v);
-        mx = fmaxf(mx, v);
-    }
-}
-
 // Load time: (min, max) of each tile's non-NaN field values ((+inf, -inf)
 // when it has none).  A tile can hold a voxel with lo <= f <= hi only if
 // max >= lo and min <= hi, so these decide, exactly, which tiles a grow must
 // test at all.  Block = one tile, wave = t-slices; when X is a multiple of 4
 // eight lanes read one 128-byte tile row with 16-byte loads, so a wave
 // instruction covers 8 whole rows.
-__global__ __launch_bounds__(256) void k_tile_summaries(Geom g, const float* __restrict__ f,
-                                                        float2* __restrict__ tsum) {
+__global__ __launch_bounds__(256) void k_tile_summaries(Geom g, const float* __restrict__ f, int vec,
+                                                        float* __restrict__ copy, float2* __restrict__ tsum) {
     __shared__ float s_mn[4], s_mx[4];
     const uint32_t tile = blockIdx.x;
     int tx, ty, tz, tt;
     tile_coords(g, tile, tx, ty, tz, tt);
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     float mn = __builtin_inff(), mx = -__builtin_inff();
-    if ((g.X & 3) == 0) {
+    if (vec) {
         const int quad = lane & 7;
         const int x = tx * 32 + quad * 4;
         for (int tl = wave; tl < g.BT; tl += 4) {
@@ -1163,6 +1180,10 @@ __global__ __launch_bounds__(256) void k_tile_summaries(Geom g, const float* __r
             }
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
+                const int row = i * 8 + (lane >> 3);
+                const int y = ty * 8 + (row & 7), z = tz * 8 + (row >> 3);
+                if (copy && x < g.X && y < g.Y && z < g.Z)
+                    *reinterpret_cast<v4f*>(copy + ((size_t)(t * g.Z + z) * g.Y + y) * g.X + x) = v[i];
                 minmax_skip_nan(v[i].x, mn, mx);
                 minmax_skip_nan(v[i].y, mn, mx);
                 minmax_skip_nan(v[i].z, mn, mx);
@@ -1177,8 +1198,12 @@ __global__ __launch_bounds__(256) void k_tile_summaries(Geom g, const float* __r
             if (t >= g.T) break;
             for (int row = lane >> 5; row < 64; row += 2) {
                 const int y = ty * 8 + (row & 7), z = tz * 8 + (row >> 3);
-                if (x < g.X && y < g.Y && z < g.Z)
-                    minmax_skip_nan(f[((size_t)(t * g.Z + z) * g.Y + y) * g.X + x], mn, mx);
+                if (x < g.X && y < g.Y && z < g.Z) {
+                    const size_t i = ((size_t)(t * g.Z + z) * g.Y + y) * g.X + x;
+                    const float v = f[i];
+                    if (copy) copy[i] = v;
+                    minmax_skip_nan(v, mn, mx);
+                }
             }
         }
     }
@@ -1194,48 +1219,6 @@ __global__ __launch_bounds__(256) void k_tile_summaries(Geom g, const float* __r
     if (threadIdx.x == 0)
         tsum[tile] = make_float2(fminf(fminf(s_mn[0], s_mn[1]), fminf(s_mn[2], s_mn[3])),
                                  fmaxf(fmaxf(s_mx[0], s_mx[1]), fmaxf(s_mx[2], s_mx[3])));
-}
-
-// Load time: (min, max) of each particle's non-NaN values over its steps
-// (padding steps hold NaN).  A group of G lanes reads one particle's row with
-// 16-byte loads (G = 16, or Tpad / 4 for short rows), so a wave instruction
-// covers whole rows.
-__global__ __launch_bounds__(256) void k_particle_summaries(PGeom pg, const float* __restrict__ at,
-                                                            float2* __restrict__ psum) {
-    if (pg.Tpad < 4) {
-        for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < pg.P;
-             p += (int64_t)gridDim.x * blockDim.x) {
-            float mn = __builtin_inff(), mx = -__builtin_inff();
-            for (int t = 0; t < pg.Tpad; ++t) minmax_skip_nan(at[p * pg.Tpad + t], mn, mx);
-            psum[p] = make_float2(mn, mx);
-        }
-        return;
-    }
-    const int G = pg.Tpad >= 64 ? 16 : (pg.Tpad >> 2);
-    const int per_wave = 64 / G;
-    const int lane = lane_id(), sub = lane & (G - 1);
-    const int64_t wave_id = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    const int nq = pg.Tpad >> 2;
-    for (int64_t p0 = wave_id * per_wave; p0 < pg.P; p0 += nwaves * per_wave) {
-        const int64_t p = p0 + lane / G;
-        float mn = __builtin_inff(), mx = -__builtin_inff();
-        if (p < pg.P) {
-            const v4f* row = reinterpret_cast<const v4f*>(at + p * pg.Tpad);
-            for (int c = sub; c < nq; c += G) {
-                const v4f v = __builtin_nontemporal_load(row + c);
-                minmax_skip_nan(v.x, mn, mx);
-                minmax_skip_nan(v.y, mn, mx);
-                minmax_skip_nan(v.z, mn, mx);
-                minmax_skip_nan(v.w, mn, mx);
-            }
-        }
-        for (int o = 1; o < G; o <<= 1) {
-            mn = fminf(mn, __shfl_xor(mn, o));
-            mx = fmaxf(mx, __shfl_xor(mx, o));
-        }
-        if (p < pg.P && sub == 0) psum[p] = make_float2(mn, mx);
-    }
 }
 
 // Tiles whose value range meets the field band, as a list.
@@ -2155,20 +2138,16 @@ void launch_reset(const Dev& d, hipStream_t s) {
 }
 
 void launch_bin_particles(const Geom& g, const PGeom& pg, const float* xyz, const float* attr,
-                          uint32_t* bins, float* attr_t, hipStream_t s) {
+                          uint32_t* bins, float* attr_t, float* copy, float2* psum, hipStream_t s) {
     if (pg.P == 0) return;
     const unsigned nb = (unsigned)((pg.P + 63) / 64);
-    hipLaunchKernelGGL(k_bin_particles, dim3(nb), dim3(256), 0, s, g, pg, xyz, attr, bins, attr_t);
+    hipLaunchKernelGGL(k_bin_particles, dim3(nb), dim3(256), 0, s, g, pg, xyz, attr, bins, attr_t, copy, psum);
 }
 
-void launch_summaries(const Geom& g, const float* field, float2* tsum, hipStream_t s) {
-    hipLaunchKernelGGL(k_tile_summaries, dim3(g.NT), dim3(256), 0, s, g, field, tsum);
-}
-
-void launch_particle_summaries(const PGeom& pg, const float* attr_t, float2* psum, hipStream_t s) {
-    if (pg.P == 0) return;
-    hipLaunchKernelGGL(k_particle_summaries, dim3(grid_for(pg.P, 256, 8192)), dim3(256), 0, s, pg,
-                       attr_t, psum);
+void launch_summaries(const Geom& g, const float* field, float* copy, float2* tsum, hipStream_t s) {
+    // 16-byte loads for whole vectors per row; a caller's pointer may be unaligned
+    const int vec = (g.X & 3) == 0 && ((reinterpret_cast<uintptr_t>(field) | reinterpret_cast<uintptr_t>(copy)) & 15) == 0;
+    hipLaunchKernelGGL(k_tile_summaries, dim3(g.NT), dim3(256), 0, s, g, field, vec, copy, tsum);
 }
 
 void launch_admit_field(const Dev& d, hipStream_t s) {

@@ -134,10 +134,11 @@ struct Dev {
 // ---- launchers (kernels.hip) ----
 void launch_fill_u32(uint32_t* p, uint32_t v, uint64_t n, hipStream_t s);
 void launch_reset(const Dev& d, hipStream_t s);
+// copy (or null): xyz [T][P][3] then attr [T][P], as loaded.
 void launch_bin_particles(const Geom& g, const PGeom& pg, const float* xyz, const float* attr,
-                          uint32_t* bins, float* attr_t, hipStream_t s);
-void launch_summaries(const Geom& g, const float* field, float2* tsum, hipStream_t s);
-void launch_particle_summaries(const PGeom& pg, const float* attr_t, float2* psum, hipStream_t s);
+                          uint32_t* bins, float* attr_t, float* copy, float2* psum, hipStream_t s);
+// copy (or null): the field as loaded.
+void launch_summaries(const Geom& g, const float* field, float* copy, float2* tsum, hipStream_t s);
 void launch_admit_field(const Dev& d, hipStream_t s);
 void launch_admit_particles(const Dev& d, hipStream_t s);
 void launch_seeds(const Dev& d, const int32_t* seeds, int64_t S, hipStream_t s);
