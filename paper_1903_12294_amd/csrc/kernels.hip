@@ -1796,12 +1796,15 @@ __global__ __launch_bounds__(256) void k_rounds(Dev d, uint32_t round0, uint32_t
         if (nwork == 0 || (max_rounds && r - round0 >= max_rounds)) break;
         // sweep (and clear the flags the previous round's pull consumed)
         for (uint32_t i = tid; i < d.g.NT; i += nthreads) d.chg[(par ^ 1) * d.g.NT + i] = 0;
+        if (tid == 0) store_relaxed(&d.counters[C_CHG0 + (par ^ 1)], 0u);
         sweep_phase<BT>(d, par, wave0, nwaves);
         visits += nwork;  // only thread 0 records it
         if (!grid_sync(d, epoch)) break;
         // pull (fused with close and push for one label word per particle)
         if (tid < (unsigned)kWorkSubs) store_relaxed(&d.wcnt[(par * kWorkSubs + tid) * kWcntStride], 0u);
-        if (parts) {
+        // (no tile's members changed since the last pull: nothing can join)
+        const bool pull = parts && load_relaxed(&d.counters[C_CHG0 + par]) != 0u;  // the same in every thread
+        if (pull) {
             const uint32_t n = load_relaxed(&d.counters[C_NLIST]);
             if (d.pg.W == 1) closed += pull_close_wave<kCoopNE, kCoopNE>(d, par, wave0, nwaves, n, my_list);
             else pull_entries(d, tid, nthreads, n, par);
@@ -2097,9 +2100,14 @@ bool coop_rounds(const Dev& d, uint32_t round0, uint32_t max_rounds, int device,
     Dev dd = d;
     uint32_t r0 = round0, mr = max_rounds;
     void* args[] = {&dd, &r0, &mr};
-    // Two blocks (8 waves) per CU: measured faster than four at 256^3 x 64,
-    // where more blocks only add barrier arrivals.
-    const dim3 grid((unsigned)(std::min(per_cu, 2) * ncu));
+    // At most two blocks (8 waves) per CU: measured faster than four at 256^3 x
+    // 64, where more blocks only add barrier arrivals; and no more than a round
+    // can use, since every block of the grid takes part in every barrier (and
+    // invalidates its L2): a round's list holds a small part of the tiles, and
+    // the coupled list a small part of the steps.  GRIDNOTE
+    const uint64_t steps = (uint64_t)d.pg.P * d.pg.Tpad;
+    const uint64_t use = std::max<uint64_t>(std::max<uint64_t>(d.g.NT / 64, steps >> 17), 8);
+    const dim3 grid((unsigned)std::min<uint64_t>(use, (uint64_t)std::min(per_cu, 2) * ncu));
     return hipLaunchCooperativeKernel((const void*)k_rounds<BT>, grid, dim3(256), args, 0, s) ==
            hipSuccess;
 }
