@@ -163,11 +163,17 @@ struct mf4d_ctx {
 
     bool has_crit = false;
     float crit[4] = {0, 0, 0, 0};
-    int32_t* seeds = nullptr;
+    int32_t* seeds = nullptr;  // on the device: more than kFewSeeds of them
+    FewSeeds few{};            // up to kFewSeeds: passed with the launch that sets them
     int64_t S = 0;
     int64_t seeds_cap = 0;
     int64_t max_rounds = 0;
     int64_t last_rounds = 0;  // rounds of the last grow that converged (launch mode)
+    int ncand = C_NCAND0;     // counter of this grow's candidate tiles (the two take turns)
+    bool one_try = false;       // this grow's rounds start in the one-block kernel
+    bool few_left = false;      // its few seeds are left to that kernel
+    bool one_declined = false;  // the one-block rounds met more work than they take (until data or criteria change)
+    int coop_blocks = 0;      // blocks of the cooperative rounds kernel that fit the device (0: not asked yet)
 
     // grow state: 0 nothing grown, 1 converged, 2 stopped by the round cap
     int state = 0;
@@ -177,6 +183,7 @@ struct mf4d_ctx {
     hipEvent_t rev[4 * 4] = {};  // per launched round of a chunk: before sweep, pull, close, after
     double ms_phase[3] = {0, 0, 0};  // sweep, pull, close of the current grow
     bool members_pending[2] = {false, false};  // member counts in flight (field, particles)
+    bool members_slots[2] = {false, false};    // they are still in the per-block slots (not folded)
     bool phase_timing = false;  // events around launched round kernels
     bool timed = false;         // the current grow records its events
 
@@ -189,15 +196,14 @@ struct mf4d_ctx {
     hipStream_t side = nullptr;
     hipEvent_t ev_labels = nullptr;   // recorded after the last work that changed the labels
     bool labels_marked = false;
-    hipEvent_t ev_pread = nullptr;    // the particle read-out on the side stream is done
+    hipEvent_t ev_pread = nullptr;    // a particle read-out on the side stream is done
     bool stats_ready = false;         // h_stat / h_counters already hold this grow's statistics
     // read-outs of mf4d_grow_read, queued behind the rounds (device buffers)
     uint32_t* rd_f = nullptr;
     uint8_t* rd_p = nullptr;
     bool reads_done = false;          // the queued read-outs ran on the final labels
-    hipEvent_t ev_chunk = nullptr;    // end of the last queued chunk of rounds
-    hipEvent_t ev_stat = nullptr;     // its statistics copied to the host
-    uint32_t* gsnap = nullptr;        // [2][C_NCOUNTERS]: chunk-end counters per label set (read gate)
+    uint32_t seq = 0;                 // number of the last finish queued (it writes it to h_seq)
+    uint32_t* h_seq = nullptr;        // pinned, behind the counters
     // Asynchronous read-outs (mf4d_set_read_async): a grow_read leaves its
     // read-outs deferred; the next asynchronous grow_read grows on the other
     // of two label sets and issues them on the side stream once its own
@@ -230,7 +236,7 @@ struct mf4d_ctx {
     int submitted = 0;
     Dev sub_d{};                      // its buffers and criteria
     int64_t sub_chunk = 0;            // rounds in its queued chunk
-    int sub_npar = 0;
+    bool sub_one = false;             // it is the one-block kernel's
     uint32_t* sub_f = nullptr;
     size_t sub_nwords = 0;
     uint8_t* sub_p = nullptr;
@@ -486,6 +492,8 @@ Dev make_dev(mf4d_ctx* c) {
     d.psum = c->psum;
     d.cand = c->cand;
     d.tpred = nullptr;
+    d.ncand = c->ncand;
+    d.keep_members = 0;
     d.admit_all = c->admit_all || c->schedule == MF4D_SCHED_JACOBI;  // Jacobi sweeps read every word
     d.forward_only = c->forward_only;
     for (int i = 0; i < 4; ++i) d.crit[i] = c->crit[i];
@@ -549,66 +557,41 @@ int settle_async(mf4d_ctx* c) {
     return MF4D_OK;
 }
 
-// Queue the read-outs of mf4d_grow_read behind the rounds queued so far: the
-// particle labels on the side stream after ev_chunk, the field labels on the
-// context stream.  Gated on the chunk's counter copy: with a closed gate they
-// do nothing.  The context stream's wait for the side stream is queued by the
-// caller (join_reads).
-int queue_reads(mf4d_ctx* c, const ReadGate& gate) {
+// Member counts that a finish left in the slots are folded into the
+// statistics (clearing the slots): before anything else counts there, or when
+// they are asked for.
+void fold_members(mf4d_ctx* c) {
     const Dev d = make_dev(c);
-    hipStream_t s = c->stream;
-    HIP_TRY(hipStreamWaitEvent(c->side, c->ev_chunk, 0));
-    if (c->rd_p) {
-        launch_read_particles(d, c->rd_p, c->side, gate);
-        launch_fold_slots(d, SL_MEMBERS_P, S_MEMBERS_P, c->side, true);
-    }
-    if (c->rd_f) {
-        launch_read_field(d, c->rd_f, s, gate);
-        launch_fold_slots(d, SL_MEMBERS_F, S_MEMBERS_F, s, true);
-    }
-    HIP_TRY(hipEventRecord(c->ev_pread, c->side));
-    return MF4D_OK;
+    if (c->members_slots[0]) launch_fold_slots(d, SL_MEMBERS_F, S_MEMBERS_F, c->stream, true);
+    if (c->members_slots[1]) launch_fold_slots(d, SL_MEMBERS_P, S_MEMBERS_P, c->stream, true);
+    c->members_slots[0] = c->members_slots[1] = false;
 }
 
-// After a chunk's read-outs were queued: the context stream waits for the
-// side stream's part.
-int join_reads(mf4d_ctx* c) {
-    if (!c->rd_p) return MF4D_OK;
-    HIP_TRY(hipStreamWaitEvent(c->stream, c->ev_pread, 0));
-    return MF4D_OK;
-}
-
-// Statistics and counters to the host in one copy; read-outs pending are
-// queued behind it (they run while the host waits for the copy only).
-// queue_stat_copy queues; read_chunk also waits for the copy.
-int queue_stat_copy(mf4d_ctx* c, const ReadGate& gate) {
-    hipStream_t s = c->stream;
-    HIP_TRY(hipEventRecord(c->ev_chunk, s));
-    HIP_TRY(hipMemcpyAsync(c->h_stat, c->stat64, kStatBytes, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipEventRecord(c->ev_stat, s));
-    if (c->rd_f || c->rd_p) {
-        int rc = queue_reads(c, gate);
-        if (rc) return rc;
-    }
+// Queue the end of a grow or of a chunk of `rounds` rounds (0: unknown): its
+// statistics to the host and, if the rounds reached the fixed point (or
+// always), the read-outs pending.
+int queue_finish(mf4d_ctx* c, const Dev& d, uint32_t rounds, bool always) {
+    fold_members(c);
+    launch_finish(d, c->rd_f, c->rd_p, rounds, always, c->h_stat, ++c->seq, c->stream);
     HIP_TRY(hipGetLastError());
     return MF4D_OK;
 }
 
-// The host waits for a chunk's statistics by polling the event: a grow's
-// rounds take well under a millisecond, and a blocking wait adds a wake-up to
-// every grow while the device idles until the next grow is queued.
+// The host waits for the statistics by polling the sequence number that the
+// finish writes behind them: a grow's rounds take well under a millisecond, and a
+// blocking wait adds a wake-up to every grow while the device idles until the
+// next one is queued.  Every 2^14 polls it asks whether the stream has ended
+// without writing it (a failed launch).
 int wait_stat(mf4d_ctx* c) {
-    hipError_t q;
-    while ((q = hipEventQuery(c->ev_stat)) == hipErrorNotReady) {
+    for (uint32_t polls = 1; __atomic_load_n(c->h_seq, __ATOMIC_ACQUIRE) != c->seq; ++polls) {
+        if (polls % (1u << 14)) continue;
+        const hipError_t q = hipStreamQuery(c->stream);
+        if (q == hipErrorNotReady) continue;
+        HIP_TRY(q);
+        if (__atomic_load_n(c->h_seq, __ATOMIC_ACQUIRE) != c->seq)
+            return fail(MF4D_ERR_HIP, "internal error: the grow's end was not reported");
     }
-    HIP_TRY(q);
     return MF4D_OK;
-}
-
-int read_chunk(mf4d_ctx* c, const ReadGate& gate) {
-    int rc = queue_stat_copy(c, gate);
-    if (rc) return rc;
-    return wait_stat(c);
 }
 
 // Jacobi sweeps until one adds nothing (converged) or the cap is hit; each
@@ -657,12 +640,19 @@ int run_jacobi(mf4d_ctx* c, const Dev& d, int64_t* rounds_done) {
 // events per round).
 struct RoundChunk {
     int64_t n;  // rounds queued (0: the round cap was reached)
-    int npar;   // parity of the round after the chunk
+    bool one;   // the one-block kernel, which runs every round it can (n: no bound)
 };
 
+// The seeds left to the one-block kernel (none the second time).
+FewSeeds take_few(mf4d_ctx* c) {
+    const FewSeeds f = c->few_left ? c->few : FewSeeds{};
+    c->few_left = false;
+    return f;
+}
+
 // Queue the chunk of rounds that starts r rounds into the grow, its
-// chunk-end kernel, the statistics copy and the read-outs pending (gated on
-// this chunk reaching the fixed point).  The host does not wait.
+// statistics and the read-outs pending (gated on this chunk reaching the fixed
+// point).  The host does not wait.
 int queue_chunk(mf4d_ctx* c, const Dev& d, int64_t r, RoundChunk* ch) {
     constexpr int64_t kRoundChunk = 4, kMaxChunk = 16;
     const uint32_t cap = (uint32_t)(c->max_rounds > 0 ? c->max_rounds : 0);
@@ -670,8 +660,14 @@ int queue_chunk(mf4d_ctx* c, const Dev& d, int64_t r, RoundChunk* ch) {
     if (r == 0 && !c->timed) chunk = std::min(std::max(c->last_rounds, kRoundChunk), kMaxChunk);
     if (cap && cap - r < chunk) chunk = cap - r;
     ch->n = chunk > 0 ? chunk : 0;
-    ch->npar = 0;
+    ch->one = false;
     if (chunk <= 0) return MF4D_OK;
+    // a small volume: every round in one block (it may decline)
+    if (r == 0 && c->one_try) {
+        launch_rounds_one(d, c->round, cap, take_few(c), c->stream);
+        ch->one = true;
+        return queue_finish(c, d, 0, false);
+    }
     for (int64_t k = 0; k < chunk; ++k) {
         launch_round(d, (uint32_t)(c->round + k), c->stream, c->timed ? c->rev + 4 * k : nullptr);
         if (c->async_grow && c->dread.valid && r == 0 && k + 1 == c->issue_round) {
@@ -680,13 +676,7 @@ int queue_chunk(mf4d_ctx* c, const Dev& d, int64_t r, RoundChunk* ch) {
             if (rc) return rc;
         }
     }
-    // work total and the grow's statistics, read back together, so that
-    // finish_stats needs no wait of its own after the last chunk
-    const int npar = (int)((c->round + chunk) & 1);
-    uint32_t* snap = (c->rd_f || c->rd_p) ? c->gsnap + c->lset * C_NCOUNTERS : nullptr;
-    launch_chunk_end(d, npar, snap, c->stream);
-    ch->npar = npar;
-    return queue_stat_copy(c, ReadGate{snap, (uint32_t)(r + chunk), npar});
+    return queue_finish(c, d, (uint32_t)(r + chunk), false);
 }
 
 // Wait for a queued chunk's counters: the rounds it did (r advances by
@@ -696,6 +686,7 @@ int settle_chunk(mf4d_ctx* c, int64_t* r, const RoundChunk& ch, bool* converged)
     if (rc) return rc;
     c->stats_ready = true;
     const int64_t done = (int64_t)c->h_counters[C_ROUNDS] - *r;
+    if (c->timed && ch.n > 0) HIP_TRY(hipEventSynchronize(c->rev[4 * (ch.n - 1) + 3]));
     for (int64_t k = 0; c->timed && k < done && k < ch.n; ++k)
         for (int ph = 0; ph < 3; ++ph) {
             float ms = 0;
@@ -704,8 +695,11 @@ int settle_chunk(mf4d_ctx* c, int64_t* r, const RoundChunk& ch, bool* converged)
         }
     c->round += (uint32_t)done;
     *r += done;
-    *converged = done < ch.n || c->h_counters[C_NWORK0 + (c->round & 1)] == 0;
-    return join_reads(c);
+    const bool idle = c->h_counters[C_NWORK0] + c->h_counters[C_NWORK1] == 0;
+    *converged = idle || (!ch.one && done < ch.n);
+    if (ch.one) c->one_try = false;
+    if (ch.one && !idle && done == 0) c->one_declined = true;
+    return MF4D_OK;
 }
 
 // Rounds until a round's work list is empty (converged) or the cap is hit.
@@ -717,17 +711,35 @@ int run_rounds(mf4d_ctx* c, const Dev& d, int64_t* rounds_done, const RoundChunk
     const uint32_t cap = (uint32_t)(c->max_rounds > 0 ? c->max_rounds : 0);
     const uint32_t r0 = c->round;
     if (c->schedule == MF4D_SCHED_PERSISTENT && !queued) {
-        if (c->round != 0) {  // a fresh grow's reset cleared them
+        if (c->round != 0) {  // a fresh grow's start cleared them
             launch_fill_u32(c->counters + C_ERR, 0, 2, c->stream);  // C_ERR, C_ROUNDS
             launch_fill_u32(c->bar, 0, kBarWords, c->stream);
         }
-        if (launch_rounds_persistent(d, r0, cap, c->device, c->stream)) {
-            launch_fold_grow_slots(d, c->stream);
+        if (c->one_try) {
+            launch_rounds_one(d, r0, cap, take_few(c), c->stream);
+            int rc = queue_finish(c, d, 0, false);
+            if (rc) return rc;
+            rc = wait_stat(c);
+            if (rc) return rc;
+            const uint32_t done = c->h_counters[C_ROUNDS];
+            const bool idle = c->h_counters[C_NWORK0] + c->h_counters[C_NWORK1] == 0;
+            if (idle || done) {
+                c->stats_ready = true;
+                c->reads_done = idle && (c->rd_f || c->rd_p);
+                c->round = r0 + done;
+                *rounds_done = done;
+                c->state = idle ? 1 : 2;
+                return MF4D_OK;
+            }
+            c->one_declined = true;
+            c->one_try = false;
+        }
+        if (launch_rounds_persistent(d, r0, cap, c->device, &c->coop_blocks, c->stream)) {
             // read-outs pending run unconditionally: the launch ran every
             // round it was going to
-            int rc = read_chunk(c, ReadGate{});
+            int rc = queue_finish(c, d, 0, true);
             if (rc) return rc;
-            rc = join_reads(c);
+            rc = wait_stat(c);
             if (rc) return rc;
             c->reads_done = c->rd_f || c->rd_p;
             c->stats_ready = true;
@@ -746,7 +758,7 @@ int run_rounds(mf4d_ctx* c, const Dev& d, int64_t* rounds_done, const RoundChunk
     // waiting for each chunk's counters (settle_chunk).
     if (!queued && c->round != 0) launch_fill_u32(c->counters + C_ROUNDS, 0, 1, c->stream);  // fresh: reset cleared it
     int64_t r = 0;
-    RoundChunk ch{0, 0};
+    RoundChunk ch{0, false};
     if (queued) ch = *queued;
     while (true) {
         if (!queued) {
@@ -848,25 +860,29 @@ int mf4d_create(mf4d_ctx** out, int device, void* hip_stream) {
     int rc = dev_alloc(&c->stat64, S_NSTAT + C_NCOUNTERS / 2);
     if (!rc) c->counters = reinterpret_cast<uint32_t*>(c->stat64 + S_NSTAT);
     if (!rc) rc = dev_alloc(&c->bar, kBarWords);
-    if (!rc) rc = dev_alloc(&c->gsnap, 2 * (size_t)C_NCOUNTERS);
     if (!rc) rc = dev_alloc(&c->slots, (size_t)kSlotStats * kSlots);
     if (!rc) launch_fill_u32((uint32_t*)c->slots, 0, 2ull * kSlotStats * kSlots, c->stream);
+    if (!rc) launch_fill_u32((uint32_t*)c->stat64, 0, 2ull * S_NSTAT + C_NCOUNTERS, c->stream);
     if (!rc) {
         const char* env = getenv("MF4D_SCHED");
         if (env && strcmp(env, "launch") == 0) c->schedule = MF4D_SCHED_LAUNCH;
         const char* adm = getenv("MF4D_ADMIT");
         if (adm && strcmp(adm, "all") == 0) c->admit_all = 1;
     }
-    if (!rc && hipHostMalloc((void**)&c->h_stat, kStatBytes) != hipSuccess)
+    if (!rc && hipHostMalloc((void**)&c->h_stat, kStatBytes + sizeof(uint32_t)) != hipSuccess)
         rc = fail(MF4D_ERR_OOM, "pinned host allocation failed");
-    if (!rc) c->h_counters = reinterpret_cast<uint32_t*>(c->h_stat + S_NSTAT);
+    if (!rc) {
+        c->h_counters = reinterpret_cast<uint32_t*>(c->h_stat + S_NSTAT);
+        c->h_seq = c->h_counters + C_NCOUNTERS;
+        *c->h_seq = 0;
+    }
     for (int i = 0; !rc && i < 4; ++i)
         if (hipEventCreate(&c->ev[i]) != hipSuccess) rc = fail(MF4D_ERR_HIP, "hipEventCreate failed");
     for (int i = 0; !rc && i < 16; ++i)
         if (hipEventCreate(&c->rev[i]) != hipSuccess) rc = fail(MF4D_ERR_HIP, "hipEventCreate failed");
     if (!rc && hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess)
         rc = fail(MF4D_ERR_HIP, "hipStreamCreateWithFlags failed");
-    for (hipEvent_t* e : {&c->ev_labels, &c->ev_pread, &c->ev_chunk, &c->ev_stat, &c->ev_read[0], &c->ev_read[1], &c->ev_issue})
+    for (hipEvent_t* e : {&c->ev_labels, &c->ev_pread, &c->ev_read[0], &c->ev_read[1], &c->ev_issue})
         if (!rc && hipEventCreateWithFlags(e, hipEventDisableTiming) != hipSuccess)
             rc = fail(MF4D_ERR_HIP, "hipEventCreate failed");
     if (rc) {
@@ -890,7 +906,6 @@ void mf4d_destroy(mf4d_ctx* c) {
     dev_free(c->stat64);
     dev_free(c->slots);
     dev_free(c->bar);
-    dev_free(c->gsnap);
     dev_free(c->seeds);
     dev_free(c->btab);
     dev_free(c->qseeds);
@@ -912,7 +927,7 @@ void mf4d_destroy(mf4d_ctx* c) {
         c->staging = nullptr;
     }
     if (c->side) (void)hipStreamDestroy(c->side);
-    for (hipEvent_t e : {c->ev_labels, c->ev_pread, c->ev_chunk, c->ev_stat, c->ev_read[0], c->ev_read[1], c->ev_issue})
+    for (hipEvent_t e : {c->ev_labels, c->ev_pread, c->ev_read[0], c->ev_read[1], c->ev_issue})
         if (e) (void)hipEventDestroy(e);
     c->h_counters = nullptr;  // inside h_stat
     if (c->h_stat) (void)hipHostFree(c->h_stat);
@@ -962,6 +977,7 @@ int mf4d_load_field(mf4d_ctx* c, const float* field, int X, int Y, int Z, int T,
     HIP_TRY(hipSetDevice(c->device));
     const size_t V = (size_t)X * Y * Z * T;
     const BrickDims bd{T, (Z + 7) / 8, (Y + 7) / 8, (X + 7) / 8};
+    c->one_declined = false;
     const bool same = c->has_field && c->g.X == X && c->g.Y == Y && c->g.Z == Z && c->g.T == T && c->g.BT == g.BT;
     c->state = 0;
     int rc = MF4D_OK;
@@ -1060,6 +1076,7 @@ int mf4d_load_particles_rate(mf4d_ctx* c, const float* xyz, const float* attr, i
                     (long long)P, pg.Tpad);
     HIP_TRY(hipSetDevice(c->device));
     c->state = 0;
+    c->one_declined = false;
     drop_particles(c);
     const size_t Q = (size_t)P * pg.Tpad;
     const size_t nxyz = (size_t)P * pg.T * 3, nat = (size_t)P * pg.T;
@@ -1119,6 +1136,7 @@ int mf4d_set_criteria(mf4d_ctx* c, float f_lo, float f_hi, float a_lo, float a_h
     c->crit[2] = a_lo;
     c->crit[3] = a_hi;
     c->has_crit = true;
+    c->one_declined = false;
     c->state = 0;
     return MF4D_OK;
 }
@@ -1153,6 +1171,14 @@ int mf4d_set_seeds(mf4d_ctx* c, const int32_t* xyzt, int64_t S, int where) {
                         (long long)i, s[0], s[1], s[2], s[3], c->g.X, c->g.Y, c->g.Z, c->g.T);
         }
     }
+    if (S <= kFewSeeds) {
+        for (int64_t i = 0; i < 4 * S; ++i) c->few.v[i] = hv[i];
+        c->few.n = (int)S;
+        delete[] h;
+        c->S = S;
+        c->state = 0;
+        return MF4D_OK;
+    }
     if (S > c->seeds_cap) {
         release_kept(c);
         int32_t* ns = nullptr;
@@ -1165,14 +1191,10 @@ int mf4d_set_seeds(mf4d_ctx* c, const int32_t* xyzt, int64_t S, int where) {
         c->seeds = ns;
         c->seeds_cap = S;
     }
-    if (S > 0) {
-        hipError_t e = hipMemcpyAsync(c->seeds, hv, S * 4 * sizeof(int32_t),
-                                      where == MF4D_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice,
-                                      c->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-        delete[] h;
-        if (e != hipSuccess) return fail(MF4D_ERR_HIP, "seed upload failed: %s", hipGetErrorString(e));
-    }
+    hipError_t e = hipMemcpyAsync(c->seeds, hv, S * 4 * sizeof(int32_t), hipMemcpyHostToDevice, c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    delete[] h;
+    if (e != hipSuccess) return fail(MF4D_ERR_HIP, "seed upload failed: %s", hipGetErrorString(e));
     c->S = S;
     c->state = 0;
     return MF4D_OK;
@@ -1325,12 +1347,16 @@ static int grow_begin(mf4d_ctx* c, GrowRun* gr) {
         if (rc) return rc;
     }
     hipStream_t s = c->stream;
-    const Dev d = make_dev(c);
+    c->ncand = c->ncand == C_NCAND0 ? C_NCAND1 : C_NCAND0;
+    if (c->async_grow) fold_members(c);  // asynchronous read-outs count in clean slots
+    Dev d = make_dev(c);
+    d.keep_members = c->async_grow;
     c->state = 0;
     c->round = 0;
     c->ms_phase[0] = c->ms_phase[1] = c->ms_phase[2] = 0;
     c->members_pending[0] = c->members_pending[1] = false;
-    launch_reset(d, s);
+    c->members_slots[0] = c->members_slots[1] = false;  // cleared by the start
+    launch_begin(d, s);
     c->timed = c->phase_timing;
     if (c->timed) HIP_TRY(hipEventRecord(c->ev[0], s));
     Dev dp = d;
@@ -1366,11 +1392,17 @@ static int grow_begin(mf4d_ctx* c, GrowRun* gr) {
         HIP_TRY(hipcub::DeviceRadixSort::SortPairsDescending(c->pr_tmp, bytes, keys, skeys, vals, plist, (int)NT,
                                                              0, 32, s));
     }
-    launch_admit_field(dp, s);
-    if (c->timed) HIP_TRY(hipEventRecord(c->ev[1], s));
-    launch_admit_particles(d, s);
-    if (c->timed) HIP_TRY(hipEventRecord(c->ev[2], s));
-    launch_seeds(d, c->seeds, c->S, s);
+    if (c->timed || !launch_admit_both(dp, s)) {
+        launch_admit_field(dp, s);
+        if (c->timed) HIP_TRY(hipEventRecord(c->ev[1], s));
+        launch_admit_particles(d, s);
+        if (c->timed) HIP_TRY(hipEventRecord(c->ev[2], s));
+    }
+    c->one_try = !c->timed && !c->async_grow && !ordered && c->schedule != MF4D_SCHED_JACOBI && !c->one_declined &&
+                 rounds_one_fits(d);
+    c->few_left = c->one_try && c->S <= kFewSeeds;
+    if (c->S > kFewSeeds) launch_seeds(d, c->seeds, c->S, s);
+    else if (!c->few_left) launch_seeds_few(d, c->few, s);
     if (c->async_grow && c->dread.valid && (c->schedule != MF4D_SCHED_LAUNCH || c->issue_round == 0)) {
         // the grow before's read-outs, beside this grow's rounds (after its
         // admissibility passes, the bandwidth-heavy part; with launched
@@ -1474,8 +1506,8 @@ int finish_grow_read(mf4d_ctx* c, int rc, uint32_t* field_dst, size_t nwords, ui
     if (rc != MF4D_OK && rc != MF4D_ERR_NOT_CONVERGED) return rc;
     // the masks are those of the labels as they stand, converged or not
     if (done) {
-        c->members_pending[0] = field_dst != nullptr;
-        c->members_pending[1] = particle_dst != nullptr;
+        c->members_pending[0] = c->members_slots[0] = field_dst != nullptr;
+        c->members_pending[1] = c->members_slots[1] = particle_dst != nullptr;
     } else {
         if (field_dst) {
             int r2 = mf4d_read_field_mask(c, field_dst, nwords, MF4D_DEVICE);
@@ -1496,7 +1528,7 @@ int complete_submitted(mf4d_ctx* c, mf4d_stats* out) {
     c->submitted = 0;
     HIP_TRY(hipSetDevice(c->device));
     const GrowRun gr{c->sub_d, false};
-    const RoundChunk ch{c->sub_chunk, c->sub_npar};
+    const RoundChunk ch{c->sub_chunk, c->sub_one};
     int64_t rounds = 0;
     int rc = run_rounds(c, gr.d, &rounds, &ch);
     if (!rc) rc = grow_end(c, gr, rounds, out);
@@ -1566,7 +1598,7 @@ int mf4d_grow_submit(mf4d_ctx* c, uint32_t* field_dst, size_t nwords, uint8_t* p
     c->reads_done = false;
     GrowRun gr;
     rc = grow_begin(c, &gr);
-    RoundChunk ch{0, 0};
+    RoundChunk ch{0, false};
     if (!rc) rc = queue_chunk(c, gr.d, 0, &ch);
     if (rc) {
         c->rd_f = nullptr;
@@ -1575,7 +1607,7 @@ int mf4d_grow_submit(mf4d_ctx* c, uint32_t* field_dst, size_t nwords, uint8_t* p
     }
     c->sub_d = gr.d;
     c->sub_chunk = ch.n;
-    c->sub_npar = ch.npar;
+    c->sub_one = ch.one;
     c->sub_f = field_dst;
     c->sub_nwords = nwords;
     c->sub_p = particle_dst;
@@ -1638,6 +1670,7 @@ int mf4d_reset_labels(mf4d_ctx* c) {
 // the host (once, when asked for) and record them.
 static int settle_members(mf4d_ctx* c) {
     if (!c->members_pending[0] && !c->members_pending[1]) return MF4D_OK;
+    fold_members(c);
     HIP_TRY(hipMemcpyAsync(c->h_stat + S_MEMBERS_F, c->stat64 + S_MEMBERS_F, 2 * sizeof(unsigned long long),
                            hipMemcpyDeviceToHost, c->stream));
     int rc = sync(c);
@@ -1668,6 +1701,7 @@ int mf4d_read_field_mask(mf4d_ctx* c, uint32_t* dst, size_t nwords, int where) {
         if (rc) return rc;
         out = (uint32_t*)st;
     }
+    fold_members(c);
     launch_read_field(make_dev(c), out, c->stream);
     launch_fold_slots(make_dev(c), SL_MEMBERS_F, S_MEMBERS_F, c->stream, true);
     if (where == MF4D_HOST)
@@ -1701,7 +1735,8 @@ int mf4d_read_particle_mask(mf4d_ctx* c, uint8_t* dst, size_t n, int where) {
     // last work that changed the labels and beside whatever the context
     // stream does meanwhile (the field read-out); the context stream then
     // waits for it, so the call stays ordered on that stream.
-    const bool side = where == MF4D_DEVICE && c->labels_marked;
+    const bool side = where == MF4D_DEVICE && c->labels_marked && !c->members_slots[0] && !c->members_slots[1];
+    fold_members(c);
     hipStream_t rs = side ? c->side : c->stream;
     if (side) HIP_TRY(hipStreamWaitEvent(c->side, c->ev_labels, 0));
     launch_read_particles(make_dev(c), out, rs);
@@ -1765,7 +1800,8 @@ int mf4d_grow_seed_ids(mf4d_ctx* c, int32_t* field_ids, size_t nf, int32_t* part
     hipStream_t s = c->stream;
     const int64_t S = c->S;
     std::vector<int32_t> hs((size_t)S * 4);
-    if (S > 0) HIP_TRY(hipMemcpy(hs.data(), c->seeds, hs.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+    if (S > kFewSeeds) HIP_TRY(hipMemcpy(hs.data(), c->seeds, hs.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+    else std::copy(c->few.v, c->few.v + 4 * S, hs.begin());
     int32_t* fo = field_ids;
     int32_t* po = want_p ? particle_ids : nullptr;
     release_kept(c);
@@ -1794,7 +1830,7 @@ int mf4d_grow_seed_ids(mf4d_ctx* c, int32_t* field_ids, size_t nf, int32_t* part
         launch_fill_u32((uint32_t*)po, 0xFFFFFFFFu, Qp, s);
         launch_fill_u32((uint32_t*)sc.seen_p, 0u, 2 * (size_t)P * pw, s);
     }
-    int32_t* const all_seeds = c->seeds;
+    const FewSeeds few = c->few;  // each grow below has one seed of its own
     int64_t ngrow = 0;
     for (int64_t i = 0; i < S; ++i) {
         const int32_t* sd = &hs[(size_t)i * 4];
@@ -1808,10 +1844,11 @@ int mf4d_grow_seed_ids(mf4d_ctx* c, int32_t* field_ids, size_t nf, int32_t* part
         rc = sync(c);
         if (rc) return rc;
         if (cur != -1 || !(c->crit[0] <= fv && fv <= c->crit[1])) continue;
-        c->seeds = all_seeds + 4 * i;
+        std::copy(sd, sd + 4, c->few.v);
+        c->few.n = 1;
         c->S = 1;
         rc = mf4d_grow(c, nullptr);
-        c->seeds = all_seeds;
+        c->few = few;
         c->S = S;
         if (rc) {
             c->state = 0;

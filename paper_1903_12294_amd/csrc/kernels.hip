@@ -104,43 +104,40 @@ __device__ __forceinline__ bool admissible_bit(const Dev& d, uint32_t b) {
     return false;
 }
 
-// Admissibility words of one (z_l, y_l) row of a tile at timestep t: one
-// lane's 32 x-bits (eight 16-byte non-temporal loads when whole and aligned).
-__device__ __forceinline__ uint32_t row_admissibility(const Dev& d, int tx, int y, int z, int t) {
-    const Geom& g = d.g;
-    if (t >= g.T || y >= g.Y || z >= g.Z) return 0u;
-    const float lo = d.crit[0], hi = d.crit[1];
-    const float* rp = d.field + ((size_t)(t * g.Z + z) * g.Y + y) * g.X + tx * 32;
-    const int nx = min(32, g.X - tx * 32);
-    uint32_t w = 0;
-    if ((g.X & 3) == 0 && nx == 32) {
-        typedef float v4f_ __attribute__((ext_vector_type(4)));
-        v4f_ v[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = __builtin_nontemporal_load(reinterpret_cast<const v4f_*>(rp) + k);
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-            w |= ((uint32_t)in_band(v[k].x, lo, hi) | ((uint32_t)in_band(v[k].y, lo, hi) << 1) |
-                  ((uint32_t)in_band(v[k].z, lo, hi) << 2) | ((uint32_t)in_band(v[k].w, lo, hi) << 3))
-                 << (4 * k);
-    } else {
-        for (int k = 0; k < nx; ++k) w |= (uint32_t)in_band(rp[k], lo, hi) << k;
-    }
-    return w;
-}
-
 // Admissibility words of one t-slice of a tile (64 rows of 32 x), computed by
 // the whole wave: eight lanes read one 128-byte row with 16-byte loads, so an
 // instruction covers 8 whole rows; the eight nibble-words of a row are ORed
 // and handed to the lane that owns the row.  Returns the word of row `lane`
-// ((z_l, y_l) = (lane >> 3, lane & 7)).  Call with the whole wave.
+// ((z_l, y_l) = (lane >> 3, lane & 7)).  Rows that are not whole 16-byte vectors
+// are read two per instruction, one lane per voxel, and a ballot is their two
+// words (157 x 101 x 75 x 21: the pass over 255 tiles took 25 us with a lane walking
+// its own row; now tiles and particles together take 11.7).  Call with the whole wave.
 __device__ __forceinline__ uint32_t slice_admissibility(const Dev& d, int tx, int ty, int tz, int t) {
     const Geom& g = d.g;
     const int lane = lane_id();
-    if ((g.X & 3) != 0) return row_admissibility(d, tx, ty * 8 + (lane & 7), tz * 8 + (lane >> 3), t);
     if (t >= g.T) return 0u;
     typedef float v4f_ __attribute__((ext_vector_type(4)));
     const float lo = d.crit[0], hi = d.crit[1];
+    if ((g.X & 3) != 0) {
+        const int x = tx * 32 + (lane & 31);
+        uint32_t mine = 0;
+        for (int i0 = 0; i0 < 32; i0 += 16) {
+            float v[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int row = 2 * (i0 + i) + (lane >> 5);  // (z_l, y_l) = (row >> 3, row & 7)
+                const int y = ty * 8 + (row & 7), z = tz * 8 + (row >> 3);
+                v[i] = __builtin_nanf("");
+                if (x < g.X && y < g.Y && z < g.Z) v[i] = d.field[((size_t)(t * g.Z + z) * g.Y + y) * g.X + x];
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const unsigned long long w = __ballot(in_band(v[i], lo, hi));
+                if ((lane >> 1) == i0 + i) mine = (uint32_t)(w >> (32 * (lane & 1)));
+            }
+        }
+        return mine;
+    }
     const int quad = lane & 7, grp = lane >> 3;
     const int x = tx * 32 + quad * 4;
     v4f_ v[8];
@@ -232,66 +229,29 @@ __device__ __forceinline__ uint32_t block_append256(uint32_t n, uint32_t* counte
 // ---------------------------------------------------------------------------
 // scheduling
 
-// Put up to 8 tiles on the work list of round parity `par` (each once per
-// round), skipping tiles with no admissible voxel-step.  Each step is issued
-// for all tiles before the next (flag loads, then exchanges, then appends), so
-// the round trips of the tiles overlap instead of queueing.  A flag already
-// seen set needs no exchange: no one clears it during this phase.
-__device__ __forceinline__ void schedule_batch(const Dev& d, const uint32_t* nb, int k, int par) {
-    uint32_t* dirty = d.dirty + (size_t)par * d.g.NT;
-    uint32_t cur[8];
-    uint8_t act[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        act[i] = 0;
-        cur[i] = 1u;
-        if (i < k) {
-            act[i] = d.active[nb[i]];
-            cur[i] = dirty[nb[i]];
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) cur[i] = (i < k && act[i] && cur[i] == 0u) ? atomicExch(&dirty[nb[i]], 1u) : 1u;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        if (cur[i] == 0u) {
-            const uint32_t j = (uint32_t)(par * kWorkSubs) + (nb[i] & (kWorkSubs - 1));
-            const uint32_t slot = atomicAdd(&d.wcnt[j * kWcntStride], 1u);
-            d.work[(size_t)j * d.g.WCAP + slot] = nb[i];
-        }
-    }
+// Append a tile to its work sub-list of round parity `par`.
+__device__ __forceinline__ void append_work(const Dev& d, uint32_t tile, int par) {
+    const uint32_t j = (uint32_t)(par * kWorkSubs) + (tile & (kWorkSubs - 1));
+    const uint32_t slot = atomicAdd(&d.wcnt[j * kWcntStride], 1u);
+    d.work[(size_t)j * d.g.WCAP + slot] = tile;
 }
 
-// As schedule_batch, for a sweep's few neighbours: the flag exchange is
-// issued with the activity loads (two round trips instead of three).  A flag
-// set on a tile with no admissible voxel-step is never read: such a tile is
-// never listed.
-__device__ __forceinline__ void schedule_batch_direct(const Dev& d, const uint32_t* nb, int k, int par) {
-    uint32_t* dirty = d.dirty + (size_t)par * d.g.NT;
-    uint32_t cur[8];
-    uint8_t act[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        act[i] = 0;
-        cur[i] = 1u;
-        if (i < k) {
-            act[i] = d.active[nb[i]];
-            cur[i] = atomicExch(&dirty[nb[i]], 1u);
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        if (i < k && act[i] && cur[i] == 0u) {
-            const uint32_t j = (uint32_t)(par * kWorkSubs) + (nb[i] & (kWorkSubs - 1));
-            const uint32_t slot = atomicAdd(&d.wcnt[j * kWcntStride], 1u);
-            d.work[(size_t)j * d.g.WCAP + slot] = nb[i];
-        }
-    }
+// Put this lane's tile on the work list of round parity `par` (once per round)
+// unless it holds no admissible voxel-step.  The flag exchange is issued with
+// the activity load (two round trips in all); a flag set on a tile with no
+// admissible voxel-step is never read: such a tile is never listed.
+__device__ __forceinline__ void schedule_lane(const Dev& d, uint32_t tile, int par) {
+    const uint8_t act = d.active[tile];
+    const uint32_t cur = atomicExch(&d.dirty[(size_t)par * d.g.NT + tile], 1u);
+    if (act && cur == 0u) append_work(d, tile, par);
 }
 
-// As schedule_batch for up to N tiles (nb[i] = ~0u: none; all their flag
-// loads, then exchanges, then appends issued together; fixed indices only, so
-// that the arrays stay in registers).
+// Put up to N tiles on the work list of round parity `par` (each once per
+// round; nb[i] = ~0u: none), skipping tiles with no admissible voxel-step.  Each
+// step is issued for all tiles before the next (flag loads, then exchanges, then
+// appends), so the round trips of the tiles overlap instead of queueing; fixed
+// indices only, so that the arrays stay in registers.  A flag already seen set
+// needs no exchange: no one clears it during this phase.
 template <int N>
 __device__ __forceinline__ void schedule_batch_n(const Dev& d, const uint32_t* nb, int par) {
     uint32_t* dirty = d.dirty + (size_t)par * d.g.NT;
@@ -310,11 +270,7 @@ __device__ __forceinline__ void schedule_batch_n(const Dev& d, const uint32_t* n
     for (int i = 0; i < N; ++i) cur[i] = (nb[i] != ~0u && act[i] && cur[i] == 0u) ? atomicExch(&dirty[nb[i]], 1u) : 1u;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        if (cur[i] == 0u) {
-            const uint32_t j = (uint32_t)(par * kWorkSubs) + (nb[i] & (kWorkSubs - 1));
-            const uint32_t slot = atomicAdd(&d.wcnt[j * kWcntStride], 1u);
-            d.work[(size_t)j * d.g.WCAP + slot] = nb[i];
-        }
+        if (cur[i] == 0u) append_work(d, nb[i], par);
     }
 }
 
@@ -322,33 +278,9 @@ __device__ __forceinline__ void schedule_batch_n(const Dev& d, const uint32_t* n
 // round parity `par`: each owning tile is flagged changed (its coupled steps
 // must be pulled) and scheduled.  Its sweep sees the flag and schedules every
 // tile across a face that holds members, since it cannot tell the bits set
-// here from older ones.  Up to 4 voxels (b = kNoVoxel: none), one round trip
-// per step for all of them.
-__device__ void mark_voxels(const Dev& d, const uint32_t* b, int par) {
-    const Geom& g = d.g;
-    uint32_t nb[8];
-    int k = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (b[i] == kNoVoxel) continue;
-        const uint32_t tile = b[i] >> (5 + 6 + g.logBT);
-        bool dup = false;
-        for (int j = 0; j < k; ++j) dup |= nb[j] == tile;
-        if (dup) continue;
-        d.chg[par * g.NT + tile] = 1;
-        d.counters[C_CHG0 + par] = 1u;
-        nb[k++] = tile;
-    }
-    schedule_batch(d, nb, k, par);
-}
-
-__device__ __forceinline__ void mark_voxel(const Dev& d, uint32_t b, int par) {
-    const uint32_t v[4] = {b, kNoVoxel, kNoVoxel, kNoVoxel};
-    mark_voxels(d, v, par);
-}
-
-// mark_voxels for up to N voxels (kNoVoxel: none); a tile already named by an
-// earlier voxel of the lane is marked once.
+// here from older ones.  Up to N voxels (b = kNoVoxel: none), one round trip
+// per step for all of them; a tile already named by an earlier voxel of the lane
+// is marked once.
 template <int N>
 __device__ void mark_voxels_n(const Dev& d, const uint32_t* b, int par) {
     const Geom& g = d.g;
@@ -367,6 +299,11 @@ __device__ void mark_voxels_n(const Dev& d, const uint32_t* b, int par) {
     schedule_batch_n<N>(d, tl, par);
 }
 
+__device__ __forceinline__ void mark_voxel(const Dev& d, uint32_t b, int par) {
+    const uint32_t v[1] = {b};
+    mark_voxels_n<1>(d, v, par);
+}
+
 // ---------------------------------------------------------------------------
 // the three phases of a round
 
@@ -378,7 +315,7 @@ __device__ void mark_voxels_n(const Dev& d, const uint32_t* b, int par) {
 // this tile gains bits, the tile across that face is scheduled for the next
 // round.  Every lane of the wave must call it.
 template <int BT>
-__device__ void sweep_tile(const Dev& d, uint32_t tile, int par) {
+__device__ __forceinline__ void sweep_tile(const Dev& d, uint32_t tile, int par) {
     const Geom& g = d.g;
     const int lane = lane_id();
     const int yl = lane & 7, zl = lane >> 3;
@@ -439,12 +376,14 @@ __device__ void sweep_tile(const Dev& d, uint32_t tile, int par) {
     if (act == 2) {
         // deferred tile: test its admissibility now
         uint32_t any = 0;
-#pragma unroll
+#pragma unroll 1
         for (int t = 0; t < BT; ++t) {
-            a[t] = slice_admissibility(d, tx, ty, tz, (tt << g.logBT) + t);
-            Ab[t * 64 + lane] = a[t];
-            any |= a[t];
+            const uint32_t w = slice_admissibility(d, tx, ty, tz, (tt << g.logBT) + t);
+            Ab[t * 64 + lane] = w;
+            any |= w;
         }
+#pragma unroll
+        for (int t = 0; t < BT; ++t) a[t] = Ab[t * 64 + lane];  // this lane's own stores
         const bool has = __ballot(any != 0) != 0;
         if (lane == 0) {
             d.active[tile] = has ? 1 : 0;
@@ -509,23 +448,18 @@ __device__ void sweep_tile(const Dev& d, uint32_t tile, int par) {
         const bool fym = __ballot(yl == 0 && fany) != 0, fyp = __ballot(yl == 7 && fany) != 0;
         const bool fzm = __ballot(zl == 0 && fany) != 0, fzp = __ballot(zl == 7 && fany) != 0;
         const bool ftm = __ballot(nt0 != 0) != 0, ftp = __ballot(nt1 != 0) != 0;
-        if (lane == 0) {
-            if (changed) {
-                d.chg[par * g.NT + tile] = 1;
-                d.counters[C_CHG0 + par] = 1u;
-            }
-            const int nx = par ^ 1;
-            uint32_t nb[8];
-            int k = 0;
-            if (fxm && tx > 0) nb[k++] = tile - 1;
-            if (fxp && tx + 1 < g.NXt) nb[k++] = tile + 1;
-            if (fym && ty > 0) nb[k++] = tile - sy;
-            if (fyp && ty + 1 < g.NYt) nb[k++] = tile + sy;
-            if (fzm && tz > 0) nb[k++] = tile - sz;
-            if (fzp && tz + 1 < g.NZt) nb[k++] = tile + sz;
-            if (ftm && tt > 0) nb[k++] = tile - st;
-            if (ftp && tt + 1 < g.NTt) nb[k++] = tile + st;
-            schedule_batch_direct(d, nb, k, nx);
+        if (changed && lane == 0) {
+            d.chg[par * g.NT + tile] = 1;
+            d.counters[C_CHG0 + par] = 1u;
+        }
+        // one neighbour per lane: x-, x+, y-, y+, z-, z+, t-, t+
+        const uint32_t go = (fxm && tx > 0 ? 1u : 0u) | (fxp && tx + 1 < g.NXt ? 2u : 0u) |
+                            (fym && ty > 0 ? 4u : 0u) | (fyp && ty + 1 < g.NYt ? 8u : 0u) |
+                            (fzm && tz > 0 ? 16u : 0u) | (fzp && tz + 1 < g.NZt ? 32u : 0u) |
+                            (ftm && tt > 0 ? 64u : 0u) | (ftp && tt + 1 < g.NTt ? 128u : 0u);
+        if (lane < 8 && ((go >> lane) & 1u)) {
+            const uint32_t step = lane < 2 ? 1u : (lane < 4 ? sy : (lane < 6 ? sz : st));
+            schedule_lane(d, lane & 1 ? tile + step : tile - step, par ^ 1);
         }
     }
 }
@@ -909,10 +843,41 @@ __device__ __forceinline__ void block_slot_sum(const Dev& d, int which, uint32_t
 constexpr int kBarSubs = 8;
 constexpr int kBarTop = 0, kBarGen = 32, kBarSub0 = 64;  // word offsets in d.bar (kBarWords)
 
+constexpr uint32_t kBarFlat = 32;  // up to this many blocks arrive at the top counter directly
+
+// Thread 0 of a block waits for epoch e; 0 when a barrier timed out.
+__device__ uint32_t wait_epoch(const Dev& d, uint32_t e) {
+    uint32_t ok = 1;
+    uint32_t polls = 0;
+    // Poll with relaxed loads: an acquire per poll would invalidate this
+    // XCD's L2 on every iteration and starve the waves still working.  One
+    // acquire fence after the wait makes the other blocks' writes visible.
+    while (__hip_atomic_load(d.bar + kBarGen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < e) {
+        __builtin_amdgcn_s_sleep(2);
+        if (++polls > (1u << 22)) {
+            atomicExch(&d.counters[C_ERR], 1u);
+            ok = 0;
+            break;
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (load_relaxed(&d.counters[C_ERR])) ok = 0;
+    return ok;
+}
+
 __device__ bool grid_sync(const Dev& d, uint32_t& epoch) {
     __shared__ uint32_t s_ok;
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 0 && gridDim.x <= kBarFlat) {
+        // few arrivals (at most 0.4 us of them serialised): one level
+        const uint32_t e = ++epoch;
+        if (__hip_atomic_fetch_add(d.bar + kBarTop, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT) + 1 ==
+            e * gridDim.x) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            __hip_atomic_store(d.bar + kBarGen, e, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        s_ok = wait_epoch(d, e);
+    } else if (threadIdx.x == 0) {
         const uint32_t e = ++epoch;
         const uint32_t j = blockIdx.x % kBarSubs;
         const uint32_t nsub = gridDim.x / kBarSubs + (j < gridDim.x % kBarSubs ? 1u : 0u);
@@ -930,22 +895,7 @@ __device__ bool grid_sync(const Dev& d, uint32_t& epoch) {
                 __hip_atomic_store(d.bar + kBarGen, e, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
-        uint32_t ok = 1;
-        uint32_t polls = 0;
-        // Poll with relaxed loads: an acquire per poll would invalidate this
-        // XCD's L2 on every iteration and starve the waves still working.  One
-        // acquire fence after the wait makes the other blocks' writes visible.
-        while (__hip_atomic_load(d.bar + kBarGen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < e) {
-            __builtin_amdgcn_s_sleep(2);
-            if (++polls > (1u << 22)) {
-                atomicExch(&d.counters[C_ERR], 1u);
-                ok = 0;
-                break;
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        if (load_relaxed(&d.counters[C_ERR])) ok = 0;
-        s_ok = ok;
+        s_ok = wait_epoch(d, e);
     }
     __syncthreads();
     return s_ok != 0;
@@ -991,8 +941,11 @@ __global__ void k_fill_u32(uint32_t* p, uint32_t v, uint64_t n) {
         p[i] = v;
 }
 
-// Zero the per-grow scheduling state in one launch.
-__global__ void k_reset(Dev d) {
+// Start of a grow: the per-grow scheduling state zeroed and the candidate
+// tiles (whose value range meets the field band) listed, in one launch.  The
+// list's counter is one of two, used in turn: each grow clears the other.
+__global__ __launch_bounds__(256) void k_begin(Dev d) {
+    __shared__ uint32_t s_tmp[8];
     const uint64_t tid = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     const uint64_t n_dirty = 2ull * d.g.NT;
@@ -1003,17 +956,29 @@ __global__ void k_reset(Dev d) {
     for (uint64_t i = tid; i < n_chg; i += stride) reinterpret_cast<uint32_t*>(d.chg)[i] = 0;
     for (uint64_t i = tid; i < n_act; i += stride) reinterpret_cast<uint32_t*>(d.active)[i] = 0;
     for (uint64_t i = tid; i < n_pd; i += stride) d.pdirty[i] = 0;
-    if (tid < C_NCOUNTERS) d.counters[tid] = 0;
-    // the member counts (slots and statistics) belong to the read-outs, which
-    // may still run for the grow before (they assign them; their folds clear
-    // the slots)
+    if (tid < C_NCOUNTERS && tid != (uint64_t)d.ncand) d.counters[tid] = 0;
+    // with asynchronous read-outs the member counts (slots and statistics)
+    // belong to those, which may still run for the grow before (they assign
+    // them; their folds clear the slots)
     if (tid < S_NSTAT && tid != S_MEMBERS_F && tid != S_MEMBERS_P) d.stat64[tid] = 0;
     for (uint64_t i = tid; i < (uint64_t)kBarWords; i += stride) d.bar[i] = 0;
     for (uint64_t i = tid; i < (uint64_t)kSlotStats * kSlots; i += stride) {
         const uint64_t row = i / kSlots;
-        if (row != SL_MEMBERS_F && row != SL_MEMBERS_P) d.slots[i] = 0ull;
+        if (!d.keep_members || (row != SL_MEMBERS_F && row != SL_MEMBERS_P)) d.slots[i] = 0ull;
     }
     for (uint64_t i = tid; i < 2ull * kWorkSubs; i += stride) d.wcnt[i * kWcntStride] = 0u;
+    if (d.admit_all) return;
+    const float lo = d.crit[0], hi = d.crit[1];
+    for (uint32_t b0 = blockIdx.x * blockDim.x; b0 < d.g.NT; b0 += gridDim.x * blockDim.x) {  // block-uniform
+        const uint32_t i = b0 + threadIdx.x;
+        bool c = false;
+        if (i < d.g.NT) {
+            const float2 r = d.tsum[i];
+            c = r.y >= lo && r.x <= hi;
+        }
+        const uint32_t k = block_append256(c ? 1u : 0u, &d.counters[d.ncand], s_tmp);
+        if (c) d.cand[k] = i;
+    }
 }
 
 __device__ __forceinline__ void minmax_skip_nan(float v, float& mn, float& mx) {
@@ -1221,32 +1186,16 @@ __global__ __launch_bounds__(256) void k_tile_summaries(Geom g, const float* __r
                                  fmaxf(fmaxf(s_mx[0], s_mx[1]), fmaxf(s_mx[2], s_mx[3])));
 }
 
-// Tiles whose value range meets the field band, as a list.
-__global__ __launch_bounds__(256) void k_tile_candidates(Dev d) {
-    __shared__ uint32_t s_tmp[8];
-    const float lo = d.crit[0], hi = d.crit[1];
-    for (uint32_t b0 = blockIdx.x * blockDim.x; b0 < d.g.NT; b0 += gridDim.x * blockDim.x) {
-        const uint32_t i = b0 + threadIdx.x;
-        bool c = false;
-        if (i < d.g.NT) {
-            const float2 r = d.tsum[i];
-            c = r.y >= lo && r.x <= hi;
-        }
-        const uint32_t k = block_append256(c ? 1u : 0u, &d.counters[C_NCAND], s_tmp);
-        if (c) d.cand[k] = i;
-    }
-}
-
 // Admissibility of the voxel-steps of candidate tiles, and their labels
 // cleared.  Block = one tile at a time; each wave handles t-slices, each lane
 // one (z_l, y_l) row of 32 x.  With a predictor, candidates it does not mark
 // are only cleared and deferred to the first sweep that reaches them.
-__global__ __launch_bounds__(256) void k_admit_tiles(Dev d) {
+__device__ __forceinline__ void admit_tiles(const Dev& d, uint32_t blk, uint32_t nblk) {
     const Geom& g = d.g;
     const int lane = lane_id(), wave = threadIdx.x >> 6;
-    const uint32_t n = d.counters[C_NCAND];
+    const uint32_t n = d.counters[d.ncand];
     uint32_t tested = 0, active = 0;  // this block's counts (thread 0)
-    for (uint32_t ci = blockIdx.x; ci < n; ci += gridDim.x) {
+    for (uint32_t ci = blk; ci < n; ci += nblk) {
         const uint32_t tile = d.cand[ci];
         int tx, ty, tz, tt;
         tile_coords(g, tile, tx, ty, tz, tt);
@@ -1329,7 +1278,7 @@ __device__ __forceinline__ void flush_stage(const Dev& d, const uint2* s_buf, ui
 // LDS and then tests their units; the coupled list keeps each particle's
 // entries side by side in step order.
 constexpr int kAdmitChunk = 1024;
-__global__ __launch_bounds__(256) void k_admit_particles(Dev d) {
+__device__ __forceinline__ void admit_particles(const Dev& d, uint32_t blk, uint32_t nblk) {
     __shared__ __align__(8) uint32_t s_tmp[10];
     __shared__ uint2 s_buf[kStage];
     __shared__ uint32_t s_cand[kAdmitChunk];
@@ -1342,8 +1291,7 @@ __global__ __launch_bounds__(256) void k_admit_particles(Dev d) {
     const v4f* src = reinterpret_cast<const v4f*>(d.attr_t);
     const uint4* bsrc = reinterpret_cast<const uint4*>(d.bins);
     uint32_t nbuf = 0;  // entries staged; the same in every thread
-    for (int64_t c0 = (int64_t)blockIdx.x * kAdmitChunk; c0 < pg.P;
-         c0 += (int64_t)gridDim.x * kAdmitChunk) {  // block-uniform
+    for (int64_t c0 = (int64_t)blk * kAdmitChunk; c0 < pg.P; c0 += (int64_t)nblk * kAdmitChunk) {  // block-uniform
         uint32_t flags = 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -1453,6 +1401,16 @@ __global__ __launch_bounds__(256) void k_admit_particles(Dev d) {
     if (nbuf) flush_stage(d, s_buf, nbuf, s_tmp);
 }
 
+__global__ __launch_bounds__(256) void k_admit_tiles(Dev d) { admit_tiles(d, blockIdx.x, gridDim.x); }
+__global__ __launch_bounds__(256) void k_admit_particles(Dev d) { admit_particles(d, blockIdx.x, gridDim.x); }
+
+// Both in one launch, the particles in the first np blocks (they take longest):
+// where neither pass fills the GPU their chains of loads run side by side.
+__global__ __launch_bounds__(256) void k_admit_both(Dev d, uint32_t np) {
+    if (blockIdx.x < np) admit_particles(d, blockIdx.x, np);
+    else admit_tiles(d, blockIdx.x - np, gridDim.x - np);
+}
+
 // Same for Tpad < 4 (T <= 2): one thread per particle.
 __global__ void k_admit_particles_short(Dev d) {
     const PGeom& pg = d.pg;
@@ -1492,10 +1450,7 @@ __global__ __launch_bounds__(256) void k_couple(Dev d) {
     }
 }
 
-__global__ void k_seeds(Dev d, const int32_t* __restrict__ seeds, int64_t S) {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= S) return;
-    const int32_t* s = seeds + 4 * i;
+__device__ __forceinline__ void seed_one(const Dev& d, const int32_t* s) {
     const uint32_t b = bit_index(d.g, s[0], s[1], s[2], s[3]);
     if (admissible_bit(d, b)) {
         const uint32_t bit = 1u << (b & 31);
@@ -1503,6 +1458,16 @@ __global__ void k_seeds(Dev d, const int32_t* __restrict__ seeds, int64_t S) {
     } else {
         atomicAdd(&d.counters[C_DROPPED], 1u);
     }
+}
+
+__global__ void k_seeds(Dev d, const int32_t* __restrict__ seeds, int64_t S) {
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i < S) seed_one(d, seeds + 4 * i);
+}
+
+// A few seeds as launch arguments: no copy to the device, and no wait for it.
+__global__ __launch_bounds__(64) void k_seeds_few(Dev d, FewSeeds f) {
+    if ((int)threadIdx.x < f.n) seed_one(d, f.v + 4 * threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1576,9 +1541,8 @@ __global__ __launch_bounds__(256) void k_priority_sweep(Dev d, const uint32_t* _
 __global__ __launch_bounds__(256) void k_verify_schedule(Dev d, int par) {
     for (uint32_t t0 = blockIdx.x * blockDim.x; t0 < d.g.NT; t0 += gridDim.x * blockDim.x) {
         const uint32_t tile = t0 + threadIdx.x;
-        uint32_t nb[1] = {tile};
-        const int k = tile < d.g.NT && d.active[tile] == 1 ? 1 : 0;
-        schedule_batch(d, nb, k, par);
+        const uint32_t nb[1] = {tile < d.g.NT && d.active[tile] == 1 ? tile : ~0u};
+        schedule_batch_n<1>(d, nb, par);
     }
 }
 
@@ -1688,24 +1652,6 @@ __global__ void k_work_total(Dev d, int par) {
     uint32_t total;
     wave_excl_scan(d.wcnt[(par * kWorkSubs + lane_id()) * kWcntStride], total);
     if (threadIdx.x == 0) d.counters[C_NWORK0 + par] = total;
-}
-
-// End of a chunk of rounds: the work total (first wave), a copy of the round
-// count and that total for the read-outs' gate (snap: C_NCOUNTERS words, not
-// touched by later grows' rounds), and the statistics fold.
-__global__ __launch_bounds__(1024) void k_chunk_end(Dev d, int par, FoldList f, uint32_t* snap) {
-    if (threadIdx.x < 64) {
-        uint32_t total;
-        wave_excl_scan(d.wcnt[(par * kWorkSubs + lane_id()) * kWcntStride], total);
-        if (threadIdx.x == 0) {
-            d.counters[C_NWORK0 + par] = total;
-            if (snap) {
-                snap[C_NWORK0 + par] = total;
-                snap[C_ROUNDS] = d.counters[C_ROUNDS];
-            }
-        }
-    }
-    fold_list(d, f);
 }
 
 // ---- one round as three launches ----
@@ -1829,24 +1775,72 @@ __global__ __launch_bounds__(256) void k_rounds(Dev d, uint32_t round0, uint32_t
     }
 }
 
-// ---- read-out ----
-
-__device__ __forceinline__ bool gate_open(const ReadGate& gate) {
-    return !gate.counters || gate.counters[C_ROUNDS] < gate.rounds || gate.counters[C_NWORK0 + gate.par] == 0u;
+// ---- all rounds in one block ----
+// A volume with few active tiles spends its rounds in launches and grid
+// barriers: here one block of eight waves sets the seeds and runs the rounds with
+// __syncthreads between the phases.  It declines the rounds when more than
+// max_tiles candidate tiles or max_list coupled steps turn up: then they run as
+// usual.  Bound by its chains of dependent loads.  32^3 x 8 (12 tiles, 5 rounds):
+// 114 us with its seeds; 210 us, and a launch more, as a cooperative launch over the whole GPU.
+constexpr int kOneThreads = 512;
+template <int BT>
+__global__ __launch_bounds__(kOneThreads) void k_rounds_one(Dev d, uint32_t round0, uint32_t max_rounds,
+                                                            uint32_t max_tiles, uint32_t max_list, FewSeeds f) {
+    __shared__ uint32_t s_list[kOneThreads / 64 * 64 * kCoopNE];
+    if ((int)threadIdx.x < f.n) seed_one(d, f.v + 4 * threadIdx.x);
+    __syncthreads();
+    const uint32_t n = d.counters[C_NLIST];
+    if (n > max_list || (d.admit_all ? d.g.NT : d.counters[d.ncand]) > max_tiles) return;  // block-uniform
+    const uint32_t wave = threadIdx.x >> 6, nwaves = kOneThreads / 64;
+    const bool parts = d.pg.P > 0;
+    uint32_t* my_list = s_list + 64 * kCoopNE * wave;
+    uint32_t r = round0, visits = 0, closed = 0;
+    while (true) {
+        const int par = r & 1;
+        uint32_t nwork;
+        wave_excl_scan(load_relaxed(&d.wcnt[(par * kWorkSubs + lane_id()) * kWcntStride]), nwork);
+        if (nwork == 0 || (max_rounds && r - round0 >= max_rounds)) break;  // the same in every thread
+        for (uint32_t i = threadIdx.x; i < d.g.NT; i += kOneThreads) d.chg[(par ^ 1) * d.g.NT + i] = 0;
+        if (threadIdx.x == 0) store_relaxed(&d.counters[C_CHG0 + (par ^ 1)], 0u);
+        sweep_phase<BT>(d, par, wave, nwaves);
+        visits += nwork;
+        __syncthreads();
+        if (threadIdx.x < (unsigned)kWorkSubs)
+            store_relaxed(&d.wcnt[(par * kWorkSubs + threadIdx.x) * kWcntStride], 0u);
+        if (parts && load_relaxed(&d.counters[C_CHG0 + par]) != 0u) {
+            if (d.pg.W == 1) {
+                closed += pull_close_wave<kCoopNE, kCoopNE>(d, par, wave, nwaves, n, my_list);
+            } else {
+                pull_entries(d, threadIdx.x, kOneThreads, n, par);
+                __syncthreads();
+                const uint32_t c = close_phase(d, par ^ 1, wave, nwaves, my_list);  // same in every lane
+                if (lane_id() == 0) closed += c;
+            }
+        }
+        __syncthreads();
+        ++r;
+    }
+    block_slot_sum(d, SL_PART_VISITS, closed);
+    if (threadIdx.x == 0) {
+        if (visits) atomicAdd(&d.stat64[S_TILE_VISITS], (unsigned long long)visits);
+        d.counters[C_ROUNDS] = r - round0;
+    }
 }
+
+// ---- read-out ----
 
 // Field labels -> canonical bit words ((t*Z + z)*Y + y)*X + x, with a member
 // count.  When X is a multiple of 32 a canonical word is one tile word: a block
 // stages up to 8 x-consecutive tiles in LDS (rows padded by one word against
 // bank conflicts) and writes whole canonical rows.  Otherwise bit by bit.
 template <int BT>
-__global__ __launch_bounds__(256) void k_read_field_tiles(Dev d, uint32_t* __restrict__ out, int vec, ReadGate gate) {
+__device__ __forceinline__ uint32_t read_field_tiles(const Dev& d, uint32_t* __restrict__ out, int vec, uint32_t blk,
+                                                     uint32_t* sl) {
     typedef unsigned int v4u __attribute__((ext_vector_type(4)));
     constexpr int WPT = 64 * BT;
-    __shared__ uint32_t sl[8 * (WPT + 1)];
-    if (!gate_open(gate)) return;  // the same in every thread
     const Geom& g = d.g;
-    const int ty = blockIdx.x, tz = blockIdx.y, tt = blockIdx.z;
+    const int ty = (int)(blk % (uint32_t)g.NYt), tz = (int)(blk / (uint32_t)g.NYt % (uint32_t)g.NZt);
+    const int tt = (int)(blk / ((uint32_t)g.NYt * (uint32_t)g.NZt));
     uint32_t cnt = 0;
     for (int tx0 = 0; tx0 < g.NXt; tx0 += 8) {
         const int ntx = min(8, g.NXt - tx0);
@@ -1893,96 +1887,186 @@ __global__ __launch_bounds__(256) void k_read_field_tiles(Dev d, uint32_t* __res
         }
         __syncthreads();
     }
-    block_slot_sum(d, SL_MEMBERS_F, cnt);
+    return cnt;
 }
 
-__global__ __launch_bounds__(256) void k_read_field_bits(Dev d, uint32_t* __restrict__ out, ReadGate gate) {
-    if (!gate_open(gate)) return;
+// Canonical words of a grid whose rows are not whole words: a thread takes one
+// word, which covers parts of one or more rows; each part is cut from the one or
+// two tile words that hold it (157 x 101 x 75 x 21: 17.7 us with the particles'
+// read-out and the counts beside it; 68 bit by bit, alone).
+__device__ __forceinline__ uint32_t read_field_words(const Dev& d, uint32_t* __restrict__ out, uint32_t blk,
+                                                     uint32_t nblk) {
     const Geom& g = d.g;
-    const uint64_t V = (uint64_t)g.X * g.Y * g.Z * g.T;
-    const uint64_t nw = (V + 31) >> 5;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    const uint32_t V = (uint32_t)g.X * g.Y * g.Z * g.T;  // < 2^32 - 1 (checked by the load)
+    const uint32_t nw = (uint32_t)(((uint64_t)V + 31) >> 5);
     uint32_t cnt = 0;
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < nw; i += stride) {
+    for (uint64_t i = blk * 256ull + threadIdx.x; i < nw; i += nblk * 256ull) {
+        uint32_t r = (uint32_t)i * 32u;
+        int x = (int)(r % (uint32_t)g.X);
+        r /= (uint32_t)g.X;
+        int y = (int)(r % (uint32_t)g.Y);
+        r /= (uint32_t)g.Y;
+        int z = (int)(r % (uint32_t)g.Z), t = (int)(r / (uint32_t)g.Z);
         uint32_t w = 0;
-        for (int k = 0; k < 32; ++k) {
-            const uint64_t bi = i * 32 + k;
-            if (bi >= V) break;
-            const uint32_t x = (uint32_t)(bi % g.X);
-            const uint64_t r = bi / g.X;
-            const int y = r % g.Y;
-            const uint64_t r2 = r / g.Y;
-            const int z = r2 % g.Z, t = (int)(r2 / g.Z);
-            const uint32_t b = bit_index(g, (int)x, y, z, t);
-            if (d.active[b >> (5 + 6 + g.logBT)] && test_bit(d.Lf, b)) w |= 1u << k;
+        for (int k = 0; k < 32 && t < g.T;) {
+            const int n = min(32 - k, g.X - x);
+            const int sh = x & 31;
+            const uint32_t tile = tile_of(g, x >> 5, y >> 3, z >> 3, t >> g.logBT);
+            const uint32_t wi = (uint32_t)((((t & (g.BT - 1)) << 3) + (z & 7)) << 3) + (y & 7);
+            const uint32_t next = sh + n > 32 ? tile + 1 : tile;  // the row goes on in the next tile
+            const uint8_t a0 = d.active[tile], a1 = d.active[next];
+            const uint32_t l0 = d.Lf[(size_t)tile * g.WPT + wi], l1 = d.Lf[(size_t)next * g.WPT + wi];
+            uint32_t v = a0 ? l0 >> sh : 0u;
+            if (sh + n > 32 && a1) v |= l1 << (32 - sh);
+            if (n < 32) v &= (1u << n) - 1u;
+            w |= v << k;
+            k += n;
+            x += n;
+            if (x == g.X) {
+                x = 0;
+                if (++y == g.Y) {
+                    y = 0;
+                    if (++z == g.Z) {
+                        z = 0;
+                        ++t;
+                    }
+                }
+            }
         }
         out[i] = w;
         cnt += __popc(w);
     }
-    block_slot_sum(d, SL_MEMBERS_F, cnt);
+    return cnt;
 }
 
-// Particle labels -> uint8 [T][P].  Fast path (P a multiple of 16): a thread
-// owns 16 consecutive particles and, label word by label word, writes their 16
-// bytes of each step as one 16-byte store.
-__global__ __launch_bounds__(256) void k_read_particles16(Dev d, uint8_t* __restrict__ out, ReadGate gate) {
-    if (!gate_open(gate)) return;
+// Particle labels -> uint8 [T][P].  A thread owns 16 consecutive particles and,
+// label word by label word, writes their 16 bytes of each step in one store
+// (rows of P bytes that are not whole 16-byte vectors: an unaligned one; the last
+// P % 16 particles byte by byte).
+__device__ __forceinline__ uint32_t read_particles(const Dev& d, uint8_t* __restrict__ out, int vec, uint32_t blk) {
+    typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+    typedef unsigned int v4u_any __attribute__((ext_vector_type(4), aligned(1)));
     const PGeom& pg = d.pg;
-    const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const int64_t p0 = q * 16;
+    const int64_t p0 = (blk * 256ll + threadIdx.x) * 16;
     uint32_t cnt = 0;
-    if (p0 < pg.P) {
+    if (p0 >= pg.P) return 0;
+    const int np = (int)min((int64_t)16, pg.P - p0);
+    uint32_t fw[4] = {0, 0, 0, 0};
+    if (np == 16) {
         const uint4 fl = *reinterpret_cast<const uint4*>(d.pflag + p0);  // 16 candidate flags
-        const uint32_t fw[4] = {fl.x, fl.y, fl.z, fl.w};
-        const int nw = (pg.T + 63) >> 6;  // words holding real steps
-        for (int w = 0; w < nw; ++w) {
-            unsigned long long lw[16];
+        fw[0] = fl.x; fw[1] = fl.y; fw[2] = fl.z; fw[3] = fl.w;
+    } else {
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                lw[k] = (fw[k >> 2] >> (8 * (k & 3))) & 0xFFu ? d.Lp[(size_t)(p0 + k) * pg.W + w] : 0ull;
-                cnt += __popcll(lw[k]);
-            }
-            const int tend = min(64, pg.T - w * 64);
-            for (int t = 0; t < tend; ++t) {
-                uint32_t v[4];
+        for (int k = 0; k < 16; ++k)
+            if (k < np) fw[k >> 2] |= (uint32_t)d.pflag[p0 + k] << (8 * (k & 3));
+    }
+    const int nw = (pg.T + 63) >> 6;  // words holding real steps
+    for (int w = 0; w < nw; ++w) {
+        unsigned long long lw[16];
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    v[j] = (uint32_t)((lw[4 * j] >> t) & 1) | ((uint32_t)((lw[4 * j + 1] >> t) & 1) << 8) |
-                           ((uint32_t)((lw[4 * j + 2] >> t) & 1) << 16) |
-                           ((uint32_t)((lw[4 * j + 3] >> t) & 1) << 24);
-                typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-                __builtin_nontemporal_store((v4u){v[0], v[1], v[2], v[3]},
-                                            reinterpret_cast<v4u*>(out + (int64_t)(w * 64 + t) * pg.P + p0));
+        for (int k = 0; k < 16; ++k) {
+            lw[k] = (fw[k >> 2] >> (8 * (k & 3))) & 0xFFu ? d.Lp[(size_t)(p0 + k) * pg.W + w] : 0ull;
+            cnt += __popcll(lw[k]);
+        }
+        const int tend = min(64, pg.T - w * 64);
+        for (int t = 0; t < tend; ++t) {
+            v4u v;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                v[j] = (uint32_t)((lw[4 * j] >> t) & 1) | ((uint32_t)((lw[4 * j + 1] >> t) & 1) << 8) |
+                       ((uint32_t)((lw[4 * j + 2] >> t) & 1) << 16) | ((uint32_t)((lw[4 * j + 3] >> t) & 1) << 24);
+            uint8_t* o = out + (int64_t)(w * 64 + t) * pg.P + p0;
+            if (vec) {  // P a multiple of 16: np is 16
+                __builtin_nontemporal_store(v, reinterpret_cast<v4u*>(o));
+            } else if (np == 16) {
+                *reinterpret_cast<v4u_any*>(o) = v;
+            } else {
+#pragma unroll
+                for (int k = 0; k < 16; ++k)
+                    if (k < np) o[k] = (uint8_t)(v[k >> 2] >> (8 * (k & 3)));
             }
         }
     }
-    block_slot_sum(d, SL_MEMBERS_P, cnt);
+    return cnt;
 }
 
-// General particle read-out: a thread owns 4 consecutive particles.
-__global__ __launch_bounds__(256) void k_read_particles(Dev d, uint8_t* __restrict__ out, ReadGate gate) {
-    if (!gate_open(gate)) return;
-    const PGeom& pg = d.pg;
-    const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const int64_t p0 = q * 4;
-    uint32_t cnt = 0;
-    if (p0 < pg.P) {
-        const int np = (int)min((int64_t)4, pg.P - p0);
-        for (int w = 0; w < pg.W; ++w) {
-            unsigned long long lw[4] = {0, 0, 0, 0};
-            for (int k = 0; k < np; ++k) {
-                lw[k] = d.pflag[p0 + k] ? d.Lp[(size_t)(p0 + k) * pg.W + w] : 0ull;
-                cnt += __popcll(lw[k]);
+template <int BT>
+constexpr int read_lds() { return 8 * (64 * BT + 1); }
+
+template <int BT>
+__global__ __launch_bounds__(256) void k_read_field_tiles(Dev d, uint32_t* __restrict__ out, int vec) {
+    __shared__ uint32_t sl[read_lds<BT>()];
+    block_slot_sum(d, SL_MEMBERS_F, read_field_tiles<BT>(d, out, vec, blockIdx.x, sl));
+}
+__global__ __launch_bounds__(256) void k_read_field_words(Dev d, uint32_t* __restrict__ out) {
+    block_slot_sum(d, SL_MEMBERS_F, read_field_words(d, out, blockIdx.x, gridDim.x));
+}
+__global__ __launch_bounds__(256) void k_read_particles(Dev d, uint8_t* __restrict__ out, int vec) {
+    block_slot_sum(d, SL_MEMBERS_P, read_particles(d, out, vec, blockIdx.x));
+}
+
+// End of a grow, or of a chunk of its launched rounds, in one launch: the first
+// block folds the statistics and hands them and the counters to the host (into
+// pinned memory, then the sequence number the host polls), and unless the rounds
+// left work every block reads out its share of the masks: fields first, then
+// particles.  It replaces a statistics kernel, a copy, four kernels on two streams
+// and the events between them.
+template <int BT>
+__global__ __launch_bounds__(256) void k_finish(Dev d, Finish f) {
+    __shared__ uint32_t sl[read_lds<BT>()];
+    __shared__ unsigned long long s_w[3][4];
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    uint32_t total[2];
+#pragma unroll
+    for (int par = 0; par < 2; ++par) wave_excl_scan(d.wcnt[(par * kWorkSubs + lane) * kWcntStride], total[par]);
+    if (blockIdx.x == 0) {
+        constexpr int which[3] = {SL_PART_VISITS, SL_ACTIVE, SL_TESTED};
+        constexpr int dst[3] = {S_PART_VISITS, S_ACTIVE_TILES, S_TILES_TESTED};
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            unsigned long long v = 0;
+            for (int i = threadIdx.x; i < kSlots; i += 256) {
+                v += d.slots[which[k] * kSlots + i];
+                d.slots[which[k] * kSlots + i] = 0ull;
             }
-            const int tend = min(64, pg.T - w * 64);
-            for (int tl = 0; tl < tend; ++tl) {
-                const int64_t t = w * 64 + tl;
-                uint8_t* o = out + t * pg.P + p0;
-                for (int k = 0; k < np; ++k) o[k] = (uint8_t)((lw[k] >> tl) & 1);
-            }
+            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+            if (lane == 0) s_w[k][wave] = v;
         }
+        __syncthreads();
+        if (threadIdx.x < S_NSTAT) {
+            unsigned long long v = d.stat64[threadIdx.x];
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                if ((int)threadIdx.x == dst[k]) {
+                    v += s_w[k][0] + s_w[k][1] + s_w[k][2] + s_w[k][3];
+                    d.stat64[threadIdx.x] = v;
+                }
+            f.host[threadIdx.x] = v;
+        } else if (threadIdx.x < S_NSTAT + C_NCOUNTERS) {
+            const int c = threadIdx.x - S_NSTAT;
+            uint32_t v = d.counters[c];
+            if (c == C_NWORK0 || c == C_NWORK1) {
+                v = total[c - C_NWORK0];
+                d.counters[c] = v;
+            }
+            reinterpret_cast<uint32_t*>(f.host + S_NSTAT)[c] = v;
+        }
+        __threadfence_system();
+        __syncthreads();
+        if (threadIdx.x == 0)
+            __hip_atomic_store(reinterpret_cast<uint32_t*>(f.host + S_NSTAT) + C_NCOUNTERS, f.seq, __ATOMIC_RELEASE,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
     }
-    block_slot_sum(d, SL_MEMBERS_P, cnt);
+    // the rounds reached the fixed point: fewer had work than were queued, or no
+    // list holds any
+    if (total[0] + total[1] != 0 && !(f.rounds && d.counters[C_ROUNDS] < f.rounds) && !f.always) return;  // grid-uniform
+    if (blockIdx.x < f.nf) {
+        const uint32_t cnt = f.words ? read_field_words(d, f.fout, blockIdx.x, f.nf)
+                                     : read_field_tiles<BT>(d, f.fout, f.fvec, blockIdx.x, sl);
+        block_slot_sum(d, SL_MEMBERS_F, cnt);
+    } else if (blockIdx.x < f.nf + f.np) {
+        block_slot_sum(d, SL_MEMBERS_P, read_particles(d, f.pout, f.pvec, blockIdx.x - f.nf));
+    }
 }
 
 // Trajectory segments of the grown feature (Section 3.4): a member step stays
@@ -2089,14 +2173,17 @@ inline unsigned grid_for(uint64_t n, unsigned block, unsigned cap) {
 }
 
 template <int BT>
-bool coop_rounds(const Dev& d, uint32_t round0, uint32_t max_rounds, int device, hipStream_t s) {
-    int per_cu = 0, ncu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_rounds<BT>, 256, 0) != hipSuccess ||
-        per_cu <= 0)
-        return false;
-    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
-        ncu <= 0)
-        return false;
+bool coop_rounds(const Dev& d, uint32_t round0, uint32_t max_rounds, int device, int* fit, hipStream_t s) {
+    if (*fit == 0) {
+        int per_cu = 0, ncu = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_rounds<BT>, 256, 0) != hipSuccess ||
+            per_cu <= 0)
+            return false;
+        if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
+            ncu <= 0)
+            return false;
+        *fit = std::min(per_cu, 2) * ncu;
+    }
     Dev dd = d;
     uint32_t r0 = round0, mr = max_rounds;
     void* args[] = {&dd, &r0, &mr};
@@ -2109,7 +2196,7 @@ bool coop_rounds(const Dev& d, uint32_t round0, uint32_t max_rounds, int device,
     // with 30 (and quiet pulls skipped); 32^3 x 8: 418 and 361 us with 8.
     const uint64_t steps = (uint64_t)d.pg.P * d.pg.Tpad;
     const uint64_t use = std::max<uint64_t>(std::max<uint64_t>(d.g.NT / 64, steps >> 17), 8);
-    const dim3 grid((unsigned)std::min<uint64_t>(use, (uint64_t)std::min(per_cu, 2) * ncu));
+    const dim3 grid((unsigned)std::min<uint64_t>(use, (uint64_t)*fit));
     return hipLaunchCooperativeKernel((const void*)k_rounds<BT>, grid, dim3(256), args, 0, s) ==
            hipSuccess;
 }
@@ -2133,18 +2220,14 @@ void launch_fold_grow_slots(const Dev& d, hipStream_t s) {
     hipLaunchKernelGGL(k_fold_slots, dim3(1), dim3(1024), 0, s, d, kGrowFold);
 }
 
-void launch_chunk_end(const Dev& d, int par, uint32_t* snap, hipStream_t s) {
-    hipLaunchKernelGGL(k_chunk_end, dim3(1), dim3(1024), 0, s, d, par, kGrowFold, snap);
-}
-
 void launch_fill_u32(uint32_t* p, uint32_t v, uint64_t n, hipStream_t s) {
     if (n == 0) return;
     hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(n, 256, 8192)), dim3(256), 0, s, p, v, n);
 }
 
-void launch_reset(const Dev& d, hipStream_t s) {
+void launch_begin(const Dev& d, hipStream_t s) {
     const uint64_t n = 2ull * d.g.NT + (uint64_t)(d.pg.P + 31) / 32;
-    hipLaunchKernelGGL(k_reset, dim3(grid_for(n, 256, 2048)), dim3(256), 0, s, d);
+    hipLaunchKernelGGL(k_begin, dim3(grid_for(n, 256, 2048)), dim3(256), 0, s, d);
 }
 
 void launch_bin_particles(const Geom& g, const PGeom& pg, const float* xyz, const float* attr,
@@ -2160,13 +2243,24 @@ void launch_summaries(const Geom& g, const float* field, float* copy, float2* ts
     hipLaunchKernelGGL(k_tile_summaries, dim3(g.NT), dim3(256), 0, s, g, field, vec, copy, tsum);
 }
 
+// The field's and the particles' admissibility in one launch.  Up to
+// kBothTiles tiles neither pass fills the GPU: side by side they take as long as
+// the slower one (128^3 x 32: 14.7 us, 22 one after the other).  Above, each
+// is bound by memory alone and the other would only take its registers.
+constexpr uint32_t kBothTiles = 8192;
+bool launch_admit_both(const Dev& d, hipStream_t s) {
+    if (d.admit_all || d.pg.P == 0 || d.pg.Tpad < 4 || d.g.NT > kBothTiles) return false;
+    const unsigned np = grid_for((uint64_t)d.pg.P, kAdmitChunk, 2048);
+    hipLaunchKernelGGL(k_admit_both, dim3(np + grid_for(d.g.NT, 1, 2048)), dim3(256), 0, s, d, np);
+    return true;
+}
+
 void launch_admit_field(const Dev& d, hipStream_t s) {
     if (d.admit_all) {
         hipLaunchKernelGGL(k_admit_field, dim3(d.g.NYt, d.g.NZt, d.g.T), dim3(256), 0, s, d);
         hipLaunchKernelGGL(k_count_active, dim3(grid_for(d.g.NT, 256, 1024)), dim3(256), 0, s, d);
     } else {
         // counts its active and tested tiles itself
-        hipLaunchKernelGGL(k_tile_candidates, dim3(grid_for(d.g.NT, 256, 1024)), dim3(256), 0, s, d);
         hipLaunchKernelGGL(k_admit_tiles, dim3(grid_for(d.g.NT, 1, 8192)), dim3(256), 0, s, d);
     }
 }
@@ -2175,8 +2269,6 @@ void launch_admit_particles(const Dev& d, hipStream_t s) {
     const PGeom& pg = d.pg;
     if (pg.P == 0) return;
     if (pg.Tpad >= 4) {
-        const uint64_t n4 = ((uint64_t)pg.P * pg.Tpad) >> 2;
-        (void)n4;
         hipLaunchKernelGGL(k_admit_particles, dim3(grid_for((uint64_t)pg.P, kAdmitChunk, 2048)), dim3(256), 0,
                            s, d);
     } else {
@@ -2185,6 +2277,10 @@ void launch_admit_particles(const Dev& d, hipStream_t s) {
         hipLaunchKernelGGL(k_couple, dim3(grid_for((uint64_t)pg.P * pg.W, 256, 8192)), dim3(256), 0,
                            s, d);
     }
+}
+
+void launch_seeds_few(const Dev& d, const FewSeeds& f, hipStream_t s) {
+    if (f.n > 0) hipLaunchKernelGGL(k_seeds_few, dim3(1), dim3(64), 0, s, d, f);
 }
 
 void launch_seeds(const Dev& d, const int32_t* seeds, int64_t S, hipStream_t s) {
@@ -2220,43 +2316,85 @@ void launch_round(const Dev& d, uint32_t round, hipStream_t s, hipEvent_t* ev) {
     if (ev) (void)hipEventRecord(ev[3], s);
 }
 
-bool launch_rounds_persistent(const Dev& d, uint32_t round0, uint32_t max_rounds, int device,
+bool launch_rounds_persistent(const Dev& d, uint32_t round0, uint32_t max_rounds, int device, int* fit,
                               hipStream_t s) {
     switch (d.g.BT) {
-        case 4: return coop_rounds<4>(d, round0, max_rounds, device, s);
-        case 8: return coop_rounds<8>(d, round0, max_rounds, device, s);
-        default: return coop_rounds<16>(d, round0, max_rounds, device, s);
+        case 4: return coop_rounds<4>(d, round0, max_rounds, device, fit, s);
+        case 8: return coop_rounds<8>(d, round0, max_rounds, device, fit, s);
+        default: return coop_rounds<16>(d, round0, max_rounds, device, fit, s);
     }
 }
 
-void launch_read_field(const Dev& d, uint32_t* out, hipStream_t s, const ReadGate& gate) {
-    const Geom& g = d.g;
-    if ((g.X & 31) == 0) {
-        const dim3 grid(g.NYt, g.NZt, g.NTt);
-        // 16-byte stores when every x-run of tiles is a multiple of 4 words
-        const int vec = (g.NXt & 3) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
-        switch (g.BT) {
-            case 4: hipLaunchKernelGGL(k_read_field_tiles<4>, grid, dim3(256), 0, s, d, out, vec, gate); break;
-            case 8: hipLaunchKernelGGL(k_read_field_tiles<8>, grid, dim3(256), 0, s, d, out, vec, gate); break;
-            default: hipLaunchKernelGGL(k_read_field_tiles<16>, grid, dim3(256), 0, s, d, out, vec, gate); break;
-        }
-        return;
+bool rounds_one_fits(const Dev& d) { return d.g.NT <= 512 && (uint64_t)d.pg.P * d.pg.Tpad <= 1u << 19; }
+
+void launch_rounds_one(const Dev& d, uint32_t round0, uint32_t max_rounds, const FewSeeds& f, hipStream_t s) {
+    // Beyond these sizes eight waves fall behind launches over the whole GPU: a
+    // round of launches costs 20 to 25 us, of this kernel about 8 us per eight
+    // tiles of its list and 5 us per 2,048 coupled steps.
+    constexpr uint32_t kTiles = 64, kList = 8192;
+    switch (d.g.BT) {
+        case 4: hipLaunchKernelGGL(k_rounds_one<4>, dim3(1), dim3(kOneThreads), 0, s, d, round0, max_rounds, kTiles, kList, f); break;
+        case 8: hipLaunchKernelGGL(k_rounds_one<8>, dim3(1), dim3(kOneThreads), 0, s, d, round0, max_rounds, kTiles, kList, f); break;
+        default: hipLaunchKernelGGL(k_rounds_one<16>, dim3(1), dim3(kOneThreads), 0, s, d, round0, max_rounds, kTiles, kList, f); break;
     }
+}
+
+namespace {
+// Blocks of the field read-out, and whether it goes by canonical words (rows
+// that are not whole words) or by tiles (vec: 16-byte stores, where every x-run
+// of tiles is a multiple of 4 words and out is aligned).
+unsigned field_read_shape(const Geom& g, const uint32_t* out, int& words, int& vec) {
+    words = (g.X & 31) != 0;
+    vec = (g.NXt & 3) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
     const uint64_t V = (uint64_t)g.X * g.Y * g.Z * g.T;
-    hipLaunchKernelGGL(k_read_field_bits, dim3(grid_for((V + 31) / 32, 256, 16384)), dim3(256), 0,
-                       s, d, out, gate);
+    return words ? grid_for((V + 31) / 32, 256, 16384) : (unsigned)(g.NYt * g.NZt * g.NTt);
+}
+int particle_read_vec(const PGeom& pg, const uint8_t* out) {
+    return (pg.P & 15) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+}
+unsigned particle_read_blocks(const PGeom& pg) { return (unsigned)((pg.P + 16 * 256 - 1) / (16 * 256)); }
+}  // namespace
+
+void launch_finish(const Dev& d, uint32_t* fout, uint8_t* pout, uint32_t rounds, bool always,
+                   unsigned long long* host, uint32_t seq, hipStream_t s) {
+    Finish f{};
+    f.fout = fout;
+    f.pout = pout;
+    if (fout) f.nf = field_read_shape(d.g, fout, f.words, f.fvec);
+    if (pout && d.pg.P > 0) {
+        f.np = particle_read_blocks(d.pg);
+        f.pvec = particle_read_vec(d.pg, pout);
+    }
+    f.rounds = rounds;
+    f.always = always;
+    f.host = host;
+    f.seq = seq;
+    const dim3 grid(f.nf + f.np ? f.nf + f.np : 1);
+    switch (d.g.BT) {
+        case 4: hipLaunchKernelGGL(k_finish<4>, grid, dim3(256), 0, s, d, f); break;
+        case 8: hipLaunchKernelGGL(k_finish<8>, grid, dim3(256), 0, s, d, f); break;
+        default: hipLaunchKernelGGL(k_finish<16>, grid, dim3(256), 0, s, d, f); break;
+    }
 }
 
-void launch_read_particles(const Dev& d, uint8_t* out, hipStream_t s, const ReadGate& gate) {
-    const PGeom& pg = d.pg;
-    if (pg.P == 0) return;
-    if ((pg.P & 15) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
-        hipLaunchKernelGGL(k_read_particles16, dim3(grid_for(pg.P / 16, 256, 1u << 20)), dim3(256),
-                           0, s, d, out, gate);
+void launch_read_field(const Dev& d, uint32_t* out, hipStream_t s) {
+    int words, vec;
+    const dim3 grid(field_read_shape(d.g, out, words, vec));
+    if (words) {
+        hipLaunchKernelGGL(k_read_field_words, grid, dim3(256), 0, s, d, out);
         return;
     }
-    hipLaunchKernelGGL(k_read_particles, dim3(grid_for((pg.P + 3) / 4, 256, 1u << 20)), dim3(256),
-                       0, s, d, out, gate);
+    switch (d.g.BT) {
+        case 4: hipLaunchKernelGGL(k_read_field_tiles<4>, grid, dim3(256), 0, s, d, out, vec); break;
+        case 8: hipLaunchKernelGGL(k_read_field_tiles<8>, grid, dim3(256), 0, s, d, out, vec); break;
+        default: hipLaunchKernelGGL(k_read_field_tiles<16>, grid, dim3(256), 0, s, d, out, vec); break;
+    }
+}
+
+void launch_read_particles(const Dev& d, uint8_t* out, hipStream_t s) {
+    if (d.pg.P == 0) return;
+    hipLaunchKernelGGL(k_read_particles, dim3(particle_read_blocks(d.pg)), dim3(256), 0, s, d, out,
+                       particle_read_vec(d.pg, out));
 }
 
 void launch_particle_segments(const Dev& d, uint8_t* out, hipStream_t s) {

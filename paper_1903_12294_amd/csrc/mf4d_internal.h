@@ -60,12 +60,12 @@ struct PGeom {
 enum Counter : int {
     C_NWORK0 = 0,  // tiles on work list 0 (even rounds), summed from its sub-lists for the host
     C_NWORK1 = 1,  // tiles on work list 1 (odd rounds), likewise
-    C_UNUSED2 = 2, // (free)
+    C_NCAND1 = 2,  // candidate tiles of every other grow (Dev::ncand says which)
     C_NLIST = 3,   // coupled particle-steps on the flat list
     C_DROPPED = 4, // dropped seeds
     C_ERR = 5,     // set by the persistent kernel if a grid barrier timed out
     C_ROUNDS = 6,  // rounds completed by the persistent kernel
-    C_NCAND = 7,   // candidate tiles
+    C_NCAND0 = 7,  // candidate tiles
     C_RACT = 8,    // launched rounds: 1 if the current round has work (set by its sweep)
     C_JCHANGED = 9,  // Jacobi sweeps: the sweep added a node
     C_CHG0 = 10,   // some tile is flagged changed for round parity 0 (cleared by the sweep of parity 1)
@@ -85,15 +85,23 @@ enum Stat64 : int {
     S_NSTAT = 8
 };
 
-// Condition under which a queued read-out runs: with counters null always;
-// else only if the chunk of rounds queued before it reached the fixed point,
-// i.e. fewer than `rounds` rounds had work (counters[C_ROUNDS]) or the work
-// list of parity `par` for the next round is empty.  A closed gate makes the
-// read-out a no-op, so that it can be queued before the host knows.
-struct ReadGate {
-    const uint32_t* counters;
-    uint32_t rounds;
-    int par;
+// What k_finish does: see launch_finish.
+struct Finish {
+    uint32_t* fout;            // field mask words, or null
+    uint8_t* pout;             // particle mask, or null
+    uint32_t nf, np;           // blocks of the two read-outs
+    int words, fvec, pvec;     // field by canonical words; 16-byte stores
+    uint32_t rounds;           // rounds queued before it (0: unknown)
+    int always;                // read out whether or not work is left
+    unsigned long long* host;  // pinned: S_NSTAT statistics, C_NCOUNTERS counters, the sequence number
+    uint32_t seq;
+};
+
+// A few seeds (x, y, z, t), passed as launch arguments.
+constexpr int kFewSeeds = 64;
+struct FewSeeds {
+    int n;
+    int32_t v[4 * kFewSeeds];
 };
 
 // Every device buffer of a context, passed by value to the kernels.
@@ -126,6 +134,8 @@ struct Dev {
     const uint8_t* tpred;    // NT or null: candidate tiles to test before the rounds
     float crit[4];
     int admit_all;           // 1: test every voxel-step; 0: only candidate tiles
+    int ncand;               // C_NCAND0 or C_NCAND1: the counter of this grow's candidate tiles
+    int keep_members;        // 1: read-outs of another grow may still use the member slots
     int forward_only;        // 1: membership runs along a trajectory from t to t + 1 only
     int pull_all;            // 1: the pull tests every coupled step, changed tile or not
                              // (the verification round of the score-ordered schedulers)
@@ -133,25 +143,42 @@ struct Dev {
 
 // ---- launchers (kernels.hip) ----
 void launch_fill_u32(uint32_t* p, uint32_t v, uint64_t n, hipStream_t s);
-void launch_reset(const Dev& d, hipStream_t s);
+// Start of a grow: scheduling state zeroed, candidate tiles listed.
+void launch_begin(const Dev& d, hipStream_t s);
 // copy (or null): xyz [T][P][3] then attr [T][P], as loaded.
 void launch_bin_particles(const Geom& g, const PGeom& pg, const float* xyz, const float* attr,
                           uint32_t* bins, float* attr_t, float* copy, float2* psum, hipStream_t s);
 // copy (or null): the field as loaded.
 void launch_summaries(const Geom& g, const float* field, float* copy, float2* tsum, hipStream_t s);
+// Both kinds of admissibility in one launch; false where they go separately.
+bool launch_admit_both(const Dev& d, hipStream_t s);
 void launch_admit_field(const Dev& d, hipStream_t s);
 void launch_admit_particles(const Dev& d, hipStream_t s);
 void launch_seeds(const Dev& d, const int32_t* seeds, int64_t S, hipStream_t s);
+void launch_seeds_few(const Dev& d, const FewSeeds& f, hipStream_t s);
 // One round as three launches (sweep, pull, close/push); a round whose work
 // list is empty does nothing, so rounds can be queued ahead of the host.
 void launch_round(const Dev& d, uint32_t round, hipStream_t s, hipEvent_t* ev = nullptr);  // ev: 4 events or null
 // Sum of the work sub-list lengths of parity `par` into counters[C_NWORK0 + par].
 void launch_work_total(const Dev& d, int par, hipStream_t s);
 // Rounds in one cooperative persistent launch; false if it cannot be launched.
-bool launch_rounds_persistent(const Dev& d, uint32_t round0, uint32_t max_rounds, int device,
+// *fit: blocks of the tile depth's kernel that fit the device at once (0: not
+// known yet; the context keeps it).
+bool launch_rounds_persistent(const Dev& d, uint32_t round0, uint32_t max_rounds, int device, int* fit,
                               hipStream_t s);
-void launch_read_field(const Dev& d, uint32_t* out, hipStream_t s, const ReadGate& gate = ReadGate{});
-void launch_read_particles(const Dev& d, uint8_t* out, hipStream_t s, const ReadGate& gate = ReadGate{});
+// Seeds (f.n of them, if any) and rounds in one block, for volumes that fit.  The
+// kernel may decline the rounds on the device (more work than expected): the work
+// lists then hold the seeds' tiles and counters[C_ROUNDS] is 0.
+bool rounds_one_fits(const Dev& d);
+void launch_rounds_one(const Dev& d, uint32_t round0, uint32_t max_rounds, const FewSeeds& f, hipStream_t s);
+// End of a grow or of a chunk of `rounds` launched rounds: per-grow statistics
+// folded, statistics and counters to the host (then seq), and the read-outs
+// (fout, pout; either may be null) if the rounds reached the fixed point or
+// `always`.  Member counts stay in their slots (launch_fold_slots).
+void launch_finish(const Dev& d, uint32_t* fout, uint8_t* pout, uint32_t rounds, bool always,
+                   unsigned long long* host, uint32_t seq, hipStream_t s);
+void launch_read_field(const Dev& d, uint32_t* out, hipStream_t s);
+void launch_read_particles(const Dev& d, uint8_t* out, hipStream_t s);
 // Trajectory segments of the grown feature as uint8 [T][P] (Section 3.4).
 void launch_particle_segments(const Dev& d, uint8_t* out, hipStream_t s);
 // Fold one single-seed grow into per-seed ids: members of the canonical field
@@ -184,10 +211,5 @@ void launch_fold_slots(const Dev& d, int which, int dst, hipStream_t s, bool ass
 // The per-grow statistics (particle visits, active and tested tiles) folded
 // (added) in one launch.
 void launch_fold_grow_slots(const Dev& d, hipStream_t s);
-// End of a chunk of launched rounds, in one launch: the work total of parity
-// par (as launch_work_total), with snap non-null a copy of counters[C_ROUNDS]
-// and of that total into snap (the read-outs' gate), and the per-grow
-// statistics folded (as launch_fold_grow_slots).
-void launch_chunk_end(const Dev& d, int par, uint32_t* snap, hipStream_t s);
 
 }  // namespace mf4d

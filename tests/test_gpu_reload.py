@@ -92,7 +92,7 @@ def test_kept_buffers_are_given_back():
         g.set_criteria(*i["crit"])
         g.set_seeds(i["seeds"])
         g.grow()
-        assert lib.mf4d_device_bytes() == alone + i["seeds"].nbytes
+        assert lib.mf4d_device_bytes() == alone  # (a few seeds need no buffer)
         with pytest.raises(_lib.MF4DError):
             g.read_particle_mask(np.zeros((i["T"], i["P"]), np.uint8))
     finally:
