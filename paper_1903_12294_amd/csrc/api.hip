@@ -258,7 +258,7 @@ struct mf4d_ctx {
     uint32_t* b_prank = nullptr;  // [P][Tpad] ranks of the particle-steps
     uint32_t* b_dirty = nullptr;
     uint8_t* b_chg = nullptr;
-    uint32_t* b_work = nullptr;
+    uint2* b_work = nullptr;
     uint32_t* b_wcnt = nullptr;
     uint32_t b_wcap = 0;
     uint32_t* b_counters = nullptr;

@@ -44,9 +44,9 @@ struct DevB {
     uint32_t* pplanes;       // [T][P][8] labels = output
     const float* tab;        // kTabWords
     uint8_t* active;         // NTB (+8)
-    uint32_t* dirty;         // 2 x NTB
+    uint32_t* dirty;         // 2 x NTB: why a tile is flagged (faces, own members)
     uint8_t* chg;            // 2 x NTB (+8)
-    uint32_t* work;          // [2][kBSubs][WCAPB] work sub-lists of round parity 0 / 1
+    uint2* work;             // [2][kBSubs][WCAPB] work sub-lists of round parity 0 / 1: tile, flags
     uint32_t* wcnt;          // [2][kBSubs] sub-list lengths, kBCntStride words apart
     uint32_t WCAPB;          // capacity of one sub-list = ceil(NTB / kBSubs)
     uint2* clist;            // coupled steps (flat step index, canonical voxel index)

@@ -17,7 +17,8 @@
 // organised in 4D tiles of 512 voxel-steps (a power-of-two extent per axis,
 // chosen per context, e.g. 8 x 4 x 4 x 4), one thread per voxel-step, with
 // the round protocol of the single-query grower: sweep, pull, close/push,
-// double-buffered work lists by round parity.
+// double-buffered work lists by round parity.  A tile is flagged with the faces
+// across which its neighbours gained members: its visit reads only those.
 #include "mf4d_internal.h"
 #include "batched.h"
 
@@ -70,12 +71,15 @@ __device__ __forceinline__ Mask8 band_mask(const BandTables& tb, int Q, float v)
 }
 
 // Prefix-mask tables of one sample type staged in LDS: lo rows then hi rows,
-// [257][8] words each.
+// [257][8] words each, of which the Q + 1 rows in use are copied.
 constexpr int kLdsTab = 2 * 257 * 8;
 
 __device__ __forceinline__ void stage_tables(const DevB& d, int type, uint32_t* s_tab) {
     const uint32_t* src = reinterpret_cast<const uint32_t*>(d.tab + 1024) + (size_t)type * 2 * 257 * 8;
-    for (int i = threadIdx.x; i < kLdsTab; i += blockDim.x) s_tab[i] = src[i];
+    for (int i = threadIdx.x; i < (d.Q + 1) * 8; i += blockDim.x) {
+        s_tab[i] = src[i];
+        s_tab[257 * 8 + i] = src[257 * 8 + i];
+    }
 }
 
 // Word k of the mask of a node with packed ranks r, from staged tables.
@@ -125,61 +129,58 @@ __device__ __forceinline__ void bit_to_xyzt(const Geom& g, uint32_t b, int& x, i
     t = (tt << g.logBT) + (wi >> 6);
 }
 
-// Scheduling flags a tile for the round of parity `par` with a plain store
-// (no round trip to wait for); kb_compact turns the flags into that round's
-// work list, dropping tiles without an admissible node.
-__device__ __forceinline__ void bschedule(const DevB& d, uint32_t tile, int par) {
-    d.dirty[par * d.NTB + tile] = 1u;
+// Scheduling flags a tile for the round of parity `par` (bit f: its neighbour
+// across face f gained members there, faces in the order x-, x+, y-, .. t+;
+// kOwn: it gained members itself outside a sweep) without a round trip to wait
+// for; kb_compact turns the flags into that round's work list, dropping tiles
+// without an admissible node.
+constexpr uint32_t kOwn = 1u << 8;
+__device__ __forceinline__ void bschedule(const DevB& d, uint32_t tile, int par, uint32_t bits) {
+    atomicOr(&d.dirty[par * d.NTB + tile], bits);
 }
 
-template <int N>
-__device__ __forceinline__ void bschedule_n(const DevB& d, const uint32_t (&tiles)[N], int par) {
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-        if (tiles[i] != ~0u) bschedule(d, tiles[i], par);
-}
-
-// The voxel's tile (flagged for the pull) and the tiles whose face it
-// touches, at most one per axis: slots 0 (own) and 1..4 of nb (~0u: none).
-__device__ __forceinline__ void voxel_targets(const DevB& d, int x, int y, int z, int t, int par,
-                                              uint32_t* nb) {
+// A voxel that gained members outside a sweep: its tile (flagged for the pull
+// too) and the tiles whose face it touches.
+__device__ __forceinline__ void bmark_voxel(const DevB& d, int x, int y, int z, int t, int par) {
     const uint32_t tile = btile_of(d, x, y, z, t);
     d.chg[par * d.NTB + tile] = 1;
+    bschedule(d, tile, par, kOwn);
     const uint32_t sy = d.NXb, sz = d.NXb * d.NYb, st = sz * d.NZb;
     const int mx = (1 << d.lx) - 1, my = (1 << d.ly) - 1, mz = (1 << d.lz) - 1, mt = (1 << d.lt) - 1;
-    nb[0] = tile;
-    nb[1] = nb[2] = nb[3] = nb[4] = ~0u;
-    if ((x & mx) == 0 && x > 0) nb[1] = tile - 1;
-    else if ((x & mx) == mx && x + 1 < d.X) nb[1] = tile + 1;
-    if ((y & my) == 0 && y > 0) nb[2] = tile - sy;
-    else if ((y & my) == my && y + 1 < d.Y) nb[2] = tile + sy;
-    if ((z & mz) == 0 && z > 0) nb[3] = tile - sz;
-    else if ((z & mz) == mz && z + 1 < d.Z) nb[3] = tile + sz;
-    if ((t & mt) == 0 && t > 0) nb[4] = tile - st;
-    else if ((t & mt) == mt && t + 1 < d.T) nb[4] = tile + st;
-}
-
-__device__ __forceinline__ void bmark_voxel(const DevB& d, int x, int y, int z, int t, int par) {
-    uint32_t nb[5];
-    voxel_targets(d, x, y, z, t, par, nb);
-    bschedule_n<5>(d, nb, par);
+    if ((x & mx) == 0 && x > 0) bschedule(d, tile - 1, par, 1u << 1);
+    if ((x & mx) == mx && x + 1 < d.X) bschedule(d, tile + 1, par, 1u << 0);
+    if ((y & my) == 0 && y > 0) bschedule(d, tile - sy, par, 1u << 3);
+    if ((y & my) == my && y + 1 < d.Y) bschedule(d, tile + sy, par, 1u << 2);
+    if ((z & mz) == 0 && z > 0) bschedule(d, tile - sz, par, 1u << 5);
+    if ((z & mz) == mz && z + 1 < d.Z) bschedule(d, tile + sz, par, 1u << 4);
+    if ((t & mt) == 0 && t > 0) bschedule(d, tile - st, par, 1u << 7);
+    if ((t & mt) == mt && t + 1 < d.T) bschedule(d, tile + st, par, 1u << 6);
 }
 
 // N voxels (bit positions, kNoVoxel: none) marked together.
 template <int N>
 __device__ __forceinline__ void bmark_voxels_n(const DevB& d, const uint32_t (&b)[N], int par) {
-    uint32_t nb[5 * N];
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-#pragma unroll
-        for (int j = 0; j < 5; ++j) nb[5 * i + j] = ~0u;
         if (b[i] != kNoVoxel) {
             int x, y, z, t;
             bit_to_xyzt(d.g, b[i], x, y, z, t);
-            voxel_targets(d, x, y, z, t, par, nb + 5 * i);
+            bmark_voxel(d, x, y, z, t, par);
         }
     }
-    bschedule_n<5 * N>(d, nb, par);
+}
+
+// Lane i of eight (a tile's faces in order) flags the neighbour across face i
+// of a tile whose nodes there gained members (faces: those faces).
+__device__ __forceinline__ void bschedule_face(const DevB& d, uint32_t tile, int bx, int by, int bz, int bt, int i,
+                                               uint32_t faces, int par) {
+    if (!((faces >> i) & 1u)) return;
+    const uint32_t sy = d.NXb, sz = d.NXb * d.NYb, st = sz * d.NZb;
+    const int axis = i >> 1;
+    const int b = axis == 0 ? bx : axis == 1 ? by : axis == 2 ? bz : bt;
+    const int n = axis == 0 ? d.NXb : axis == 1 ? d.NYb : axis == 2 ? d.NZb : d.NTb;
+    const uint32_t st_a = axis == 0 ? 1u : axis == 1 ? sy : axis == 2 ? sz : st;
+    if ((i & 1) ? b + 1 < n : b > 0) bschedule(d, (i & 1) ? tile + st_a : tile - st_a, par, 1u << (i ^ 1));
 }
 
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s_tmp,
@@ -324,24 +325,262 @@ __global__ void kb_seeds(DevB d, const int32_t* __restrict__ seeds, int64_t S) {
     }
 }
 
-// Lane moves within a row of 16 lanes (DPP): lane i receives lane i - N
-// (shr) or i + N (shl) of its row; a lane whose source lies outside the row
-// receives 0.  Register-only: no LDS traffic.
+// Lane moves (DPP), register only: the neighbour in a group of four lanes (its
+// first and last lane receive their own value), and four
+// lanes up or down in a row of 16 (0 from outside the row).
 template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_row(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
+__device__ __forceinline__ uint32_t dpp(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
 }
-constexpr int kDppRowShr1 = 0x111, kDppRowShr4 = 0x114, kDppRowShl1 = 0x101, kDppRowShl4 = 0x104;
+constexpr int kQuadPrev = 0x90, kQuadNext = 0xF9, kRowPrev4 = 0x114, kRowNext4 = 0x104;
+constexpr int kRowRor1 = 0x121, kRowRor2 = 0x122, kRowRor4 = 0x124, kRowRor8 = 0x128;
+
+// The work list of a round seen as one list: its sub-lists' prefix sums.
+__device__ __forceinline__ void stage_work(const DevB& d, int par, uint32_t* s_pref) {
+    if (threadIdx.x < kBSubs) {
+        // the first wave scans the sub-list lengths
+        const uint32_t c = d.wcnt[((uint32_t)par * kBSubs + threadIdx.x) * kBCntStride];
+        uint32_t x = c;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(x, o);
+            if ((int)threadIdx.x >= o) x += y;
+        }
+        s_pref[threadIdx.x + 1] = x;
+        if (threadIdx.x == 0) s_pref[0] = 0;
+    }
+    __syncthreads();
+}
+__device__ __forceinline__ uint2 work_item(const DevB& d, int par, const uint32_t* s_pref, uint32_t w) {
+    // the sub-list holding flat item w: the last j with s_pref[j] <= w
+    int lo = 0, hi = kBSubs;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (s_pref[mid] <= w) lo = mid; else hi = mid;
+    }
+    return d.work[((size_t)par * kBSubs + lo) * d.WCAPB + (w - s_pref[lo])];
+}
+// A round's counters: rounds are queued ahead of the host, and a round whose
+// work list is empty does nothing (recorded for its pull and close).
+__device__ __forceinline__ void begin_round(const DevB& d, uint32_t nwork) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        d.counters[BC_NDIRTYP] = 0;
+        d.counters[BC_RACT] = nwork ? 1u : 0u;
+        if (nwork) {
+            d.counters[BC_ROUNDS] += 1u;
+            d.stat64[S_TILE_VISITS] += nwork;
+        }
+    }
+}
+
+// Sweep of tiles with at least four nodes along x and along y.  A row of 16
+// lanes takes one word (32 queries) of one tile: a lane holds an x by y piece of
+// the tile at every z and t, 32 nodes, in registers.  A line of nodes along z or
+// t, or within a piece, is closed by one pass up and one down; between pieces
+// the word moves by DPP.  No LDS and no barrier: the loop of a wave ends when
+// none of its four rows gained a bit (labels only grow).  Only nodes that admit
+// a query of the word are read, and only the faces the tile is flagged for.
+// Few queries fill the rows with tiles instead of words.
+// Bound by the chain of loads (list, ranks, labels and halos) and the issue of
+// the passes.  128^3 x 32, 256 queries, 67,600 visits of 4 x 4 x 4 x 8 tiles:
+// 1,598 us; 3,058 with a block of 512 threads per tile passing all eight words
+// through LDS and reading every face.
+template <int LX, int LY, int LZ, int LT>
+__global__ __launch_bounds__(256) void kb_sweep_rows(DevB d, int par) {
+    static_assert(LX >= 2 && LY >= 2 && LX + LY + LZ + LT == 9, "512 nodes, 4 x 4 lanes");
+    constexpr int NX = 1 << (LX - 2), NY = 1 << (LY - 2), NZ = 1 << LZ, NT = 1 << LT;
+    __shared__ uint32_t s_ftab[kLdsTab];
+    __shared__ uint32_t s_pref[kBSubs + 1];
+    stage_work(d, par, s_pref);
+    const uint32_t nwork = s_pref[kBSubs];
+    begin_round(d, nwork);
+    const uint32_t nw = (uint32_t)(d.Q + 31) >> 5;
+    const uint64_t items = (uint64_t)nwork * nw;
+    if (blockIdx.x * 16ull >= items) return;  // block-uniform
+    stage_tables(d, 0, s_ftab);
+    __syncthreads();
+    const int lane = lane_id(), li = lane & 15, xl = lane & 3, yl = (lane >> 2) & 3;
+    const uint64_t sy = (uint64_t)d.X, sz = sy * d.Y, st = sz * d.Z;
+    const uint64_t wave = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    for (uint64_t i0 = wave * 4; i0 < items; i0 += (uint64_t)gridDim.x * 16) {  // wave-uniform
+        const uint64_t it = i0 + (lane >> 4);
+        uint32_t word = 0, tile = 0, flags = 0;
+        int xlim = 0, ylim = 0, zlim = 0, tlim = 0;
+        int bx = 0, by = 0, bz = 0, bt = 0;
+        if (it < items) {
+            const uint32_t w = (uint32_t)(it / nw);
+            word = (uint32_t)(it - (uint64_t)w * nw);
+            const uint2 e = work_item(d, par, s_pref, w);
+            tile = e.x;
+            flags = e.y;
+            btile_coords(d, tile, bx, by, bz, bt);
+            xlim = d.X - ((bx << LX) + xl * NX);
+            ylim = d.Y - ((by << LY) + yl * NY);
+            zlim = d.Z - (bz << LZ);
+            tlim = d.T - (bt << LT);
+        }
+        const uint64_t v0 = vindex(d, (bx << LX) + xl * NX, (by << LY) + yl * NY, bz << LZ, bt << LT);
+        auto at = [](int jx, int jy, int jz, int jt) { return ((jt * NZ + jz) * NY + jy) * NX + jx; };
+        uint32_t a[32], l[32];
+#pragma unroll
+        for (int j = 0; j < 32; ++j) {
+            const int jx = j % NX, jy = j / NX % NY, jz = j / (NX * NY) % NZ, jt = j / (NX * NY * NZ);
+            const bool in = jx < xlim && jy < ylim && jz < zlim && jt < tlim;
+            a[j] = 0;
+            if (in) a[j] = d.vrank[v0 + jx + jy * sy + jz * sz + jt * st];
+        }
+#pragma unroll
+        for (int j = 0; j < 32; ++j) a[j] = rank_word(s_ftab, a[j], word);
+        uint32_t* fp = d.fplanes + v0 * 8 + word;
+        // a node that admits none of the word's queries has none of them
+#pragma unroll
+        for (int j = 0; j < 32; ++j) {
+            const int jx = j % NX, jy = j / NX % NY, jz = j / (NX * NY) % NZ, jt = j / (NX * NY * NZ);
+            l[j] = 0;
+            if (a[j]) l[j] = fp[(jx + jy * sy + jz * sz + jt * st) * 8];
+        }
+        uint32_t l0[32];
+#pragma unroll
+        for (int j = 0; j < 32; ++j) l0[j] = l[j];
+        // halos: node j's neighbour off nodes away, where the lane has it
+        auto halo = [&](int j, bool has, int64_t off) {
+            const int jx = j % NX, jy = j / NX % NY, jz = j / (NX * NY) % NZ, jt = j / (NX * NY * NZ);
+            const uint32_t* q = fp + ((int64_t)(jx + jy * sy + jz * sz + jt * st) + off) * 8;
+            const bool use = has && a[j] != 0;
+            // (a load for every lane, from a place that is always there when
+            // unused, so that the loads of a face go out together)
+            const uint32_t h = *(use ? q : reinterpret_cast<const uint32_t*>(d.tab));
+            return use ? h : 0u;
+        };
+        const bool xm = (flags & 1u) && xl == 0, xp = (flags & 2u) && xl == 3;
+        const bool ym = (flags & 4u) && yl == 0, yp = (flags & 8u) && yl == 3;
+        uint32_t h[32];
+#define MF4D_FACE(COND, HAS, OFF, FIRST)                                  \
+    if (__ballot(HAS)) {                                                  \
+        _Pragma("unroll") for (int j = 0; j < 32; ++j) {                  \
+            const int jx = j % NX, jy = j / NX % NY, jz = j / (NX * NY) % NZ, jt = j / (NX * NY * NZ); \
+            (void)jx; (void)jy; (void)jz; (void)jt;                       \
+            h[j] = (COND) ? halo(j, HAS, OFF) : 0u;                       \
+        }                                                                 \
+        _Pragma("unroll") for (int j = 0; j < 32; ++j) l[j] |= h[j] & a[j]; \
+    }
+        if constexpr (NX == 1) {
+            MF4D_FACE(true, xm || xp, xm ? -1ll : 1ll, 0)
+        } else {
+            MF4D_FACE(jx == 0, xm, -1ll, 0)
+            MF4D_FACE(jx == NX - 1, xp, 1ll, 0)
+        }
+        if constexpr (NY == 1) {
+            MF4D_FACE(true, ym || yp, ym ? -(int64_t)sy : (int64_t)sy, 0)
+        } else {
+            MF4D_FACE(jy == 0, ym, -(int64_t)sy, 0)
+            MF4D_FACE(jy == NY - 1, yp, (int64_t)sy, 0)
+        }
+        MF4D_FACE(jz == 0, (flags & 16u) != 0, -(int64_t)sz, 0)
+        MF4D_FACE(jz == NZ - 1, (flags & 32u) != 0, (int64_t)sz, 0)
+        MF4D_FACE(jt == 0, (flags & 64u) != 0, -(int64_t)st, 0)
+        MF4D_FACE(jt == NT - 1, (flags & 128u) != 0, (int64_t)st, 0)
+#undef MF4D_FACE
+        // (the lane that keeps its own value would join the ends of a piece, which
+        // are neighbours, or one node, only in pieces of up to two)
+        const uint32_t first = NX <= 2 || xl != 0 ? ~0u : 0u, last = NX <= 2 || xl != 3 ? ~0u : 0u;
+        uint32_t cnt = 0;
+#pragma unroll
+        for (int j = 0; j < 32; ++j) cnt += __popc(l[j]);
+        while (true) {
+            // lines along t, then z
+#pragma unroll
+            for (int r = 0; r < 32 / NT; ++r) {
+#pragma unroll
+                for (int k = 1; k < NT; ++k) l[k * (32 / NT) + r] |= l[(k - 1) * (32 / NT) + r] & a[k * (32 / NT) + r];
+#pragma unroll
+                for (int k = NT - 2; k >= 0; --k) l[k * (32 / NT) + r] |= l[(k + 1) * (32 / NT) + r] & a[k * (32 / NT) + r];
+            }
+#pragma unroll
+            for (int jt = 0; jt < NT; ++jt)
+#pragma unroll
+                for (int r = 0; r < NX * NY; ++r) {
+                    const int b = jt * NZ * NY * NX + r;
+#pragma unroll
+                    for (int k = 1; k < NZ; ++k) l[b + k * NX * NY] |= l[b + (k - 1) * NX * NY] & a[b + k * NX * NY];
+#pragma unroll
+                    for (int k = NZ - 2; k >= 0; --k)
+                        l[b + k * NX * NY] |= l[b + (k + 1) * NX * NY] & a[b + k * NX * NY];
+                }
+#pragma unroll
+            for (int jt = 0; jt < NT; ++jt)
+#pragma unroll
+                for (int jz = 0; jz < NZ; ++jz) {
+                    if constexpr (NX == 1 && NY == 1) {
+                        const int j = at(0, 0, jz, jt);
+                        uint32_t n = dpp<kQuadPrev>(l[j]);
+                        n |= dpp<kQuadNext>(l[j]);
+                        n |= dpp<kRowPrev4>(l[j]);
+                        n |= dpp<kRowNext4>(l[j]);
+                        l[j] |= n & a[j];
+                    } else {
+#pragma unroll
+                        for (int jy = 0; jy < NY; ++jy) {
+                            const int b = at(0, jy, jz, jt);
+                            l[b] |= dpp<kQuadPrev>(l[b + NX - 1]) & a[b] & first;
+#pragma unroll
+                            for (int k = 1; k < NX; ++k) l[b + k] |= l[b + k - 1] & a[b + k];
+                            l[b + NX - 1] |= dpp<kQuadNext>(l[b]) & a[b + NX - 1] & last;
+#pragma unroll
+                            for (int k = NX - 2; k >= 0; --k) l[b + k] |= l[b + k + 1] & a[b + k];
+                        }
+#pragma unroll
+                        for (int jx = 0; jx < NX; ++jx) {
+                            const int b = at(jx, 0, jz, jt);
+                            l[b] |= dpp<kRowPrev4>(l[b + (NY - 1) * NX]) & a[b];
+#pragma unroll
+                            for (int k = 1; k < NY; ++k) l[b + k * NX] |= l[b + (k - 1) * NX] & a[b + k * NX];
+                            l[b + (NY - 1) * NX] |= dpp<kRowNext4>(l[b]) & a[b + (NY - 1) * NX];
+#pragma unroll
+                            for (int k = NY - 2; k >= 0; --k) l[b + k * NX] |= l[b + (k + 1) * NX] & a[b + k * NX];
+                        }
+                    }
+                }
+            uint32_t now = 0;
+#pragma unroll
+            for (int j = 0; j < 32; ++j) now += __popc(l[j]);
+            const bool grew = now != cnt;
+            cnt = now;
+            if (__ballot(grew) == 0) break;
+        }
+        // Other rows write other words, and nothing else writes this one's
+        // nodes meanwhile (seeds and pushes come in other phases): plain stores.
+        uint32_t any = 0, z0 = 0, z1 = 0, t0 = 0, t1 = 0, x0 = 0, x1 = 0, y0 = 0, y1 = 0;
+#pragma unroll
+        for (int j = 0; j < 32; ++j) {
+            const int jx = j % NX, jy = j / NX % NY, jz = j / (NX * NY) % NZ, jt = j / (NX * NY * NZ);
+            const uint32_t g = l[j] ^ l0[j];
+            if (g) fp[(jx + jy * sy + jz * sz + jt * st) * 8] = l[j];
+            any |= g;
+            if (jx == 0) x0 |= g;
+            if (jx == NX - 1) x1 |= g;
+            if (jy == 0) y0 |= g;
+            if (jy == NY - 1) y1 |= g;
+            if (jz == 0) z0 |= g;
+            if (jz == NZ - 1) z1 |= g;
+            if (jt == 0) t0 |= g;
+            if (jt == NT - 1) t1 |= g;
+        }
+        uint32_t f = (xl == 0 && x0 ? 1u : 0u) | (xl == 3 && x1 ? 2u : 0u) | (yl == 0 && y0 ? 4u : 0u) |
+                     (yl == 3 && y1 ? 8u : 0u) | (z0 ? 16u : 0u) | (z1 ? 32u : 0u) | (t0 ? 64u : 0u) |
+                     (t1 ? 128u : 0u) | (any ? 256u : 0u);
+        f |= dpp<kRowRor8>(f);
+        f |= dpp<kRowRor4>(f);
+        f |= dpp<kRowRor2>(f);
+        f |= dpp<kRowRor1>(f);
+        if (li < 8) bschedule_face(d, tile, bx, by, bz, bt, li, f, par ^ 1);
+        else if (li == 8 && f) d.chg[par * d.NTB + tile] = 1;
+    }
+}
 
 // Sweep one tile (block of 512 threads, one voxel-step each) to a local fixed
 // point: Jacobi steps through LDS over the 8 in-tile neighbours, the out-of-
-// tile neighbours entering as fixed halos.  Tiles of 4 x 4 x 4 x 8 take a
-// faster route: a wave holds one 4 x 4 x 4 cube at one t (a row of 16 lanes
-// is one z-plane), so x and y neighbours are DPP row moves and z neighbours
-// lane permutes; each wave runs its cube to a fixed point with the t
-// neighbours held fixed, and only the t neighbours go through LDS, once per
-// block-wide pass.
-template <bool kCube>
+// tile neighbours entering as fixed halos.  For tiles too thin for the rows above.
 __device__ void bsweep_tile(const DevB& d, uint32_t tile, int par, uint32_t* s_lab,
                             uint32_t* s_flags, const uint32_t* s_ftab) {
     int bx, by, bz, bt;
@@ -358,21 +597,17 @@ __device__ void bsweep_tile(const DevB& d, uint32_t tile, int par, uint32_t* s_l
         s_flags[1] = 0;
         s_flags[2] = 0;
     }
-    // a: the admissible queries per word; the cube route recomputes them
-    // from the node's ranks where it needs them (fewer registers, more
-    // blocks per CU)
-    uint32_t a[8], l[8], h[8];
-    uint32_t rv = 0;  // ranks 0: no query admits the node
+    uint32_t a[8], l[8], h[8];  // a: the admissible queries per word
     const uint64_t v = in ? vindex(d, x, y, z, t) : 0;
     if (in) {
-        rv = d.vrank[v];
+        const uint32_t rv = d.vrank[v];
         const uint4* lp = reinterpret_cast<const uint4*>(d.fplanes + v * 8);
         const uint4 l01 = lp[0], l23 = lp[1];
         l[0] = l01.x; l[1] = l01.y; l[2] = l01.z; l[3] = l01.w;
         l[4] = l23.x; l[5] = l23.y; l[6] = l23.z; l[7] = l23.w;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            a[k] = kCube ? 0u : rank_word(s_ftab, rv, k);
+            a[k] = rank_word(s_ftab, rv, k);
             h[k] = 0;
         }
         // halos: neighbours outside the tile (inside the grid), each load
@@ -413,7 +648,7 @@ __device__ void bsweep_tile(const DevB& d, uint32_t tile, int par, uint32_t* s_l
         uint32_t room = 0, src = 0;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            room |= ((kCube ? rank_word(s_ftab, rv, k) : a[k]) & ~l[k]) ? 1u << k : 0u;
+            room |= (a[k] & ~l[k]) ? 1u << k : 0u;
             src |= (l[k] | h[k]) ? 1u << k : 0u;
         }
         __syncthreads();  // the flags were cleared
@@ -447,55 +682,7 @@ __device__ void bsweep_tile(const DevB& d, uint32_t tile, int par, uint32_t* s_l
             s_lab[(k) * 512 + tid] = sv;                                    \
         }                                                                   \
     }
-    // The cube route: word k's in-wave fixed point with its t neighbours'
-    // words (read from LDS) and the halos held fixed.  A lane gains only
-    // bits admissible for it; labels only grow, so the loop ends.
-#define MF4D_CUBE_WORD(k)                                                       \
-    if ((need >> (k)) & 1u) {                                                  \
-        uint32_t fx = h[k];                                                    \
-        if (nt0 >= 0) fx |= s_lab[(k) * 512 + nt0];                            \
-        if (nt1 >= 0) fx |= s_lab[(k) * 512 + nt1];                            \
-        const uint32_t ak = rank_word(s_ftab, rv, k);                          \
-        uint32_t cur = l[k];                                                   \
-        while (true) {                                                         \
-            const uint32_t xm = dpp_row<kDppRowShr1>(cur);                     \
-            const uint32_t xp = dpp_row<kDppRowShl1>(cur);                     \
-            const uint32_t ym = dpp_row<kDppRowShr4>(cur);                     \
-            const uint32_t yp = dpp_row<kDppRowShl4>(cur);                     \
-            const uint32_t zm = (uint32_t)__shfl((int)cur, (lane - 16) & 63);   \
-            const uint32_t zp = (uint32_t)__shfl((int)cur, (lane + 16) & 63);   \
-            uint32_t nb = fx;                                                  \
-            if (xl > 0) nb |= xm;                                              \
-            if (xl < 3) nb |= xp;                                              \
-            if (yl > 0) nb |= ym;                                              \
-            if (yl < 3) nb |= yp;                                              \
-            if (zl > 0) nb |= zm;                                              \
-            if (zl < 3) nb |= zp;                                              \
-            const uint32_t nv = cur | (nb & ak);                               \
-            const bool grew = nv != cur;                                       \
-            cur = nv;                                                          \
-            if (__ballot(grew) == 0) break;                                    \
-        }                                                                      \
-        if (cur != l[k]) {                                                     \
-            diff = 1u;                                                         \
-            grown = 1u;                                                        \
-            l[k] = cur;                                                        \
-        }                                                                      \
-    }
-    if (kCube && need) {
-        const int lane = tid & 63;
-        while (true) {
-            MF4D_STORE_WORD(0) MF4D_STORE_WORD(1) MF4D_STORE_WORD(2) MF4D_STORE_WORD(3)
-            MF4D_STORE_WORD(4) MF4D_STORE_WORD(5) MF4D_STORE_WORD(6) MF4D_STORE_WORD(7)
-            __syncthreads();
-            uint32_t diff = 0;
-            MF4D_CUBE_WORD(0) MF4D_CUBE_WORD(1) MF4D_CUBE_WORD(2) MF4D_CUBE_WORD(3)
-            MF4D_CUBE_WORD(4) MF4D_CUBE_WORD(5) MF4D_CUBE_WORD(6) MF4D_CUBE_WORD(7)
-            // every wave has read its t neighbours before the next pass
-            // stores; a pass with no change anywhere is the fixed point
-            if (!__syncthreads_or(diff != 0)) break;
-        }
-    } else if (need) {
+    if (need) {
         MF4D_STORE_WORD(0) MF4D_STORE_WORD(1) MF4D_STORE_WORD(2) MF4D_STORE_WORD(3)
         MF4D_STORE_WORD(4) MF4D_STORE_WORD(5) MF4D_STORE_WORD(6) MF4D_STORE_WORD(7)
         __syncthreads();
@@ -506,7 +693,6 @@ __device__ void bsweep_tile(const DevB& d, uint32_t tile, int par, uint32_t* s_l
             if (!__syncthreads_or(diff != 0)) break;
         }
     }
-#undef MF4D_CUBE_WORD
 #undef MF4D_STORE_WORD
 #undef MF4D_STEP_WORD
     uint32_t any = 0;
@@ -537,72 +723,24 @@ __device__ void bsweep_tile(const DevB& d, uint32_t tile, int par, uint32_t* s_l
     // lanes 0..7 of the first wave flag the tiles across the eight faces
     // that gained bits
     const uint32_t f = s_flags[0];
-    if (f && tid < 8) {
-        if (tid == 0) d.chg[par * d.NTB + tile] = 1;
-        const uint32_t sy = d.NXb, sz = d.NXb * d.NYb, st = sz * d.NZb;
-        uint32_t nb[1] = {~0u};
-        if ((f >> tid) & 1u) {
-            switch (tid) {
-                case 0: if (bx > 0) nb[0] = tile - 1; break;
-                case 1: if (bx + 1 < d.NXb) nb[0] = tile + 1; break;
-                case 2: if (by > 0) nb[0] = tile - sy; break;
-                case 3: if (by + 1 < d.NYb) nb[0] = tile + sy; break;
-                case 4: if (bz > 0) nb[0] = tile - sz; break;
-                case 5: if (bz + 1 < d.NZb) nb[0] = tile + sz; break;
-                case 6: if (bt > 0) nb[0] = tile - st; break;
-                default: if (bt + 1 < d.NTb) nb[0] = tile + st; break;
-            }
-        }
-        bschedule_n<1>(d, nb, par ^ 1);
-    }
+    if (f && tid == 8) d.chg[par * d.NTB + tile] = 1;
+    if (f && tid < 8) bschedule_face(d, tile, bx, by, bz, bt, tid, f, par ^ 1);
     __syncthreads();
 }
 
-// A round's sweep.  Rounds are queued ahead of the host: a round whose work
-// list is empty does nothing (its sweep records that for the round's pull and
-// close), and BC_ROUNDS counts the rounds that had work.
-// kCube: tiles of 4 x 4 x 4 x 8 (the cube route of bsweep_tile).
-template <bool kCube>
 __global__ __launch_bounds__(512) void kb_sweep(DevB d, int par) {
     __shared__ uint32_t s_lab[8 * 512];
     __shared__ uint32_t s_flags[4];
     __shared__ uint32_t s_ftab[kLdsTab];
-    __shared__ uint32_t s_pref[kBSubs + 1];  // sub-list prefix sums
-    if (threadIdx.x < kBSubs) {
-        // the first wave scans the sub-list lengths
-        const uint32_t c = d.wcnt[((uint32_t)par * kBSubs + threadIdx.x) * kBCntStride];
-        uint32_t x = c;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t y = __shfl_up(x, o);
-            if ((int)threadIdx.x >= o) x += y;
-        }
-        s_pref[threadIdx.x + 1] = x;
-        if (threadIdx.x == 0) s_pref[0] = 0;
-    }
-    __syncthreads();
+    __shared__ uint32_t s_pref[kBSubs + 1];
+    stage_work(d, par, s_pref);
     const uint32_t nwork = s_pref[kBSubs];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        d.counters[BC_NDIRTYP] = 0;
-        d.counters[BC_RACT] = nwork ? 1u : 0u;
-        if (nwork) d.counters[BC_ROUNDS] += 1u;
-    }
+    begin_round(d, nwork);
     if (blockIdx.x >= nwork) return;  // block-uniform
     stage_tables(d, 0, s_ftab);
     __syncthreads();
-    uint32_t visits = 0;
-    for (uint32_t w = blockIdx.x; w < nwork; w += gridDim.x) {
-        // the sub-list holding flat item w: the last j with s_pref[j] <= w
-        int lo = 0, hi = kBSubs;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (s_pref[mid] <= w) lo = mid; else hi = mid;
-        }
-        const uint32_t tile = d.work[((size_t)par * kBSubs + lo) * d.WCAPB + (w - s_pref[lo])];
-        bsweep_tile<kCube>(d, tile, par, s_lab, s_flags, s_ftab);
-        ++visits;
-    }
-    if (threadIdx.x == 0 && visits) atomicAdd(&d.stat64[S_TILE_VISITS], (unsigned long long)visits);
+    for (uint32_t w = blockIdx.x; w < nwork; w += gridDim.x)
+        bsweep_tile(d, work_item(d, par, s_pref, w).x, par, s_lab, s_flags, s_ftab);
 }
 
 // Pull: a coupled step gains the queries for which its voxel is a member and
@@ -854,7 +992,7 @@ __global__ __launch_bounds__(256) void kb_close(DevB d, int par) {
     }
 }
 
-// The work list of the round of parity `par` from the tiles flagged for it
+// The work list (tile, flags) of the round of parity `par` from the tiles flagged for it
 // (the flags cleared for that parity's next use): a flagged tile joins if it
 // holds a node admissible for some query.  Appends go to sub-list (tile mod
 // kBSubs): 64 counters on separate lines.  force: also after a round without
@@ -864,12 +1002,13 @@ __global__ __launch_bounds__(256) void kb_compact(DevB d, int par, int force) {
     const uint32_t stride = gridDim.x * blockDim.x;
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < d.NTB; i += stride) {
         uint32_t* f = &d.dirty[(size_t)par * d.NTB + i];
-        if (*f) {
+        const uint32_t bits = *f;
+        if (bits) {
             *f = 0u;
             if (d.active[i]) {
                 const uint32_t j = (uint32_t)par * kBSubs + (i & (kBSubs - 1));
                 const uint32_t k = atomicAdd(&d.wcnt[j * kBCntStride], 1u);
-                d.work[(size_t)j * d.WCAPB + k] = i;
+                d.work[(size_t)j * d.WCAPB + k] = make_uint2(i, bits);
             }
         }
     }
@@ -939,10 +1078,21 @@ void launch_b_prepare(const DevB& d, const int32_t* seeds, int64_t S, hipStream_
 
 void launch_b_round(const DevB& d, uint32_t round, hipStream_t s) {
     const int par = round & 1;
-    if (d.lx == 2 && d.ly == 2 && d.lz == 2)
-        hipLaunchKernelGGL(kb_sweep<true>, dim3(grid_for(d.NTB, 1, 2048)), dim3(512), 0, s, d, par);
-    else
-        hipLaunchKernelGGL(kb_sweep<false>, dim3(grid_for(d.NTB, 1, 2048)), dim3(512), 0, s, d, par);
+    // the shapes of at least 4 x 4 nodes along x and y that the search over tile
+    // shapes tries; any other goes through LDS
+    const unsigned rows = grid_for(((uint64_t)d.NTB * ((d.Q + 31) / 32) + 3) / 4, 4, 1024);
+    const int shape = d.lx * 1000 + d.ly * 100 + d.lz * 10 + d.lt;
+    switch (shape) {
+        case 2223: hipLaunchKernelGGL((kb_sweep_rows<2, 2, 2, 3>), dim3(rows), dim3(256), 0, s, d, par); break;
+        case 3222: hipLaunchKernelGGL((kb_sweep_rows<3, 2, 2, 2>), dim3(rows), dim3(256), 0, s, d, par); break;
+        case 3330: hipLaunchKernelGGL((kb_sweep_rows<3, 3, 3, 0>), dim3(rows), dim3(256), 0, s, d, par); break;
+        case 3321: hipLaunchKernelGGL((kb_sweep_rows<3, 3, 2, 1>), dim3(rows), dim3(256), 0, s, d, par); break;
+        case 4221: hipLaunchKernelGGL((kb_sweep_rows<4, 2, 2, 1>), dim3(rows), dim3(256), 0, s, d, par); break;
+        case 4320: hipLaunchKernelGGL((kb_sweep_rows<4, 3, 2, 0>), dim3(rows), dim3(256), 0, s, d, par); break;
+        case 5220: hipLaunchKernelGGL((kb_sweep_rows<5, 2, 2, 0>), dim3(rows), dim3(256), 0, s, d, par); break;
+        case 2322: hipLaunchKernelGGL((kb_sweep_rows<2, 3, 2, 2>), dim3(rows), dim3(256), 0, s, d, par); break;
+        default: hipLaunchKernelGGL(kb_sweep, dim3(grid_for(d.NTB, 1, 2048)), dim3(512), 0, s, d, par); break;
+    }
     if (d.P > 0) {
         hipLaunchKernelGGL(kb_pull, dim3(grid_for((uint64_t)d.P * d.Tpad, 256, 2048)), dim3(256), 0,
                            s, d, par);
