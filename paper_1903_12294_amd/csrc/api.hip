@@ -255,9 +255,9 @@ struct mf4d_ctx {
     int blog[4] = {3, 2, 2, 2};  // log2 of the batched tile extents (x, y, z, t)
     uint8_t* b_active = nullptr;
     uint32_t* b_vrank = nullptr;  // [V] ranks of the voxel-steps under the query bands
-    uint32_t* b_prank = nullptr;  // [P][Tpad] ranks of the particle-steps
+    uint2* b_prv = nullptr;       // [P][Tpad] ranks and coupled voxel of the particle-steps
     uint32_t* b_dirty = nullptr;
-    uint8_t* b_chg = nullptr;
+    uint32_t* b_tile = nullptr;   // 2 x NTB: coupled steps per tile, where they start
     uint2* b_work = nullptr;
     uint32_t* b_wcnt = nullptr;
     uint32_t b_wcap = 0;
@@ -361,7 +361,7 @@ void free_field_extras(mf4d_ctx* c) {
     dev_free(c->b_active);
     dev_free(c->b_vrank);
     dev_free(c->b_dirty);
-    dev_free(c->b_chg);
+    dev_free(c->b_tile);
     dev_free(c->b_work);
     dev_free(c->b_wcnt);
     dev_free(c->b_fown);
@@ -394,7 +394,7 @@ void free_field(mf4d_ctx* c) {
 void drop_particles(mf4d_ctx* c) {
     quiesce_side(c);
     dev_free(c->jlp);
-    dev_free(c->b_prank);
+    dev_free(c->b_prv);
     dev_free(c->porder);
     dev_free(c->spos);
     dev_free(c->sattr);
@@ -1958,7 +1958,7 @@ int mf4d_set_batched_tile(mf4d_ctx* c, int bx, int by, int bz, int bt) {
     for (int i = 0; i < 4; ++i) c->blog[i] = lg[i];
     dev_free(c->b_active);
     dev_free(c->b_dirty);
-    dev_free(c->b_chg);
+    dev_free(c->b_tile);
     dev_free(c->b_work);
     c->NTB = 0;
     return MF4D_OK;
@@ -2018,15 +2018,15 @@ int mf4d_grow_batched(mf4d_ctx* c, uint32_t* fplanes, size_t fwords, uint32_t* p
         const uint64_t ntb = (uint64_t)NXb * NYb * NZb * NTb;
         int rc = dev_alloc(&c->b_active, (size_t)ntb + 8);
         if (!rc) rc = dev_alloc(&c->b_dirty, 2 * (size_t)ntb);
-        if (!rc) rc = dev_alloc(&c->b_chg, 2 * (size_t)ntb + 8);
+        if (!rc) rc = dev_alloc(&c->b_tile, 2 * (size_t)ntb);
         const uint32_t wcap = (uint32_t)((ntb + kBSubs - 1) / kBSubs);
         if (!rc) rc = dev_alloc(&c->b_work, 2 * (size_t)kBSubs * wcap);
-        if (!rc && !c->b_wcnt) rc = dev_alloc(&c->b_wcnt, 2 * (size_t)kBSubs * kBCntStride);
+        if (!rc && !c->b_wcnt) rc = dev_alloc(&c->b_wcnt, 3 * (size_t)kBSubs * kBCntStride);
         if (!rc && !c->b_counters) rc = dev_alloc(&c->b_counters, BC_NCOUNTERS);
         if (rc) {
             dev_free(c->b_active);
             dev_free(c->b_dirty);
-            dev_free(c->b_chg);
+            dev_free(c->b_tile);
             dev_free(c->b_work);
             dev_free(c->b_wcnt);
             return rc;
@@ -2039,8 +2039,8 @@ int mf4d_grow_batched(mf4d_ctx* c, uint32_t* fplanes, size_t fwords, uint32_t* p
         int rc = dev_alloc(&c->b_vrank, (size_t)V);
         if (rc) return rc;
     }
-    if (P > 0 && !c->b_prank) {
-        int rc = dev_alloc(&c->b_prank, (size_t)P * c->pg.Tpad);
+    if (P > 0 && !c->b_prv) {
+        int rc = dev_alloc(&c->b_prv, (size_t)P * c->pg.Tpad);
         if (rc) return rc;
     }
     uint32_t* fo = fplanes;
@@ -2065,20 +2065,23 @@ int mf4d_grow_batched(mf4d_ctx* c, uint32_t* fplanes, size_t fwords, uint32_t* p
     d.field = c->field;
     d.attr_t = c->attr_t;
     d.vrank = c->b_vrank;
-    d.prank = P > 0 ? c->b_prank : nullptr;
+    d.prv = P > 0 ? c->b_prv : nullptr;
     d.bins = c->bins;
     d.fplanes = fo;
     d.pplanes = P > 0 ? po : nullptr;
     d.tab = c->btab;
     d.active = c->b_active;
     d.dirty = c->b_dirty;
-    d.chg = c->b_chg;
+    d.tcnt = c->b_tile;
+    d.tbase = c->b_tile + c->NTB;
     d.work = c->b_work;
     d.wcnt = c->b_wcnt;
+    d.dcnt = c->b_wcnt + 2 * kBSubs * kBCntStride;
     d.WCAPB = c->b_wcap;
     d.clist = c->clist;
     d.pdirty = c->pdirty;
     d.dlist = c->dlist;
+    d.DCAPB = (uint32_t)((P + kBSubs - 1) / kBSubs);
     d.counters = c->b_counters;
     d.stat64 = c->stat64;
     d.forward_only = c->forward_only;

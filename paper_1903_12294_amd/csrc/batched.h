@@ -8,8 +8,7 @@ namespace mf4d {
 enum BCounter : int {
     BC_NWORK0 = 0,
     BC_NWORK1 = 1,
-    BC_NDIRTYP = 2,
-    BC_NLIST = 3,
+    BC_NLIST = 3,  // coupled steps given a place in the list
     BC_DROPPED = 4,
     BC_RACT = 5,    // the current round has work (set by its sweep)
     BC_ROUNDS = 6,  // rounds that had work (since last cleared by the host)
@@ -38,31 +37,33 @@ struct DevB {
     const float* field;      // fp32 [T][Z][Y][X]
     const float* attr_t;     // fp32 [P][Tpad]
     uint32_t* vrank;         // [V] ranks of each voxel-step: rank_lo | rank_hi << 16
-    uint32_t* prank;         // [P][Tpad] ranks of each particle-step, likewise
+    uint2* prv;              // [P][Tpad] ranks of each particle-step, likewise; its voxel if coupled, else kNoVoxel
     const uint32_t* bins;    // [P][Tpad] tile-layout bit position or kNoVoxel
     uint32_t* fplanes;       // [V][8] labels = output
     uint32_t* pplanes;       // [T][P][8] labels = output
     const float* tab;        // kTabWords
     uint8_t* active;         // NTB (+8)
     uint32_t* dirty;         // 2 x NTB: why a tile is flagged (faces, own members)
-    uint8_t* chg;            // 2 x NTB (+8)
     uint2* work;             // [2][kBSubs][WCAPB] work sub-lists of round parity 0 / 1: tile, flags
     uint32_t* wcnt;          // [2][kBSubs] sub-list lengths, kBCntStride words apart
     uint32_t WCAPB;          // capacity of one sub-list = ceil(NTB / kBSubs)
-    uint2* clist;            // coupled steps (flat step index, canonical voxel index)
+    uint2* clist;            // coupled steps (flat step index, canonical voxel index) by tile
+    uint32_t* tcnt;          // NTB: coupled steps of a tile
+    uint32_t* tbase;         // NTB: where they start in clist
     uint32_t* pdirty;        // P bits
-    uint32_t* dlist;         // P
+    uint32_t* dlist;         // P: particles that gained, kBSubs sub-lists of DCAPB
+    uint32_t* dcnt;          // [kBSubs] their lengths, kBCntStride words apart
+    uint32_t DCAPB;          // ceil(P / kBSubs): particle p goes to sub-list p / DCAPB
     uint32_t* counters;      // BCounter
     unsigned long long* stat64;
     int forward_only;        // 1: membership runs along a trajectory from t to t + 1 only
 };
 
 void launch_b_prepare(const DevB& d, const int32_t* seeds, int64_t S, hipStream_t s);
-// One round (sweep, pull, close); a round whose work list is empty does
+// One round (sweep, close, next list); a round whose work list is empty does
 // nothing, so rounds are queued ahead of the host.
 void launch_b_round(const DevB& d, uint32_t round, hipStream_t s);
 // Total length of the work list of parity par into counters[BC_NWORK0 + par].
 void launch_b_work_total(const DevB& d, int par, hipStream_t s);
-void launch_b_count(const DevB& d, hipStream_t s);
 
 }  // namespace mf4d

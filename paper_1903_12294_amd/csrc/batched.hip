@@ -10,14 +10,17 @@
 // The two ranks of every voxel-step and particle-step (rank_lo | rank_hi <<
 // 16) are computed once per grow, when its admissibility is first read, and
 // kept: sweeps, pulls and closes rebuild a node's 256-bit mask from them with
-// two rows of the prefix tables (staged in LDS), no search.
+// two rows of the prefix tables (staged in LDS), no search.  A particle-step
+// that can exchange members with its voxel (some query admits both) is coupled:
+// its voxel is kept beside its ranks, and the coupled steps are listed by tile.
 //
 // Field labels are grown in place in the caller's [V][8] output (canonical
 // voxel order); particle labels in the caller's [T][P][8] output.  Work is
 // organised in 4D tiles of 512 voxel-steps (a power-of-two extent per axis,
-// chosen per context, e.g. 8 x 4 x 4 x 4), one thread per voxel-step, with
-// the round protocol of the single-query grower: sweep, pull, close/push,
-// double-buffered work lists by round parity.  A tile is flagged with the faces
+// chosen per context, e.g. 8 x 4 x 4 x 4).  A round sweeps the tiles of its
+// work list, each handing what it gained to its own coupled steps; closes the
+// trajectories of the particles that gained, pushing into their voxels; and
+// lists the tiles flagged meanwhile (double-buffered by round parity).  A tile is flagged with the faces
 // across which its neighbours gained members: its visit reads only those.
 #include "mf4d_internal.h"
 #include "batched.h"
@@ -139,11 +142,10 @@ __device__ __forceinline__ void bschedule(const DevB& d, uint32_t tile, int par,
     atomicOr(&d.dirty[par * d.NTB + tile], bits);
 }
 
-// A voxel that gained members outside a sweep: its tile (flagged for the pull
-// too) and the tiles whose face it touches.
+// A voxel that gained members outside a sweep: its tile and the tiles whose face
+// it touches.
 __device__ __forceinline__ void bmark_voxel(const DevB& d, int x, int y, int z, int t, int par) {
     const uint32_t tile = btile_of(d, x, y, z, t);
-    d.chg[par * d.NTB + tile] = 1;
     bschedule(d, tile, par, kOwn);
     const uint32_t sy = d.NXb, sz = d.NXb * d.NYb, st = sz * d.NZb;
     const int mx = (1 << d.lx) - 1, my = (1 << d.ly) - 1, mz = (1 << d.lz) - 1, mt = (1 << d.lt) - 1;
@@ -157,17 +159,14 @@ __device__ __forceinline__ void bmark_voxel(const DevB& d, int x, int y, int z, 
     if ((t & mt) == mt && t + 1 < d.T) bschedule(d, tile + st, par, 1u << 6);
 }
 
-// N voxels (bit positions, kNoVoxel: none) marked together.
-template <int N>
-__device__ __forceinline__ void bmark_voxels_n(const DevB& d, const uint32_t (&b)[N], int par) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        if (b[i] != kNoVoxel) {
-            int x, y, z, t;
-            bit_to_xyzt(d.g, b[i], x, y, z, t);
-            bmark_voxel(d, x, y, z, t, par);
-        }
-    }
+// Coordinates of a canonical voxel index.
+__device__ __forceinline__ void voxel_coords(const DevB& d, uint32_t v, int& x, int& y, int& z, int& t) {
+    x = (int)(v % (uint32_t)d.X);
+    v /= (uint32_t)d.X;
+    y = (int)(v % (uint32_t)d.Y);
+    v /= (uint32_t)d.Y;
+    z = (int)(v % (uint32_t)d.Z);
+    t = (int)(v / (uint32_t)d.Z);
 }
 
 // Lane i of eight (a tile's faces in order) flags the neighbour across face i
@@ -183,37 +182,6 @@ __device__ __forceinline__ void bschedule_face(const DevB& d, uint32_t tile, int
     if ((i & 1) ? b + 1 < n : b > 0) bschedule(d, (i & 1) ? tile + st_a : tile - st_a, par, 1u << (i ^ 1));
 }
 
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s_tmp,
-                                                        uint32_t& total) {
-    const int lane = lane_id(), wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    uint32_t x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
-    if (lane == 63) s_tmp[wave] = x;
-    __syncthreads();
-    uint32_t wbase = 0;
-    total = 0;
-    for (int w = 0; w < nw; ++w) {
-        if (w < wave) wbase += s_tmp[w];
-        total += s_tmp[w];
-    }
-    __syncthreads();
-    return wbase + x - v;
-}
-
-__device__ __forceinline__ uint32_t block_append(uint32_t n, uint32_t* counter, uint32_t* s_tmp) {
-    uint32_t total;
-    const uint32_t ex = block_exclusive_scan(n, s_tmp, total);
-    if (threadIdx.x == 0) s_tmp[16] = total ? atomicAdd(counter, total) : 0u;
-    __syncthreads();
-    const uint32_t base = s_tmp[16];
-    __syncthreads();
-    return base + ex;
-}
-
 // ---------------------------------------------------------------------------
 
 // The sorted bounds of one sample type staged in LDS (lo ascending, then hi
@@ -222,25 +190,31 @@ __device__ __forceinline__ void stage_bounds(const DevB& d, int type, float* s_b
     for (int i = threadIdx.x; i < 512; i += blockDim.x) s_b[i] = d.tab[512 * type + i];
 }
 
-// Clear both output planes, record every voxel-step's ranks, mark tiles that
-// hold a node admissible for some query.  One thread per voxel-step
-// (canonical order), a grid-stride loop.
+// Clear the field planes, record every voxel-step's ranks, mark tiles that hold
+// a node admissible for some query.  A block takes 1,024 voxel-steps at a time,
+// four a thread, whose rank searches interleave, and stores their 32 KB of planes
+// in order, 16 bytes a lane.  Bound by those stores.
+// 128^3 x 32: 612 us; 760 with a thread storing its own nodes' 32 bytes.
 __global__ __launch_bounds__(256) void kb_admit_field(DevB d) {
     __shared__ float s_b[512];
     stage_bounds(d, 0, s_b);
     __syncthreads();
     const uint32_t* ftab = reinterpret_cast<const uint32_t*>(d.tab + 1024);
     const uint64_t V = (uint64_t)d.X * d.Y * d.Z * d.T;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    // four voxel-steps per thread and pass (stride apart, so each load and
-    // store instruction stays coalesced): their rank searches interleave
-    constexpr int kU = 4;
-    for (uint64_t v0 = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; v0 < V; v0 += kU * stride) {
+    constexpr int kU = 4, kStep = kU * 256;
+    for (uint64_t b0 = (uint64_t)blockIdx.x * kStep; b0 < V; b0 += (uint64_t)gridDim.x * kStep) {
         float f[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            const uint64_t v = v0 + u * stride;
+            const uint64_t v = b0 + u * 256 + threadIdx.x;
             f[u] = v < V ? __builtin_nontemporal_load(d.field + v) : 0.0f;
+        }
+        const uint64_t n4 = (V - b0 < (uint64_t)kStep ? V - b0 : (uint64_t)kStep) * 2;  // 16-byte pieces
+        uint4* o = reinterpret_cast<uint4*>(d.fplanes + b0 * 8);
+#pragma unroll
+        for (int u = 0; u < 2 * kU; ++u) {
+            const uint32_t i = u * 256 + threadIdx.x;
+            if (i < n4) o[i] = make_uint4(0, 0, 0, 0);
         }
         uint32_t r[kU];
 #pragma unroll
@@ -248,65 +222,97 @@ __global__ __launch_bounds__(256) void kb_admit_field(DevB d) {
             r[u] = (uint32_t)rank_le(s_b, d.Q, f[u]) | ((uint32_t)rank_ge(s_b + 256, d.Q, f[u]) << 16);
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            const uint64_t v = v0 + u * stride;
+            const uint64_t v = b0 + u * 256 + threadIdx.x;
             if (v >= V) continue;
             d.vrank[v] = r[u];
-            uint4* o = reinterpret_cast<uint4*>(d.fplanes + v * 8);
-            o[0] = make_uint4(0, 0, 0, 0);
-            o[1] = make_uint4(0, 0, 0, 0);
             uint32_t any = 0;
             if ((r[u] & 0xFFFFu) && (r[u] >> 16)) {
 #pragma unroll
                 for (int k = 0; k < 8; ++k) any |= rank_word(ftab, r[u], k);
             }
             if (any) {
-                const int x = (int)(v % d.X);
-                const uint64_t q = v / d.X;
-                const int y = (int)(q % d.Y);
-                const uint64_t q2 = q / d.Y;
-                const int z = (int)(q2 % d.Z), t = (int)(q2 / d.Z);
+                int x, y, z, t;
+                voxel_coords(d, (uint32_t)v, x, y, z, t);
                 d.active[btile_of(d, x, y, z, t)] = 1;
             }
         }
     }
 }
 
-// Clear the particle planes and list the coupled steps: admissible for some
-// query and lying in a voxel, as (flat step index, canonical voxel index).
+// Clear the particle planes, record every particle-step's ranks and, where it is
+// coupled (it lies in a voxel and some query admits both), its voxel, counted for
+// the voxel's tile.  Four steps a thread, whose loads and searches interleave.
+// 262,144 x 32: 105 us, and 21 to list the coupled steps; 229 with a list appended
+// to by whole blocks.
 __global__ __launch_bounds__(256) void kb_admit_particles(DevB d) {
-    __shared__ uint32_t s_tmp[20];
     __shared__ float s_b[512];
     stage_bounds(d, 1, s_b);
     __syncthreads();
-    const uint32_t* ptab = reinterpret_cast<const uint32_t*>(d.tab + 1024) + 2 * 257 * 8;
+    const uint32_t* ftab = reinterpret_cast<const uint32_t*>(d.tab + 1024);
+    const uint32_t* ptab = ftab + 2 * 257 * 8;
     const uint64_t n = (uint64_t)d.P * d.Tpad;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     const uint64_t np = (uint64_t)d.Tp * d.P * 2;  // uint4 per particle-step: 2
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < np; i += stride)
-        reinterpret_cast<uint4*>(d.pplanes)[i] = make_uint4(0, 0, 0, 0);
-    for (uint64_t b0 = blockIdx.x * (uint64_t)blockDim.x; b0 < n; b0 += stride) {
-        const uint64_t e = b0 + threadIdx.x;
-        bool c = false;
-        uint32_t vox = 0;
-        if (e < n) {
-            const float a = d.attr_t[e];
-            const uint32_t r = (uint32_t)rank_le(s_b, d.Q, a) | ((uint32_t)rank_ge(s_b + 256, d.Q, a) << 16);
-            d.prank[e] = r;
-            uint32_t any = 0;
-            if ((r & 0xFFFFu) && (r >> 16)) {
+    const uint64_t tid = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
+    for (uint64_t i = tid; i < np; i += stride) reinterpret_cast<uint4*>(d.pplanes)[i] = make_uint4(0, 0, 0, 0);
+    constexpr int kU = 4;
+    for (uint64_t e0 = tid; e0 < n; e0 += kU * stride) {
+        float a[kU];
+        uint32_t b[kU], r[kU], vr[kU], vox[kU];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) any |= rank_word(ptab, r, k);
-            }
-            const uint32_t b = d.bins[e];
-            if (any && b != kNoVoxel) {
-                int x, y, z, t;
-                bit_to_xyzt(d.g, b, x, y, z, t);
-                vox = (uint32_t)vindex(d, x, y, z, t);
-                c = true;
+        for (int u = 0; u < kU; ++u) {
+            const uint64_t e = e0 + u * stride;
+            a[u] = 0.0f;
+            b[u] = kNoVoxel;
+            if (e < n) {
+                a[u] = d.attr_t[e];
+                b[u] = d.bins[e];
             }
         }
-        const uint32_t k = block_append(c ? 1u : 0u, &d.counters[BC_NLIST], s_tmp);
-        if (c) d.clist[k] = make_uint2((uint32_t)e, vox);
+#pragma unroll
+        for (int u = 0; u < kU; ++u)
+            r[u] = (uint32_t)rank_le(s_b, d.Q, a[u]) | ((uint32_t)rank_ge(s_b + 256, d.Q, a[u]) << 16);
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            vox[u] = kNoVoxel;
+            vr[u] = 0;
+            if (b[u] != kNoVoxel && (r[u] & 0xFFFFu) && (r[u] >> 16)) {
+                int x, y, z, t;
+                bit_to_xyzt(d.g, b[u], x, y, z, t);
+                vox[u] = (uint32_t)vindex(d, x, y, z, t);
+                vr[u] = d.vrank[vox[u]];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const uint64_t e = e0 + u * stride;
+            if (e >= n) continue;
+            uint32_t any = 0;
+            if ((vr[u] & 0xFFFFu) && (vr[u] >> 16)) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) any |= rank_word(ptab, r[u], k) & rank_word(ftab, vr[u], k);
+            }
+            if (any) {
+                int x, y, z, t;
+                voxel_coords(d, vox[u], x, y, z, t);
+                atomicAdd(&d.tcnt[btile_of(d, x, y, z, t)], 1u);
+            }
+            d.prv[e] = make_uint2(r[u], any ? vox[u] : kNoVoxel);
+        }
+    }
+}
+
+// The coupled steps into their tiles' ranges of the list (kb_compact has given
+// every tile the end of its range, which becomes its start here).
+__global__ __launch_bounds__(256) void kb_couple(DevB d) {
+    const uint32_t n = (uint32_t)((uint64_t)d.P * d.Tpad);
+    const uint32_t stride = gridDim.x * blockDim.x;
+    for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
+        const uint32_t vox = d.prv[e].y;
+        if (vox == kNoVoxel) continue;
+        int x, y, z, t;
+        voxel_coords(d, vox, x, y, z, t);
+        d.clist[atomicSub(&d.tbase[btile_of(d, x, y, z, t)], 1u) - 1] = make_uint2(e, vox);
     }
 }
 
@@ -332,14 +338,18 @@ template <int CTRL>
 __device__ __forceinline__ uint32_t dpp(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
 }
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_ones(uint32_t v) {  // all ones from outside the row
+    return (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, CTRL, 0xF, 0xF, false);
+}
 constexpr int kQuadPrev = 0x90, kQuadNext = 0xF9, kRowPrev4 = 0x114, kRowNext4 = 0x104;
 constexpr int kRowRor1 = 0x121, kRowRor2 = 0x122, kRowRor4 = 0x124, kRowRor8 = 0x128;
 
-// The work list of a round seen as one list: its sub-lists' prefix sums.
-__device__ __forceinline__ void stage_work(const DevB& d, int par, uint32_t* s_pref) {
+// A list kept as kBSubs sub-lists seen as one: the sub-lists' prefix sums.
+__device__ __forceinline__ void stage_list(const uint32_t* cnt, uint32_t* s_pref) {
     if (threadIdx.x < kBSubs) {
         // the first wave scans the sub-list lengths
-        const uint32_t c = d.wcnt[((uint32_t)par * kBSubs + threadIdx.x) * kBCntStride];
+        const uint32_t c = cnt[threadIdx.x * kBCntStride];
         uint32_t x = c;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
@@ -351,24 +361,69 @@ __device__ __forceinline__ void stage_work(const DevB& d, int par, uint32_t* s_p
     }
     __syncthreads();
 }
+// The sub-list holding item w: the last j with s_pref[j] <= w.
+__device__ __forceinline__ int sub_list(const uint32_t* s_pref, uint32_t w) {
+    int lo = 0;
+#pragma unroll
+    for (int h = kBSubs / 2; h > 0; h >>= 1)
+        if (s_pref[lo + h] <= w) lo += h;
+    return lo;
+}
+__device__ __forceinline__ const uint32_t* work_counts(const DevB& d, int par) {
+    return d.wcnt + (size_t)par * kBSubs * kBCntStride;
+}
 __device__ __forceinline__ uint2 work_item(const DevB& d, int par, const uint32_t* s_pref, uint32_t w) {
-    // the sub-list holding flat item w: the last j with s_pref[j] <= w
-    int lo = 0, hi = kBSubs;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (s_pref[mid] <= w) lo = mid; else hi = mid;
-    }
-    return d.work[((size_t)par * kBSubs + lo) * d.WCAPB + (w - s_pref[lo])];
+    const int j = sub_list(s_pref, w);
+    return d.work[((size_t)par * kBSubs + j) * d.WCAPB + (w - s_pref[j])];
 }
 // A round's counters: rounds are queued ahead of the host, and a round whose
-// work list is empty does nothing (recorded for its pull and close).
+// work list is empty does nothing (recorded for its close).
 __device__ __forceinline__ void begin_round(const DevB& d, uint32_t nwork) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        d.counters[BC_NDIRTYP] = 0;
         d.counters[BC_RACT] = nwork ? 1u : 0u;
         if (nwork) {
             d.counters[BC_ROUNDS] += 1u;
             d.stat64[S_TILE_VISITS] += nwork;
+        }
+    }
+}
+
+// Word `word` of a swept tile handed to its coupled steps by 16 lanes (lane li),
+// part `part` of `parts` rows that share the word: a step gains the queries for
+// which its voxel is a member and it is admissible.  Nothing else writes the
+// word of these steps meanwhile.  A particle that gained is listed once.
+__device__ __forceinline__ void pull_row(const DevB& d, uint32_t tile, uint32_t word, int li, int part, int parts,
+                                         const uint32_t* s_ptab) {
+    const uint32_t n = d.tcnt[tile], base = d.tbase[tile];
+    constexpr int kU = 4;
+    for (uint32_t i0 = part * 16 + li; i0 < n; i0 += kU * 16 * parts) {
+        uint2 ent[kU];
+        uint32_t p[kU], m[kU], r[kU], lp[kU];
+        uint64_t at[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const uint32_t i = i0 + u * 16 * parts;
+            ent[u] = d.clist[base + (i < n ? i : i0)];
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            p[u] = ent[u].x / (uint32_t)d.Tpad;
+            at[u] = ((uint64_t)(ent[u].x - p[u] * (uint32_t)d.Tpad) * d.P + p[u]) * 8 + word;
+            m[u] = d.fplanes[(uint64_t)ent[u].y * 8 + word];
+            r[u] = d.prv[ent[u].x].x;
+            lp[u] = d.pplanes[at[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const uint32_t nw = m[u] & ~lp[u] & rank_word(s_ptab, r[u], word);
+            if (nw && i0 + u * 16 * parts < n) {
+                d.pplanes[at[u]] = lp[u] | nw;
+                const uint32_t pb = 1u << (p[u] & 31);
+                if (!(atomicOr(&d.pdirty[p[u] >> 5], pb) & pb)) {
+                    const uint32_t j = p[u] / d.DCAPB;
+                    d.dlist[j * d.DCAPB + atomicAdd(&d.dcnt[j * kBCntStride], 1u)] = p[u];
+                }
+            }
         }
     }
 }
@@ -383,21 +438,24 @@ __device__ __forceinline__ void begin_round(const DevB& d, uint32_t nwork) {
 // Few queries fill the rows with tiles instead of words.
 // Bound by the chain of loads (list, ranks, labels and halos) and the issue of
 // the passes.  128^3 x 32, 256 queries, 67,600 visits of 4 x 4 x 4 x 8 tiles:
-// 1,598 us; 3,058 with a block of 512 threads per tile passing all eight words
+// 1,598 us without the coupled steps, 1,838 with them (453 as a pass over all of
+// them); 3,058 with a block of 512 threads per tile passing all eight words
 // through LDS and reading every face.
 template <int LX, int LY, int LZ, int LT>
 __global__ __launch_bounds__(256) void kb_sweep_rows(DevB d, int par) {
     static_assert(LX >= 2 && LY >= 2 && LX + LY + LZ + LT == 9, "512 nodes, 4 x 4 lanes");
     constexpr int NX = 1 << (LX - 2), NY = 1 << (LY - 2), NZ = 1 << LZ, NT = 1 << LT;
     __shared__ uint32_t s_ftab[kLdsTab];
+    __shared__ uint32_t s_ptab[kLdsTab];
     __shared__ uint32_t s_pref[kBSubs + 1];
-    stage_work(d, par, s_pref);
+    stage_list(work_counts(d, par), s_pref);
     const uint32_t nwork = s_pref[kBSubs];
     begin_round(d, nwork);
     const uint32_t nw = (uint32_t)(d.Q + 31) >> 5;
     const uint64_t items = (uint64_t)nwork * nw;
     if (blockIdx.x * 16ull >= items) return;  // block-uniform
     stage_tables(d, 0, s_ftab);
+    if (d.P > 0) stage_tables(d, 1, s_ptab);
     __syncthreads();
     const int lane = lane_id(), li = lane & 15, xl = lane & 3, yl = (lane >> 2) & 3;
     const uint64_t sy = (uint64_t)d.X, sz = sy * d.Y, st = sz * d.Z;
@@ -574,15 +632,18 @@ __global__ __launch_bounds__(256) void kb_sweep_rows(DevB d, int par) {
         f |= dpp<kRowRor2>(f);
         f |= dpp<kRowRor1>(f);
         if (li < 8) bschedule_face(d, tile, bx, by, bz, bt, li, f, par ^ 1);
-        else if (li == 8 && f) d.chg[par * d.NTB + tile] = 1;
+        // the row's nodes are read again by other lanes of the row
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        if (d.P > 0 && it < items && (f || (flags & kOwn))) pull_row(d, tile, word, li, 0, 1, s_ptab);
     }
 }
 
 // Sweep one tile (block of 512 threads, one voxel-step each) to a local fixed
 // point: Jacobi steps through LDS over the 8 in-tile neighbours, the out-of-
 // tile neighbours entering as fixed halos.  For tiles too thin for the rows above.
-__device__ void bsweep_tile(const DevB& d, uint32_t tile, int par, uint32_t* s_lab,
-                            uint32_t* s_flags, const uint32_t* s_ftab) {
+__device__ void bsweep_tile(const DevB& d, uint2 item, int par, uint32_t* s_lab, uint32_t* s_flags,
+                            const uint32_t* s_ftab, const uint32_t* s_ptab) {
+    const uint32_t tile = item.x;
     int bx, by, bz, bt;
     btile_coords(d, tile, bx, by, bz, bt);
     const int tid = threadIdx.x;
@@ -723,8 +784,11 @@ __device__ void bsweep_tile(const DevB& d, uint32_t tile, int par, uint32_t* s_l
     // lanes 0..7 of the first wave flag the tiles across the eight faces
     // that gained bits
     const uint32_t f = s_flags[0];
-    if (f && tid == 8) d.chg[par * d.NTB + tile] = 1;
     if (f && tid < 8) bschedule_face(d, tile, bx, by, bz, bt, tid, f, par ^ 1);
+    // 32 rows of 16 lanes: four to a word
+    const uint32_t word = (tid >> 4) & 7;
+    if (d.P > 0 && (f || (item.y & kOwn)) && word < (uint32_t)(d.Q + 31) >> 5)
+        pull_row(d, tile, word, tid & 15, tid >> 7, 4, s_ptab);
     __syncthreads();
 }
 
@@ -732,262 +796,173 @@ __global__ __launch_bounds__(512) void kb_sweep(DevB d, int par) {
     __shared__ uint32_t s_lab[8 * 512];
     __shared__ uint32_t s_flags[4];
     __shared__ uint32_t s_ftab[kLdsTab];
+    __shared__ uint32_t s_ptab[kLdsTab];
     __shared__ uint32_t s_pref[kBSubs + 1];
-    stage_work(d, par, s_pref);
+    stage_list(work_counts(d, par), s_pref);
     const uint32_t nwork = s_pref[kBSubs];
     begin_round(d, nwork);
     if (blockIdx.x >= nwork) return;  // block-uniform
     stage_tables(d, 0, s_ftab);
+    if (d.P > 0) stage_tables(d, 1, s_ptab);
     __syncthreads();
     for (uint32_t w = blockIdx.x; w < nwork; w += gridDim.x)
-        bsweep_tile(d, work_item(d, par, s_pref, w).x, par, s_lab, s_flags, s_ftab);
+        bsweep_tile(d, work_item(d, par, s_pref, w), par, s_lab, s_flags, s_ftab, s_ptab);
 }
 
-// Pull: a coupled step gains the queries for which its voxel is a member and
-// it is admissible.
-__global__ __launch_bounds__(256) void kb_pull(DevB d, int par) {
-    __shared__ uint32_t s_tmp[20];
-    if (!d.counters[BC_RACT]) return;
-    const uint32_t* ptab = reinterpret_cast<const uint32_t*>(d.tab + 1024) + 2 * 257 * 8;
-    const uint32_t n = d.counters[BC_NLIST];
-    for (uint32_t b0 = blockIdx.x * blockDim.x; b0 < n; b0 += gridDim.x * blockDim.x) {
-        const uint32_t i = b0 + threadIdx.x;
-        bool first = false;
-        uint32_t p = 0;
-        if (i < n) {
-            const uint2 ent = d.clist[i];
-            const uint32_t vox = ent.y;
-            int x = (int)(vox % d.X);
-            uint32_t r = vox / d.X;
-            const int y = r % d.Y;
-            r /= d.Y;
-            const int z = r % d.Z, t = r / d.Z;
-            if (d.chg[par * d.NTB + btile_of(d, x, y, z, t)]) {
-                p = ent.x / (uint32_t)d.Tpad;
-                const uint32_t ts = ent.x - p * (uint32_t)d.Tpad;
-                const uint32_t* lf = d.fplanes + (uint64_t)vox * 8;
-                uint32_t* lp = d.pplanes + ((uint64_t)ts * d.P + p) * 8;
-                bool any = false;
-                bool got = false;
-                Mask8 m;
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    m.w[k] = lf[k] & ~lp[k];
-                    any |= m.w[k] != 0;
-                }
-                if (any) {
-                    const uint32_t rp = d.prank[ent.x];
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        const uint32_t nw = m.w[k] & rank_word(ptab, rp, k);
-                        if (nw && (~atomicOr(&lp[k], nw) & nw)) got = true;
-                    }
-                }
-                if (got) {
-                    const uint32_t pb = 1u << (p & 31);
-                    first = !(atomicOr(&d.pdirty[p >> 5], pb) & pb);
-                }
-            }
-        }
-        const uint32_t k = block_append(first ? 1u : 0u, &d.counters[BC_NDIRTYP], s_tmp);
-        if (first) d.dlist[k] = p;
+// L with lane SRC's value (a uniform read) joined into the row ROW of 16 lanes
+// where A admits it.
+#define MF4D_CROSS(SRC, ROW) \
+    L |= (uint32_t)__builtin_amdgcn_readlane((int)L, SRC) & (row == (ROW) ? A0 : 0u);
+// A run of admissible steps carries members both ways: inclusive scans over the
+// lanes (steps) of (labels, all admissible since), up and then down, within rows
+// of 16 lanes by DPP, then across the rows of a group of G lanes.
+template <int G>
+__device__ __forceinline__ uint32_t spread_up(uint32_t L, uint32_t A0) {
+    const int row = lane_id() >> 4;
+    uint32_t A = A0;
+#define MF4D_UP(CTRL)              \
+    {                              \
+        L |= dpp<CTRL>(L) & A;     \
+        A &= dpp_ones<CTRL>(A);    \
     }
+    MF4D_UP(0x111) MF4D_UP(0x112) MF4D_UP(0x114) MF4D_UP(0x118)
+#undef MF4D_UP
+    A0 = A;
+    if (G >= 32) {
+        MF4D_CROSS(15, 1)
+        if (G == 64) MF4D_CROSS(31, 2)
+        MF4D_CROSS(47, 3)
+    }
+    return L;
 }
-
-// Close and push the dirty particles for every query plane, eight lanes per
-// particle: lane k of a group of eight carries word k (queries 32k .. 32k +
-// 31) along the particle's steps.  A forward and a backward pass spread the
-// members over admissible runs (the forward pass alone with forward-only
-// coupling); a step that gains queries pushes them into its voxel where the
-// voxel is admissible, and one lane of the group marks the voxel when any
-// word of it was gained.  The steps go in chunks of kChunk: every load of a
-// chunk (labels, ranks, bins; then the pushed voxels' ranks; then their
-// atomics) is issued together, so a chunk costs a few round trips instead of
-// a few per step.  Every lane runs every chunk (ballots).
-constexpr int kChunk = 16;
-
-// A whole trajectory of up to kWhole steps closed in registers (lane k of the
-// particle's group of eight carries word k): every step's label, ranks and bin
-// are loaded at once (one round trip), the forward and the backward pass run
-// on them, and the new bits are written and pushed in two halves, each half's
-// loads and atomics issued together.  Every lane of the wave calls it.
-constexpr int kWhole = 32;
-__device__ __forceinline__ void close_whole(const DevB& d, uint32_t p, bool valid, int k, int grp, int npar,
-                                            const uint32_t* s_ptab, const uint32_t* s_ftab) {
-    const int Tp = d.Tp;
-    uint32_t lab[kWhole], cur[kWhole], adm[kWhole], bin[kWhole];
-#pragma unroll
-    for (int j = 0; j < kWhole; ++j) {
-        cur[j] = 0;
-        adm[j] = 0;
-        bin[j] = kNoVoxel;
-        if (valid && j < Tp) {
-            cur[j] = d.pplanes[((uint64_t)j * d.P + p) * 8 + k];
-            adm[j] = d.prank[(uint64_t)p * d.Tpad + j];
-            bin[j] = d.bins[(uint64_t)p * d.Tpad + j];
-        }
+template <int G>
+__device__ __forceinline__ uint32_t spread_down(uint32_t L, uint32_t A0) {
+    const int row = lane_id() >> 4;
+    uint32_t A = A0;
+#define MF4D_DOWN(CTRL)            \
+    {                              \
+        L |= dpp<CTRL>(L) & A;     \
+        A &= dpp_ones<CTRL>(A);    \
     }
-#pragma unroll
-    for (int j = 0; j < kWhole; ++j) adm[j] = j < Tp && valid ? rank_word(s_ptab, adm[j], k) : 0u;
-    uint32_t carry = 0;
-#pragma unroll
-    for (int j = 0; j < kWhole; ++j) {
-        lab[j] = cur[j] | (carry & adm[j]);
-        carry = lab[j];
+    MF4D_DOWN(0x101) MF4D_DOWN(0x102) MF4D_DOWN(0x104) MF4D_DOWN(0x108)
+#undef MF4D_DOWN
+    A0 = A;
+    if (G >= 32) {
+        MF4D_CROSS(48, 2)
+        if (G == 64) MF4D_CROSS(32, 1)
+        MF4D_CROSS(16, 0)
     }
-    if (!d.forward_only) {
-        carry = 0;
-#pragma unroll
-        for (int j = kWhole - 1; j >= 0; --j) {
-            lab[j] |= carry & adm[j];
-            carry = lab[j];
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < kWhole; ++j) lab[j] &= ~cur[j];  // the new bits
-    // the voxels that gained bits in any word, each marked once, by lane
-    // jj & 7 of the particle's group: four per lane at most, in one batch
-    // after both halves
-    uint32_t marks[4] = {kNoVoxel, kNoVoxel, kNoVoxel, kNoVoxel};
-#pragma unroll
-    for (int h = 0; h < kWhole; h += 16) {
-        uint32_t bb[16];
-        uint64_t vv[16];
-#pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {
-            const int j = h + jj;
-            bb[jj] = kNoVoxel;
-            if (lab[j]) atomicOr(&d.pplanes[((uint64_t)j * d.P + p) * 8 + k], lab[j]);
-            const bool gnew = ((__ballot(lab[j] != 0) >> (8 * grp)) & 0xFFull) != 0;
-            if (gnew) bb[jj] = bin[j];
-        }
-        uint32_t rv[16];
-#pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {
-            vv[jj] = ~0ull;
-            rv[jj] = 0u;
-            if (bb[jj] != kNoVoxel) {
-                int x, y, z, tt;
-                bit_to_xyzt(d.g, bb[jj], x, y, z, tt);
-                vv[jj] = vindex(d, x, y, z, tt);
-                if (lab[h + jj]) rv[jj] = d.vrank[vv[jj]];
-            }
-        }
-        uint32_t got[16];
-#pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {
-            got[jj] = 0;
-            if (vv[jj] != ~0ull && lab[h + jj]) {
-                const uint32_t pw = lab[h + jj] & rank_word(s_ftab, rv[jj], k);
-                if (pw) got[jj] = ~atomicOr(&d.fplanes[vv[jj] * 8 + k], pw) & pw;
-            }
-        }
-#pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {
-            const uint32_t gg = (uint32_t)(__ballot(got[jj] != 0) >> (8 * grp)) & 0xFFu;
-            if (gg && (jj & 7) == k) marks[(h >> 3) + (jj >> 3)] = bb[jj];
-        }
-    }
-    bmark_voxels_n<4>(d, marks, npar);
+    return L;
 }
+#undef MF4D_CROSS
 
+// Close and push the particles that gained, a lane per step: G lanes (16, 32 or
+// 64, the smallest that hold a trajectory) take a particle, longer trajectories
+// go in pieces of 64 steps, up and then down, each piece taking the last lane's
+// labels of the one before.  A step that gains queries pushes them into its voxel
+// where the voxel is admissible (a plain read of the voxel's labels leaves out
+// what it has; the unions need no answer), and marks the voxel.
+// Bound by the chain of loads list - labels and ranks - voxels.
+// 128^3 x 32, 256 queries, 161,600 visits in 34 rounds: 569 us; 984 with a
+// lane per word walking the steps.
+template <int G>
 __global__ __launch_bounds__(256) void kb_close(DevB d, int par) {
     __shared__ uint32_t s_ptab[kLdsTab];
     __shared__ uint32_t s_ftab[kLdsTab];
-    const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t stride = gridDim.x * blockDim.x;
+    __shared__ uint32_t s_pref[kBSubs + 1];
     if (!d.counters[BC_RACT]) return;
-    // the swept list is empty again (the close runs in every round, with or
-    // without particles; the next list of this parity is built after the
-    // round after this one)
-    if (blockIdx.x == 0 && threadIdx.x < kBSubs) d.wcnt[((uint32_t)par * kBSubs + threadIdx.x) * kBCntStride] = 0u;
-    for (uint32_t i = tid; i < d.NTB; i += stride) d.chg[par * d.NTB + i] = 0;
-    const uint32_t nd = d.counters[BC_NDIRTYP];
-    if (tid == 0 && nd) atomicAdd(&d.stat64[S_PART_VISITS], (unsigned long long)nd);
-    const uint32_t per_block = (blockDim.x >> 6) * 8;
-    if ((uint64_t)blockIdx.x * per_block >= nd) return;  // block-uniform
+    stage_list(d.dcnt, s_pref);
+    const uint32_t nd = s_pref[kBSubs];
+    if (blockIdx.x == 0 && threadIdx.x == 0) d.stat64[S_PART_VISITS] += nd;
+    constexpr uint32_t kPer = 64 / G;  // particles of a wave
+    if (blockIdx.x * 4 * kPer >= nd) return;  // block-uniform
     stage_tables(d, 1, s_ptab);
     stage_tables(d, 0, s_ftab);
     __syncthreads();
-    const int lane = lane_id(), k = lane & 7, grp = lane >> 3;
+    const int lane = lane_id(), step = lane & (G - 1);
     const int npar = par ^ 1;
+    const int npiece = (d.Tp + G - 1) / G;  // 1 unless G = 64
     const int ndir = d.forward_only ? 1 : 2;
-    const int nch = (d.Tp + kChunk - 1) / kChunk;
-    const uint32_t wave = tid >> 6, nwaves = stride >> 6;
-    for (uint32_t base = wave * 8; base < nd; base += nwaves * 8) {  // wave-uniform
-        const uint32_t i = base + grp;
+    const int nw = (d.Q + 31) >> 5;
+    for (uint32_t i0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * kPer; i0 < nd; i0 += gridDim.x * 4 * kPer) {
+        const uint32_t i = i0 + lane / G;
         const bool valid = i < nd;
-        const uint32_t p = valid ? d.dlist[i] : 0u;
-        if (valid && k == 0) atomicAnd(&d.pdirty[p >> 5], ~(1u << (p & 31)));
-        if (d.Tp <= kWhole) {
-            close_whole(d, p, valid, k, grp, npar, s_ptab, s_ftab);
-            continue;
+        uint32_t p = 0;
+        if (valid) {
+            const int j = sub_list(s_pref, i);
+            p = d.dlist[j * d.DCAPB + (i - s_pref[j])];
+            if (step == 0) atomicAnd(&d.pdirty[p >> 5], ~(1u << (p & 31)));
         }
-        for (int dir = 0; dir < ndir; ++dir) {
-            uint32_t carry = 0;
-            for (int ci = 0; ci < nch; ++ci) {
-                const int c0 = (dir == 0 ? ci : nch - 1 - ci) * kChunk;
-                const int cn = d.Tp - c0 < kChunk ? d.Tp - c0 : kChunk;
-                uint32_t cur[kChunk], rk[kChunk], bb[kChunk];
+        // one piece: up and down at once; more: all up, then all down
+        const int nrun = npiece == 1 ? 1 : ndir * npiece;
+        uint32_t carry[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        for (int q = 0; q < nrun; ++q) {
+            const bool down = q >= npiece;
+            if (q == npiece) {
 #pragma unroll
-                for (int j = 0; j < kChunk; ++j) {
-                    cur[j] = 0;
-                    rk[j] = 0;
-                    bb[j] = kNoVoxel;
-                    if (valid && j < cn) {
-                        const uint64_t e = (uint64_t)p * d.Tpad + c0 + j;
-                        cur[j] = d.pplanes[((uint64_t)(c0 + j) * d.P + p) * 8 + k];
-                        rk[j] = d.prank[e];
-                        bb[j] = d.bins[e];
+                for (int k = 0; k < 8; ++k) carry[k] = 0;
+            }
+            const int j = (down ? 2 * npiece - 1 - q : q) * G + step;
+            const bool have = valid && j < d.Tp;
+            uint2 rv = make_uint2(0, kNoVoxel);
+            uint32_t l[8], n[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) l[k] = 0;
+            uint4* lp = reinterpret_cast<uint4*>(d.pplanes + ((uint64_t)j * d.P + p) * 8);
+            if (have) {
+                rv = d.prv[(uint64_t)p * d.Tpad + j];
+                const uint4 a = lp[0], b = lp[1];
+                l[0] = a.x; l[1] = a.y; l[2] = a.z; l[3] = a.w;
+                l[4] = b.x; l[5] = b.y; l[6] = b.z; l[7] = b.w;
+            }
+            uint32_t any = 0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                n[k] = 0;
+                // (carries exist in pieces of 64 only, one particle to a wave)
+                if (k < nw && __ballot((l[k] | carry[k]) != 0)) {
+                    const uint32_t A = rank_word(s_ptab, rv.x, k);
+                    uint32_t L = l[k];
+                    if (npiece == 1) {
+                        L = spread_up<G>(L, A);
+                        if (ndir == 2) L = spread_down<G>(L, A);
+                    } else if (!down) {
+                        if (lane == 0) L |= carry[k] & A;
+                        L = spread_up<G>(L, A);
+                        carry[k] = (uint32_t)__builtin_amdgcn_readlane((int)L, 63);
+                    } else {
+                        if (lane == 63) L |= carry[k] & A;
+                        L = spread_down<G>(L, A);
+                        carry[k] = (uint32_t)__builtin_amdgcn_readlane((int)L, 0);
                     }
+                    n[k] = L & ~l[k];
+                    any |= n[k];
                 }
-                uint32_t nw[kChunk];
+            }
+            if (any) {
+                lp[0] = make_uint4(l[0] | n[0], l[1] | n[1], l[2] | n[2], l[3] | n[3]);
+                lp[1] = make_uint4(l[4] | n[4], l[5] | n[5], l[6] | n[6], l[7] | n[7]);
+                if (rv.y != kNoVoxel) {
+                    const uint32_t vr = d.vrank[rv.y];
+                    uint32_t* fl = d.fplanes + (uint64_t)rv.y * 8;
+                    const uint4 a = reinterpret_cast<const uint4*>(fl)[0], b = reinterpret_cast<const uint4*>(fl)[1];
+                    const uint32_t have8[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+                    uint32_t pushed = 0;
 #pragma unroll
-                for (int jj = 0; jj < kChunk; ++jj) {
-                    const int j = dir == 0 ? jj : kChunk - 1 - jj;
-                    nw[j] = 0;
-                    if (j < cn) {
-                        const uint32_t l = cur[j] | (carry & rank_word(s_ptab, rk[j], k));
-                        nw[j] = l & ~cur[j];
-                        carry = l;
+                    for (int k = 0; k < 8; ++k) {
+                        const uint32_t pw = n[k] ? n[k] & ~have8[k] & rank_word(s_ftab, vr, k) : 0u;
+                        if (pw) atomicOr(&fl[k], pw);
+                        pushed |= pw;
                     }
-                }
-                // new bits: the labels, then the pushed voxels' ranks, then
-                // their label atomics, each for the whole chunk at once
-                uint64_t vv[kChunk];
-#pragma unroll
-                for (int j = 0; j < kChunk; ++j) {
-                    if (nw[j]) atomicOr(&d.pplanes[((uint64_t)(c0 + j) * d.P + p) * 8 + k], nw[j]);
-                    const bool gnew = ((__ballot(nw[j] != 0) >> (8 * grp)) & 0xFFull) != 0;
-                    vv[j] = ~0ull;
-                    if (gnew && bb[j] != kNoVoxel) {
-                        int x, y, z, tt;
-                        bit_to_xyzt(d.g, bb[j], x, y, z, tt);
-                        vv[j] = vindex(d, x, y, z, tt);
-                    }
-                }
-                uint32_t rv[kChunk];
-#pragma unroll
-                for (int j = 0; j < kChunk; ++j) rv[j] = vv[j] != ~0ull && nw[j] ? d.vrank[vv[j]] : 0u;
-                uint32_t got[kChunk];
-#pragma unroll
-                for (int j = 0; j < kChunk; ++j) {
-                    got[j] = 0;
-                    if (vv[j] != ~0ull && nw[j]) {
-                        const uint32_t pw = nw[j] & rank_word(s_ftab, rv[j], k);
-                        if (pw) got[j] = ~atomicOr(&d.fplanes[vv[j] * 8 + k], pw) & pw;
-                    }
-                }
-#pragma unroll
-                for (int j = 0; j < kChunk; ++j) {
-                    const uint32_t gg = (uint32_t)(__ballot(got[j] != 0) >> (8 * grp)) & 0xFFu;
-                    if (got[j] && k == __builtin_ctz(gg)) {
-                        int x, y, z, tt;
-                        bit_to_xyzt(d.g, bb[j], x, y, z, tt);
-                        bmark_voxel(d, x, y, z, tt, npar);
+                    if (pushed) {
+                        int x, y, z, t;
+                        voxel_coords(d, rv.y, x, y, z, t);
+                        bmark_voxel(d, x, y, z, t, npar);
                     }
                 }
             }
+            // the pieces of the way down read what the way up wrote
+            if (npiece > 1) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
         }
     }
 }
@@ -995,21 +970,41 @@ __global__ __launch_bounds__(256) void kb_close(DevB d, int par) {
 // The work list (tile, flags) of the round of parity `par` from the tiles flagged for it
 // (the flags cleared for that parity's next use): a flagged tile joins if it
 // holds a node admissible for some query.  Appends go to sub-list (tile mod
-// kBSubs): 64 counters on separate lines.  force: also after a round without
-// work (the list after seeding).
-__global__ __launch_bounds__(256) void kb_compact(DevB d, int par, int force) {
-    if (!force && !d.counters[BC_RACT]) return;
+// kBSubs): 64 counters on separate lines.  The lists that the round before has
+// worked off are emptied.  first: after seeding; also gives every tile its range
+// of the coupled list (its end, which kb_couple counts down).
+__global__ __launch_bounds__(256) void kb_compact(DevB d, int par, int first) {
+    if (!first && !d.counters[BC_RACT]) return;
+    if (blockIdx.x == 0 && threadIdx.x < kBSubs) {
+        d.wcnt[((uint32_t)(par ^ 1) * kBSubs + threadIdx.x) * kBCntStride] = 0u;
+        d.dcnt[threadIdx.x * kBCntStride] = 0u;
+    }
     const uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < d.NTB; i += stride) {
-        uint32_t* f = &d.dirty[(size_t)par * d.NTB + i];
-        const uint32_t bits = *f;
-        if (bits) {
-            *f = 0u;
-            if (d.active[i]) {
-                const uint32_t j = (uint32_t)par * kBSubs + (i & (kBSubs - 1));
-                const uint32_t k = atomicAdd(&d.wcnt[j * kBCntStride], 1u);
-                d.work[(size_t)j * d.WCAPB + k] = make_uint2(i, bits);
+    for (uint32_t i0 = blockIdx.x * blockDim.x; i0 < d.NTB; i0 += stride) {  // block-uniform
+        const uint32_t i = i0 + threadIdx.x;
+        if (i < d.NTB) {
+            uint32_t* f = &d.dirty[(size_t)par * d.NTB + i];
+            const uint32_t bits = *f;
+            if (bits) {
+                *f = 0u;
+                if (d.active[i]) {
+                    const uint32_t j = (uint32_t)par * kBSubs + (i & (kBSubs - 1));
+                    const uint32_t k = atomicAdd(&d.wcnt[j * kBCntStride], 1u);
+                    d.work[(size_t)j * d.WCAPB + k] = make_uint2(i, bits);
+                }
             }
+        }
+        if (first && d.P > 0) {
+            uint32_t x = i < d.NTB ? d.tcnt[i] : 0u;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t y = __shfl_up(x, o);
+                if (lane_id() >= o) x += y;
+            }
+            uint32_t base = 0;
+            if (lane_id() == 63 && x) base = atomicAdd(&d.counters[BC_NLIST], x);
+            base = __shfl(base, 63);
+            if (i < d.NTB) d.tbase[i] = base + x;
         }
     }
 }
@@ -1025,33 +1020,14 @@ __global__ void kb_reset(DevB d) {
     const uint64_t tid = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t i = tid; i < 2ull * d.NTB; i += stride) d.dirty[i] = 0;
-    for (uint64_t i = tid; i < (2ull * d.NTB + 3) / 4; i += stride)
-        reinterpret_cast<uint32_t*>(d.chg)[i] = 0;
+    for (uint64_t i = tid; i < d.NTB; i += stride) d.tcnt[i] = 0;
     for (uint64_t i = tid; i < ((uint64_t)d.NTB + 3) / 4; i += stride)
         reinterpret_cast<uint32_t*>(d.active)[i] = 0;
     for (uint64_t i = tid; i < (uint64_t)(d.P + 31) / 32; i += stride) d.pdirty[i] = 0;
     if (tid < BC_NCOUNTERS) d.counters[tid] = 0;
     if (tid < 2 * kBSubs) d.wcnt[tid * kBCntStride] = 0;
+    if (tid < kBSubs) d.dcnt[tid * kBCntStride] = 0;
     if (tid < S_NSTAT) d.stat64[tid] = 0;
-}
-
-__global__ void kb_count(DevB d) {
-    const uint64_t nf = (uint64_t)d.X * d.Y * d.Z * d.T * 8;
-    const uint64_t np = (uint64_t)d.Tp * d.P * 8;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    unsigned long long cf = 0, cp = 0;
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < nf; i += stride)
-        cf += __popc(d.fplanes[i]);
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < np; i += stride)
-        cp += __popc(d.pplanes[i]);
-    for (int o = 32; o > 0; o >>= 1) {
-        cf += __shfl_xor(cf, o);
-        cp += __shfl_xor(cp, o);
-    }
-    if (lane_id() == 0) {
-        if (cf) atomicAdd(&d.stat64[S_MEMBERS_F], cf);
-        if (cp) atomicAdd(&d.stat64[S_MEMBERS_P], cp);
-    }
 }
 
 inline unsigned grid_for(uint64_t n, unsigned block, unsigned cap) {
@@ -1065,15 +1041,15 @@ inline unsigned grid_for(uint64_t n, unsigned block, unsigned cap) {
 
 void launch_b_prepare(const DevB& d, const int32_t* seeds, int64_t S, hipStream_t s) {
     const uint64_t V = (uint64_t)d.X * d.Y * d.Z * d.T;
+    const uint64_t n = (uint64_t)d.P * d.Tpad;
     hipLaunchKernelGGL(kb_reset, dim3(grid_for(2ull * d.NTB + d.P / 32 + 1, 256, 2048)), dim3(256),
                        0, s, d);
-    hipLaunchKernelGGL(kb_admit_field, dim3(grid_for(V, 256, 4096)), dim3(256), 0, s, d);
-    if (d.P > 0)
-        hipLaunchKernelGGL(kb_admit_particles,
-                           dim3(grid_for((uint64_t)d.P * d.Tpad, 256, 8192)), dim3(256), 0, s, d);
+    hipLaunchKernelGGL(kb_admit_field, dim3(grid_for(V, 1024, 4096)), dim3(256), 0, s, d);
+    if (d.P > 0) hipLaunchKernelGGL(kb_admit_particles, dim3(grid_for(n, 1024, 8192)), dim3(256), 0, s, d);
     if (S > 0)
         hipLaunchKernelGGL(kb_seeds, dim3(grid_for(S, 256, 1u << 20)), dim3(256), 0, s, d, seeds, S);
     hipLaunchKernelGGL(kb_compact, dim3(grid_for(d.NTB, 256, 1024)), dim3(256), 0, s, d, 0, 1);
+    if (d.P > 0) hipLaunchKernelGGL(kb_couple, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, d);
 }
 
 void launch_b_round(const DevB& d, uint32_t round, hipStream_t s) {
@@ -1094,23 +1070,17 @@ void launch_b_round(const DevB& d, uint32_t round, hipStream_t s) {
         default: hipLaunchKernelGGL(kb_sweep, dim3(grid_for(d.NTB, 1, 2048)), dim3(512), 0, s, d, par); break;
     }
     if (d.P > 0) {
-        hipLaunchKernelGGL(kb_pull, dim3(grid_for((uint64_t)d.P * d.Tpad, 256, 2048)), dim3(256), 0,
-                           s, d, par);
-        const uint64_t nclose = (uint64_t)d.NTB > (uint64_t)d.P ? (uint64_t)d.NTB : (uint64_t)d.P;
-        hipLaunchKernelGGL(kb_close, dim3(grid_for(nclose, 256, 2048)), dim3(256), 0, s, d, par);
-    } else {
-        hipLaunchKernelGGL(kb_close, dim3(grid_for(d.NTB, 256, 2048)), dim3(256), 0, s, d, par);
+        const int G = d.Tp <= 16 ? 16 : d.Tp <= 32 ? 32 : 64;
+        const dim3 close(grid_for((uint64_t)d.P, 4 * (64 / G), 1024));
+        if (G == 16) hipLaunchKernelGGL(kb_close<16>, close, dim3(256), 0, s, d, par);
+        else if (G == 32) hipLaunchKernelGGL(kb_close<32>, close, dim3(256), 0, s, d, par);
+        else hipLaunchKernelGGL(kb_close<64>, close, dim3(256), 0, s, d, par);
     }
     hipLaunchKernelGGL(kb_compact, dim3(grid_for(d.NTB, 256, 1024)), dim3(256), 0, s, d, par ^ 1, 0);
 }
 
 void launch_b_work_total(const DevB& d, int par, hipStream_t s) {
     hipLaunchKernelGGL(kb_work_total, dim3(1), dim3(64), 0, s, d, par);
-}
-
-void launch_b_count(const DevB& d, hipStream_t s) {
-    const uint64_t V = (uint64_t)d.X * d.Y * d.Z * d.T;
-    hipLaunchKernelGGL(kb_count, dim3(grid_for(V * 8, 256, 8192)), dim3(256), 0, s, d);
 }
 
 }  // namespace mf4d
