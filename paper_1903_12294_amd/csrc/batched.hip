@@ -343,7 +343,6 @@ __device__ __forceinline__ uint32_t dpp_ones(uint32_t v) {  // all ones from out
     return (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, CTRL, 0xF, 0xF, false);
 }
 constexpr int kQuadPrev = 0x90, kQuadNext = 0xF9, kRowPrev4 = 0x114, kRowNext4 = 0x104;
-constexpr int kRowRor1 = 0x121, kRowRor2 = 0x122, kRowRor4 = 0x124, kRowRor8 = 0x128;
 
 // A list kept as kBSubs sub-lists seen as one: the sub-lists' prefix sums.
 __device__ __forceinline__ void stage_list(const uint32_t* cnt, uint32_t* s_pref) {
@@ -388,21 +387,29 @@ __device__ __forceinline__ void begin_round(const DevB& d, uint32_t nwork) {
     }
 }
 
-// Word `word` of a swept tile handed to its coupled steps by 16 lanes (lane li),
-// part `part` of `parts` rows that share the word: a step gains the queries for
-// which its voxel is a member and it is admissible.  Nothing else writes the
-// word of these steps meanwhile.  A particle that gained is listed once.
-__device__ __forceinline__ void pull_row(const DevB& d, uint32_t tile, uint32_t word, int li, int part, int parts,
-                                         const uint32_t* s_ptab) {
+// A particle that gained, for the close: listed once.
+__device__ __forceinline__ void list_particle(const DevB& d, uint32_t p) {
+    const uint32_t pb = 1u << (p & 31);
+    if (!(atomicOr(&d.pdirty[p >> 5], pb) & pb)) {
+        const uint32_t j = p / d.DCAPB;
+        d.dlist[j * d.DCAPB + atomicAdd(&d.dcnt[j * kBCntStride], 1u)] = p;
+    }
+}
+
+// Word `word` of a swept tile handed to its coupled steps by 64 lanes (li: which):
+// a step gains the queries for which its voxel is a member and it is admissible.
+// Nothing else writes the word of these steps meanwhile.
+__device__ __forceinline__ void pull_word(const DevB& d, uint32_t tile, uint32_t word, int li,
+                                          const uint32_t* s_ptab) {
     const uint32_t n = d.tcnt[tile], base = d.tbase[tile];
-    constexpr int kU = 4;
-    for (uint32_t i0 = part * 16 + li; i0 < n; i0 += kU * 16 * parts) {
+    constexpr uint32_t kU = 4, W = 64;
+    for (uint32_t i0 = li; i0 < n; i0 += kU * W) {
         uint2 ent[kU];
         uint32_t p[kU], m[kU], r[kU], lp[kU];
         uint64_t at[kU];
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const uint32_t i = i0 + u * 16 * parts;
+        for (uint32_t u = 0; u < kU; ++u) {
+            const uint32_t i = i0 + u * W;
             ent[u] = d.clist[base + (i < n ? i : i0)];
         }
 #pragma unroll
@@ -416,231 +423,288 @@ __device__ __forceinline__ void pull_row(const DevB& d, uint32_t tile, uint32_t 
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             const uint32_t nw = m[u] & ~lp[u] & rank_word(s_ptab, r[u], word);
-            if (nw && i0 + u * 16 * parts < n) {
+            if (nw && i0 + u * W < n) {
                 d.pplanes[at[u]] = lp[u] | nw;
-                const uint32_t pb = 1u << (p[u] & 31);
-                if (!(atomicOr(&d.pdirty[p[u] >> 5], pb) & pb)) {
-                    const uint32_t j = p[u] / d.DCAPB;
-                    d.dlist[j * d.DCAPB + atomicAdd(&d.dcnt[j * kBCntStride], 1u)] = p[u];
-                }
+                list_particle(d, p[u]);
             }
         }
     }
 }
 
-// Sweep of tiles with at least four nodes along x and along y.  A row of 16
-// lanes takes one word (32 queries) of one tile: a lane holds an x by y piece of
-// the tile at every z and t, 32 nodes, in registers.  A line of nodes along z or
-// t, or within a piece, is closed by one pass up and one down; between pieces
-// the word moves by DPP.  No LDS and no barrier: the loop of a wave ends when
-// none of its four rows gained a bit (labels only grow).  Only nodes that admit
-// a query of the word are read, and only the faces the tile is flagged for.
-// Few queries fill the rows with tiles instead of words.
-// Bound by the chain of loads (list, ranks, labels and halos) and the issue of
-// the passes.  128^3 x 32, 256 queries, 67,600 visits of 4 x 4 x 4 x 8 tiles:
-// 1,598 us without the coupled steps, 1,838 with them (453 as a pass over all of
-// them); 3,058 with a block of 512 threads per tile passing all eight words
-// through LDS and reading every face.
+// Four words of a swept tile handed to its coupled steps by a wave: as pull_word,
+// with 16-byte reads and writes.
+__device__ __forceinline__ uint4 rank_words4(const uint32_t* s_tab, uint32_t r, uint32_t k) {
+    const uint4 a = *reinterpret_cast<const uint4*>(s_tab + (r & 0xFFFFu) * 8 + k);
+    const uint4 b = *reinterpret_cast<const uint4*>(s_tab + 257 * 8 + (r >> 16) * 8 + k);
+    return make_uint4(a.x & b.x, a.y & b.y, a.z & b.z, a.w & b.w);
+}
+__device__ __forceinline__ void pull_words4(const DevB& d, uint32_t tile, uint32_t word, const uint32_t* s_ptab) {
+    const uint32_t n = d.tcnt[tile], base = d.tbase[tile];
+    for (uint32_t i = lane_id(); i < n; i += 64) {
+        const uint2 ent = d.clist[base + i];
+        const uint32_t p = ent.x / (uint32_t)d.Tpad;
+        uint4* pp = reinterpret_cast<uint4*>(
+            d.pplanes + ((uint64_t)(ent.x - p * (uint32_t)d.Tpad) * d.P + p) * 8 + word);
+        const uint4 m = *reinterpret_cast<const uint4*>(d.fplanes + (uint64_t)ent.y * 8 + word);
+        const uint4 a = rank_words4(s_ptab, d.prv[ent.x].x, word);
+        const uint4 l = *pp;
+        const uint4 g = make_uint4(l.x | (m.x & a.x), l.y | (m.y & a.y), l.z | (m.z & a.z), l.w | (m.w & a.w));
+        if ((g.x ^ l.x) | (g.y ^ l.y) | (g.z ^ l.z) | (g.w ^ l.w)) {
+            *pp = g;
+            list_particle(d, p);
+        }
+    }
+}
+
+// Sweep of tiles with at least four nodes along x and along y.  A wave takes four
+// words (128 queries) of one tile, a lane an x by y piece of one quarter of the
+// tile along t (along z at an extent below four): eight nodes, in registers.  A
+// line of nodes within a lane is closed by one pass up and one down; between lanes
+// the words move by DPP, between quarters by lane permutes.  No barrier: a word's
+// loop ends when it gained nothing in the wave (labels only grow).  Only nodes that
+// admit a query of the words are read, and only the faces the tile is flagged for;
+// what a tile gained it hands to its coupled steps.
+// Bound by the chain list - ranks - labels and faces, and where many tiles wait by
+// the vector memory unit, which takes a cycle for every lane's 32-byte sector
+// whatever its width: a lane moves 16 bytes.  128^3 x 32, 256 queries, 67,600
+// visits of 4 x 4 x 4 x 8 tiles: 1,428 us with the coupled steps; 1,770 with one
+// word to 32 lanes (which is slower for 8 to 128 queries too: 64^3 x 16, 24
+// queries, a whole call 567 us, here 451); 3,058, and 494 for the steps, with a
+// block of 512 threads per tile passing eight words through LDS and reading every
+// face.
 template <int LX, int LY, int LZ, int LT>
-__global__ __launch_bounds__(256) void kb_sweep_rows(DevB d, int par) {
-    static_assert(LX >= 2 && LY >= 2 && LX + LY + LZ + LT == 9, "512 nodes, 4 x 4 lanes");
-    constexpr int NX = 1 << (LX - 2), NY = 1 << (LY - 2), NZ = 1 << LZ, NT = 1 << LT;
-    __shared__ uint32_t s_ftab[kLdsTab];
-    __shared__ uint32_t s_ptab[kLdsTab];
+__global__ __launch_bounds__(256) void kb_sweep_tiles(DevB d, int par) {
+    constexpr bool kT = LT >= 2;  // the quarters lie along t
+    constexpr int NX = 1 << (LX - 2), NY = 1 << (LY - 2), NZ = kT ? 1 << LZ : 1 << (LZ - 2),
+                  NT = kT ? 1 << (LT - 2) : 1 << LT, N = 8;
+    static_assert(LX >= 2 && LY >= 2 && (kT || LZ >= 2) && NX * NY * NZ * NT == N, "8 nodes a lane");
+    // (a quarter's end lanes receive their own first or last layer: a neighbour, or the node itself)
+    static_assert((kT ? NT : NZ) <= 2, "layers of a quarter");
+    __shared__ __attribute__((aligned(16))) uint32_t s_ftab[kLdsTab];
+    __shared__ __attribute__((aligned(16))) uint32_t s_ptab[kLdsTab];
     __shared__ uint32_t s_pref[kBSubs + 1];
     stage_list(work_counts(d, par), s_pref);
     const uint32_t nwork = s_pref[kBSubs];
     begin_round(d, nwork);
-    const uint32_t nw = (uint32_t)(d.Q + 31) >> 5;
-    const uint64_t items = (uint64_t)nwork * nw;
-    if (blockIdx.x * 16ull >= items) return;  // block-uniform
+    const uint32_t ng = ((uint32_t)d.Q + 127) >> 7;
+    const uint32_t items = nwork * ng;  // at most 2 x NTB
+    if (blockIdx.x * 4 >= items) return;  // block-uniform
     stage_tables(d, 0, s_ftab);
     if (d.P > 0) stage_tables(d, 1, s_ptab);
     __syncthreads();
-    const int lane = lane_id(), li = lane & 15, xl = lane & 3, yl = (lane >> 2) & 3;
+    const int lane = lane_id(), xl = lane & 3, yl = (lane >> 2) & 3, qr = lane >> 4;
+    const int prev = qr > 0 ? lane - 16 : lane, next = qr < 3 ? lane + 16 : lane;
     const uint64_t sy = (uint64_t)d.X, sz = sy * d.Y, st = sz * d.Z;
-    const uint64_t wave = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    for (uint64_t i0 = wave * 4; i0 < items; i0 += (uint64_t)gridDim.x * 16) {  // wave-uniform
-        const uint64_t it = i0 + (lane >> 4);
-        uint32_t word = 0, tile = 0, flags = 0;
-        int xlim = 0, ylim = 0, zlim = 0, tlim = 0;
-        int bx = 0, by = 0, bz = 0, bt = 0;
-        if (it < items) {
-            const uint32_t w = (uint32_t)(it / nw);
-            word = (uint32_t)(it - (uint64_t)w * nw);
-            const uint2 e = work_item(d, par, s_pref, w);
-            tile = e.x;
-            flags = e.y;
-            btile_coords(d, tile, bx, by, bz, bt);
-            xlim = d.X - ((bx << LX) + xl * NX);
-            ylim = d.Y - ((by << LY) + yl * NY);
-            zlim = d.Z - (bz << LZ);
-            tlim = d.T - (bt << LT);
-        }
-        const uint64_t v0 = vindex(d, (bx << LX) + xl * NX, (by << LY) + yl * NY, bz << LZ, bt << LT);
-        auto at = [](int jx, int jy, int jz, int jt) { return ((jt * NZ + jz) * NY + jy) * NX + jx; };
-        uint32_t a[32], l[32];
-#pragma unroll
-        for (int j = 0; j < 32; ++j) {
-            const int jx = j % NX, jy = j / NX % NY, jz = j / (NX * NY) % NZ, jt = j / (NX * NY * NZ);
-            const bool in = jx < xlim && jy < ylim && jz < zlim && jt < tlim;
-            a[j] = 0;
-            if (in) a[j] = d.vrank[v0 + jx + jy * sy + jz * sz + jt * st];
-        }
-#pragma unroll
-        for (int j = 0; j < 32; ++j) a[j] = rank_word(s_ftab, a[j], word);
-        uint32_t* fp = d.fplanes + v0 * 8 + word;
-        // a node that admits none of the word's queries has none of them
-#pragma unroll
-        for (int j = 0; j < 32; ++j) {
-            const int jx = j % NX, jy = j / NX % NY, jz = j / (NX * NY) % NZ, jt = j / (NX * NY * NZ);
-            l[j] = 0;
-            if (a[j]) l[j] = fp[(jx + jy * sy + jz * sz + jt * st) * 8];
-        }
-        uint32_t l0[32];
-#pragma unroll
-        for (int j = 0; j < 32; ++j) l0[j] = l[j];
-        // halos: node j's neighbour off nodes away, where the lane has it
-        auto halo = [&](int j, bool has, int64_t off) {
-            const int jx = j % NX, jy = j / NX % NY, jz = j / (NX * NY) % NZ, jt = j / (NX * NY * NZ);
-            const uint32_t* q = fp + ((int64_t)(jx + jy * sy + jz * sz + jt * st) + off) * 8;
-            const bool use = has && a[j] != 0;
-            // (a load for every lane, from a place that is always there when
-            // unused, so that the loads of a face go out together)
-            const uint32_t h = *(use ? q : reinterpret_cast<const uint32_t*>(d.tab));
-            return use ? h : 0u;
+    const uint4* zero = reinterpret_cast<const uint4*>(d.tab + 1024);  // row 0 of a mask table
+    const uint32_t first = NX <= 2 || xl != 0 ? ~0u : 0u, last = NX <= 2 || xl != 3 ? ~0u : 0u;
+    for (uint32_t it0 = blockIdx.x * 4 + (threadIdx.x >> 6); it0 < items; it0 += gridDim.x * 4) {
+        const uint32_t it = (uint32_t)__builtin_amdgcn_readfirstlane((int)it0);
+        const uint32_t w = ng == 2 ? it >> 1 : it, word = ng == 2 ? (it & 1) * 4 : 0;
+        const uint2 e = work_item(d, par, s_pref, w);
+        const uint32_t tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)e.x);
+        const uint32_t flags = (uint32_t)__builtin_amdgcn_readfirstlane((int)e.y);
+        int bx, by, bz, bt;
+        btile_coords(d, tile, bx, by, bz, bt);
+        const int x0 = (bx << LX) + xl * NX, y0 = (by << LY) + yl * NY, z0 = (bz << LZ) + (kT ? 0 : qr * NZ),
+                  t0 = (bt << LT) + (kT ? qr * NT : 0);
+        const uint64_t v0 = vindex(d, x0, y0, z0, t0);
+        auto off = [&](int j) {
+            return (uint64_t)(j % NX) + (uint64_t)(j / NX % NY) * sy + (uint64_t)(j / (NX * NY) % NZ) * sz +
+                   (uint64_t)(j / (NX * NY * NZ)) * st;
         };
+        uint32_t rv[N], a[N][4], l[N][4], cnt[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const bool in = x0 + j % NX < d.X && y0 + j / NX % NY < d.Y && z0 + j / (NX * NY) % NZ < d.Z &&
+                            t0 + j / (NX * NY * NZ) < d.T;
+            rv[j] = 0;
+            if (in) rv[j] = d.vrank[v0 + off(j)];
+        }
+        uint32_t adm = 0;  // bit j: node j admits one of the words' queries
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const uint4 m = rank_words4(s_ftab, rv[j], word);
+            a[j][0] = m.x; a[j][1] = m.y; a[j][2] = m.z; a[j][3] = m.w;
+            if (m.x | m.y | m.z | m.w) adm |= 1u << j;
+        }
+        uint4* fp = reinterpret_cast<uint4*>(d.fplanes + v0 * 8 + word);
+        // node j's neighbour o nodes away (0 where the lane has none)
+        auto read = [&](int j, bool has, int64_t o) {
+            return *(has && ((adm >> j) & 1u) ? fp + ((int64_t)off(j) + o) * 2 : zero);
+        };
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const uint4 v = read(j, true, 0);
+            l[j][0] = v.x; l[j][1] = v.y; l[j][2] = v.z; l[j][3] = v.w;
+            cnt[j] = __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+        }
+#define MF4D_FACE(FLAGS, COND, HAS, OFF)                                           \
+    if (flags & (FLAGS)) {                                                         \
+        uint4 h[N];                                                                \
+        _Pragma("unroll") for (int j = 0; j < N; ++j) {                            \
+            const int jx = j % NX, jy = j / NX % NY, jz = j / (NX * NY) % NZ, jt = j / (NX * NY * NZ); \
+            (void)jx; (void)jy; (void)jz; (void)jt;                                \
+            if (COND) h[j] = read(j, HAS, OFF);                                    \
+            else h[j] = make_uint4(0, 0, 0, 0);                                    \
+        }                                                                          \
+        _Pragma("unroll") for (int j = 0; j < N; ++j) {                            \
+            l[j][0] |= h[j].x & a[j][0];                                           \
+            l[j][1] |= h[j].y & a[j][1];                                           \
+            l[j][2] |= h[j].z & a[j][2];                                           \
+            l[j][3] |= h[j].w & a[j][3];                                           \
+        }                                                                          \
+    }
         const bool xm = (flags & 1u) && xl == 0, xp = (flags & 2u) && xl == 3;
         const bool ym = (flags & 4u) && yl == 0, yp = (flags & 8u) && yl == 3;
-        uint32_t h[32];
-#define MF4D_FACE(COND, HAS, OFF, FIRST)                                  \
-    if (__ballot(HAS)) {                                                  \
-        _Pragma("unroll") for (int j = 0; j < 32; ++j) {                  \
-            const int jx = j % NX, jy = j / NX % NY, jz = j / (NX * NY) % NZ, jt = j / (NX * NY * NZ); \
-            (void)jx; (void)jy; (void)jz; (void)jt;                       \
-            h[j] = (COND) ? halo(j, HAS, OFF) : 0u;                       \
-        }                                                                 \
-        _Pragma("unroll") for (int j = 0; j < 32; ++j) l[j] |= h[j] & a[j]; \
-    }
+        const bool qm = qr == 0, qp = qr == 3;
         if constexpr (NX == 1) {
-            MF4D_FACE(true, xm || xp, xm ? -1ll : 1ll, 0)
+            MF4D_FACE(3u, true, xm || xp, xm ? -1ll : 1ll)
         } else {
-            MF4D_FACE(jx == 0, xm, -1ll, 0)
-            MF4D_FACE(jx == NX - 1, xp, 1ll, 0)
+            MF4D_FACE(1u, jx == 0, xm, -1ll)
+            MF4D_FACE(2u, jx == NX - 1, xp, 1ll)
         }
         if constexpr (NY == 1) {
-            MF4D_FACE(true, ym || yp, ym ? -(int64_t)sy : (int64_t)sy, 0)
+            MF4D_FACE(12u, true, ym || yp, ym ? -(int64_t)sy : (int64_t)sy)
         } else {
-            MF4D_FACE(jy == 0, ym, -(int64_t)sy, 0)
-            MF4D_FACE(jy == NY - 1, yp, (int64_t)sy, 0)
+            MF4D_FACE(4u, jy == 0, ym, -(int64_t)sy)
+            MF4D_FACE(8u, jy == NY - 1, yp, (int64_t)sy)
         }
-        MF4D_FACE(jz == 0, (flags & 16u) != 0, -(int64_t)sz, 0)
-        MF4D_FACE(jz == NZ - 1, (flags & 32u) != 0, (int64_t)sz, 0)
-        MF4D_FACE(jt == 0, (flags & 64u) != 0, -(int64_t)st, 0)
-        MF4D_FACE(jt == NT - 1, (flags & 128u) != 0, (int64_t)st, 0)
+        MF4D_FACE(16u, jz == 0, kT || qm, -(int64_t)sz)
+        MF4D_FACE(32u, jz == NZ - 1, kT || qp, (int64_t)sz)
+        MF4D_FACE(64u, jt == 0, !kT || qm, -(int64_t)st)
+        MF4D_FACE(128u, jt == NT - 1, !kT || qp, (int64_t)st)
 #undef MF4D_FACE
-        // (the lane that keeps its own value would join the ends of a piece, which
-        // are neighbours, or one node, only in pieces of up to two)
-        const uint32_t first = NX <= 2 || xl != 0 ? ~0u : 0u, last = NX <= 2 || xl != 3 ? ~0u : 0u;
-        uint32_t cnt = 0;
+        auto at = [](int jx, int jy, int jz, int jt) { return ((jt * NZ + jz) * NY + jy) * NX + jx; };
 #pragma unroll
-        for (int j = 0; j < 32; ++j) cnt += __popc(l[j]);
-        while (true) {
-            // lines along t, then z
+        for (int k = 0; k < 4; ++k) {
+            uint32_t room = 0, src = 0, c = 0;
 #pragma unroll
-            for (int r = 0; r < 32 / NT; ++r) {
-#pragma unroll
-                for (int k = 1; k < NT; ++k) l[k * (32 / NT) + r] |= l[(k - 1) * (32 / NT) + r] & a[k * (32 / NT) + r];
-#pragma unroll
-                for (int k = NT - 2; k >= 0; --k) l[k * (32 / NT) + r] |= l[(k + 1) * (32 / NT) + r] & a[k * (32 / NT) + r];
+            for (int j = 0; j < N; ++j) {
+                room |= a[j][k] & ~l[j][k];
+                src |= l[j][k];
+                c += __popc(l[j][k]);
             }
+            if (!__ballot(room) || !__ballot(src)) continue;  // nothing to gain, or nowhere to gain it from
+            while (true) {
+                // lines along t, z within the lane
 #pragma unroll
-            for (int jt = 0; jt < NT; ++jt)
+                for (int r = 0; r < N / NT; ++r) {
 #pragma unroll
-                for (int r = 0; r < NX * NY; ++r) {
-                    const int b = jt * NZ * NY * NX + r;
+                    for (int i = 1; i < NT; ++i) l[i * (N / NT) + r][k] |= l[(i - 1) * (N / NT) + r][k] & a[i * (N / NT) + r][k];
 #pragma unroll
-                    for (int k = 1; k < NZ; ++k) l[b + k * NX * NY] |= l[b + (k - 1) * NX * NY] & a[b + k * NX * NY];
-#pragma unroll
-                    for (int k = NZ - 2; k >= 0; --k)
-                        l[b + k * NX * NY] |= l[b + (k + 1) * NX * NY] & a[b + k * NX * NY];
+                    for (int i = NT - 2; i >= 0; --i)
+                        l[i * (N / NT) + r][k] |= l[(i + 1) * (N / NT) + r][k] & a[i * (N / NT) + r][k];
                 }
 #pragma unroll
-            for (int jt = 0; jt < NT; ++jt)
+                for (int jt = 0; jt < NT; ++jt)
 #pragma unroll
-                for (int jz = 0; jz < NZ; ++jz) {
-                    if constexpr (NX == 1 && NY == 1) {
-                        const int j = at(0, 0, jz, jt);
-                        uint32_t n = dpp<kQuadPrev>(l[j]);
-                        n |= dpp<kQuadNext>(l[j]);
-                        n |= dpp<kRowPrev4>(l[j]);
-                        n |= dpp<kRowNext4>(l[j]);
-                        l[j] |= n & a[j];
-                    } else {
+                    for (int r = 0; r < NX * NY; ++r) {
+                        const int b = jt * NZ * NY * NX + r, s = NX * NY;
 #pragma unroll
-                        for (int jy = 0; jy < NY; ++jy) {
-                            const int b = at(0, jy, jz, jt);
-                            l[b] |= dpp<kQuadPrev>(l[b + NX - 1]) & a[b] & first;
+                        for (int i = 1; i < NZ; ++i) l[b + i * s][k] |= l[b + (i - 1) * s][k] & a[b + i * s][k];
 #pragma unroll
-                            for (int k = 1; k < NX; ++k) l[b + k] |= l[b + k - 1] & a[b + k];
-                            l[b + NX - 1] |= dpp<kQuadNext>(l[b]) & a[b + NX - 1] & last;
+                        for (int i = NZ - 2; i >= 0; --i) l[b + i * s][k] |= l[b + (i + 1) * s][k] & a[b + i * s][k];
+                    }
 #pragma unroll
-                            for (int k = NX - 2; k >= 0; --k) l[b + k] |= l[b + k + 1] & a[b + k];
-                        }
+                for (int jt = 0; jt < NT; ++jt)
 #pragma unroll
-                        for (int jx = 0; jx < NX; ++jx) {
-                            const int b = at(jx, 0, jz, jt);
-                            l[b] |= dpp<kRowPrev4>(l[b + (NY - 1) * NX]) & a[b];
+                    for (int jz = 0; jz < NZ; ++jz) {
+                        if constexpr (NX == 1 && NY == 1) {
+                            const int j = at(0, 0, jz, jt);
+                            uint32_t n = dpp<kQuadPrev>(l[j][k]);
+                            n |= dpp<kQuadNext>(l[j][k]);
+                            n |= dpp<kRowPrev4>(l[j][k]);
+                            n |= dpp<kRowNext4>(l[j][k]);
+                            l[j][k] |= n & a[j][k];
+                        } else {
 #pragma unroll
-                            for (int k = 1; k < NY; ++k) l[b + k * NX] |= l[b + (k - 1) * NX] & a[b + k * NX];
-                            l[b + (NY - 1) * NX] |= dpp<kRowNext4>(l[b]) & a[b + (NY - 1) * NX];
+                            for (int jy = 0; jy < NY; ++jy) {
+                                const int b = at(0, jy, jz, jt);
+                                l[b][k] |= dpp<kQuadPrev>(l[b + NX - 1][k]) & a[b][k] & first;
 #pragma unroll
-                            for (int k = NY - 2; k >= 0; --k) l[b + k * NX] |= l[b + (k + 1) * NX] & a[b + k * NX];
+                                for (int i = 1; i < NX; ++i) l[b + i][k] |= l[b + i - 1][k] & a[b + i][k];
+                                l[b + NX - 1][k] |= dpp<kQuadNext>(l[b][k]) & a[b + NX - 1][k] & last;
+#pragma unroll
+                                for (int i = NX - 2; i >= 0; --i) l[b + i][k] |= l[b + i + 1][k] & a[b + i][k];
+                            }
+#pragma unroll
+                            for (int jx = 0; jx < NX; ++jx) {
+                                const int b = at(jx, 0, jz, jt), z = b + (NY - 1) * NX;
+                                l[b][k] |= dpp<kRowPrev4>(l[z][k]) & a[b][k];
+#pragma unroll
+                                for (int i = 1; i < NY; ++i) l[b + i * NX][k] |= l[b + (i - 1) * NX][k] & a[b + i * NX][k];
+                                l[z][k] |= dpp<kRowNext4>(l[b][k]) & a[z][k];
+#pragma unroll
+                                for (int i = NY - 2; i >= 0; --i)
+                                    l[b + i * NX][k] |= l[b + (i + 1) * NX][k] & a[b + i * NX][k];
+                            }
                         }
                     }
+                // the layers where quarters meet
+                constexpr int L = kT ? NX * NY * NZ : NX * NY;  // nodes between two layers
+                uint32_t up[N], dn[N];
+#pragma unroll
+                for (int j = 0; j < N; ++j) {
+                    const int i = kT ? j / (NX * NY * NZ) : j / (NX * NY) % NZ;  // layer of the quarter
+                    if (i != 0) continue;
+                    up[j] = (uint32_t)__shfl((int)l[j + ((kT ? NT : NZ) - 1) * L][k], prev);
+                    dn[j] = (uint32_t)__shfl((int)l[j][k], next);
                 }
-            uint32_t now = 0;
 #pragma unroll
-            for (int j = 0; j < 32; ++j) now += __popc(l[j]);
-            const bool grew = now != cnt;
-            cnt = now;
-            if (__ballot(grew) == 0) break;
-        }
-        // Other rows write other words, and nothing else writes this one's
-        // nodes meanwhile (seeds and pushes come in other phases): plain stores.
-        uint32_t any = 0, z0 = 0, z1 = 0, t0 = 0, t1 = 0, x0 = 0, x1 = 0, y0 = 0, y1 = 0;
+                for (int j = 0; j < N; ++j) {
+                    const int i = kT ? j / (NX * NY * NZ) : j / (NX * NY) % NZ;
+                    if (i != 0) continue;
+                    const int z = j + ((kT ? NT : NZ) - 1) * L;
+                    l[j][k] |= up[j] & a[j][k];
+                    l[z][k] |= dn[j] & a[z][k];
+                }
+                uint32_t now = 0;
 #pragma unroll
-        for (int j = 0; j < 32; ++j) {
-            const int jx = j % NX, jy = j / NX % NY, jz = j / (NX * NY) % NZ, jt = j / (NX * NY * NZ);
-            const uint32_t g = l[j] ^ l0[j];
-            if (g) fp[(jx + jy * sy + jz * sz + jt * st) * 8] = l[j];
-            any |= g;
-            if (jx == 0) x0 |= g;
-            if (jx == NX - 1) x1 |= g;
-            if (jy == 0) y0 |= g;
-            if (jy == NY - 1) y1 |= g;
-            if (jz == 0) z0 |= g;
-            if (jz == NZ - 1) z1 |= g;
-            if (jt == 0) t0 |= g;
-            if (jt == NT - 1) t1 |= g;
+                for (int j = 0; j < N; ++j) now += __popc(l[j][k]);
+                const bool grew = now != c;
+                c = now;
+                if (!__ballot(grew)) break;
+            }
         }
-        uint32_t f = (xl == 0 && x0 ? 1u : 0u) | (xl == 3 && x1 ? 2u : 0u) | (yl == 0 && y0 ? 4u : 0u) |
-                     (yl == 3 && y1 ? 8u : 0u) | (z0 ? 16u : 0u) | (z1 ? 32u : 0u) | (t0 ? 64u : 0u) |
-                     (t1 ? 128u : 0u) | (any ? 256u : 0u);
-        f |= dpp<kRowRor8>(f);
-        f |= dpp<kRowRor4>(f);
-        f |= dpp<kRowRor2>(f);
-        f |= dpp<kRowRor1>(f);
-        if (li < 8) bschedule_face(d, tile, bx, by, bz, bt, li, f, par ^ 1);
-        // the row's nodes are read again by other lanes of the row
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-        if (d.P > 0 && it < items && (f || (flags & kOwn))) pull_row(d, tile, word, li, 0, 1, s_ptab);
+        // The other words of these nodes are another wave's, and nothing else
+        // writes them meanwhile: plain stores.
+        uint32_t g = 0;  // bit j: node j gained
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            if ((uint32_t)(__popc(l[j][0]) + __popc(l[j][1]) + __popc(l[j][2]) + __popc(l[j][3])) != cnt[j]) {
+                fp[off(j) * 2] = make_uint4(l[j][0], l[j][1], l[j][2], l[j][3]);
+                g |= 1u << j;
+            }
+        uint32_t f = 0;
+        if (__ballot(g)) {
+            uint32_t mx0 = 0, mx1 = 0, my0 = 0, my1 = 0, mz0 = 0, mz1 = 0, mt0 = 0, mt1 = 0;  // nodes on a face
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                const int jx = j % NX, jy = j / NX % NY, jz = j / (NX * NY) % NZ, jt = j / (NX * NY * NZ);
+                if (jx == 0) mx0 |= 1u << j;
+                if (jx == NX - 1) mx1 |= 1u << j;
+                if (jy == 0) my0 |= 1u << j;
+                if (jy == NY - 1) my1 |= 1u << j;
+                if (jz == 0) mz0 |= 1u << j;
+                if (jz == NZ - 1) mz1 |= 1u << j;
+                if (jt == 0) mt0 |= 1u << j;
+                if (jt == NT - 1) mt1 |= 1u << j;
+            }
+            f = kOwn | (__ballot(xl == 0 && (g & mx0)) ? 1u : 0u) | (__ballot(xl == 3 && (g & mx1)) ? 2u : 0u) |
+                (__ballot(yl == 0 && (g & my0)) ? 4u : 0u) | (__ballot(yl == 3 && (g & my1)) ? 8u : 0u) |
+                (__ballot((kT || qm) && (g & mz0)) ? 16u : 0u) | (__ballot((kT || qp) && (g & mz1)) ? 32u : 0u) |
+                (__ballot((!kT || qm) && (g & mt0)) ? 64u : 0u) | (__ballot((!kT || qp) && (g & mt1)) ? 128u : 0u);
+            if (lane < 8) bschedule_face(d, tile, bx, by, bz, bt, lane, f, par ^ 1);
+            // the nodes are read again by other lanes
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        }
+        if (d.P > 0 && ((f | flags) & kOwn)) pull_words4(d, tile, word, s_ptab);
     }
 }
 
 // Sweep one tile (block of 512 threads, one voxel-step each) to a local fixed
 // point: Jacobi steps through LDS over the 8 in-tile neighbours, the out-of-
-// tile neighbours entering as fixed halos.  For tiles too thin for the rows above.
+// tile neighbours entering as fixed halos.  For tiles too thin for the sweep above.
 __device__ void bsweep_tile(const DevB& d, uint2 item, int par, uint32_t* s_lab, uint32_t* s_flags,
                             const uint32_t* s_ftab, const uint32_t* s_ptab) {
     const uint32_t tile = item.x;
@@ -785,10 +849,10 @@ __device__ void bsweep_tile(const DevB& d, uint2 item, int par, uint32_t* s_lab,
     // that gained bits
     const uint32_t f = s_flags[0];
     if (f && tid < 8) bschedule_face(d, tile, bx, by, bz, bt, tid, f, par ^ 1);
-    // 32 rows of 16 lanes: four to a word
+    // 32 rows of 16 lanes, four to a word
     const uint32_t word = (tid >> 4) & 7;
     if (d.P > 0 && (f || (item.y & kOwn)) && word < (uint32_t)(d.Q + 31) >> 5)
-        pull_row(d, tile, word, tid & 15, tid >> 7, 4, s_ptab);
+        pull_word(d, tile, word, (tid & 15) + 16 * (tid >> 7), s_ptab);
     __syncthreads();
 }
 
@@ -1052,21 +1116,27 @@ void launch_b_prepare(const DevB& d, const int32_t* seeds, int64_t S, hipStream_
     if (d.P > 0) hipLaunchKernelGGL(kb_couple, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, d);
 }
 
+namespace {
+template <int LX, int LY, int LZ, int LT>
+void sweep_shape(const DevB& d, int par, hipStream_t s) {
+    hipLaunchKernelGGL((kb_sweep_tiles<LX, LY, LZ, LT>), dim3(grid_for((uint64_t)d.NTB * ((d.Q + 127) / 128), 4, 1024)),
+                       dim3(256), 0, s, d, par);
+}
+}  // namespace
+
 void launch_b_round(const DevB& d, uint32_t round, hipStream_t s) {
     const int par = round & 1;
     // the shapes of at least 4 x 4 nodes along x and y that the search over tile
     // shapes tries; any other goes through LDS
-    const unsigned rows = grid_for(((uint64_t)d.NTB * ((d.Q + 31) / 32) + 3) / 4, 4, 1024);
-    const int shape = d.lx * 1000 + d.ly * 100 + d.lz * 10 + d.lt;
-    switch (shape) {
-        case 2223: hipLaunchKernelGGL((kb_sweep_rows<2, 2, 2, 3>), dim3(rows), dim3(256), 0, s, d, par); break;
-        case 3222: hipLaunchKernelGGL((kb_sweep_rows<3, 2, 2, 2>), dim3(rows), dim3(256), 0, s, d, par); break;
-        case 3330: hipLaunchKernelGGL((kb_sweep_rows<3, 3, 3, 0>), dim3(rows), dim3(256), 0, s, d, par); break;
-        case 3321: hipLaunchKernelGGL((kb_sweep_rows<3, 3, 2, 1>), dim3(rows), dim3(256), 0, s, d, par); break;
-        case 4221: hipLaunchKernelGGL((kb_sweep_rows<4, 2, 2, 1>), dim3(rows), dim3(256), 0, s, d, par); break;
-        case 4320: hipLaunchKernelGGL((kb_sweep_rows<4, 3, 2, 0>), dim3(rows), dim3(256), 0, s, d, par); break;
-        case 5220: hipLaunchKernelGGL((kb_sweep_rows<5, 2, 2, 0>), dim3(rows), dim3(256), 0, s, d, par); break;
-        case 2322: hipLaunchKernelGGL((kb_sweep_rows<2, 3, 2, 2>), dim3(rows), dim3(256), 0, s, d, par); break;
+    switch (d.lx * 1000 + d.ly * 100 + d.lz * 10 + d.lt) {
+        case 2223: sweep_shape<2, 2, 2, 3>(d, par, s); break;
+        case 3222: sweep_shape<3, 2, 2, 2>(d, par, s); break;
+        case 3330: sweep_shape<3, 3, 3, 0>(d, par, s); break;
+        case 3321: sweep_shape<3, 3, 2, 1>(d, par, s); break;
+        case 4221: sweep_shape<4, 2, 2, 1>(d, par, s); break;
+        case 4320: sweep_shape<4, 3, 2, 0>(d, par, s); break;
+        case 5220: sweep_shape<5, 2, 2, 0>(d, par, s); break;
+        case 2322: sweep_shape<2, 3, 2, 2>(d, par, s); break;
         default: hipLaunchKernelGGL(kb_sweep, dim3(grid_for(d.NTB, 1, 2048)), dim3(512), 0, s, d, par); break;
     }
     if (d.P > 0) {
