@@ -2095,23 +2095,16 @@ int mf4d_grow_batched(mf4d_ctx* c, uint32_t* fplanes, size_t fwords, uint32_t* p
     constexpr uint32_t kChunk = 8;
     uint32_t r = 0;
     while (true) {
-        launch_fill_u32(c->b_counters + BC_ROUNDS, 0, 1, s);
         for (uint32_t k = 0; k < kChunk; ++k) launch_b_round(d, r + k, s);
-        launch_b_work_total(d, 0, s);
-        launch_b_work_total(d, 1, s);
-        HIP_TRY(hipMemcpyAsync(c->h_counters, c->b_counters, BC_NCOUNTERS * sizeof(uint32_t),
-                               hipMemcpyDeviceToHost, s));
-        int rc = sync(c);
+        HIP_TRY(hipEventRecord(c->ev[3], s));
+        launch_b_report(d, c->h_stat, c->h_counters, c->h_seq, ++c->seq, s);
+        int rc = wait_stat(c);
         if (rc) return rc;
         const uint32_t done = c->h_counters[BC_ROUNDS];
         r += done;
         if (done < kChunk || c->h_counters[BC_NWORK0 + (r & 1)] == 0) break;
     }
-    HIP_TRY(hipEventRecord(c->ev[3], s));
-    HIP_TRY(hipMemcpyAsync(c->h_stat, c->stat64, S_NSTAT * sizeof(unsigned long long),
-                           hipMemcpyDeviceToHost, s));
-    int rc = sync(c);
-    if (rc) return rc;
+    HIP_TRY(hipEventSynchronize(c->ev[3]));
     mf4d_stats st{};
     st.rounds = r;
     st.tile_visits = (int64_t)c->h_stat[S_TILE_VISITS];
@@ -2130,7 +2123,7 @@ int mf4d_grow_batched(mf4d_ctx* c, uint32_t* fplanes, size_t fwords, uint32_t* p
         HIP_TRY(hipMemcpyAsync(fplanes, fo, 8 * V * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
         if (P > 0)
             HIP_TRY(hipMemcpyAsync(pplanes, po, 8 * P * Tp * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-        rc = sync(c);
+        const int rc = sync(c);
         if (rc) return rc;
     }
     c->b_grown = owned;

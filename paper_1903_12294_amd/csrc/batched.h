@@ -11,7 +11,7 @@ enum BCounter : int {
     BC_NLIST = 3,  // coupled steps given a place in the list
     BC_DROPPED = 4,
     BC_RACT = 5,    // the current round has work (set by its sweep)
-    BC_ROUNDS = 6,  // rounds that had work (since last cleared by the host)
+    BC_ROUNDS = 6,  // rounds that had work (since last reported)
     BC_NCOUNTERS = 8
 };
 
@@ -63,7 +63,8 @@ void launch_b_prepare(const DevB& d, const int32_t* seeds, int64_t S, hipStream_
 // One round (sweep, close, next list); a round whose work list is empty does
 // nothing, so rounds are queued ahead of the host.
 void launch_b_round(const DevB& d, uint32_t round, hipStream_t s);
-// Total length of the work list of parity par into counters[BC_NWORK0 + par].
-void launch_b_work_total(const DevB& d, int par, hipStream_t s);
+// Statistics and counters (the lists' lengths among them) into pinned memory, seq last.
+void launch_b_report(const DevB& d, unsigned long long* host, uint32_t* host_counters, uint32_t* host_seq,
+                     uint32_t seq, hipStream_t s);
 
 }  // namespace mf4d

@@ -78,10 +78,11 @@ __device__ __forceinline__ Mask8 band_mask(const BandTables& tb, int Q, float v)
 constexpr int kLdsTab = 2 * 257 * 8;
 
 __device__ __forceinline__ void stage_tables(const DevB& d, int type, uint32_t* s_tab) {
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(d.tab + 1024) + (size_t)type * 2 * 257 * 8;
-    for (int i = threadIdx.x; i < (d.Q + 1) * 8; i += blockDim.x) {
-        s_tab[i] = src[i];
-        s_tab[257 * 8 + i] = src[257 * 8 + i];
+    const uint4* src = reinterpret_cast<const uint4*>(d.tab + 1024) + (size_t)type * 2 * 257 * 2;
+    uint4* dst = reinterpret_cast<uint4*>(s_tab);
+    for (int i = threadIdx.x; i < (d.Q + 1) * 2; i += blockDim.x) {
+        dst[i] = src[i];
+        dst[257 * 2 + i] = src[257 * 2 + i];
     }
 }
 
@@ -467,7 +468,7 @@ __device__ __forceinline__ void pull_words4(const DevB& d, uint32_t tile, uint32
 // Bound by the chain list - ranks - labels and faces, and where many tiles wait by
 // the vector memory unit, which takes a cycle for every lane's 32-byte sector
 // whatever its width: a lane moves 16 bytes.  128^3 x 32, 256 queries, 67,600
-// visits of 4 x 4 x 4 x 8 tiles: 1,428 us with the coupled steps; 1,770 with one
+// visits of 4 x 4 x 4 x 8 tiles: 1,330 us with the coupled steps; 1,770 with one
 // word to 32 lanes (which is slower for 8 to 128 queries too: 64^3 x 16, 24
 // queries, a whole call 567 us, here 451); 3,058, and 494 for the steps, with a
 // block of 512 threads per tile passing eight words through LDS and reading every
@@ -859,8 +860,8 @@ __device__ void bsweep_tile(const DevB& d, uint2 item, int par, uint32_t* s_lab,
 __global__ __launch_bounds__(512) void kb_sweep(DevB d, int par) {
     __shared__ uint32_t s_lab[8 * 512];
     __shared__ uint32_t s_flags[4];
-    __shared__ uint32_t s_ftab[kLdsTab];
-    __shared__ uint32_t s_ptab[kLdsTab];
+    __shared__ __attribute__((aligned(16))) uint32_t s_ftab[kLdsTab];
+    __shared__ __attribute__((aligned(16))) uint32_t s_ptab[kLdsTab];
     __shared__ uint32_t s_pref[kBSubs + 1];
     stage_list(work_counts(d, par), s_pref);
     const uint32_t nwork = s_pref[kBSubs];
@@ -927,12 +928,12 @@ __device__ __forceinline__ uint32_t spread_down(uint32_t L, uint32_t A0) {
 // where the voxel is admissible (a plain read of the voxel's labels leaves out
 // what it has; the unions need no answer), and marks the voxel.
 // Bound by the chain of loads list - labels and ranks - voxels.
-// 128^3 x 32, 256 queries, 161,600 visits in 34 rounds: 569 us; 984 with a
+// 128^3 x 32, 256 queries, 161,600 visits in 34 rounds: 541 us; 984 with a
 // lane per word walking the steps.
 template <int G>
 __global__ __launch_bounds__(256) void kb_close(DevB d, int par) {
-    __shared__ uint32_t s_ptab[kLdsTab];
-    __shared__ uint32_t s_ftab[kLdsTab];
+    __shared__ __attribute__((aligned(16))) uint32_t s_ptab[kLdsTab];
+    __shared__ __attribute__((aligned(16))) uint32_t s_ftab[kLdsTab];
     __shared__ uint32_t s_pref[kBSubs + 1];
     if (!d.counters[BC_RACT]) return;
     stage_list(d.dcnt, s_pref);
@@ -1073,11 +1074,22 @@ __global__ __launch_bounds__(256) void kb_compact(DevB d, int par, int first) {
     }
 }
 
-// Total length of the work list of parity par, for the host.
-__global__ void kb_work_total(DevB d, int par) {
-    uint32_t x = d.wcnt[((uint32_t)par * kBSubs + threadIdx.x) * kBCntStride];
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-    if (threadIdx.x == 0) d.counters[BC_NWORK0 + par] = x;
+// The end of a chunk of rounds for the host, one wave: the work lists' lengths,
+// the counters and the statistics into pinned memory, then the sequence number the
+// host polls.  The count of rounds starts again at 0.
+__global__ void kb_report(DevB d, unsigned long long* host, uint32_t* host_counters, uint32_t* host_seq,
+                          uint32_t seq) {
+    const int lane = threadIdx.x;
+    for (int par = 0; par < 2; ++par) {
+        uint32_t x = work_counts(d, par)[lane * kBCntStride];
+        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+        if (lane == 0) host_counters[BC_NWORK0 + par] = x;
+    }
+    if (lane > BC_NWORK1 && lane < BC_NCOUNTERS) host_counters[lane] = d.counters[lane];
+    if (lane < S_NSTAT) host[lane] = d.stat64[lane];
+    if (lane == BC_ROUNDS) d.counters[BC_ROUNDS] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+    if (lane == 0) __hip_atomic_store(host_seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 __global__ void kb_reset(DevB d) {
@@ -1149,8 +1161,9 @@ void launch_b_round(const DevB& d, uint32_t round, hipStream_t s) {
     hipLaunchKernelGGL(kb_compact, dim3(grid_for(d.NTB, 256, 1024)), dim3(256), 0, s, d, par ^ 1, 0);
 }
 
-void launch_b_work_total(const DevB& d, int par, hipStream_t s) {
-    hipLaunchKernelGGL(kb_work_total, dim3(1), dim3(64), 0, s, d, par);
+void launch_b_report(const DevB& d, unsigned long long* host, uint32_t* host_counters, uint32_t* host_seq,
+                     uint32_t seq, hipStream_t s) {
+    hipLaunchKernelGGL(kb_report, dim3(1), dim3(64), 0, s, d, host, host_counters, host_seq, seq);
 }
 
 }  // namespace mf4d
