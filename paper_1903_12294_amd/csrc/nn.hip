@@ -33,6 +33,7 @@ namespace mf4d {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
@@ -102,39 +103,71 @@ __device__ __forceinline__ int halo_shift(int k) {
 template <class T>
 constexpr int pieces() { return sizeof(T) == 4 ? 3 : 1; }
 
-// Stage the (TZ+2)(TY+2)(TX+2)-position input tile, CIN channels of each
-// position (of the 16 stored), zero outside the grid, as matrix operands: plane
-// (piece, 8-channel half) holds 16 bytes (8 bf16) per position, so the 16
-// positions an instruction reads lie side by side (no bank conflict), and an
-// fp32 value is split here, once, not again for each of the 27 offsets.
+// The (TZ+2)(TY+2)(TX+2)-position input tile, CIN channels of each position (of
+// the 16 stored), zero outside the grid, staged as matrix operands: plane (piece,
+// 8-channel half) holds 16 bytes (8 bf16) per position, so the 16 positions an
+// instruction reads lie side by side (no bank conflict), and an fp32 value is
+// split here, once, not again for each of the 27 offsets.  A block of 256
+// threads; each owns the same places of every tile, so their addresses are
+// worked out once and a tile's values can be loaded ahead into registers.
 // T = uint16_t (bf16) or float.
 template <int CIN, class T>
-__device__ void load_halo(const ConvDims& c, const T* __restrict__ x, int n, int z0, int y0, int x0,
-                          uint4* s_x) {
-    constexpr int kHalf = CIN / 8;
-    for (int i = threadIdx.x; i < kHalo * kHalf; i += blockDim.x) {
-        const int p = i / kHalf, v = i % kHalf;
-        const int hx = p % HX, hy = (p / HX) % HY, hz = p / (HX * HY);
-        const int zz = z0 + hz - 1, yy = y0 + hy - 1, xx = x0 + hx - 1;
-        const bool in = zz >= 0 && zz < c.D && yy >= 0 && yy < c.H && xx >= 0 && xx < c.W;
-        const T* src = x + ((((size_t)n * c.D + zz) * c.H + yy) * c.W + xx) * 16 + v * 8;
-        if constexpr (sizeof(T) == 4) {
-            float4 u0 = make_float4(0.f, 0.f, 0.f, 0.f), u1 = u0;
-            if (in) {
-                u0 = reinterpret_cast<const float4*>(src)[0];
-                u1 = reinterpret_cast<const float4*>(src)[1];
-            }
-            const float f[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
-            uint4 hi, mid, lo;
-            split8x3(f, hi, mid, lo);
-            s_x[v * kHalo + p] = hi;
-            s_x[(kHalf + v) * kHalo + p] = mid;
-            s_x[(2 * kHalf + v) * kHalo + p] = lo;
-        } else {
-            s_x[v * kHalo + p] = in ? *reinterpret_cast<const uint4*>(src) : make_uint4(0, 0, 0, 0);
+struct Halo {
+    static constexpr int kHalf = CIN / 8, kItems = kHalo * kHalf, kPer = (kItems + 255) / 256;
+    static constexpr int kVec = sizeof(T) * 8 / 16;  // 16-byte loads per item
+    int rel[kPer];      // positions from the tile's first one (inside the grid below 2^31, as all are)
+    uint32_t at[kPer];  // hx, hy, hz (8 bits each), 1 << 24: none
+    uint4 val[kPer * kVec];
+
+    __device__ __forceinline__ void init(const ConvDims& c) {
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int i = threadIdx.x + u * 256;
+            const int p = i / kHalf;
+            const int hx = p % HX, hy = (p / HX) % HY, hz = p / (HX * HY);
+            rel[u] = (int)(((uint32_t)(hz - 1) * c.H + hy - 1) * c.W + hx - 1);
+            at[u] = i < kItems ? hx | (hy << 8) | (hz << 16) : 1u << 24;
         }
     }
-}
+    __device__ __forceinline__ void load(const ConvDims& c, const T* __restrict__ x, int n, int z0, int y0, int x0) {
+        // (256 is a multiple of kHalf: a thread's items are all of one half)
+        const T* base = x + ((((size_t)n * c.D + z0) * c.H + y0) * c.W + x0) * 16 + threadIdx.x % kHalf * 8;
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const uint32_t hx = at[u] & 255u, hy = (at[u] >> 8) & 255u, hz = at[u] >> 16;
+            const bool in = (uint32_t)(x0 - 1) + hx < (uint32_t)c.W && (uint32_t)(y0 - 1) + hy < (uint32_t)c.H &&
+                            hz < 256u && (uint32_t)(z0 - 1) + hz < (uint32_t)c.D;
+#pragma unroll
+            for (int e = 0; e < kVec; ++e) val[u * kVec + e] = make_uint4(0, 0, 0, 0);
+            if (in) {
+                const uint4* src = reinterpret_cast<const uint4*>(base + (int64_t)rel[u] * 16);
+#pragma unroll
+                for (int e = 0; e < kVec; ++e) val[u * kVec + e] = src[e];
+            }
+        }
+    }
+    __device__ __forceinline__ void stage(uint4* s_x) const {
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int i = threadIdx.x + u * 256;
+            if (i >= kItems) continue;
+            const int p = i / kHalf, v = i % kHalf;
+            if constexpr (sizeof(T) == 4) {
+                const uint4 a = val[2 * u], b = val[2 * u + 1];
+                const float f[8] = {__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z),
+                                    __uint_as_float(a.w), __uint_as_float(b.x), __uint_as_float(b.y),
+                                    __uint_as_float(b.z), __uint_as_float(b.w)};
+                uint4 hi, mid, lo;
+                split8x3(f, hi, mid, lo);
+                s_x[v * kHalo + p] = hi;
+                s_x[(kHalf + v) * kHalo + p] = mid;
+                s_x[(2 * kHalf + v) * kHalo + p] = lo;
+            } else {
+                s_x[v * kHalo + p] = val[u];
+            }
+        }
+    }
+};
 
 // Instructions per 16 x 16 output tile: two offsets x 16 channels or four
 // offsets x 8 channels each.
@@ -166,13 +199,16 @@ enum ConvOut : int { OUT_BF16 = 0, OUT_F32 = 1, OUT_LOGIT = 2 };
 //
 // The weights are the first operand, the positions the second: a lane then
 // holds four consecutive channels of one position, and a wave stores 16 whole
-// positions (512 bytes bf16, 1 KB fp32) in one instruction.  Bound by the
-// latency of a block's load - split - multiply - store phases (512 blocks of
-// work for 256 CUs at 32 x 16^3); the fp32 layers went from 60 to 18 us there
-// and the bf16 ones at 64 x 32^3 from 77 to 66 us when the split moved out of the
-// offset loop and the stores became whole.
+// positions (512 bytes bf16, 1 KB fp32) in one instruction.  A wave takes the four
+// rows of one y, four independent chains, whose LDS addresses differ by constants:
+// no address arithmetic between its multiplies.  A block goes over several tiles,
+// loading the next one's values while it multiplies; the blocks of an XCD (every
+// eighth) take neighbouring tiles, whose halos then meet in its L2.  Bound by the
+// LDS reads (1 KB a multiply) and, at the largest, the activations' traffic.
+// 64 x 32^3, layer 1 / 2 / 3: 30 / 49 / 42 us; 48 / 66 / 57 with a block per tile and the
+// addresses worked out per multiply.
 template <int CIN, class T, int OUT>
-__global__ __launch_bounds__(256) void k_conv(ConvDims c, const T* __restrict__ x, const uint4* __restrict__ wpk,
+__global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 3) void k_conv(ConvDims c, const T* __restrict__ x, const uint4* __restrict__ wpk,
                                               const float* __restrict__ bias, int relu,
                                               const float* __restrict__ mask, void* __restrict__ out, int vec) {
     constexpr int NP = pieces<T>(), NK = ksteps<CIN>(), kHalf = CIN / 8;
@@ -180,65 +216,89 @@ __global__ __launch_bounds__(256) void k_conv(ConvDims c, const T* __restrict__ 
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     const int row = lane & 15, grp = lane >> 4;
     uint4 bw[NK];
+    const uint4* op[NK];  // this lane's operand of each step in the row z = 0
 #pragma unroll
-    for (int j = 0; j < NK; ++j) bw[j] = wpk[j * 64 + lane];
+    for (int j = 0; j < NK; ++j) {
+        int k, c0;
+        step_part<CIN>(j, grp, k, c0);
+        bw[j] = wpk[j * 64 + lane];
+        op[j] = s_x + (c0 >> 3) * kHalo + (HY + wave + 1) * HX + row + 1 + halo_shift(k < 27 ? k : 26);
+    }
+    int k_last, c_last;
+    step_part<CIN>(NK - 1, grp, k_last, c_last);
     v4f b = {0.0f, 0.0f, 0.0f, 0.0f};
     if (bias)
 #pragma unroll
         for (int i = 0; i < 4; ++i) b[i] = bias[4 * grp + i];
     const uint32_t nblocks = (uint32_t)c.N * c.nbz * c.nby * c.nbx;
-    for (uint32_t blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
-        int n, z0, y0, x0;
-        block_origin(c, blk, n, z0, y0, x0);
+    // XCD i % 8 takes the tiles [i * per, (i + 1) * per)
+    const uint32_t per = (nblocks + 7) / 8, first = (blockIdx.x & 7) * per;
+    const uint32_t last = first + per < nblocks ? first + per : nblocks, step = gridDim.x >> 3;
+    uint32_t blk = first + (blockIdx.x >> 3);
+    if (blk >= last) return;  // block-uniform
+    Halo<CIN, T> halo;
+    halo.init(c);
+    int n, z0, y0, x0;
+    block_origin(c, blk, n, z0, y0, x0);
+    halo.load(c, x, n, z0, y0, x0);
+    while (true) {
         __syncthreads();
-        load_halo<CIN>(c, x, n, z0, y0, x0, s_x);
+        halo.stage(s_x);
         __syncthreads();
-        for (int r = wave; r < TZ * TY; r += 4) {
-            const int zl = r / TY, yl = r % TY;
-            const int base = ((zl + 1) * HY + (yl + 1)) * HX + (row + 1);
-            v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
+        const int zb = z0, yb = y0, xb = x0;
+        const size_t pos0 = (((size_t)n * c.D + z0) * c.H + y0) * c.W + x0;
+        blk += step;
+        const bool more = blk < last;  // block-uniform
+        if (more) {
+            block_origin(c, blk, n, z0, y0, x0);
+            halo.load(c, x, n, z0, y0, x0);
+        }
+        v4f acc[TZ];
 #pragma unroll
-            for (int j = 0; j < NK; ++j) {
-                int k, c0;
-                step_part<CIN>(j, grp, k, c0);
-                const int p = (c0 >> 3) * kHalo + base + halo_shift(k < 27 ? k : 26);
+        for (int i = 0; i < TZ; ++i) acc[i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                for (int q = 0; q < NP; ++q) {
-                    uint4 a = s_x[q * kHalf * kHalo + p];
-                    if (k >= 27) a = make_uint4(0, 0, 0, 0);
-                    acc = mfma(bw[j], a, acc);
+        for (int j = 0; j < NK; ++j)
+#pragma unroll
+            for (int q = 0; q < NP; ++q)
+#pragma unroll
+                for (int i = 0; i < TZ; ++i) {
+                    uint4 a = op[j][q * kHalf * kHalo + i * HY * HX];
+                    if (j == NK - 1 && k_last >= 27) a = make_uint4(0, 0, 0, 0);
+                    acc[i] = mfma(bw[j], a, acc[i]);
                 }
-            }
-            // acc[i] = D[output channel 4*grp + i][position x0 + row]
-            const int z = z0 + zl, y = y0 + yl, xx = x0 + row;
-            if (z >= c.D || y >= c.H || xx >= c.W) continue;
-            const size_t pos = (((size_t)n * c.D + z) * c.H + y) * c.W + xx;
-            acc += b;
-            if (relu)
+        // acc[i][e] = D[output channel 4*grp + e][position (zb + i, yb + wave, xb + row)]
+        if (yb + wave < c.H && xb + row < c.W) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[i] = fmaxf(acc[i], 0.0f);
-            if (mask) {
-                const v4f m = *reinterpret_cast<const v4f*>(mask + pos * 16 + 4 * grp);
+            for (int i = 0; i < TZ; ++i) {
+                if (zb + i >= c.D) break;
+                const size_t pos = pos0 + ((uint32_t)(i * c.H + wave) * (uint32_t)c.W + row);
+                v4f r = acc[i] + b;
+                if (relu)
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (!(m[i] > 0.0f)) acc[i] = 0.0f;
-            }
-            if (OUT == OUT_BF16) {
-                const uint2 h = make_uint2(f2bf(acc[0]) | ((uint32_t)f2bf(acc[1]) << 16),
-                                           f2bf(acc[2]) | ((uint32_t)f2bf(acc[3]) << 16));
-                reinterpret_cast<uint2*>(static_cast<uint16_t*>(out) + pos * 16)[grp] = h;
-            } else if (OUT == OUT_F32) {
-                float* o = static_cast<float*>(out) + pos * 16 + 4 * grp;
-                if (vec) {
-                    *reinterpret_cast<v4f*>(o) = acc;
-                } else {
+                    for (int e = 0; e < 4; ++e) r[e] = fmaxf(r[e], 0.0f);
+                if (mask) {
+                    const v4f m = *reinterpret_cast<const v4f*>(mask + pos * 16 + 4 * grp);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) o[i] = acc[i];
+                    for (int e = 0; e < 4; ++e)
+                        if (!(m[e] > 0.0f)) r[e] = 0.0f;
                 }
-            } else if (grp == 0) {
-                static_cast<float*>(out)[pos] = acc[0];
+                if (OUT == OUT_BF16) {
+                    const bf16x4 h = __builtin_convertvector(r, bf16x4);  // to nearest even
+                    *reinterpret_cast<bf16x4*>(static_cast<uint16_t*>(out) + pos * 16 + 4 * grp) = h;
+                } else if (OUT == OUT_F32) {
+                    float* o = static_cast<float*>(out) + pos * 16 + 4 * grp;
+                    if (vec) {
+                        *reinterpret_cast<v4f*>(o) = r;
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) o[e] = r[e];
+                    }
+                } else if (grp == 0) {
+                    static_cast<float*>(out)[pos] = r[0];
+                }
             }
         }
+        if (!more) break;
     }
 }
 
@@ -711,8 +771,9 @@ void conv_launch(int N, int D, int H, int W, const T* x, const uint4* wpk, const
     const ConvDims c = conv_dims(N, D, H, W);
     const uint32_t nb = (uint32_t)c.N * c.nbz * c.nby * c.nbx;
     const int vec = (reinterpret_cast<uintptr_t>(out) & 15) == 0;  // a caller's dx may not be
-    hipLaunchKernelGGL((k_conv<CIN, T, OUT>), dim3(grid_for(nb, 1, 8192)), dim3(256), 0, s, c, x, wpk, bias, relu,
-                       mask, out, vec);
+    // blocks in eighths, one to an XCD, as many as are resident at once (bf16 three a CU, fp32 two)
+    const unsigned blocks = 8 * grid_for(nb, 8, sizeof(T) == 4 ? 64 : 96);
+    hipLaunchKernelGGL((k_conv<CIN, T, OUT>), dim3(blocks), dim3(256), 0, s, c, x, wpk, bias, relu, mask, out, vec);
 }
 
 // Gradients of layer `layer` (and, with loss, the mean loss from part_loss).
