@@ -67,3 +67,55 @@ def test_edges_match_oracle(X, Y, Z, T, P, S, bt, lo, device_seeds):
             assert np.array_equal(g.read_field_mask(), ofm)
             if P:
                 assert np.array_equal(g.read_particle_mask(), opm)
+
+
+@pytest.mark.parametrize("mode", ["both", "forward"])
+@pytest.mark.parametrize("schedule", ["launch", "persistent"])
+@pytest.mark.parametrize("T,P", [(65, 90), (128, 64), (129, 33), (192, 200), (200, 1), (256, 65), (257, 70)])
+def test_long_trajectories_match_oracle(T, P, schedule, mode):
+    """Two to five label words a trajectory, with runs of admissible steps across
+    their boundaries."""
+    from paper_1903_12294_amd import Grower
+    from tests.test_oracle_pins import _random_instance
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"[grow edges] T={T} P={P} {schedule} {mode}", flush=True)
+    rng = np.random.default_rng(T + P)
+    i = _random_instance(rng, 11, 6, 5, T, P, 6)
+    i["attr"] = np.where(rng.random((T, P)) < 0.98, np.float32(1.0), i["attr"]).astype(np.float32)
+    crit = np.array([0.75, np.inf, 0.75, np.inf], np.float32)
+    ofm, opm, ost = oracle_grow(i["field"], i["xyz"], i["attr"], crit, i["seeds"], forward_only=mode == "forward")
+    assert ost["members_particle"] > T // 2
+    with Grower(device=0, schedule=schedule) as g:
+        g.set_trajectory_mode(mode)
+        g.load_field(i["field"])
+        g.load_particles(i["xyz"], i["attr"])
+        g.set_criteria(*crit)
+        g.set_seeds(i["seeds"])
+        for _ in range(2):
+            g.grow()
+            assert np.array_equal(g.read_field_mask(), ofm)
+            assert np.array_equal(g.read_particle_mask(), opm)
+
+
+@pytest.mark.parametrize("P", [31, 32, 33, 8191, 8193, 16385, 300000])
+def test_admission_chunks_match_oracle(P):
+    """Particle counts around the sizes at which a block's share of the admission
+    doubles."""
+    from paper_1903_12294_amd import Grower
+    from tests.test_oracle_pins import _random_instance
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"[grow edges] admission P={P}", flush=True)
+    i = _random_instance(np.random.default_rng(P), 16, 9, 7, 5, P, 4)
+    crit = np.array([0.5, np.inf, 0.75, np.inf], np.float32)
+    ofm, opm, ost = oracle_grow(i["field"], i["xyz"], i["attr"], crit, i["seeds"])
+    assert ost["members_particle"] > P // 10
+    with Grower(device=0) as g:
+        g.load_field(i["field"])
+        g.load_particles(i["xyz"], i["attr"])
+        g.set_criteria(*crit)
+        g.set_seeds(i["seeds"])
+        g.grow()
+        assert np.array_equal(g.read_field_mask(), ofm)
+        assert np.array_equal(g.read_particle_mask(), opm)
