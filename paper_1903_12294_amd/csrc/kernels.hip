@@ -826,23 +826,46 @@ __device__ uint32_t pull_close_wave(const Dev& d, int par, uint32_t wave_id, uin
             mem[k] = ent[k].y != kNoVoxel && pull_tile(d, chg, ent[k].y >> tshift) && test_bit(d.Lf, ent[k].y);
         uint32_t pk[NE];
         unsigned long long nwk[NE];
+        // four sets at a time: their label reads go out together, then their atomics
 #pragma unroll
-        for (int k = 0; k < NE; ++k) {
-            pk[k] = 0;
-            nwk[k] = 0ull;
-            if (!__ballot(mem[k])) continue;  // wave-uniform
-            const uint32_t p = pg.logTpad >= 0 ? ent[k].x >> pg.logTpad : ent[k].x / (uint32_t)pg.Tpad;
-            const uint32_t ts = ent[k].x - p * (uint32_t)pg.Tpad;
-            bool last;
-            const unsigned long long mine =
-                run_or(ent[k].y != kNoVoxel ? p : 0xFFFFFFFFu, mem[k] ? 1ull << ts : 0ull, last);
-            if (!last || !mine) continue;
-            if (!(mine & ~d.Lp[p])) continue;  // joined already: no atomic
-            const unsigned long long cl = close_word(mine, d.Ap[p], d.forward_only);
-            const unsigned long long old = atomicOr(&d.Lp[p], cl);
-            joins += __popcll(mine & ~old);
-            nwk[k] = cl & ~old & ~mine;
-            pk[k] = p;
+        for (int g = 0; g < NE; g += 4) {
+            unsigned long long mine[4], a[4], old[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int k = g + i;
+                mine[i] = 0ull;
+                pk[k] = 0;
+                if (!__ballot(mem[k])) continue;  // wave-uniform
+                const uint32_t p = pg.logTpad >= 0 ? ent[k].x >> pg.logTpad : ent[k].x / (uint32_t)pg.Tpad;
+                const uint32_t ts = ent[k].x - p * (uint32_t)pg.Tpad;
+                bool last;
+                const unsigned long long run =
+                    run_or(ent[k].y != kNoVoxel ? p : 0xFFFFFFFFu, mem[k] ? 1ull << ts : 0ull, last);
+                if (last) {
+                    mine[i] = run;
+                    pk[k] = p;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                old[i] = ~0ull;
+                a[i] = 0ull;
+                if (mine[i]) {
+                    old[i] = d.Lp[pk[g + i]];
+                    a[i] = d.Ap[pk[g + i]];
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                a[i] = close_word(mine[i], a[i], d.forward_only);
+                // (joined already: no atomic)
+                old[i] = mine[i] & ~old[i] ? atomicOr(&d.Lp[pk[g + i]], a[i]) : ~0ull;
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                joins += __popcll(mine[i] & ~old[i]);
+                nwk[g + i] = a[i] & ~old[i] & ~mine[i];
+            }
         }
         while (true) {
             unsigned long long anyn = 0ull;
@@ -1846,7 +1869,7 @@ __global__ __launch_bounds__(256) void k_rounds(Dev d, uint32_t round0, uint32_t
 // __syncthreads between the phases.  It declines the rounds when more than
 // max_tiles candidate tiles or max_list coupled steps turn up: then they run as
 // usual.  Bound by its chains of dependent loads.  32^3 x 8 (12 tiles, 5 rounds):
-// 114 us with its seeds; 210 us, and a launch more, as a cooperative launch over the whole GPU.
+// 104 us with its seeds; 210 us, and a launch more, as a cooperative launch over the whole GPU.
 constexpr int kOneThreads = 512;
 template <int BT>
 __global__ __launch_bounds__(kOneThreads) void k_rounds_one(Dev d, uint32_t round0, uint32_t max_rounds,
