@@ -409,14 +409,16 @@ __device__ __forceinline__ void sweep_tile(const Dev& d, uint32_t tile, int par)
             const uint32_t zp = (uint32_t)__builtin_amdgcn_ds_bpermute(izp, v);
             s[t] = (l[t] | xin[t] | yh[t] | zh[t] | ym | yp | zm | zp) & a[t];
         }
-        // forward along t; each slice's spatial inputs and what reaches it
-        // from the slice before are completed along x (runs) in one fill
-        s[0] = fill_runs32(s[0] | (tm & a[0]), a[0]);
+        // forward and backward along t, then each slice completed along x (runs)
+        // in one fill, independent of the others
+        s[0] |= tm & a[0];
 #pragma unroll
-        for (int t = 1; t < BT; ++t) s[t] = fill_runs32(s[t] | (s[t - 1] & a[t]), a[t]);
-        s[BT - 1] |= fill_runs32(tp & a[BT - 1], a[BT - 1]);
+        for (int t = 1; t < BT; ++t) s[t] |= s[t - 1] & a[t];
+        s[BT - 1] |= tp & a[BT - 1];
 #pragma unroll
-        for (int t = BT - 2; t >= 0; --t) s[t] |= fill_runs32(s[t + 1] & a[t], a[t]);
+        for (int t = BT - 2; t >= 0; --t) s[t] |= s[t + 1] & a[t];
+#pragma unroll
+        for (int t = 0; t < BT; ++t) s[t] = fill_runs32(s[t], a[t]);
         uint32_t diff = 0;
 #pragma unroll
         for (int t = 0; t < BT; ++t) {
@@ -1766,15 +1768,17 @@ __global__ __launch_bounds__(256) void k_round_sweep(Dev d, int par) {
 
 __global__ __launch_bounds__(256) void k_round_pull(Dev d, int par) {
     __shared__ uint32_t s_list[4 * 256];
-    if (!d.counters[C_RACT]) return;
+    // (read together: a wave's time here is its chain of reads)
+    const uint32_t act = load_relaxed(&d.counters[C_RACT]), chg = load_relaxed(&d.counters[C_CHG0 + par]),
+                   n = load_relaxed(&d.counters[C_NLIST]);
+    if (!act) return;
     // the swept list is empty again (its dirty flags were cleared by the sweeps)
     if (blockIdx.x == 0 && threadIdx.x < (unsigned)kWorkSubs)
         d.wcnt[(par * kWorkSubs + threadIdx.x) * kWcntStride] = 0u;
     // no tile's members changed since the last pull (set flags raise the
     // parity's flag word): nothing can join
-    if (!d.pull_all && !d.counters[C_CHG0 + par]) return;
+    if (!d.pull_all && !chg) return;
     const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t n = d.counters[C_NLIST];
     if (d.pg.W == 1) {
         const uint32_t joins =
             pull_close_wave<4, 4>(d, par, tid >> 6, (gridDim.x * blockDim.x) >> 6, n, s_list + 256 * (threadIdx.x >> 6));
@@ -1869,7 +1873,7 @@ __global__ __launch_bounds__(256) void k_rounds(Dev d, uint32_t round0, uint32_t
 // __syncthreads between the phases.  It declines the rounds when more than
 // max_tiles candidate tiles or max_list coupled steps turn up: then they run as
 // usual.  Bound by its chains of dependent loads.  32^3 x 8 (12 tiles, 5 rounds):
-// 104 us with its seeds; 210 us, and a launch more, as a cooperative launch over the whole GPU.
+// 98 us with its seeds; 210 us, and a launch more, as a cooperative launch over the whole GPU.
 constexpr int kOneThreads = 512;
 template <int BT>
 __global__ __launch_bounds__(kOneThreads) void k_rounds_one(Dev d, uint32_t round0, uint32_t max_rounds,
