@@ -187,15 +187,14 @@ __device__ __forceinline__ void step_part(int j, int g, int& k, int& c0) {
     }
 }
 
-enum ConvOut : int { OUT_BF16 = 0, OUT_F32 = 1, OUT_LOGIT = 2 };
+enum ConvOut : int { OUT_BF16 = 0, OUT_F32 = 1 };
 
 // out = conv(x, w) + bias, optionally ReLU, optionally zero where mask <= 0
 // (mask: the layer's forward activation, fp32 [..][16]: the ReLU derivative).
 // x: T [..][16], CIN channels read; fp32 inputs as three bf16 operands.  wpk:
 // packed weight operands, [ksteps][64 lanes] x 16 bytes.  Output OUT_BF16: bf16
 // [..][16]; OUT_F32: fp32 [..][16] (16-byte stores with vec, else one value at
-// a time for a caller's unaligned buffer); OUT_LOGIT: channel 0 as fp32
-// [N][D][H][W].
+// a time for a caller's unaligned buffer).
 //
 // The weights are the first operand, the positions the second: a lane then
 // holds four consecutive channels of one position, and a wave stores 16 whole
@@ -205,7 +204,7 @@ enum ConvOut : int { OUT_BF16 = 0, OUT_F32 = 1, OUT_LOGIT = 2 };
 // loading the next one's values while it multiplies; the blocks of an XCD (every
 // eighth) take neighbouring tiles, whose halos then meet in its L2.  Bound by the
 // LDS reads (1 KB a multiply) and, at the largest, the activations' traffic.
-// 64 x 32^3, layer 1 / 2 / 3: 30 / 49 / 42 us; 48 / 66 / 57 with a block per tile and the
+// 64 x 32^3, layers 1 and 2: 30 and 49 us; 48 and 66 with a block per tile and the
 // addresses worked out per multiply.
 template <int CIN, class T, int OUT>
 __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 3) void k_conv(ConvDims c, const T* __restrict__ x, const uint4* __restrict__ wpk,
@@ -285,7 +284,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 3) void k_conv(ConvDims c
                 if (OUT == OUT_BF16) {
                     const bf16x4 h = __builtin_convertvector(r, bf16x4);  // to nearest even
                     *reinterpret_cast<bf16x4*>(static_cast<uint16_t*>(out) + pos * 16 + 4 * grp) = h;
-                } else if (OUT == OUT_F32) {
+                } else {
                     float* o = static_cast<float*>(out) + pos * 16 + 4 * grp;
                     if (vec) {
                         *reinterpret_cast<v4f*>(o) = r;
@@ -293,11 +292,89 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 3) void k_conv(ConvDims c
 #pragma unroll
                         for (int e = 0; e < 4; ++e) o[e] = r[e];
                     }
-                } else if (grp == 0) {
-                    static_cast<float*>(out)[pos] = r[0];
                 }
             }
         }
+        if (!more) break;
+    }
+}
+
+// The last layer, one output channel: out[position] (fp32 [N][D][H][W]) = conv(x, w)
+// + bias over 16 channels.  As 16 output channels of which one is real it would
+// take 14 multiplies, each reading 1 KB of LDS, for 16 positions.  Here the rows of
+// the first operand are the nine (dz, dy) instead (row 4 (dz + 1) + dy + 1), its
+// columns dx and the channels: two multiplies give a row of 16 positions' part of
+// all nine, 72 a tile instead of 224.  A wave goes over the rows y of one z and
+// adds the parts of dy in registers; those of dz, one in each group of 16 lanes,
+// meet in LDS.  wpk: the operand of k_conv (offset k, channels 8h ..: step k / 2, lane
+// 32 (k & 1) + 16 h).  Tiles, blocks and loads ahead as in k_conv.
+// 64 x 32^3: 27 us, 42 as one of 16 channels.
+template <class T>
+__global__ __launch_bounds__(256) void k_logit(ConvDims c, const T* __restrict__ x, const uint4* __restrict__ wpk,
+                                               const float* __restrict__ bias, float* __restrict__ out) {
+    constexpr int NP = pieces<T>();
+    __shared__ uint4 s_x[NP * 2 * kHalo];
+    __shared__ float s_o[HZ][3][TY][TX];
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const int row = lane & 15, grp = lane >> 4, half = grp & 1;
+    // step 0: dx = -1 (groups 0, 1) and 0 (groups 2, 3); step 1: dx = 1 (groups 0, 1)
+    const int dxi[2] = {grp >> 1, 2};
+    uint4 bw[2];
+    const uint4* op[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const bool real = row >> 2 < 3 && (row & 3) < 3 && (j == 0 || grp < 2);
+        const int k = (row >> 2) * 9 + (row & 3) * 3 + dxi[j];
+        bw[j] = real ? wpk[(k >> 1) * 64 + (k & 1) * 32 + half * 16] : make_uint4(0, 0, 0, 0);
+        op[j] = s_x + half * kHalo + row + dxi[j];
+    }
+    const float b = bias[0];
+    const uint32_t nblocks = (uint32_t)c.N * c.nbz * c.nby * c.nbx;
+    const uint32_t per = (nblocks + 7) / 8, first = (blockIdx.x & 7) * per;
+    const uint32_t last = first + per < nblocks ? first + per : nblocks, step = gridDim.x >> 3;
+    uint32_t blk = first + (blockIdx.x >> 3);
+    if (blk >= last) return;  // block-uniform
+    Halo<16, T> halo;
+    halo.init(c);
+    int n, z0, y0, x0;
+    block_origin(c, blk, n, z0, y0, x0);
+    halo.load(c, x, n, z0, y0, x0);
+    while (true) {
+        __syncthreads();
+        halo.stage(s_x);
+        __syncthreads();
+        const int zb = z0, yb = y0, xb = x0;
+        const size_t pos0 = (((size_t)n * c.D + z0) * c.H + y0) * c.W + x0;
+        blk += step;
+        const bool more = blk < last;  // block-uniform
+        if (more) {
+            block_origin(c, blk, n, z0, y0, x0);
+            halo.load(c, x, n, z0, y0, x0);
+        }
+        for (int hz = wave; hz < HZ; hz += 4) {  // wave-uniform
+            v4f acc[HY];
+#pragma unroll
+            for (int hy = 0; hy < HY; ++hy) acc[hy] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int q = 0; q < NP; ++q)
+#pragma unroll
+                    for (int hy = 0; hy < HY; ++hy) {
+                        uint4 a = op[j][q * 2 * kHalo + (hz * HY + hy) * HX];
+                        if (j == 1 && grp >= 2) a = make_uint4(0, 0, 0, 0);
+                        acc[hy] = mfma(bw[j], a, acc[hy]);
+                    }
+            // acc[hy][i]: dy = i - 1, dz = grp - 1 of the row (hz, hy): for output y = hy - i, z = hz - grp
+            if (grp < 3)
+#pragma unroll
+                for (int y = 0; y < TY; ++y) s_o[hz][grp][y][row] = (acc[y][0] + acc[y + 1][1]) + acc[y + 2][2];
+        }
+        __syncthreads();
+        const int z = zb + wave, y = yb + grp, xx = xb + row;  // a position a thread
+        if (z < c.D && y < c.H && xx < c.W)
+            out[pos0 + ((uint32_t)(wave * c.H + grp) * (uint32_t)c.W + row)] =
+                ((s_o[wave][0][grp][row] + s_o[wave + 1][1][grp][row]) + s_o[wave + 2][2][grp][row]) + b;
         if (!more) break;
     }
 }
@@ -776,6 +853,16 @@ void conv_launch(int N, int D, int H, int W, const T* x, const uint4* wpk, const
     hipLaunchKernelGGL((k_conv<CIN, T, OUT>), dim3(blocks), dim3(256), 0, s, c, x, wpk, bias, relu, mask, out, vec);
 }
 
+template <class T>
+void logit_launch(int N, int D, int H, int W, const T* x, const uint4* wpk, const float* bias, float* out,
+                  hipStream_t s) {
+    const ConvDims c = conv_dims(N, D, H, W);
+    const uint32_t nb = (uint32_t)c.N * c.nbz * c.nby * c.nbx;
+    // as many as are resident at once (bf16 four a CU, fp32 two)
+    const unsigned blocks = 8 * grid_for(nb, 8, sizeof(T) == 4 ? 64 : 128);
+    hipLaunchKernelGGL((k_logit<T>), dim3(blocks), dim3(256), 0, s, c, x, wpk, bias, out);
+}
+
 // Gradients of layer `layer` (and, with loss, the mean loss from part_loss).
 template <int CIN, class T>
 void wgrad_launch(int N, int D, int H, int W, const T* x, const float* dz, float* part_w, float* part_b,
@@ -799,14 +886,14 @@ void launch_infer(int N, int D, int H, int W, const uint16_t* x, const uint4* wp
                   uint16_t* a1, uint16_t* a2, float* logits, hipStream_t s) {
     conv_launch<8, uint16_t, OUT_BF16>(N, D, H, W, x, wpk + 0 * kPackSlot, bias, 1, nullptr, a1, s);
     conv_launch<16, uint16_t, OUT_BF16>(N, D, H, W, a1, wpk + 1 * kPackSlot, bias + 16, 1, nullptr, a2, s);
-    conv_launch<16, uint16_t, OUT_LOGIT>(N, D, H, W, a2, wpk + 2 * kPackSlot, bias + 32, 0, nullptr, logits, s);
+    logit_launch<uint16_t>(N, D, H, W, a2, wpk + 2 * kPackSlot, bias + 32, logits, s);
 }
 
 void launch_train_forward(int N, int D, int H, int W, const uint16_t* x, const uint4* wpk, const float* bias,
                           float* a1, float* a2, float* logits, hipStream_t s) {
     conv_launch<8, uint16_t, OUT_F32>(N, D, H, W, x, wpk + 0 * kPackSlot, bias, 1, nullptr, a1, s);
     conv_launch<16, float, OUT_F32>(N, D, H, W, a1, wpk + 1 * kPackSlot, bias + 16, 1, nullptr, a2, s);
-    conv_launch<16, float, OUT_LOGIT>(N, D, H, W, a2, wpk + 2 * kPackSlot, bias + 32, 0, nullptr, logits, s);
+    logit_launch<float>(N, D, H, W, a2, wpk + 2 * kPackSlot, bias + 32, logits, s);
 }
 
 void launch_train_backward(int N, int D, int H, int W, const uint16_t* x, const uint4* wpk, const float* logits,
