@@ -2284,7 +2284,7 @@ int mf4d_slic_set_params(mf4d_ctx* c, const int* k4, float w_d, float w_f, float
         dev_free(c->mbuf);
         c->merged = false;
         c->sK = 0;
-        int rc = dev_alloc(&c->sacc, (size_t)K * kSlicAcc);
+        int rc = dev_alloc(&c->sacc, (size_t)K * slic_copies(K) * kSlicAcc);
         if (!rc) rc = dev_alloc(&c->scen, (size_t)K * 6);
         if (!rc) rc = dev_alloc(&c->scen32, (size_t)K * 8);
         if (!rc) rc = dev_alloc(&c->scnt, (size_t)K * 2);
@@ -2370,6 +2370,7 @@ int mf4d_slic_run(mf4d_ctx* c, int* iterations) {
     s.sattr = P ? c->sattr : nullptr;
     s.labels = c->slabels;
     s.acc = c->sacc;
+    s.copies = slic_copies(c->sK);
     s.cen = c->scen;
     s.cen32 = c->scen32;
     s.cnt = c->scnt;

@@ -12,6 +12,11 @@ namespace mf4d {
 // value) and the counts of field and point samples, as 64-bit integers.
 enum SlicAcc : int { SA_X = 0, SA_Y, SA_Z, SA_T, SA_P, SA_F, SA_NF, SA_NP, kSlicAcc = 8 };
 
+// Copies of the centres' sums, among which the blocks spread their additions: up to
+// eight while they are few (the update reads them all: 1 us more for 128 centres
+// in eight copies).  35 x 28 x 10 x 44, 6 centres: 16 us a pass, 58 with one copy.
+constexpr int slic_copies(int64_t K) { return K <= 32 ? 8 : K <= 64 ? 4 : K <= 128 ? 2 : 1; }
+
 // Device counters of a run.
 enum SlicCounter : int {
     SC_MOVED = 0,   // centres whose values changed by more than eps this update
@@ -36,7 +41,8 @@ struct DevS {
     const float* sattr;  // [Tp * P]: their values, same order
     int32_t* labels;     // [V + Tp * P]: field samples [T][Z][Y][X], then point samples in
                          // visiting order
-    unsigned long long* acc;  // [K][kSlicAcc]
+    unsigned long long* acc;  // [copies][K][kSlicAcc]
+    int copies;               // of the sums, a power of two (slic_copies)
     double* cen;         // [K][6]: x, y, z, t, p, f
     float* cen32;        // [K][8]: the same rounded to fp32, then 2 unused
     long long* cnt;      // [K][2]: field and point samples of each centre

@@ -30,6 +30,13 @@ CASES = [
     # one term so far above the others that many distances agree to the last
     # place, where the oracle (no fused products) may rank them otherwise
     ("great weights",    35,  15, 9,  4,  128, (5, 3, 3, 2),    (1e20, 1e30, 1e25), 1e15, 2, False),
+    # the sums' copies: 8, 4, 4, 2, 2, 1
+    ("32 centres",       44,  18, 9,  5,  700, (4, 4, 2, 1),    (1.0, 4.0, 4.0), 1.0, 3, True),
+    ("33 centres",       44,  18, 9,  5,  700, (11, 3, 1, 1),   (1.0, 4.0, 4.0), 1.0, 3, True),
+    ("64 centres",       44,  18, 9,  5,  700, (4, 4, 2, 2),    (1.0, 4.0, 4.0), 1.0, 3, True),
+    ("65 centres",       44,  18, 9,  5,  700, (13, 5, 1, 1),   (1.0, 4.0, 4.0), 1.0, 3, True),
+    ("128 centres",      44,  18, 9,  5,  700, (8, 4, 2, 2),    (1.0, 4.0, 4.0), 1.0, 3, True),
+    ("129 centres",      44,  18, 9,  5,  700, (43, 3, 1, 1),   (1.0, 4.0, 4.0), 1.0, 3, True),
     ("many blocks",      160, 96, 80, 8,  3000, (10, 6, 5, 2),  (1.0, 8.0, 8.0), 2.0, 3, False),
 ]
 
