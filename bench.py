@@ -45,10 +45,10 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, published
 # HBM bytes per launch read from the FETCH_SIZE / WRITE_SIZE counters (scaled by a
 # 1 GiB copy), per (kernel, library version); a kernel changed since then has none.
-# Source: profiles/grow_256x256x256x64_bt16_launch_hbm_counters.md (0.7.7).
+# Source: profiles/grow_256x256x256x64_bt16_launch_hbm_counters.md (0.8.0).
 MEASURED_TRAFFIC = {
-    ("k_round_pull", "mf4d 0.7.7 (gfx950)"): 45795399,
-    ("k_round_sweep<16>", "mf4d 0.7.7 (gfx950)"): 14023401,
+    ("k_round_pull", "mf4d 0.8.0 (gfx950)"): 47965501,
+    ("k_round_sweep<16>", "mf4d 0.8.0 (gfx950)"): 14037289,
 }
 PREDICTOR = os.path.join(ROOT, "paper_1903_12294_amd", "predictor.npy")
 

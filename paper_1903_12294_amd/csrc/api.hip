@@ -836,7 +836,7 @@ extern "C" {
 
 // Bumped whenever a kernel changes: autotuner caches and recorded hardware
 // counter figures are keyed by it.
-const char* mf4d_version(void) { return "mf4d 0.7.7 (gfx950)"; }
+const char* mf4d_version(void) { return "mf4d 0.8.0 (gfx950)"; }
 
 const char* mf4d_last_error(void) { return g_err.c_str(); }
 
