@@ -102,6 +102,33 @@ void dev_free(T*& p) {
     p = nullptr;
 }
 
+// Whether kernels may read `bytes` at a caller's device pointer directly.  Whole
+// inside one allocation of this device: yes.  Inside an allocation that ends
+// before them: refused here, as a copy would refuse it (a kernel would read past
+// its end).  Anything else that a copy accepts (pinned or plain host memory,
+// another device's, mapped address ranges): no, it has to be copied.
+int device_readable(const void* p, size_t bytes, int device, bool* direct) {
+    *direct = false;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
+        (void)hipGetLastError();
+        return MF4D_OK;
+    }
+    const size_t at = (size_t)((const char*)p - (const char*)base);
+    if (at > size || bytes > size - at)
+        return fail(MF4D_ERR_HIP, "%zu bytes at a device pointer, its allocation ends after %zu", bytes,
+                    at > size ? (size_t)0 : size - at);
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return MF4D_OK;
+    }
+    *direct = a.type == hipMemoryTypeDevice && !a.isManaged && a.device == device &&
+              (reinterpret_cast<uintptr_t>(p) & (sizeof(float) - 1)) == 0;
+    return MF4D_OK;
+}
+
 int ilog2(int v) {
     int r = 0;
     while ((1 << r) < v) ++r;
@@ -1009,18 +1036,23 @@ int mf4d_load_field(mf4d_ctx* c, const float* field, int X, int Y, int Z, int T,
         free_field(c);
         return rc;
     }
-    // a device field is copied by the pass that summarises its tiles
-    if (where == MF4D_HOST) {
-        const hipError_t e = hipMemcpyAsync(c->field, field, V * sizeof(float), hipMemcpyHostToDevice, c->stream);
-        if (e != hipSuccess) {
-            free_field(c);
-            return fail(MF4D_ERR_HIP, "field upload failed: %s", hipGetErrorString(e));
-        }
+    // a field in this device's memory is copied by the pass that summarises its tiles
+    bool direct = false;
+    if (where == MF4D_DEVICE) rc = device_readable(field, V * sizeof(float), c->device, &direct);
+    if (!rc && !direct) {
+        const hipError_t e = hipMemcpyAsync(c->field, field, V * sizeof(float),
+                                            where == MF4D_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice,
+                                            c->stream);
+        if (e != hipSuccess) rc = fail(MF4D_ERR_HIP, "field upload failed: %s", hipGetErrorString(e));
+    }
+    if (rc) {
+        free_field(c);
+        return rc;
     }
     launch_fill_u32(c->Af, 0, g.nwords, c->stream);
     launch_fill_u32(c->Lf, 0, g.nwords, c->stream);
-    if (where == MF4D_HOST) launch_summaries(g, c->field, nullptr, c->tsum, c->stream);
-    else launch_summaries(g, field, c->field, c->tsum, c->stream);
+    if (direct) launch_summaries(g, field, c->field, c->tsum, c->stream);
+    else launch_summaries(g, c->field, nullptr, c->tsum, c->stream);
     c->bstats_valid = false;
     rc = sync(c);
     if (rc) {
