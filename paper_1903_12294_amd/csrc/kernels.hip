@@ -953,14 +953,15 @@ __device__ uint32_t wait_epoch(const Dev& d, uint32_t e) {
     return ok;
 }
 
-__device__ bool grid_sync(const Dev& d, uint32_t& epoch) {
+// The first nblk blocks of the grid meet.
+__device__ bool grid_sync(const Dev& d, uint32_t nblk, uint32_t& epoch) {
     __shared__ uint32_t s_ok;
     __syncthreads();
-    if (threadIdx.x == 0 && gridDim.x <= kBarFlat) {
+    if (threadIdx.x == 0 && nblk <= kBarFlat) {
         // few arrivals (at most 0.4 us of them serialised): one level
         const uint32_t e = ++epoch;
         if (__hip_atomic_fetch_add(d.bar + kBarTop, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT) + 1 ==
-            e * gridDim.x) {
+            e * nblk) {
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             __hip_atomic_store(d.bar + kBarGen, e, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -968,8 +969,8 @@ __device__ bool grid_sync(const Dev& d, uint32_t& epoch) {
     } else if (threadIdx.x == 0) {
         const uint32_t e = ++epoch;
         const uint32_t j = blockIdx.x % kBarSubs;
-        const uint32_t nsub = gridDim.x / kBarSubs + (j < gridDim.x % kBarSubs ? 1u : 0u);
-        const uint32_t nact = gridDim.x < (uint32_t)kBarSubs ? gridDim.x : (uint32_t)kBarSubs;
+        const uint32_t nsub = nblk / kBarSubs + (j < nblk % kBarSubs ? 1u : 0u);
+        const uint32_t nact = nblk < (uint32_t)kBarSubs ? nblk : (uint32_t)kBarSubs;
         // Arrivals release; only a last arrival needs to acquire what the
         // others released before it passes them on (fence after the RMW).
         const uint32_t old = __hip_atomic_fetch_add(d.bar + kBarSub0 + 32 * j, 1u, __ATOMIC_RELEASE,
@@ -1805,18 +1806,36 @@ __global__ __launch_bounds__(256) void k_round_close(Dev d, int par) {
 
 // ---- all rounds in one cooperative launch ----
 // Pull entries and pushes per lane per wave step inside the persistent kernel:
-// its grid (two blocks per CU) has a quarter of the waves a launched pull has,
-// so each wave takes more entries at once, and pushes more at once, instead of
-// running the chain of round trips several times over.
+// its grid (at most two blocks per CU) has at most a quarter of the waves a
+// launched pull has, so each wave takes more entries at once, and pushes more at
+// once, instead of running the chain of round trips several times over.
 constexpr int kCoopNE = 8;
+
+// Blocks a round can use.  Every block that takes part arrives at every barrier
+// and invalidates its L2 there, and a round's list holds a small part of the
+// tiles: 64 tiles to a block (157 x 101 x 75 x 21, 255 active tiles, 7 rounds: 398 us
+// per grow and read-outs with 30 blocks, 407 with 16, 427 with 8; 643 with 512, before
+// quiet pulls were skipped).  But every pull goes over the whole coupled list:
+// 2,048 of its steps to a block, one step of its four waves.  128^3 x 32 with
+// 262,144 particles, 30% (90%) of it admitted: 1,228 (1,385) us; 3,414 (5,621) with
+// the 64 blocks that the tiles call for, 1,375 (1,544) with 512 before the other
+// changes to a grow; with 0.02 admitted 259 us, 271 with 64 blocks.  64^3 x 16, 90%: 365
+// us with 2,048 steps, 392 with 4,096, 659 with 16,384.
+__host__ __device__ inline uint32_t rounds_blocks(uint32_t tiles, uint64_t steps) {
+    const uint64_t use = tiles / 64u > (steps >> 11) ? tiles / 64u : steps >> 11;
+    return use < 8 ? 8u : use > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)use;
+}
 
 template <int BT>
 __global__ __launch_bounds__(256) void k_rounds(Dev d, uint32_t round0, uint32_t max_rounds) {
     __shared__ uint32_t s_list[4 * 64 * kCoopNE];
     __shared__ uint32_t s_cnt;
+    // blocks that take part: by the coupled steps the admission found (the same in every block)
+    const uint32_t nblk = min(rounds_blocks(d.g.NT, d.pg.P > 0 ? d.counters[C_NLIST] : 0u), gridDim.x);
+    if (blockIdx.x >= nblk) return;  // block-uniform
     uint32_t epoch = 0;
     const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t nthreads = gridDim.x * blockDim.x;
+    const uint32_t nthreads = nblk * blockDim.x;
     const uint32_t wave0 = tid >> 6, nwaves = nthreads >> 6;
     const bool parts = d.pg.P > 0;
     uint32_t* my_list = s_list + 64 * kCoopNE * (threadIdx.x >> 6);
@@ -1837,7 +1856,7 @@ __global__ __launch_bounds__(256) void k_rounds(Dev d, uint32_t round0, uint32_t
         if (tid == 0) store_relaxed(&d.counters[C_CHG0 + (par ^ 1)], 0u);
         sweep_phase<BT>(d, par, wave0, nwaves);
         visits += nwork;  // only thread 0 records it
-        if (!grid_sync(d, epoch)) break;
+        if (!grid_sync(d, nblk, epoch)) break;
         // pull (fused with close and push for one label word per particle)
         if (tid < (unsigned)kWorkSubs) store_relaxed(&d.wcnt[(par * kWorkSubs + tid) * kWcntStride], 0u);
         // (no tile's members changed since the last pull: nothing can join)
@@ -1847,12 +1866,12 @@ __global__ __launch_bounds__(256) void k_rounds(Dev d, uint32_t round0, uint32_t
             if (d.pg.W == 1) closed += pull_close_wave<kCoopNE, kCoopNE>(d, par, wave0, nwaves, n, my_list);
             else pull_entries(d, tid, nthreads, n, par);
         }
-        if (!grid_sync(d, epoch)) break;
+        if (!grid_sync(d, nblk, epoch)) break;
         // close and push, for longer trajectories
         if (parts && d.pg.W > 1) {
             const uint32_t c = close_phase(d, par ^ 1, wave0, nwaves, my_list);  // same in every lane
             if (lane_id() == 0) closed += c;
-            if (!grid_sync(d, epoch)) break;
+            if (!grid_sync(d, nblk, epoch)) break;
         }
         ++r;
     }
@@ -2278,17 +2297,11 @@ bool coop_rounds(const Dev& d, uint32_t round0, uint32_t max_rounds, int device,
     }
     Dev dd = d;
     uint32_t r0 = round0, mr = max_rounds;
-    void* args[] = {&dd, &r0, &mr};
     // At most two blocks (8 waves) per CU: measured faster than four at 256^3 x
-    // 64, where more blocks only add barrier arrivals; and no more than a round
-    // can use, since every block of the grid takes part in every barrier (and
-    // invalidates its L2): a round's list holds a small part of the tiles, and
-    // the coupled list a small part of the steps.  157 x 101 x 75 x 21 (255
-    // active tiles, 7 rounds): 643 us per grow and read-outs with 512 blocks, 556
-    // with 30 (and quiet pulls skipped); 32^3 x 8: 418 and 361 us with 8.
-    const uint64_t steps = (uint64_t)d.pg.P * d.pg.Tpad;
-    const uint64_t use = std::max<uint64_t>(std::max<uint64_t>(d.g.NT / 64, steps >> 17), 8);
-    const dim3 grid((unsigned)std::min<uint64_t>(use, (uint64_t)*fit));
+    // 64, where more blocks only add barrier arrivals; and no more than could take
+    // part (those that do not leave at once).
+    const dim3 grid(std::min(rounds_blocks(d.g.NT, (uint64_t)d.pg.P * d.pg.Tpad), (uint32_t)*fit));
+    void* args[] = {&dd, &r0, &mr};
     return hipLaunchCooperativeKernel((const void*)k_rounds<BT>, grid, dim3(256), args, 0, s) ==
            hipSuccess;
 }
