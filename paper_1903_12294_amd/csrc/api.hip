@@ -200,7 +200,7 @@ struct mf4d_ctx {
     bool one_try = false;       // this grow's rounds start in the one-block kernel
     bool few_left = false;      // its few seeds are left to that kernel
     bool one_declined = false;  // the one-block rounds met more work than they take (until data or criteria change)
-    int coop_blocks = 0;      // blocks of the cooperative rounds kernel that fit the device (0: not asked yet)
+    int coop_blocks = 0;      // blocks of this tile depth's cooperative rounds kernel that fit the device (0: not asked yet)
 
     // grow state: 0 nothing grown, 1 converged, 2 stopped by the round cap
     int state = 0;
@@ -971,6 +971,7 @@ int mf4d_set_tile(mf4d_ctx* c, int bt) {
     if (bt != 4 && bt != 8 && bt != 16) return fail(MF4D_ERR_ARG, "tile t-extent %d not in {4,8,16}", bt);
     if (c->has_field) return fail(MF4D_ERR_STATE, "tile shape must be set before the field is loaded");
     c->bt = bt;
+    c->coop_blocks = 0;  // another depth's kernel
     return MF4D_OK;
 }
 
