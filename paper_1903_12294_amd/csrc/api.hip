@@ -197,6 +197,7 @@ struct mf4d_ctx {
     int64_t max_rounds = 0;
     int64_t last_rounds = 0;  // rounds of the last grow that converged (launch mode)
     int ncand = C_NCAND0;     // counter of this grow's candidate tiles (the two take turns)
+    bool one_block = true;      // small volumes may run their rounds in one block
     bool one_try = false;       // this grow's rounds start in the one-block kernel
     bool few_left = false;      // its few seeds are left to that kernel
     bool one_declined = false;  // the one-block rounds met more work than they take (until data or criteria change)
@@ -895,6 +896,10 @@ int mf4d_create(mf4d_ctx** out, int device, void* hip_stream) {
         if (env && strcmp(env, "launch") == 0) c->schedule = MF4D_SCHED_LAUNCH;
         const char* adm = getenv("MF4D_ADMIT");
         if (adm && strcmp(adm, "all") == 0) c->admit_all = 1;
+        // debug switch: 0 sends small volumes through the schedule's own rounds
+        // (the tests compare both)
+        const char* one = getenv("MF4D_ONE_BLOCK");
+        if (one && strcmp(one, "0") == 0) c->one_block = false;
     }
     if (!rc && hipHostMalloc((void**)&c->h_stat, kStatBytes + sizeof(uint32_t)) != hipSuccess)
         rc = fail(MF4D_ERR_OOM, "pinned host allocation failed");
@@ -1431,7 +1436,7 @@ static int grow_begin(mf4d_ctx* c, GrowRun* gr) {
         launch_admit_particles(d, s);
         if (c->timed) HIP_TRY(hipEventRecord(c->ev[2], s));
     }
-    c->one_try = !c->timed && !c->async_grow && !ordered && c->schedule != MF4D_SCHED_JACOBI && !c->one_declined &&
+    c->one_try = c->one_block && !c->timed && !c->async_grow && !ordered && c->schedule != MF4D_SCHED_JACOBI && !c->one_declined &&
                  rounds_one_fits(d);
     c->few_left = c->one_try && c->S <= kFewSeeds;
     if (c->S > kFewSeeds) launch_seeds(d, c->seeds, c->S, s);
