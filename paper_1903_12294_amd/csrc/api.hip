@@ -692,7 +692,7 @@ int queue_chunk(mf4d_ctx* c, const Dev& d, int64_t r, RoundChunk* ch) {
     if (chunk <= 0) return MF4D_OK;
     // a small volume: every round in one block (it may decline)
     if (r == 0 && c->one_try) {
-        launch_rounds_one(d, c->round, cap, take_few(c), c->stream);
+        launch_rounds_one(d, true, c->round, cap, take_few(c), c->stream);
         ch->one = true;
         return queue_finish(c, d, 0, false);
     }
@@ -744,7 +744,7 @@ int run_rounds(mf4d_ctx* c, const Dev& d, int64_t* rounds_done, const RoundChunk
             launch_fill_u32(c->bar, 0, kBarWords, c->stream);
         }
         if (c->one_try) {
-            launch_rounds_one(d, r0, cap, take_few(c), c->stream);
+            launch_rounds_one(d, false, r0, cap, take_few(c), c->stream);
             int rc = queue_finish(c, d, 0, false);
             if (rc) return rc;
             rc = wait_stat(c);

@@ -2444,11 +2444,19 @@ bool launch_rounds_persistent(const Dev& d, uint32_t round0, uint32_t max_rounds
 
 bool rounds_one_fits(const Dev& d) { return d.g.NT <= 512 && (uint64_t)d.pg.P * d.pg.Tpad <= 1u << 19; }
 
-void launch_rounds_one(const Dev& d, uint32_t round0, uint32_t max_rounds, const FewSeeds& f, hipStream_t s) {
-    // Beyond these sizes eight waves fall behind launches over the whole GPU: a
-    // round of launches costs 20 to 25 us, of this kernel about 8 us per eight
-    // tiles of its list and 5 us per 2,048 coupled steps.
-    constexpr uint32_t kTiles = 64, kList = 8192;
+void launch_rounds_one(const Dev& d, bool launched, uint32_t round0, uint32_t max_rounds, const FewSeeds& f,
+                       hipStream_t s) {
+    // Beyond these sizes eight waves fall behind the whole GPU: a round of launches
+    // costs 20 to 25 us, a cooperative one 30 to 40, of this kernel about 8 us per
+    // eight tiles of its list and 5 us per 2,048 coupled steps (every pull goes over
+    // all of them).  us per grow and read-outs, this kernel / the schedule's own rounds:
+    // 64 tiles of depth 8, few of them listed at once 73 / 90 launched, 75 / 104
+    // cooperative, all of them 201 / 150 and 200 / 173; 18 tiles with 2,400 coupled
+    // steps 163 / 154 and 162 / 189, with 4,800 203 / 148 and 205 / 184; 64 tiles with
+    // 3,840 262 / 163 and 268 / 223.  What declines pays about 13 us for the attempt, so the
+    // lines lie above the crossings.
+    constexpr uint32_t kTiles = 64;
+    const uint32_t kList = launched ? 3072 : 8192;
     switch (d.g.BT) {
         case 4: hipLaunchKernelGGL(k_rounds_one<4>, dim3(1), dim3(kOneThreads), 0, s, d, round0, max_rounds, kTiles, kList, f); break;
         case 8: hipLaunchKernelGGL(k_rounds_one<8>, dim3(1), dim3(kOneThreads), 0, s, d, round0, max_rounds, kTiles, kList, f); break;

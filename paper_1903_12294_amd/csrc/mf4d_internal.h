@@ -168,9 +168,10 @@ bool launch_rounds_persistent(const Dev& d, uint32_t round0, uint32_t max_rounds
                               hipStream_t s);
 // Seeds (f.n of them, if any) and rounds in one block, for volumes that fit.  The
 // kernel may decline the rounds on the device (more work than expected): the work
-// lists then hold the seeds' tiles and counters[C_ROUNDS] is 0.
+// lists then hold the seeds' tiles and counters[C_ROUNDS] is 0.  launched: the
+// schedule's own rounds are launches (else a cooperative kernel), which take over earlier.
 bool rounds_one_fits(const Dev& d);
-void launch_rounds_one(const Dev& d, uint32_t round0, uint32_t max_rounds, const FewSeeds& f, hipStream_t s);
+void launch_rounds_one(const Dev& d, bool launched, uint32_t round0, uint32_t max_rounds, const FewSeeds& f, hipStream_t s);
 // End of a grow or of a chunk of `rounds` launched rounds: per-grow statistics
 // folded, statistics and counters to the host (then seq), and the read-outs
 // (fout, pout; either may be null) if the rounds reached the fixed point or
