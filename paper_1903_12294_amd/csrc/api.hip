@@ -200,7 +200,11 @@ struct mf4d_ctx {
     bool one_block = true;      // small volumes may run their rounds in one block
     bool one_try = false;       // this grow's rounds start in the one-block kernel
     bool few_left = false;      // its few seeds are left to that kernel
-    bool one_declined = false;  // the one-block rounds met more work than they take (until data or criteria change)
+    bool one_tried = false;     // this grow queued that kernel, its answer not read yet
+    // The one-block rounds met more work than they take: not tried again until the
+    // data, the criteria, the admissibility mode or the schedule change.
+    bool one_declined = false;
+    bool one_unsure = false;    // the last attempt was declined: the next one does not wait for its answer
     int coop_blocks = 0;      // blocks of this tile depth's cooperative rounds kernel that fit the device (0: not asked yet)
 
     // grow state: 0 nothing grown, 1 converged, 2 stopped by the round cap
@@ -668,14 +672,26 @@ int run_jacobi(mf4d_ctx* c, const Dev& d, int64_t* rounds_done) {
 // events per round).
 struct RoundChunk {
     int64_t n;  // rounds queued (0: the round cap was reached)
-    bool one;   // the one-block kernel, which runs every round it can (n: no bound)
+    bool one;   // the one-block kernel alone, which runs every round it can (n: no bound)
 };
 
-// The seeds left to the one-block kernel (none the second time).
-FewSeeds take_few(mf4d_ctx* c) {
-    const FewSeeds f = c->few_left ? c->few : FewSeeds{};
+// Queue the one-block kernel with the seeds left to it (none the second time).
+// True if the schedule's own rounds are to be queued behind it at once, without
+// waiting for its answer: where the last attempt was declined (64^3 x 16, other
+// criteria every call: 120 us a grow and read-outs, 125 with the wait, 117 without the
+// attempt).  Where the kernel runs the rounds after all, those behind it find empty
+// lists; with a round cap they could pass it.
+bool try_one(mf4d_ctx* c, const Dev& d, bool launched, uint32_t cap) {
+    launch_rounds_one(d, launched, c->round, cap, c->few_left ? c->few : FewSeeds{}, c->stream);
     c->few_left = false;
-    return f;
+    c->one_tried = true;
+    return c->one_unsure && !cap;
+}
+
+// With a grow's counters at hand: what the one-block kernel answered.
+void note_one(mf4d_ctx* c) {
+    if (c->one_tried) c->one_unsure = c->one_declined = c->h_counters[C_DECLINED] != 0;
+    c->one_tried = false;
 }
 
 // Queue the chunk of rounds that starts r rounds into the grow, its
@@ -692,9 +708,11 @@ int queue_chunk(mf4d_ctx* c, const Dev& d, int64_t r, RoundChunk* ch) {
     if (chunk <= 0) return MF4D_OK;
     // a small volume: every round in one block (it may decline)
     if (r == 0 && c->one_try) {
-        launch_rounds_one(d, true, c->round, cap, take_few(c), c->stream);
-        ch->one = true;
-        return queue_finish(c, d, 0, false);
+        c->one_try = false;
+        if (!try_one(c, d, true, cap)) {
+            ch->one = true;
+            return queue_finish(c, d, 0, false);
+        }
     }
     for (int64_t k = 0; k < chunk; ++k) {
         launch_round(d, (uint32_t)(c->round + k), c->stream, c->timed ? c->rev + 4 * k : nullptr);
@@ -721,12 +739,11 @@ int settle_chunk(mf4d_ctx* c, int64_t* r, const RoundChunk& ch, bool* converged)
             HIP_TRY(hipEventElapsedTime(&ms, c->rev[4 * k + ph], c->rev[4 * k + ph + 1]));
             c->ms_phase[ph] += ms;
         }
+    note_one(c);
     c->round += (uint32_t)done;
     *r += done;
     const bool idle = c->h_counters[C_NWORK0] + c->h_counters[C_NWORK1] == 0;
     *converged = idle || (!ch.one && done < ch.n);
-    if (ch.one) c->one_try = false;
-    if (ch.one && !idle && done == 0) c->one_declined = true;
     return MF4D_OK;
 }
 
@@ -743,12 +760,14 @@ int run_rounds(mf4d_ctx* c, const Dev& d, int64_t* rounds_done, const RoundChunk
             launch_fill_u32(c->counters + C_ERR, 0, 2, c->stream);  // C_ERR, C_ROUNDS
             launch_fill_u32(c->bar, 0, kBarWords, c->stream);
         }
-        if (c->one_try) {
-            launch_rounds_one(d, false, r0, cap, take_few(c), c->stream);
+        if (c->one_try && try_one(c, d, false, cap)) {
+            c->one_try = false;
+        } else if (c->one_try) {
             int rc = queue_finish(c, d, 0, false);
             if (rc) return rc;
             rc = wait_stat(c);
             if (rc) return rc;
+            note_one(c);
             const uint32_t done = c->h_counters[C_ROUNDS];
             const bool idle = c->h_counters[C_NWORK0] + c->h_counters[C_NWORK1] == 0;
             if (idle || done) {
@@ -759,7 +778,6 @@ int run_rounds(mf4d_ctx* c, const Dev& d, int64_t* rounds_done, const RoundChunk
                 c->state = idle ? 1 : 2;
                 return MF4D_OK;
             }
-            c->one_declined = true;
             c->one_try = false;
         }
         if (launch_rounds_persistent(d, r0, cap, c->device, &c->coop_blocks, c->stream)) {
@@ -771,6 +789,7 @@ int run_rounds(mf4d_ctx* c, const Dev& d, int64_t* rounds_done, const RoundChunk
             if (rc) return rc;
             c->reads_done = c->rd_f || c->rd_p;
             c->stats_ready = true;
+            note_one(c);
             if (c->h_counters[C_ERR] == 0) {
                 const uint32_t done = c->h_counters[C_ROUNDS];
                 c->round = r0 + done;
@@ -1169,12 +1188,10 @@ int mf4d_set_criteria(mf4d_ctx* c, float f_lo, float f_hi, float a_lo, float a_h
     settle_submit(c);  // a submitted grow first
     if (f_lo != f_lo || f_hi != f_hi || a_lo != a_lo || a_hi != a_hi)
         return fail(MF4D_ERR_ARG, "a criterion bound is NaN");
-    c->crit[0] = f_lo;
-    c->crit[1] = f_hi;
-    c->crit[2] = a_lo;
-    c->crit[3] = a_hi;
+    const float b[4] = {f_lo, f_hi, a_lo, a_hi};
+    if (!c->has_crit || memcmp(b, c->crit, sizeof b) != 0) c->one_declined = false;
+    memcpy(c->crit, b, sizeof b);
     c->has_crit = true;
-    c->one_declined = false;
     c->state = 0;
     return MF4D_OK;
 }
@@ -1251,6 +1268,7 @@ int mf4d_set_admit_mode(mf4d_ctx* c, int mode) {
     settle_submit(c);  // a submitted grow first
     if (mode != MF4D_ADMIT_TILES && mode != MF4D_ADMIT_ALL)
         return fail(MF4D_ERR_ARG, "unknown admissibility mode %d", mode);
+    if (c->admit_all != (mode == MF4D_ADMIT_ALL)) c->one_declined = false;  // what it counts depends on it
     c->admit_all = mode == MF4D_ADMIT_ALL;
     return MF4D_OK;
 }
@@ -1278,6 +1296,7 @@ int mf4d_set_schedule(mf4d_ctx* c, int mode) {
     settle_submit(c);  // a submitted grow first
     if (mode != MF4D_SCHED_PERSISTENT && mode != MF4D_SCHED_LAUNCH && mode != MF4D_SCHED_JACOBI)
         return fail(MF4D_ERR_ARG, "unknown schedule %d", mode);
+    if (c->schedule != mode) c->one_declined = false;  // so do its limits
     c->schedule = mode;
     return MF4D_OK;
 }
@@ -1438,6 +1457,7 @@ static int grow_begin(mf4d_ctx* c, GrowRun* gr) {
     }
     c->one_try = c->one_block && !c->timed && !c->async_grow && !ordered && c->schedule != MF4D_SCHED_JACOBI && !c->one_declined &&
                  rounds_one_fits(d);
+    c->one_tried = false;
     c->few_left = c->one_try && c->S <= kFewSeeds;
     if (c->S > kFewSeeds) launch_seeds(d, c->seeds, c->S, s);
     else if (!c->few_left) launch_seeds_few(d, c->few, s);

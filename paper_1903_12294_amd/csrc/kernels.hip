@@ -1881,7 +1881,8 @@ __global__ __launch_bounds__(256) void k_rounds(Dev d, uint32_t round0, uint32_t
     if (threadIdx.x == 0) slot_add(d, SL_PART_VISITS, s_cnt);
     if (tid == 0 && visits) atomicAdd(&d.stat64[S_TILE_VISITS], (unsigned long long)visits);
     if (tid == 0) {
-        store_relaxed(&d.counters[C_ROUNDS], r - round0);
+        // (none: the one-block kernel before it may have run them)
+        if (r != round0) store_relaxed(&d.counters[C_ROUNDS], r - round0);
         store_relaxed(&d.counters[C_NWORK0 + (r & 1)], nwork);  // what remains (0 when converged)
     }
 }
@@ -1901,7 +1902,10 @@ __global__ __launch_bounds__(kOneThreads) void k_rounds_one(Dev d, uint32_t roun
     if ((int)threadIdx.x < f.n) seed_one(d, f.v + 4 * threadIdx.x);
     __syncthreads();
     const uint32_t n = d.counters[C_NLIST];
-    if (n > max_list || (d.admit_all ? d.g.NT : d.counters[d.ncand]) > max_tiles) return;  // block-uniform
+    if (n > max_list || (d.admit_all ? d.g.NT : d.counters[d.ncand]) > max_tiles) {  // block-uniform
+        if (threadIdx.x == 0) d.counters[C_DECLINED] = 1u;
+        return;
+    }
     const uint32_t wave = threadIdx.x >> 6, nwaves = kOneThreads / 64;
     const bool parts = d.pg.P > 0;
     uint32_t* my_list = s_list + 64 * kCoopNE * wave;
@@ -2453,8 +2457,8 @@ void launch_rounds_one(const Dev& d, bool launched, uint32_t round0, uint32_t ma
     // 64 tiles of depth 8, few of them listed at once 73 / 90 launched, 75 / 104
     // cooperative, all of them 201 / 150 and 200 / 173; 18 tiles with 2,400 coupled
     // steps 163 / 154 and 162 / 189, with 4,800 203 / 148 and 205 / 184; 64 tiles with
-    // 3,840 262 / 163 and 268 / 223.  What declines pays about 13 us for the attempt, so the
-    // lines lie above the crossings.
+    // 3,840 262 / 163 and 268 / 223.  A first attempt that is declined costs about 13 us,
+    // so the lines lie above the crossings.
     constexpr uint32_t kTiles = 64;
     const uint32_t kList = launched ? 3072 : 8192;
     switch (d.g.BT) {

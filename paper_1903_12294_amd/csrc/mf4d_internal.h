@@ -64,12 +64,13 @@ enum Counter : int {
     C_NLIST = 3,   // coupled particle-steps on the flat list
     C_DROPPED = 4, // dropped seeds
     C_ERR = 5,     // set by the persistent kernel if a grid barrier timed out
-    C_ROUNDS = 6,  // rounds completed by the persistent kernel
+    C_ROUNDS = 6,  // rounds completed (that had work)
     C_NCAND0 = 7,  // candidate tiles
     C_RACT = 8,    // launched rounds: 1 if the current round has work (set by its sweep)
     C_JCHANGED = 9,  // Jacobi sweeps: the sweep added a node
     C_CHG0 = 10,   // some tile is flagged changed for round parity 0 (cleared by the sweep of parity 1)
     C_CHG1 = 11,   // likewise for parity 1
+    C_DECLINED = 12,  // the one-block rounds left their work to the schedule's own
     C_NCOUNTERS = 16
 };
 
@@ -168,7 +169,7 @@ bool launch_rounds_persistent(const Dev& d, uint32_t round0, uint32_t max_rounds
                               hipStream_t s);
 // Seeds (f.n of them, if any) and rounds in one block, for volumes that fit.  The
 // kernel may decline the rounds on the device (more work than expected): the work
-// lists then hold the seeds' tiles and counters[C_ROUNDS] is 0.  launched: the
+// lists then hold the seeds' tiles, counters[C_ROUNDS] is 0 and counters[C_DECLINED] 1.  launched: the
 // schedule's own rounds are launches (else a cooperative kernel), which take over earlier.
 bool rounds_one_fits(const Dev& d);
 void launch_rounds_one(const Dev& d, bool launched, uint32_t round0, uint32_t max_rounds, const FewSeeds& f, hipStream_t s);
