@@ -2054,15 +2054,19 @@ __device__ __forceinline__ uint32_t read_field_words(const Dev& d, uint32_t* __r
     return cnt;
 }
 
-// Particle labels -> uint8 [T][P].  A thread owns 16 consecutive particles and,
-// label word by label word, writes their 16 bytes of each step in one store
-// (rows of P bytes that are not whole 16-byte vectors: an unaligned one; the last
-// P % 16 particles byte by byte).
-__device__ __forceinline__ uint32_t read_particles(const Dev& d, uint8_t* __restrict__ out, int vec, uint32_t blk) {
+// Particle labels -> uint8 [T][P].  A thread owns 16 consecutive particles and
+// `seg` steps (16, 32 or 64, or whole label words of 64) and writes their 16 bytes
+// of each step in one store (rows of P bytes that are not whole 16-byte vectors: an
+// unaligned one; the last P % 16 particles byte by byte).  blk: 4,096 particles, then the
+// segment.
+__device__ __forceinline__ uint32_t read_particles(const Dev& d, uint8_t* __restrict__ out, int vec, int seg,
+                                                   uint32_t blk) {
     typedef unsigned int v4u __attribute__((ext_vector_type(4)));
     typedef unsigned int v4u_any __attribute__((ext_vector_type(4), aligned(1)));
     const PGeom& pg = d.pg;
-    const int64_t p0 = (blk * 256ll + threadIdx.x) * 16;
+    const uint32_t nseg = (uint32_t)((pg.T + seg - 1) / seg);
+    const int64_t p0 = (blk / nseg * 256ll + threadIdx.x) * 16;
+    const int t0 = (int)(blk % nseg) * seg, t1 = min(pg.T, t0 + seg);
     uint32_t cnt = 0;
     if (p0 >= pg.P) return 0;
     const int np = (int)min((int64_t)16, pg.P - p0);
@@ -2075,16 +2079,16 @@ __device__ __forceinline__ uint32_t read_particles(const Dev& d, uint8_t* __rest
         for (int k = 0; k < 16; ++k)
             if (k < np) fw[k >> 2] |= (uint32_t)d.pflag[p0 + k] << (8 * (k & 3));
     }
-    const int nw = (pg.T + 63) >> 6;  // words holding real steps
-    for (int w = 0; w < nw; ++w) {
+    for (int w = t0 >> 6; w * 64 < t1; ++w) {
+        const int first = max(t0 - w * 64, 0), end = min(64, t1 - w * 64);  // steps of the word
+        const unsigned long long steps = (~0ull >> (64 - (end - first))) << first;
         unsigned long long lw[16];
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
             lw[k] = (fw[k >> 2] >> (8 * (k & 3))) & 0xFFu ? d.Lp[(size_t)(p0 + k) * pg.W + w] : 0ull;
-            cnt += __popcll(lw[k]);
+            cnt += __popcll(lw[k] & steps);
         }
-        const int tend = min(64, pg.T - w * 64);
-        for (int t = 0; t < tend; ++t) {
+        for (int t = first; t < end; ++t) {
             v4u v;
 #pragma unroll
             for (int j = 0; j < 4; ++j)
@@ -2116,8 +2120,9 @@ __global__ __launch_bounds__(256) void k_read_field_tiles(Dev d, uint32_t* __res
 __global__ __launch_bounds__(256) void k_read_field_words(Dev d, uint32_t* __restrict__ out) {
     block_slot_sum(d, SL_MEMBERS_F, read_field_words(d, out, blockIdx.x, gridDim.x));
 }
-__global__ __launch_bounds__(256) void k_read_particles(Dev d, uint8_t* __restrict__ out, int vec) {
-    block_slot_sum(d, SL_MEMBERS_P, read_particles(d, out, vec, blockIdx.x));
+__global__ __launch_bounds__(256) void k_read_particles(Dev d, uint8_t* __restrict__ out, int vec,
+                                                        int seg) {
+    block_slot_sum(d, SL_MEMBERS_P, read_particles(d, out, vec, seg, blockIdx.x));
 }
 
 // End of a grow, or of a chunk of its launched rounds, in one launch: the first
@@ -2180,7 +2185,7 @@ __global__ __launch_bounds__(256) void k_finish(Dev d, Finish f) {
                                      : read_field_tiles<BT>(d, f.fout, f.fvec, blockIdx.x, sl);
         block_slot_sum(d, SL_MEMBERS_F, cnt);
     } else if (blockIdx.x < f.nf + f.np) {
-        block_slot_sum(d, SL_MEMBERS_P, read_particles(d, f.pout, f.pvec, blockIdx.x - f.nf));
+        block_slot_sum(d, SL_MEMBERS_P, read_particles(d, f.pout, f.pvec, f.pseg, blockIdx.x - f.nf));
     }
 }
 
@@ -2481,7 +2486,18 @@ unsigned field_read_shape(const Geom& g, const uint32_t* out, int& words, int& v
 int particle_read_vec(const PGeom& pg, const uint8_t* out) {
     return (pg.P & 15) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
 }
-unsigned particle_read_blocks(const PGeom& pg) { return (unsigned)((pg.P + 16 * 256 - 1) / (16 * 256)); }
+// Blocks of the particle read-out, and the steps a thread takes: all of them where that
+// leaves kReadBlocks blocks, else 64, 32 or 16.  Few long trajectories had a handful of
+// blocks: a read-out of 28,671 x 192 took 96 us with 7 (76 with four particles to a
+// thread), now 36; 999 x 2,000 686 (566), now 28.
+constexpr unsigned kReadBlocks = 512;
+unsigned particle_read_shape(const PGeom& pg, int& seg) {
+    const unsigned chunks = (unsigned)((pg.P + 16 * 256 - 1) / (16 * 256));
+    seg = (pg.T + 63) / 64 * 64;
+    if (chunks < kReadBlocks) seg = 64;
+    while (seg > 16 && chunks * (unsigned)((pg.T + seg - 1) / seg) < kReadBlocks) seg >>= 1;
+    return chunks * (unsigned)((pg.T + seg - 1) / seg);
+}
 }  // namespace
 
 void launch_finish(const Dev& d, uint32_t* fout, uint8_t* pout, uint32_t rounds, bool always,
@@ -2491,7 +2507,7 @@ void launch_finish(const Dev& d, uint32_t* fout, uint8_t* pout, uint32_t rounds,
     f.pout = pout;
     if (fout) f.nf = field_read_shape(d.g, fout, f.words, f.fvec);
     if (pout && d.pg.P > 0) {
-        f.np = particle_read_blocks(d.pg);
+        f.np = particle_read_shape(d.pg, f.pseg);
         f.pvec = particle_read_vec(d.pg, pout);
     }
     f.rounds = rounds;
@@ -2522,8 +2538,9 @@ void launch_read_field(const Dev& d, uint32_t* out, hipStream_t s) {
 
 void launch_read_particles(const Dev& d, uint8_t* out, hipStream_t s) {
     if (d.pg.P == 0) return;
-    hipLaunchKernelGGL(k_read_particles, dim3(particle_read_blocks(d.pg)), dim3(256), 0, s, d, out,
-                       particle_read_vec(d.pg, out));
+    int seg;
+    const dim3 grid(particle_read_shape(d.pg, seg));
+    hipLaunchKernelGGL(k_read_particles, grid, dim3(256), 0, s, d, out, particle_read_vec(d.pg, out), seg);
 }
 
 void launch_particle_segments(const Dev& d, uint8_t* out, hipStream_t s) {

@@ -92,6 +92,7 @@ struct Finish {
     uint8_t* pout;             // particle mask, or null
     uint32_t nf, np;           // blocks of the two read-outs
     int words, fvec, pvec;     // field by canonical words; 16-byte stores
+    int pseg;                  // particle steps a thread reads out
     uint32_t rounds;           // rounds queued before it (0: unknown)
     int always;                // read out whether or not work is left
     unsigned long long* host;  // pinned: S_NSTAT statistics, C_NCOUNTERS counters, the sequence number
