@@ -287,7 +287,7 @@ struct mf4d_ctx {
     int blog[4] = {3, 2, 2, 2};  // log2 of the batched tile extents (x, y, z, t)
     uint8_t* b_active = nullptr;
     uint32_t* b_vrank = nullptr;  // [V] ranks of the voxel-steps under the query bands
-    uint2* b_prv = nullptr;       // [P][Tpad] ranks and coupled voxel of the particle-steps
+    uint32_t* b_prank = nullptr;  // [P][Tpad] ranks of the particle-steps, and which are coupled
     uint32_t* b_dirty = nullptr;
     uint32_t* b_tile = nullptr;   // 2 x NTB: coupled steps per tile, where they start
     uint2* b_work = nullptr;
@@ -426,7 +426,7 @@ void free_field(mf4d_ctx* c) {
 void drop_particles(mf4d_ctx* c) {
     quiesce_side(c);
     dev_free(c->jlp);
-    dev_free(c->b_prv);
+    dev_free(c->b_prank);
     dev_free(c->porder);
     dev_free(c->spos);
     dev_free(c->sattr);
@@ -2097,8 +2097,8 @@ int mf4d_grow_batched(mf4d_ctx* c, uint32_t* fplanes, size_t fwords, uint32_t* p
         int rc = dev_alloc(&c->b_vrank, (size_t)V);
         if (rc) return rc;
     }
-    if (P > 0 && !c->b_prv) {
-        int rc = dev_alloc(&c->b_prv, (size_t)P * c->pg.Tpad);
+    if (P > 0 && !c->b_prank) {
+        int rc = dev_alloc(&c->b_prank, (size_t)P * c->pg.Tpad);
         if (rc) return rc;
     }
     uint32_t* fo = fplanes;
@@ -2123,7 +2123,7 @@ int mf4d_grow_batched(mf4d_ctx* c, uint32_t* fplanes, size_t fwords, uint32_t* p
     d.field = c->field;
     d.attr_t = c->attr_t;
     d.vrank = c->b_vrank;
-    d.prv = P > 0 ? c->b_prv : nullptr;
+    d.prank = P > 0 ? c->b_prank : nullptr;
     d.bins = c->bins;
     d.fplanes = fo;
     d.pplanes = P > 0 ? po : nullptr;

@@ -37,7 +37,7 @@ struct DevB {
     const float* field;      // fp32 [T][Z][Y][X]
     const float* attr_t;     // fp32 [P][Tpad]
     uint32_t* vrank;         // [V] ranks of each voxel-step: rank_lo | rank_hi << 16
-    uint2* prv;              // [P][Tpad] ranks of each particle-step, likewise; its voxel if coupled, else kNoVoxel
+    uint32_t* prank;         // [P][Tpad] ranks of each particle-step, likewise; bit 15: coupled
     const uint32_t* bins;    // [P][Tpad] tile-layout bit position or kNoVoxel
     uint32_t* fplanes;       // [V][8] labels = output
     uint32_t* pplanes;       // [T][P][8] labels = output

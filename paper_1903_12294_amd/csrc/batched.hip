@@ -12,7 +12,7 @@
 // kept: sweeps, pulls and closes rebuild a node's 256-bit mask from them with
 // two rows of the prefix tables (staged in LDS), no search.  A particle-step
 // that can exchange members with its voxel (some query admits both) is coupled:
-// its voxel is kept beside its ranks, and the coupled steps are listed by tile.
+// a bit beside its ranks says so, and the coupled steps are listed by tile.
 //
 // Field labels are grown in place in the caller's [V][8] output (canonical
 // voxel order); particle labels in the caller's [T][P][8] output.  Work is
@@ -86,9 +86,12 @@ __device__ __forceinline__ void stage_tables(const DevB& d, int type, uint32_t* 
     }
 }
 
+// Packed ranks: rank_lo in the low nine bits (at most 256), rank_hi from bit 16; bit
+// 15 of a particle-step's: coupled.
+constexpr uint32_t kRankLo = 0x1FFu, kCoupled = 1u << 15;
 // Word k of the mask of a node with packed ranks r, from staged tables.
 __device__ __forceinline__ uint32_t rank_word(const uint32_t* s_tab, uint32_t r, int k) {
-    return s_tab[(r & 0xFFFFu) * 8 + k] & s_tab[257 * 8 + (r >> 16) * 8 + k];
+    return s_tab[(r & kRankLo) * 8 + k] & s_tab[257 * 8 + (r >> 16) * 8 + k];
 }
 
 __device__ __forceinline__ BandTables field_tables(const DevB& d) {
@@ -240,9 +243,9 @@ __global__ __launch_bounds__(256) void kb_admit_field(DevB d) {
     }
 }
 
-// Clear the particle planes, record every particle-step's ranks and, where it is
-// coupled (it lies in a voxel and some query admits both), its voxel, counted for
-// the voxel's tile.  Four steps a thread, whose loads and searches interleave.
+// Clear the particle planes, record every particle-step's ranks and whether it is
+// coupled (it lies in a voxel and some query admits both), counted for the voxel's
+// tile.  Four steps a thread, whose loads and searches interleave.
 // 262,144 x 32: 105 us, and 21 to list the coupled steps; 229 with a list appended
 // to by whole blocks.
 __global__ __launch_bounds__(256) void kb_admit_particles(DevB d) {
@@ -298,7 +301,7 @@ __global__ __launch_bounds__(256) void kb_admit_particles(DevB d) {
                 voxel_coords(d, vox[u], x, y, z, t);
                 atomicAdd(&d.tcnt[btile_of(d, x, y, z, t)], 1u);
             }
-            d.prv[e] = make_uint2(r[u], any ? vox[u] : kNoVoxel);
+            d.prank[e] = r[u] | (any ? kCoupled : 0u);
         }
     }
 }
@@ -309,11 +312,11 @@ __global__ __launch_bounds__(256) void kb_couple(DevB d) {
     const uint32_t n = (uint32_t)((uint64_t)d.P * d.Tpad);
     const uint32_t stride = gridDim.x * blockDim.x;
     for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
-        const uint32_t vox = d.prv[e].y;
-        if (vox == kNoVoxel) continue;
+        const uint32_t b = d.bins[e];
+        if (!(d.prank[e] & kCoupled)) continue;
         int x, y, z, t;
-        voxel_coords(d, vox, x, y, z, t);
-        d.clist[atomicSub(&d.tbase[btile_of(d, x, y, z, t)], 1u) - 1] = make_uint2(e, vox);
+        bit_to_xyzt(d.g, b, x, y, z, t);
+        d.clist[atomicSub(&d.tbase[btile_of(d, x, y, z, t)], 1u) - 1] = make_uint2(e, (uint32_t)vindex(d, x, y, z, t));
     }
 }
 
@@ -418,7 +421,7 @@ __device__ __forceinline__ void pull_word(const DevB& d, uint32_t tile, uint32_t
             p[u] = ent[u].x / (uint32_t)d.Tpad;
             at[u] = ((uint64_t)(ent[u].x - p[u] * (uint32_t)d.Tpad) * d.P + p[u]) * 8 + word;
             m[u] = d.fplanes[(uint64_t)ent[u].y * 8 + word];
-            r[u] = d.prv[ent[u].x].x;
+            r[u] = d.prank[ent[u].x];
             lp[u] = d.pplanes[at[u]];
         }
 #pragma unroll
@@ -435,7 +438,7 @@ __device__ __forceinline__ void pull_word(const DevB& d, uint32_t tile, uint32_t
 // Four words of a swept tile handed to its coupled steps by a wave: as pull_word,
 // with 16-byte reads and writes.
 __device__ __forceinline__ uint4 rank_words4(const uint32_t* s_tab, uint32_t r, uint32_t k) {
-    const uint4 a = *reinterpret_cast<const uint4*>(s_tab + (r & 0xFFFFu) * 8 + k);
+    const uint4 a = *reinterpret_cast<const uint4*>(s_tab + (r & kRankLo) * 8 + k);
     const uint4 b = *reinterpret_cast<const uint4*>(s_tab + 257 * 8 + (r >> 16) * 8 + k);
     return make_uint4(a.x & b.x, a.y & b.y, a.z & b.z, a.w & b.w);
 }
@@ -447,7 +450,7 @@ __device__ __forceinline__ void pull_words4(const DevB& d, uint32_t tile, uint32
         uint4* pp = reinterpret_cast<uint4*>(
             d.pplanes + ((uint64_t)(ent.x - p * (uint32_t)d.Tpad) * d.P + p) * 8 + word);
         const uint4 m = *reinterpret_cast<const uint4*>(d.fplanes + (uint64_t)ent.y * 8 + word);
-        const uint4 a = rank_words4(s_ptab, d.prv[ent.x].x, word);
+        const uint4 a = rank_words4(s_ptab, d.prank[ent.x], word);
         const uint4 l = *pp;
         const uint4 g = make_uint4(l.x | (m.x & a.x), l.y | (m.y & a.y), l.z | (m.z & a.z), l.w | (m.w & a.w));
         if ((g.x ^ l.x) | (g.y ^ l.y) | (g.z ^ l.z) | (g.w ^ l.w)) {
@@ -969,13 +972,14 @@ __global__ __launch_bounds__(256) void kb_close(DevB d, int par) {
             }
             const int j = (down ? 2 * npiece - 1 - q : q) * G + step;
             const bool have = valid && j < d.Tp;
-            uint2 rv = make_uint2(0, kNoVoxel);
+            uint32_t rank = 0, bin = kNoVoxel;
             uint32_t l[8], n[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k) l[k] = 0;
             uint4* lp = reinterpret_cast<uint4*>(d.pplanes + ((uint64_t)j * d.P + p) * 8);
             if (have) {
-                rv = d.prv[(uint64_t)p * d.Tpad + j];
+                rank = d.prank[(uint64_t)p * d.Tpad + j];
+                bin = d.bins[(uint64_t)p * d.Tpad + j];
                 const uint4 a = lp[0], b = lp[1];
                 l[0] = a.x; l[1] = a.y; l[2] = a.z; l[3] = a.w;
                 l[4] = b.x; l[5] = b.y; l[6] = b.z; l[7] = b.w;
@@ -986,7 +990,7 @@ __global__ __launch_bounds__(256) void kb_close(DevB d, int par) {
                 n[k] = 0;
                 // (carries exist in pieces of 64 only, one particle to a wave)
                 if (k < nw && __ballot((l[k] | carry[k]) != 0)) {
-                    const uint32_t A = rank_word(s_ptab, rv.x, k);
+                    const uint32_t A = rank_word(s_ptab, rank, k);
                     uint32_t L = l[k];
                     if (npiece == 1) {
                         L = spread_up<G>(L, A);
@@ -1007,9 +1011,12 @@ __global__ __launch_bounds__(256) void kb_close(DevB d, int par) {
             if (any) {
                 lp[0] = make_uint4(l[0] | n[0], l[1] | n[1], l[2] | n[2], l[3] | n[3]);
                 lp[1] = make_uint4(l[4] | n[4], l[5] | n[5], l[6] | n[6], l[7] | n[7]);
-                if (rv.y != kNoVoxel) {
-                    const uint32_t vr = d.vrank[rv.y];
-                    uint32_t* fl = d.fplanes + (uint64_t)rv.y * 8;
+                if (rank & kCoupled) {
+                    int x, y, z, t;
+                    bit_to_xyzt(d.g, bin, x, y, z, t);
+                    const uint64_t v = vindex(d, x, y, z, t);
+                    const uint32_t vr = d.vrank[v];
+                    uint32_t* fl = d.fplanes + v * 8;
                     const uint4 a = reinterpret_cast<const uint4*>(fl)[0], b = reinterpret_cast<const uint4*>(fl)[1];
                     const uint32_t have8[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
                     uint32_t pushed = 0;
@@ -1019,11 +1026,7 @@ __global__ __launch_bounds__(256) void kb_close(DevB d, int par) {
                         if (pw) atomicOr(&fl[k], pw);
                         pushed |= pw;
                     }
-                    if (pushed) {
-                        int x, y, z, t;
-                        voxel_coords(d, rv.y, x, y, z, t);
-                        bmark_voxel(d, x, y, z, t, npar);
-                    }
+                    if (pushed) bmark_voxel(d, x, y, z, t, npar);
                 }
             }
             // the pieces of the way down read what the way up wrote
