@@ -22,8 +22,9 @@
 // fused into the sums and the hardware's square root (1 ulp):
 //   S^2 = (cf*dt)^2 + (dz^2 + (dx^2 + dy^2)),  D = w_v*|v - v_c| + w_d*S,
 // dist2 and distance below.  (The oracle rounds every operation on its own: two
-// centres whose distances from a sample agree to about 2^-22 may rank
-// otherwise there.)
+// centres whose distances from a sample agree to 2^-20 may rank otherwise there.
+// This is the arithmetic that the same distance written with single roundings
+// compiles to: the compiler fuses those too.)
 #include "slic.h"
 
 #include <math.h>
