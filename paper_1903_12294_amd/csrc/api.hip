@@ -780,6 +780,15 @@ int run_rounds(mf4d_ctx* c, const Dev& d, int64_t* rounds_done, const RoundChunk
             }
             c->one_try = false;
         }
+        // The runtime takes a cooperative launch only once the stream's earlier work has
+        // ended, and with three contexts taking turns it sleeps until then (32^3 x 8 past
+        // the one-block limits: 281 us a grow and read-outs, 221 polled for; with one
+        // context 180 and 180).  Small volumes are polled for, in place of the wait for the
+        // one-block kernel's answer; larger ones with one context would lose up to 8 us
+        // (1 x 100 x 100 x 30: 118 and 126).
+        if (c->one_block && rounds_one_fits(d))
+            while (hipStreamQuery(c->stream) == hipErrorNotReady) {
+            }
         if (launch_rounds_persistent(d, r0, cap, c->device, &c->coop_blocks, c->stream)) {
             // read-outs pending run unconditionally: the launch ran every
             // round it was going to
@@ -883,7 +892,7 @@ extern "C" {
 
 // Bumped whenever a kernel changes: autotuner caches and recorded hardware
 // counter figures are keyed by it.
-const char* mf4d_version(void) { return "mf4d 0.8.0 (gfx950)"; }
+const char* mf4d_version(void) { return "mf4d 0.8.1 (gfx950)"; }
 
 const char* mf4d_last_error(void) { return g_err.c_str(); }
 
