@@ -45,11 +45,16 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, published
 # HBM bytes per launch read from the FETCH_SIZE / WRITE_SIZE counters (scaled by a
 # 1 GiB copy), per (kernel, library version); a kernel changed since then has none.
-# Source: profiles/grow_256x256x256x64_bt16_launch_hbm_counters.md (0.8.0).
+# Source: profiles/grow_256x256x256x64_bt16_launch_hbm_counters.md (0.8.1).
 MEASURED_TRAFFIC = {
-    ("k_round_pull", "mf4d 0.8.0 (gfx950)"): 47965501,
-    ("k_round_sweep<16>", "mf4d 0.8.0 (gfx950)"): 14037289,
+    ("k_round_pull", "mf4d 0.8.1 (gfx950)"): 47983909,
+    ("k_round_sweep<16>", "mf4d 0.8.1 (gfx950)"): 14053923,
 }
+# Wave-level vector instructions of a clustering iteration (SQ_INSTS_VALU over the
+# passes of iterations 2 to 6), per (workload, library version), likewise.
+# Source: profiles/slic_256x256x256x64_k16x16x16x4_kernel_trace.md (0.8.1).
+MEASURED_VALU = {("scale-256^3x64", "mf4d 0.8.1 (gfx950)"): 5.253e9}
+VALU_ISSUE_PEAK = 6.144e11  # wave64 vector instructions/s: 256 CUs x 4 SIMDs x 2.4 GHz / 4 cycles
 PREDICTOR = os.path.join(ROOT, "paper_1903_12294_amd", "predictor.npy")
 
 
@@ -80,7 +85,7 @@ def kernel_table(V: int, Q: int, bt: int, st: dict, r: dict, admit_all: bool, la
     rows = {}
     rows["k_admit_field" if admit_all else "k_admit_tiles"] = (
         int(tested * 4 + tested // 4), r["ms_admit_field"], 1)
-    rows["read-out (k_read_field_tiles + k_read_particles16)"] = (
+    rows["read-out (k_read_field_tiles + k_read_particles)"] = (
         int(V // 8 + Q + st["active_tiles"] * tv // 8 + Q // 8), r["ms_read"], 1)
     sweep_b = int(st["tile_visits"] / rounds * visit_bytes(bt))
     pull_b = int(8 * st["coupled_steps"])
@@ -232,7 +237,7 @@ def bench_slic(torch, log, inst, name, k=SLIC_K, cpu_leg=True):
     the 32^3 x 8 workload.  Particles load at the instance's rate."""
     from oracle import segments as oseg
     from oracle import slic as oslic
-    from paper_1903_12294_amd import Grower, synth
+    from paper_1903_12294_amd import Grower, _lib, synth
     dev = torch.device("cuda:0")
     X, Y, Z = inst["dims"]
     T, P = inst["T"], inst["P"]
@@ -328,6 +333,7 @@ def bench_slic(torch, log, inst, name, k=SLIC_K, cpu_leg=True):
     # position and time (16 B), value, label read and write (28 B)
     b = 12 * V + 28 * Qs
     gbs = b / (ms_iter * 1e-3) / 1e9
+    valu = MEASURED_VALU.get((name, _lib.load_library().mf4d_version().decode()))
     log(f"[bench] slic {ms_iter:.2f} ms/iteration, {N / (ms_iter * 1e-3):.3e} samples/s, parity {parity}; "
         f"merge {ms_merge:.2f} ms, {n_feat} features, parity {merge_parity}; "
         f"segments {ms_sseg:.3f} ms, parity {seg_parity}")
@@ -336,15 +342,13 @@ def bench_slic(torch, log, inst, name, k=SLIC_K, cpu_leg=True):
                        f"c_f = {SLIC_CF}",
             "ms_per_iteration": round(ms_iter, 3), "value": round(N / (ms_iter * 1e-3), 1),
             "unit": "samples/s per iteration",
-            # bound by VALU issue in the candidate loop: the field pass's
-            # wave instructions (SQ_INSTS_VALU + SALU + branch + LDS) per second
-            # against 256 CUs x 4 SIMDs x 2.4 GHz / 4 cycles per wave64
-            # instruction, from the counter run in
-            # profiles/slic_256x256x256x64_k16x16x16x4_kernel_trace.md (not
-            # measurable without the profiler)
+            # bound by VALU issue in the candidate loop: vector instructions
+            # per second from the counter run (not measurable without the profiler;
+            # None where this workload has none for this library)
             "roofline": {"bound": "alu (distance evaluation)", "hbm_bytes_per_iteration": b,
                          "achieved_GBps": round(gbs, 1), "hbm_frac": round(gbs / HBM_PEAK_GBS, 4),
-                         "issue_peak_wave_instr_per_s": 6.144e11, "issue_frac_profiled": 0.73},
+                         "issue_peak_wave_instr_per_s": VALU_ISSUE_PEAK,
+                         "issue_frac_profiled": round(valu / (ms_iter * 1e-3) / VALU_ISSUE_PEAK, 3) if valu else None},
             "parity_sampled": parity, "parity_samples": int(len(got)),
             "merge": {"eps_m": SLIC_EPS_M, "ms": round(ms_merge, 3), "features": n_feat,
                       "largest_feature_samples": big, "parity_feature_ids": merge_parity},

@@ -246,7 +246,7 @@ __global__ __launch_bounds__(256) void kb_admit_field(DevB d) {
 // Clear the particle planes, record every particle-step's ranks and whether it is
 // coupled (it lies in a voxel and some query admits both), counted for the voxel's
 // tile.  Four steps a thread, whose loads and searches interleave.
-// 262,144 x 32: 105 us, and 21 to list the coupled steps; 229 with a list appended
+// 262,144 x 32: 98 us, and 22 to list the coupled steps; 229 with a list appended
 // to by whole blocks.
 __global__ __launch_bounds__(256) void kb_admit_particles(DevB d) {
     __shared__ float s_b[512];
