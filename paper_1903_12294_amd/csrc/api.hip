@@ -1166,10 +1166,13 @@ int mf4d_load_particles_rate(mf4d_ctx* c, const float* xyz, const float* attr, i
     const float* dx = xyz;
     const float* da = attr;
     float* copy = c->praw;  // device inputs are copied by the binning pass
-    if (!rc && where == MF4D_HOST) {
-        hipError_t e = hipMemcpyAsync(c->praw, xyz, nxyz * sizeof(float), hipMemcpyHostToDevice, c->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(c->praw + nxyz, attr, nat * sizeof(float), hipMemcpyHostToDevice, c->stream);
+    // (few long trajectories are copied before it: a block of it takes 64 particles with
+    // all their steps.  64 x 20,000: a load of 4.45 ms, 4.93 copied by its one block)
+    const bool few_long = P < 64 * 256 && pg.T > 2048;
+    if (!rc && (where == MF4D_HOST || few_long)) {
+        const hipMemcpyKind kind = where == MF4D_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice;
+        hipError_t e = hipMemcpyAsync(c->praw, xyz, nxyz * sizeof(float), kind, c->stream);
+        if (e == hipSuccess) e = hipMemcpyAsync(c->praw + nxyz, attr, nat * sizeof(float), kind, c->stream);
         if (e != hipSuccess) rc = fail(MF4D_ERR_HIP, "particle upload failed: %s", hipGetErrorString(e));
         dx = c->praw;
         da = c->praw + nxyz;

@@ -64,3 +64,34 @@ def test_field_pointer_is_checked_before_a_kernel_reads_it():
     finally:
         g.close()
         assert lib.hipFree(short) == 0
+
+
+@pytest.mark.parametrize("P,Tp", [(5, 2048), (5, 2049), (70, 3000)])
+def test_few_long_trajectories_from_device_memory(P, Tp):
+    """Above 2,048 steps the particles are copied before they are binned: masks, and the
+    clustering, which reads the copy, against the oracle."""
+    from oracle import slic as oslic
+    from paper_1903_12294_amd import Grower
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rate, T, Z, Y, X = 1024, 3, 5, 6, 9
+    rng = np.random.default_rng(P + Tp)
+    field = rng.random((T, Z, Y, X), dtype=np.float32)
+    xyz = (rng.random((Tp, P, 3)) * [X, Y, Z]).astype(np.float32)
+    attr = rng.random((Tp, P), dtype=np.float32)
+    crit, seeds = np.array([0.3, np.inf, 0.3, np.inf], np.float32), np.array([[x, 2, 2, 1] for x in range(X)], np.int32)
+    ofm, opm, _ = oracle_grow(field, xyz, attr, crit, seeds, rate=rate)
+    print(f"[pointers] long P={P} Tp={Tp}", flush=True)
+    with Grower(device=0) as g:
+        g.load_field(torch.from_numpy(field).to("cuda:0"))
+        g.load_particles(torch.from_numpy(xyz).to("cuda:0"), torch.from_numpy(attr).to("cuda:0"), rate=rate)
+        g.set_criteria(*crit)
+        g.set_seeds(seeds)
+        g.grow()
+        assert np.array_equal(g.read_field_mask(), ofm) and np.array_equal(g.read_particle_mask(), opm)
+        k, w, cf = (2, 2, 1, 1), (1.0, 2.0, 2.0), 0.5
+        g.slic_set_params(k, *w, cf, 1e-4, 2)
+        g.slic_run()
+        fl, pl = g.slic_read_labels()
+    ofl, opl, _, _, _ = oslic.slic(field, xyz, attr, k, w, cf, 1e-4, 2, rate=rate)
+    assert np.array_equal(fl, ofl) and np.array_equal(pl, opl)
