@@ -204,7 +204,7 @@ struct mf4d_ctx {
     // The one-block rounds met more work than they take: not tried again until the
     // data, the criteria, the admissibility mode or the schedule change.
     bool one_declined = false;
-    bool one_unsure = false;    // the last attempt was declined: the next one does not wait for its answer
+    int one_declines = 0;       // attempts declined in a row
     int coop_blocks = 0;      // blocks of this tile depth's cooperative rounds kernel that fit the device (0: not asked yet)
 
     // grow state: 0 nothing grown, 1 converged, 2 stopped by the round cap
@@ -677,20 +677,25 @@ struct RoundChunk {
 
 // Queue the one-block kernel with the seeds left to it (none the second time).
 // True if the schedule's own rounds are to be queued behind it at once, without
-// waiting for its answer: where the last attempt was declined (64^3 x 16, other
+// waiting for its answer: where the last two attempts were declined (64^3 x 16, other
 // criteria every call: 120 us a grow and read-outs, 125 with the wait, 117 without the
 // attempt).  Where the kernel runs the rounds after all, those behind it find empty
-// lists; with a round cap they could pass it.
+// lists, at about 4 us a launched round: after one declined attempt alone, criteria that
+// are declined and taken in turn would pay for them.  With a round cap they could pass
+// it.
 bool try_one(mf4d_ctx* c, const Dev& d, bool launched, uint32_t cap) {
     launch_rounds_one(d, launched, c->round, cap, c->few_left ? c->few : FewSeeds{}, c->stream);
     c->few_left = false;
     c->one_tried = true;
-    return c->one_unsure && !cap;
+    return c->one_declines >= 2 && !cap;
 }
 
 // With a grow's counters at hand: what the one-block kernel answered.
 void note_one(mf4d_ctx* c) {
-    if (c->one_tried) c->one_unsure = c->one_declined = c->h_counters[C_DECLINED] != 0;
+    if (c->one_tried) {
+        c->one_declined = c->h_counters[C_DECLINED] != 0;
+        c->one_declines = c->one_declined ? c->one_declines + 1 : 0;
+    }
     c->one_tried = false;
 }
 

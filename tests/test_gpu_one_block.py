@@ -45,7 +45,7 @@ def test_coupled_steps_around_the_limits(P, schedule):
 @pytest.mark.parametrize("schedule", ["launch", "persistent"])
 def test_declined_and_taken_in_turn(schedule):
     """Criteria that the one-block rounds decline (all 128 tiles admitted) and take (a
-    few tiles) in turn on one context: after a declined attempt the schedule's own
+    few tiles) in turn on one context: after two declined attempts the schedule's own
     rounds are queued behind the next one.  With equal criteria, both admissibility
     modes, a round cap with resumes, a submitted grow, more than 64 seeds."""
     from paper_1903_12294_amd import Grower
@@ -112,8 +112,12 @@ def test_declined_and_taken_in_turn(schedule):
 
         for crit, sd, how in [(wide, seeds, ""), (narrow, seeds, ""), (narrow, seeds, ""), (wide, seeds, ""),
                               (wide, seeds, ""), ((0.15, *wide[1:]), seeds, ""), (narrow, many, ""), (wide, many, ""),
-                              (narrow, seeds, "submit"), (wide, seeds, "submit"), (narrow, seeds, "submit"),
-                              (wide, seeds, "cap"), (narrow, seeds, "cap"), (wide, seeds, ""), (narrow, seeds, "cap")]:
+                              ((0.15, *wide[1:]), seeds, ""), ((0.12, *wide[1:]), seeds, ""), (narrow, seeds, ""),
+                              (narrow, seeds, "submit"), (wide, seeds, "submit"), ((0.12, *wide[1:]), many, "submit"),
+                              ((0.15, *wide[1:]), seeds, "submit"), (narrow, seeds, "submit"),
+                              (wide, seeds, "cap"), ((0.12, *wide[1:]), seeds, "cap"), (narrow, seeds, "cap"),
+                              (wide, seeds, ""), ((0.15, *wide[1:]), seeds, ""), ((0.12, *wide[1:]), seeds, "cap"),
+                              (narrow, seeds, "cap")]:
             check(crit, sd, how)
         g.set_admit_mode("all")
         check(narrow, seeds, "")
